@@ -74,6 +74,10 @@ typedef enum { SN_CONV_FWD = 0, SN_CONV_BWD_DATA = 1, SN_CONV_BWD_FILTER = 2 } s
  *  IM2COL_GEMM  explicit: unfold patches into a column buffer in the workspace
  *               (as many images per pass as fit), then a GEMM over it; the
  *               backward-data form folds the column gradient back (col2im).
+ *               With workspace for channels-last copies of the operands (every
+ *               shape, either dtype; about the tensors' own size) the patches are
+ *               never written out: in such a copy the elements under a filter row
+ *               are one contiguous run, and the GEMM reads its rows there.
  *  STAGED       implicit GEMM that stages a re-laid-out operand in the
  *               workspace: the filter packed tap-major for forward and
  *               backward-data; per-slice partial sums of dw (reduced in a fixed
@@ -96,6 +100,11 @@ typedef enum { SN_CONV_FWD = 0, SN_CONV_BWD_DATA = 1, SN_CONV_BWD_FILTER = 2 } s
  *               form already, so DIRECT runs the same kernel).  Otherwise forward and
  *               backward-data take the planes of as many images per pass as the
  *               workspace holds (min_bytes: one image).
+ *               Where the product over channels-last copies (see IM2COL_GEMM) is
+ *               estimated to be faster than these kernels and the workspace given
+ *               holds it, STAGED runs that; sn_conv_plan's bytes_used then says how
+ *               much of the budget it takes (preferred_bytes includes it for
+ *               stride-1 forward and backward-data and for strided backward-data).
  *  WINOGRAD     F(2x2, 3x3) for the fp32 path (3x3 filters, stride 1, forward and
  *               backward-data): the transformed filter, the transformed input
  *               tiles and the 16 products per tile live in the workspace, for as
@@ -174,8 +183,8 @@ sn_status sn_conv2d_fwd(const void *x, const void *w, void *y, const sn_conv_sha
 
 /* sn_conv2d_fwd for callers that cannot allocate or pass device memory beyond the tensors
  * themselves: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
- * It is sn_conv2d_fwd with algo = SN_ALGO_STAGED (same kernels, bit-identical y) whose workspace,
- * the re-laid-out filter, is a fixed array of SN_NOALLOC_SCRATCH_BYTES that the library's code
+ * It is sn_conv2d_fwd with algo = SN_ALGO_STAGED (same kernels, bit-identical y) whose workspace
+ * (the re-laid-out filter; the copies of small inputs) is a fixed array of SN_NOALLOC_SCRATCH_BYTES that the library's code
  * object holds on every GPU it is loaded on until the process ends.  No hipMalloc / hipFree or
  * other allocating call is made.  The first call on a device looks up the array's address there
  * (make that call outside a graph capture).

@@ -336,6 +336,30 @@ size_t tile_conv_packed_bytes(const ConvGeom &g, bool bwd_data)
     return align_up((size_t)pl.p.nchunks * g.R * g.S * pl.p.Mpad * 16 * sizeof(bf16_t), 256);
 }
 
+// What launch_tile_conv with a packed filter takes, in us, where that can compete with the channels-last product: 3x3
+// filters on planes whose patches are full (WIDE tilings, and everything the second-generation kernel takes), 1x1, and 5x5
+// filters with at most 64 output channels.  Per 16-channel chunk and workgroup the times below (measured over 100 shapes, 32 to
+// 512 channels, planes of 12x12 to 224x224); elsewhere the channels-last product was 1.2 to 10 times faster.
+double tile_conv_us(const ConvGeom &g, bool bwd_data)
+{
+    constexpr double NEVER = 1e9;
+    TileProblem p;
+    Plan pl;
+    if (!tile_conv_supported(g, bwd_data) || !problem_of(g, bwd_data, &p) || !make_plan(p, g.R, g.S, true, &pl)) return NEVER;
+    if (pointwise_supported(g, bwd_data)) return 0;
+    if (g.R == 1 && g.S == 1)
+        return 5 + (pl.NF == 4 ? 1.3 : 1.0) * pl.p.nchunks * std::max(1.0, (double)pl.p.nptiles * pl.p.nktiles / 256);
+    if (!(g.R == 3 && g.S == 3) && !(g.R == 5 && g.S == 5 && pl.KT == 64 && pl.NF <= 2)) return NEVER;
+    Plan pl2;
+    const bool second = make_plan2(p, g.R, g.S, &pl2);
+    if (second) pl = pl2;
+    else if (!pl.wide) return NEVER;
+    double us = pl.KT == 64 ? (pl.NF == 1 ? 1.0 : pl.NF == 2 ? 1.7 : 3.0) * (second ? 0.68 : 1)
+                            : (pl.NF == 1 ? 1.4 : pl.NF == 2 ? 2.0 : 3.0) * (second ? 0.80 : 1.15);
+    us *= g.R * g.S / 9.0;
+    return 5 + us * pl.p.nchunks * std::max(1.0, (double)pl.p.nptiles * pl.p.nktiles / 256);
+}
+
 // Pixel tiles of the plan launch_tile_conv would use (forward); 0 if the kernels do not apply.
 int tile_conv_stats_tiles(const ConvGeom &g, bool staged, bool in_aligned16)
 {

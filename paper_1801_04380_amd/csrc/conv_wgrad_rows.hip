@@ -31,6 +31,7 @@
 // into a zeroed dw with fp32 atomics (no workspace) or writes partial[slice], which
 // is then reduced in slice order.  Either way the accumulators go through LDS first
 // so that global accesses are coalesced.
+#include <cmath>
 #include "sn_internal.h"
 
 namespace sn {
@@ -591,6 +592,17 @@ bool rows_wgrad_supported(const ConvGeom &g)
 {
     RPlan pl;
     return make_rplan(g, &pl);
+}
+
+// What launch_rows_wgrad with all its partial sums takes, in us, for 3x3 and 1x1 filters on rows of more than 16 pixels (measured
+// per chunk over 60 shapes); elsewhere the channels-last product was 1.2 to 6 times faster.
+double rows_wgrad_us(const ConvGeom &g)
+{
+    RPlan pl;
+    if (!make_rplan(g, &pl) || g.R != g.S || g.R > 3 || pl.TWP == 16) return 1e9;
+    const double wgs = (double)pl.p.ctiles * pl.p.ktiles * pl.nslices, rounds = std::ceil(wgs / 256);
+    const double chunk = g.R == 1 ? 1.2 : pl.TM == 1 && pl.TP == 2 ? 2.8 : 4.2;
+    return 10 + rounds * pl.p.cps * chunk + (double)g.R * g.S * g.C * g.K * 4 * pl.nslices / 4.3e6;
 }
 
 int rows_wgrad_slices(const ConvGeom &g, int cap)

@@ -284,6 +284,55 @@ bool scatter_bwd_data(const ConvGeom &g) { return (g.sh > 1 || g.sw > 1) && poin
 // else, and every budget below that, takes the gathering kernel.
 bool phase_fwd_when_it_fits(const ConvGeom &g) { return g.R == 1 && g.S == 1 && g.K >= 512; }
 
+// ---- the channels-last product (conv_chlast.h) ---------------------------------------------------
+// It needs workspace for copies of whole tensors and runs every geometry, so it carries no name of its own: with enough
+// workspace it is what STAGED runs where it is faster than STAGED's other kernels, and what IM2COL_GEMM runs instead of
+// unfolding.
+
+// Estimated us of what runs instead (0: always keep that).  Kernels that read their operands where they are -- few input
+// channels, 1x1 layers, 1x1 / stride-2 layers written or gathered directly -- were faster on every shape measured.
+double other_us(const ConvGeom &g, sn_conv_dir dir)
+{
+    // the general kernels at their best (they were never faster than the product given enough workspace)
+    const double flops = 2.0 * g.N * g.K * g.C * g.R * g.S * g.P * g.Q, general = 10 + flops / (g.in_bf16 ? 1.5e8 : 7e7);
+    if (!g.in_bf16) return general;
+    if (smallc_supported(g) && dir != SN_CONV_BWD_DATA) return 0;
+    if (dir == SN_CONV_BWD_FILTER) {
+        if (g.sh > 1 || g.sw > 1 || !tile_wgrad_supported(g)) return general;
+        // 1x1 on planes of odd sizes or short rows: bound by memory up to 256 channels on either side, where copies are a
+        // second pass; with more the product's larger tiles win
+        if (pointwise_wgrad_supported(g))
+            return std::min(g.C, g.K) > 256 ? 1e9 : 7 + (double)g.N * g.P * g.Q * (g.C + g.K) * 2 / 1.5e6;
+        return rows_wgrad_us(g);
+    }
+    if (dir == SN_CONV_BWD_DATA && scatter_bwd_data(g)) return 0;
+    if (dir == SN_CONV_FWD && g.R == 1 && g.S == 1 && gather_fwd(g)) return 0;
+    if (g.sh > 1 || g.sw > 1 || !tile_conv_supported(g, dir == SN_CONV_BWD_DATA)) return general;
+    return tile_conv_us(g, dir == SN_CONV_BWD_DATA);
+}
+
+// Whether the channels-last product is to run under this name with this workspace: where it is the faster one (against
+// unfolding always), in few passes over the batch (each is some launches) -- more where only the general kernels are left.
+// extra_us: what the choice costs elsewhere.
+bool chlast_runs(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t ws_bytes, ChlastPlan *plan, double extra_us = 0)
+{
+    if (ws_bytes == 0 || (algo != SN_ALGO_STAGED && algo != SN_ALGO_IM2COL_GEMM)) return false;
+    const double other = algo == SN_ALGO_IM2COL_GEMM ? 1e9 : other_us(g, dir);
+    if (other <= 0 || !chlast_plan(g, dir, ws_bytes, plan)) return false;
+    const bool alone = dir == SN_CONV_BWD_FILTER ? !tile_wgrad_supported(g) : dir == SN_CONV_FWD && !tile_conv_supported(g, false);
+    return plan->passes <= (alone ? 8 : 2) && plan->us + extra_us < other;
+}
+
+constexpr size_t ALL_BYTES = ~(size_t)0 / 2;
+
+// The least it runs with: one image per pass.
+bool chlast_least(const ConvGeom &g, sn_conv_dir dir, ChlastPlan *plan)
+{
+    ConvGeom one = g;
+    one.N = 1;
+    return chlast_plan(one, dir, ALL_BYTES, plan);
+}
+
 sn_status query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *min_b, size_t *pref_b)
 {
     switch (algo) {
@@ -322,6 +371,11 @@ sn_status query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *m
         if (phase_plan(g, dir, &pp)) {
             *pref_b = phase_bytes(pp, dir, g.N);
             *min_b = pp.chunkable ? phase_bytes(pp, dir, 1) : *pref_b;
+            ChlastPlan all, one;
+            if (dir == SN_CONV_BWD_DATA && chlast_plan(g, dir, ALL_BYTES, &all) && chlast_least(g, dir, &one)) {
+                *pref_b = all.bytes;
+                *min_b = std::min(std::min(*min_b, one.bytes), all.bytes);
+            }
             return SN_OK;
         }
         if (dir == SN_CONV_BWD_FILTER) {
@@ -331,6 +385,8 @@ sn_status query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *m
         }
         if (!tile_conv_supported(g, dir == SN_CONV_BWD_DATA)) return SN_ERR_UNSUPPORTED;
         *min_b = *pref_b = tile_conv_packed_bytes(g, dir == SN_CONV_BWD_DATA);
+        ChlastPlan cl;
+        if (chlast_runs(g, dir, algo, ALL_BYTES, &cl)) *pref_b = std::max(*pref_b, cl.bytes);
         return SN_OK;
     }
     default:
@@ -387,6 +443,17 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
         *algo = (sn_conv_algo)best.algo;
         *bytes = best.ws;
         if (ms_out) *ms_out = best.ms;
+        return SN_OK;
+    }
+    // The channels-last product where it is the fastest, under the name that runs it with this budget.
+    for (sn_conv_algo a : {SN_ALGO_STAGED, SN_ALGO_IM2COL_GEMM}) {
+        size_t mn = 0, pf = 0;
+        ChlastPlan cl;
+        if (budget == 0 || query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
+        if (!chlast_runs(g, dir, SN_ALGO_STAGED, budget, &cl)) break;
+        *algo = a;
+        *bytes = a == SN_ALGO_STAGED ? std::max(cl.bytes, std::min(pf, budget)) : cl.bytes;
+        if (ms_out) *ms_out = -1.f;
         return SN_OK;
     }
     // Few input channels: the zero-workspace kernel is the memory-bound one (forward); backward-filter
@@ -487,6 +554,8 @@ sn_status run_fwd(const void *x, const void *w, void *y, const ConvGeom &g, sn_c
 {
     if (algo == SN_ALGO_DIRECT) return launch_status(direct_fwd(x, w, y, g, st));
     if (algo == SN_ALGO_WINOGRAD) return launch_status(launch_winograd(x, w, y, g, false, ws, ws_bytes, st));
+    ChlastPlan cl;
+    if (chlast_runs(g, SN_CONV_FWD, algo, ws_bytes, &cl)) return launch_status(launch_chlast(x, w, y, g, SN_CONV_FWD, ws, &cl, st));
     PhasePlan pp;
     if (algo == SN_ALGO_STAGED && gather_fwd(g)) {
         const bool planes = phase_fwd_when_it_fits(g) && phase_plan(g, SN_CONV_FWD, &pp);
@@ -531,8 +600,15 @@ sn_status run_bwd_data(const void *dy, const void *w, void *dx, const ConvGeom &
     if (algo == SN_ALGO_DIRECT) return launch_status(direct_bwd_data(dy, w, dx, g, st));
     if (algo == SN_ALGO_WINOGRAD) return launch_status(launch_winograd(dy, w, dx, g, true, ws, ws_bytes, st));
     if (algo == SN_ALGO_STAGED && scatter_bwd_data(g)) return launch_status(launch_pointwise(dy, w, dx, g, true, st));
+    ChlastPlan cl;
+    if (chlast_runs(g, SN_CONV_BWD_DATA, algo, ws_bytes, &cl)) return launch_status(launch_chlast(dy, w, dx, g, SN_CONV_BWD_DATA, ws, &cl, st));
     PhasePlan pp;
-    if (algo == SN_ALGO_STAGED && phase_plan(g, SN_CONV_BWD_DATA, &pp)) {
+    const bool phases = algo == SN_ALGO_STAGED && phase_plan(g, SN_CONV_BWD_DATA, &pp);
+    if (phases && ws_bytes < phase_bytes(pp, SN_CONV_BWD_DATA, pp.chunkable ? 1 : g.N)) {   // less than the phase planes need: many passes
+        if (!chlast_plan(g, SN_CONV_BWD_DATA, ws_bytes, &cl)) return SN_ERR_WORKSPACE_TOO_SMALL;
+        return launch_status(launch_chlast(dy, w, dx, g, SN_CONV_BWD_DATA, ws, &cl, st));
+    }
+    if (phases) {
         char *base = static_cast<char *>(ws);
         void *wp = base, *packed = base + pp.wprime_bytes, *dxs = base + phase_fixed_bytes(pp, SN_CONV_BWD_DATA);
         if (!pp.plain && launch_phase_filter(w, wp, pp.m, g, st) != hipSuccess) return SN_ERR_LAUNCH;
@@ -578,6 +654,8 @@ sn_status run_bwd_filter(const void *x, const void *dy, void *dw, const ConvGeom
         if (gather_wgrad_supported(g)) return launch_status(launch_gather_wgrad(x, dy, dwf, g, nullptr, st));
         return launch_status(launch_generic_bwd_filter(x, dy, dwf, g, generic_bwd_filter_splits(g), nullptr, false, st));
     }
+    ChlastPlan cl;
+    if (chlast_runs(g, SN_CONV_BWD_FILTER, algo, ws_bytes, &cl)) return launch_status(launch_chlast(x, dy, dw, g, SN_CONV_BWD_FILTER, ws, &cl, st));
     PhasePlan pp;
     if (algo == SN_ALGO_STAGED && phase_plan(g, SN_CONV_BWD_FILTER, &pp)) {
         // workspace: phase planes of x | dw of the inner convolution | its partial sums
@@ -803,15 +881,21 @@ sn_status sn_conv2d_fwd_bn_stats(const void *x, const void *w, void *y, const sn
         if (launch_smallc_fwd(x, w, y, g, st, part) != hipSuccess) return SN_ERR_LAUNCH;
         return launch_status(launch_bn_finalize_tiles(part, g.K, smallc_fwd_stats_tiles(g), save_mean, save_invstd, eps, st));
     }
-    if (tile_conv_supported(g, false) && (staged || algo == SN_ALGO_DIRECT)) {
+    // (the channels-last product leaves the statistics to a pass over y)
+    ChlastPlan cl;
+    const bool copied = staged && chlast_runs(g, SN_CONV_FWD, algo, workspace_bytes, &cl, 6 + (double)g.N * g.K * g.P * g.Q * out_elem(g) / 4.5e6);
+    if (copied && launch_chlast(x, w, y, g, SN_CONV_FWD, workspace, &cl, st) != hipSuccess) return SN_ERR_LAUNCH;
+    if (!copied && tile_conv_supported(g, false) && (staged || algo == SN_ALGO_DIRECT)) {
         // the tile kernels take the statistics from their accumulators: y is not read again
         const int tiles = tile_conv_stats_tiles(g, staged, true);
         if (tiles <= 0) return SN_ERR_UNSUPPORTED;
         if (launch_tile_conv(x, w, y, g, false, staged ? workspace : nullptr, st, part) != hipSuccess) return SN_ERR_LAUNCH;
         return launch_status(launch_bn_finalize_tiles(part, g.K, tiles, save_mean, save_invstd, eps, st));
     }
-    s = run_fwd(x, w, y, g, algo, workspace, workspace_bytes, st);
-    if (s != SN_OK) return s;
+    if (!copied) {
+        s = run_fwd(x, w, y, g, algo, workspace, workspace_bytes, st);
+        if (s != SN_OK) return s;
+    }
     return launch_status(launch_bn_stats(y, part, save_mean, save_invstd, g.N, g.K, g.P * g.Q, eps, g.out_bf16, st));
 }
 
@@ -842,7 +926,9 @@ sn_status sn_conv_autotune(sn_conv_dir dir, const void *a, const void *b, void *
     for (int algo = 0; algo < SN_ALGO_COUNT && result == SN_OK; ++algo) {
         size_t mn = 0, pf = 0;
         if (query(g, dir, (sn_conv_algo)algo, &mn, &pf) != SN_OK || mn > workspace_bytes) continue;
-        const size_t used = std::min(pf, workspace_bytes);
+        size_t used = std::min(pf, workspace_bytes);
+        ChlastPlan cl;
+        if (chlast_runs(g, dir, (sn_conv_algo)algo, workspace_bytes, &cl)) used = std::max(used, cl.bytes);
         // one untimed run, then `iters` runs timed one by one: the median is recorded (a mean of a
         // few back-to-back launches follows whatever else disturbs one of them)
         s = conv_call(dir, a, b, out, shape, (sn_conv_algo)algo, workspace, used, stream);

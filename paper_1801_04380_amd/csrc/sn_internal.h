@@ -59,6 +59,7 @@ size_t tile_conv_packed_bytes(const ConvGeom &g, bool bwd_data);
 hipError_t launch_tile_conv(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data,
                             void *packed, hipStream_t st, float *stats = nullptr);
 int tile_conv_stats_tiles(const ConvGeom &g, bool staged, bool in_aligned16);
+double tile_conv_us(const ConvGeom &g, bool bwd_data);   // estimate; 0: nothing is faster, very large: everything is
 
 // Stride-1 bf16 backward-filter fast path.  partial == nullptr: the slices of the
 // (n,p,q) sum combine with atomics into a zero-filled dw; otherwise slice z writes
@@ -74,6 +75,7 @@ hipError_t launch_tile_wgrad(const void *x, const void *dy, float *dw, const Con
 // The row-stationary variant for 3x3 / 1x1 filters (same contract); launch_tile_wgrad prefers it.
 bool rows_wgrad_supported(const ConvGeom &g);
 int rows_wgrad_slices(const ConvGeom &g, int cap = 0);
+double rows_wgrad_us(const ConvGeom &g);   // estimate, as tile_conv_us
 hipError_t launch_rows_wgrad(const void *x, const void *dy, float *dw, const ConvGeom &g, float *partial,
                              hipStream_t st, int cap = 0);
 
@@ -149,6 +151,17 @@ void winograd_bytes(const ConvGeom &g, bool bwd_data, size_t *min_b, size_t *pre
 long long winograd_pass_tiles(const ConvGeom &g, bool bwd_data, size_t ws_bytes);
 hipError_t launch_winograd(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, void *ws,
                            size_t ws_bytes, hipStream_t st);
+
+// Any convolution as a product over a channels-last copy of its operands in the workspace (conv_chlast.h).  chlast_plan:
+// whether it runs with this budget; the bytes it uses of it, its passes over parts of the batch and its estimated time.
+struct ChlastPlan {
+    alignas(16) char mem[2560];
+    size_t bytes;
+    int passes;
+    double us;
+};
+bool chlast_plan(const ConvGeom &g, int dir, size_t budget, ChlastPlan *plan);
+hipError_t launch_chlast(const void *a, const void *b, void *out, const ConvGeom &g, int dir, void *ws, ChlastPlan *plan, hipStream_t st);
 
 // Cheap layers.
 hipError_t launch_relu_fwd(const void *x, void *y, size_t n, int bf16, hipStream_t st);
