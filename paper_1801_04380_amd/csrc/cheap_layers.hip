@@ -1088,47 +1088,15 @@ maxpool2_bwd_kernel(const T *__restrict__ dy, const int32_t *__restrict__ idx, T
 }
 
 // 3x3 windows, stride 2, forward: a thread owns 4 neighbouring windows of one output row, i.e.
-// 9 columns of 3 input rows, which it reads as one 8-element piece and one element per row where the
-// piece lies inside the image and the tensor (anything else: element by element).  The scan of a
+// 9 columns of 3 input rows, which it reads as one 8-element piece and one element per row where all
+// of them lie inside the image (anything else: element by element).  The last group of a row is moved
+// back to end with it -- the windows it shares with the group before are written twice, with the same
+// values -- so that without padding no wave has lanes that read element by element.  The scan of a
 // window is the generic kernel's: row-major over the positions inside the image, a later element
-// wins only if strictly greater.
-template <typename T>
-__global__ void __launch_bounds__(256)
-maxpool3s2_fwd_kernel(const T *__restrict__ x, T *__restrict__ y, int32_t *__restrict__ idx, unsigned rows, int H,
-                      int W, int P, int Q, int ph, int pw, int lg, const T *__restrict__ xend)
+// wins only if strictly greater.  128 x 96 x 55x55 bf16: 46 -> 25.5 us (4.6 TB/s).
+template <typename T, bool INSIDE>
+__device__ inline void pool3_scan(const T (&e)[3][9], int h0, int v0, int H, int W, Pack<T, 4> &out, Pack<int32_t, 4> &oi)
 {
-    const unsigned row = blockIdx.x * (256u >> lg) + (threadIdx.x >> lg);
-    const int g = threadIdx.x & ((1 << lg) - 1);
-    if (row >= rows || g * 4 >= Q) return;
-    const unsigned nc = row / (unsigned)P;
-    const int p = (int)(row - nc * (unsigned)P), q0 = 4 * g;
-    const int nout = min(4, Q - q0);
-    const int h0 = 2 * p - ph, v0 = 2 * q0 - pw;
-    const T *xp = x + (size_t)nc * H * W;
-    // the 3 x 9 elements; outside the image: never looked at
-    T e[3][9];
-    const bool inside = v0 >= 0 && v0 + 9 <= W;
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        const int h = h0 + r;
-        if ((unsigned)h >= (unsigned)H) {
-#pragma unroll
-            for (int c = 0; c < 9; ++c) e[r][c] = T(0);
-            continue;
-        }
-        const T *rp = xp + (size_t)h * W + v0;
-        if (inside && rp + 9 <= xend) {
-            const Pack<T, 8> v = *reinterpret_cast<const Pack<T, 8> *>(rp);
-#pragma unroll
-            for (int c = 0; c < 8; ++c) e[r][c] = v.e[c];
-            e[r][8] = rp[8];
-        } else {
-#pragma unroll
-            for (int c = 0; c < 9; ++c) e[r][c] = (unsigned)(v0 + c) < (unsigned)W ? rp[c] : T(0);
-        }
-    }
-    Pack<T, 4> out;
-    Pack<int32_t, 4> oi;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         bool have = false;
@@ -1140,7 +1108,7 @@ maxpool3s2_fwd_kernel(const T *__restrict__ x, T *__restrict__ y, int32_t *__res
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
                 const int h = h0 + r, v = v0 + 2 * j + c;
-                if ((unsigned)h >= (unsigned)H || (unsigned)v >= (unsigned)W) continue;
+                if (!INSIDE && ((unsigned)h >= (unsigned)H || (unsigned)v >= (unsigned)W)) continue;
                 const T cand = e[r][2 * j + c];
                 const float f = ld<T>(&cand);
                 if (!have) { have = true; bv = f; best = h * W + v; raw = cand; }
@@ -1148,6 +1116,42 @@ maxpool3s2_fwd_kernel(const T *__restrict__ x, T *__restrict__ y, int32_t *__res
             }
         out.e[j] = raw;
         oi.e[j] = best;
+    }
+}
+
+template <typename T>
+__global__ void __launch_bounds__(256)
+maxpool3s2_fwd_kernel(const T *__restrict__ x, T *__restrict__ y, int32_t *__restrict__ idx, unsigned rows, int H,
+                      int W, int P, int Q, int ph, int pw, int lg)
+{
+    const unsigned row = blockIdx.x * (256u >> lg) + (threadIdx.x >> lg);
+    const int g = threadIdx.x & ((1 << lg) - 1);
+    if (row >= rows || g * 4 >= Q) return;
+    const unsigned nc = row / (unsigned)P;
+    const int p = (int)(row - nc * (unsigned)P), q0 = max(0, min(4 * g, Q - 4));
+    const int nout = min(4, Q - q0);
+    const int h0 = 2 * p - ph, v0 = 2 * q0 - pw;
+    const T *xp = x + (size_t)nc * H * W;
+    T e[3][9];
+    Pack<T, 4> out;
+    Pack<int32_t, 4> oi;
+    if (v0 >= 0 && v0 + 9 <= W && h0 >= 0 && h0 + 3 <= H) {
+        Pack<T, 9> v[3];
+#pragma unroll
+        for (int r = 0; r < 3; ++r) v[r] = *reinterpret_cast<const Pack<T, 9> *>(xp + (size_t)(h0 + r) * W + v0);
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int c = 0; c < 9; ++c) e[r][c] = v[r].e[c];
+        pool3_scan<T, true>(e, h0, v0, H, W, out, oi);
+    } else {
+        // outside the image: never looked at
+#pragma unroll
+        for (int r = 0; r < 3; ++r)
+#pragma unroll
+            for (int c = 0; c < 9; ++c)
+                e[r][c] = (unsigned)(h0 + r) < (unsigned)H && (unsigned)(v0 + c) < (unsigned)W ? xp[(size_t)(h0 + r) * W + v0 + c] : T(0);
+        pool3_scan<T, false>(e, h0, v0, H, W, out, oi);
     }
     T *yo = y + (size_t)row * Q + q0;
     int32_t *io = idx + (size_t)row * Q + q0;
@@ -1163,9 +1167,11 @@ maxpool3s2_fwd_kernel(const T *__restrict__ x, T *__restrict__ y, int32_t *__res
 
 // 3x3 windows, stride 2 (the overlapping pool of the AlexNet- and Inception-style workloads),
 // backward: a thread owns 8 neighbouring columns of one input row.  At most 2 window rows and
-// 5 window columns cover them; every window's index and gradient are read once per thread and
+// 5 window columns cover them; their indices and gradients are read as one run per window row, both
+// rows before either is used (a loop over the windows waits for memory once per window), and
 // added, in ascending (p, q) order -- the order of the one-thread-per-element kernel -- to
-// the column the index names, and the row piece leaves in one store.
+// the column the index names, and the row piece leaves in one store (the last one of a row moved
+// back to end with it).  128 x 96 x 55x55 bf16: 82 -> 60 us; the ten compares of eight columns bound it now.
 template <typename T>
 __global__ void __launch_bounds__(256)
 maxpool3s2_bwd_kernel(const T *__restrict__ dy, const int32_t *__restrict__ idx, T *__restrict__ dx, unsigned rows,
@@ -1175,7 +1181,7 @@ maxpool3s2_bwd_kernel(const T *__restrict__ dy, const int32_t *__restrict__ idx,
     const int g = threadIdx.x & ((1 << lg) - 1);
     if (row >= rows || g * 8 >= W) return;
     const unsigned nc = row / (unsigned)H;
-    const int h = (int)(row - nc * (unsigned)H), v0 = 8 * g;
+    const int h = (int)(row - nc * (unsigned)H), v0 = max(0, min(8 * g, W - 8));   // the last piece ends with the row
     const int ncol = min(8, W - v0);
     // windows p with 2p - ph <= h <= 2p - ph + 2, windows q that reach one of the columns
     const int p0 = max(0, (h + ph - 1) >> 1), p1 = min((h + ph) >> 1, P - 1);
@@ -1186,13 +1192,35 @@ maxpool3s2_bwd_kernel(const T *__restrict__ dy, const int32_t *__restrict__ idx,
     float acc[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[c] = 0.f;
-    for (int p = p0; p <= p1; ++p)
-        for (int q = q0; q <= q1; ++q) {
-            const int rel = ip[p * Q + q] - first;
-            const float d = ld<T>(gp + p * Q + q);
+    if (Q >= 5) {
+        const int qb = min(q0, Q - 5);   // windows qb .. qb + 4 hold q0 .. q1
+        Pack<int32_t, 5> wi[2];
+        Pack<T, 5> wg[2];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) acc[c] += rel == c ? d : 0.f;
+        for (int i = 0; i < 2; ++i) {
+            const int at = min(p0 + i, P - 1) * Q + qb;
+            wi[i] = *reinterpret_cast<const Pack<int32_t, 5> *>(ip + at);
+            wg[i] = *reinterpret_cast<const Pack<T, 5> *>(gp + at);
         }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 5; ++j) {
+                const bool use = p0 + i <= p1 && qb + j >= q0 && qb + j <= q1;
+                const int rel = use ? wi[i].e[j] - first : -1;
+                const float d = ld<T>(&wg[i].e[j]);
+#pragma unroll
+                for (int c = 0; c < 8; ++c) acc[c] += rel == c ? d : 0.f;
+            }
+    } else {
+        for (int p = p0; p <= p1; ++p)
+            for (int q = q0; q <= q1; ++q) {
+                const int rel = ip[p * Q + q] - first;
+                const float d = ld<T>(gp + p * Q + q);
+#pragma unroll
+                for (int c = 0; c < 8; ++c) acc[c] += rel == c ? d : 0.f;
+            }
+    }
     T *o = dx + (size_t)row * W + v0;
     if (ncol == 8) {
         Pack<T, 8> out;
@@ -1720,7 +1748,7 @@ hipError_t launch_maxpool_fwd(const void *x, void *y, int32_t *idx, int NC, int 
         return by_dtype(bf16, [&](auto *tag) {
             typedef typename std::remove_pointer<decltype(tag)>::type T;
             hipLaunchKernelGGL(maxpool3s2_fwd_kernel<T>, dim3((rows + rpb - 1) / rpb), dim3(256), 0, s, (const T *)x,
-                               (T *)y, idx, rows, H, W, P, Q, ph, pw, lg, (const T *)x + (size_t)NC * H * W);
+                               (T *)y, idx, rows, H, W, P, Q, ph, pw, lg);
         });
     }
     return by_dtype(bf16, [&](auto *tag) {

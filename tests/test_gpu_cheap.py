@@ -327,6 +327,14 @@ def test_maxpool(case, dtype):
         assert rel_l2(f64(dx), dxo) <= TOL[dtype]
 
 
+@pytest.mark.parametrize("pad", [0, 1, 2])
+@pytest.mark.parametrize("width", [3, 5, 8, 9, 10, 11, 12, 17, 19])
+def test_maxpool3s2_row_ends(width, pad):
+    """Row pieces moved back to end with their row: fewer windows or columns than a piece, one more, and padding."""
+    for dtype in ("bf16", "f32"):
+        test_maxpool(((2, 3, 9, width), (3, 3), (2, 2), (pad, pad)), dtype)
+
+
 def test_measured_ceilings_are_sane():
     """sn_measure_ceiling: every kind runs, stays below the datasheet peak it is quoted beside, and the
     operand-fed MFMA loop does not beat the register-resident one; bad arguments are refused."""
