@@ -1242,8 +1242,10 @@ maxpool3s2_bwd_kernel(const T *__restrict__ dy, const int32_t *__restrict__ idx,
 // Backward needs, for channel c, the terms r_j = dy_j x_j s_j^(-beta-1) of the channels around
 // it, each of which needs the window around j: the loop runs HALF channels ahead for s_j and
 // another HALF ahead for x, with r, s^(-beta) and dy of the channels in between in registers;
-// x and dy are read once, the forward output is not needed.  The channel loops are unrolled so
-// that the loads of several channels are in flight at once: nothing else hides their latency.
+// x and dy are read once, the forward output is not needed.  Nothing but loads of several channels
+// in flight hides their latency: each channel's x and dy are loaded LRN_AHEAD channels before they
+// are pushed into the window, with no branch around a load (channels outside the tensor load the
+// nearest one inside and count as zero).  128 x 96 x 55x55 bf16: backward 82 -> 67 us, forward 34 -> 33 us (4.5 TB/s).
 // RAG: planes that are no whole number of vectors (55x55, 27x27): a plane is ceil(HW / VEC) vectors at the
 // element's own alignment, the last one moved back so that it ends with the plane; the positions it shares
 // with the vector before are computed and written twice, with the same values.
@@ -1251,20 +1253,26 @@ template <typename T, int VEC, bool RAG = false> struct LrnIo {
     static constexpr int VB = VEC * (int)sizeof(T);
     typedef typename RawVec<VB>::type VT;
     struct __attribute__((packed, aligned(sizeof(T)))) Loose { uint32_t w[VB / 4 > 0 ? VB / 4 : 1]; };
-    __device__ static void load(const T *p, float (&f)[VEC])
+    // channel m of the C at p, the nearest one if m is outside [0, end)
+    __device__ static VT load(const T *p, int m, int end, int HW)
     {
-        if constexpr (VEC == 1) f[0] = ld<T>(p);
-        else if constexpr (RAG) {
-            const Loose l = *reinterpret_cast<const Loose *>(p);
-            VT v;
+        const T *q = p + (size_t)max(0, min(m, end - 1)) * HW;
+        VT v;
+        if constexpr (RAG) {
+            const Loose l = *reinterpret_cast<const Loose *>(q);
             __builtin_memcpy(&v, &l, VB);
-            unpack<T, VB>(v, f);
-        } else unpack<T, VB>(*reinterpret_cast<const VT *>(p), f);
+        } else v = *reinterpret_cast<const VT *>(q);
+        return v;
+    }
+    __device__ static void values(const VT &v, bool inside, int relu, float (&f)[VEC])
+    {
+        unpack<T, VB>(v, f);
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) f[i] = inside ? act(f[i], relu) : 0.f;
     }
     __device__ static void store(T *p, const float (&f)[VEC])
     {
-        if constexpr (VEC == 1) st(p, f[0]);
-        else if constexpr (RAG) {
+        if constexpr (RAG) {
             const VT v = pack<T, VB>(f);
             Loose l;
             __builtin_memcpy(&l, &v, VB);
@@ -1274,6 +1282,8 @@ template <typename T, int VEC, bool RAG = false> struct LrnIo {
 };
 
 __device__ inline float pow_neg(float s, float beta) { return __builtin_amdgcn_exp2f(-beta * __builtin_amdgcn_logf(s)); }
+
+constexpr int LRN_AHEAD = 4;
 
 template <typename T, int VEC, int HALF, bool RAG = false, bool RELU = false>
 __global__ void __launch_bounds__(256)
@@ -1291,34 +1301,48 @@ lrn_fwd_kernel(const T *__restrict__ x, T *__restrict__ y, int C, int HW, int vp
     for (int i = 0; i < SIZE; ++i)
 #pragma unroll
         for (int v = 0; v < VEC; ++v) xr[i][v] = 0.f;
-#pragma unroll 8
-    for (int m = cb - HALF; m < ce + HALF; ++m) {
+    typedef LrnIo<T, VEC, RAG> Io;
+    const T *xp = x + off;
+    T *yp = y + off;
+    const int end = min(C, ce + HALF);   // channels read: up to here
+    const auto push = [&](const typename Io::VT &v, int m) {
 #pragma unroll
         for (int i = 0; i + 1 < SIZE; ++i)
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) xr[i][v] = xr[i + 1][v];
-        if (m >= 0 && m < C) {
-            LrnIo<T, VEC, RAG>::load(x + off + (size_t)m * HW, xr[SIZE - 1]);
-            if (RELU) {   // the layer's input is the ReLU of x, which is never stored
+            for (int k_ = 0; k_ < VEC; ++k_) xr[i][k_] = xr[i + 1][k_];
+        Io::values(v, (unsigned)m < (unsigned)C, RELU, xr[SIZE - 1]);   // (with RELU the layer's input, max(x, 0), is never stored)
+    };
+    typename Io::VT head[2 * HALF + 1], ahead[LRN_AHEAD];
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) xr[SIZE - 1][v] = act(xr[SIZE - 1][v], 1);
-            }
-        } else {
+    for (int i = 0; i < 2 * HALF; ++i) head[i] = Io::load(xp, cb - HALF + i, end, HW);
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) xr[SIZE - 1][v] = 0.f;
-        }
-        const int c = m - HALF;
-        if (c < cb) continue;
+    for (int i = 0; i < LRN_AHEAD; ++i) ahead[i] = Io::load(xp, cb + HALF + i, end, HW);
+#pragma unroll
+    for (int i = 0; i < 2 * HALF; ++i) push(head[i], cb - HALF + i);
+    const auto one = [&](int c, const typename Io::VT &v) {
+        push(v, c + HALF);
         float out[VEC];
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) {
+        for (int i = 0; i < VEC; ++i) {
             float sum = 0.f;
 #pragma unroll
-            for (int i = 0; i < SIZE; ++i) sum = __builtin_fmaf(xr[i][v], xr[i][v], sum);
-            out[v] = xr[HALF][v] * pow_neg(__builtin_fmaf(a_n, sum, k), beta);
+            for (int j = 0; j < SIZE; ++j) sum = __builtin_fmaf(xr[j][i], xr[j][i], sum);
+            out[i] = xr[HALF][i] * pow_neg(__builtin_fmaf(a_n, sum, k), beta);
         }
-        LrnIo<T, VEC, RAG>::store(y + off + (size_t)c * HW, out);
+        Io::store(yp + (size_t)c * HW, out);
+    };
+    int c = cb;
+    for (; c + LRN_AHEAD <= ce; c += LRN_AHEAD) {
+#pragma unroll
+        for (int i = 0; i < LRN_AHEAD; ++i) {
+            const typename Io::VT v = ahead[i];
+            ahead[i] = Io::load(xp, c + i + HALF + LRN_AHEAD, end, HW);
+            one(c + i, v);
+        }
     }
+#pragma unroll
+    for (int i = 0; i < LRN_AHEAD; ++i)
+        if (c + i < ce) one(c + i, ahead[i]);
 }
 
 template <typename T, int VEC, int HALF, bool RAG = false, bool RELU = false>
@@ -1342,40 +1366,52 @@ lrn_bwd_kernel(const T *__restrict__ x, const T *__restrict__ dy, T *__restrict_
 #pragma unroll
         for (int i = 0; i < H1; ++i) pr[i][v] = gr[i][v] = 0.f;
     }
-#pragma unroll 8
-    for (int m = cb - 2 * HALF; m < ce + 2 * HALF; ++m) {
+    typedef LrnIo<T, VEC, RAG> Io;
+    const T *xp = x + off, *gp = dy + off;
+    T *op = dx + off;
+    const int xend = min(C, ce + 2 * HALF), gend = min(C, ce + HALF);   // channels read: up to here
+    // channel j + HALF of x arrives: channel j's window is complete (x_j = xr[HALF]) and its dy arrives with it
+    const auto push = [&](const typename Io::VT &xv, const typename Io::VT &gv, int j) {
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
 #pragma unroll
             for (int i = 0; i + 1 < SIZE; ++i) { xr[i][v] = xr[i + 1][v]; rr[i][v] = rr[i + 1][v]; }
 #pragma unroll
             for (int i = 0; i + 1 < H1; ++i) { pr[i][v] = pr[i + 1][v]; gr[i][v] = gr[i + 1][v]; }
-            xr[SIZE - 1][v] = 0.f;
-            rr[SIZE - 1][v] = pr[H1 - 1][v] = gr[H1 - 1][v] = 0.f;
         }
-        if (m >= 0 && m < C) {
-            LrnIo<T, VEC, RAG>::load(x + off + (size_t)m * HW, xr[SIZE - 1]);
-            if (RELU) {   // LRN saw max(x, 0): negative and zero x both count as 0, and their dx is 0 below
+        // LRN saw max(x, 0) with RELU: negative and zero x both count as 0, and their dx is 0 below
+        Io::values(xv, (unsigned)(j + HALF) < (unsigned)C, RELU, xr[SIZE - 1]);
+        const bool inside = (unsigned)j < (unsigned)C;
+        Io::values(gv, inside, 0, gr[H1 - 1]);
 #pragma unroll
-                for (int v = 0; v < VEC; ++v) xr[SIZE - 1][v] = act(xr[SIZE - 1][v], 1);
-            }
+        for (int v = 0; v < VEC; ++v) {
+            float sum = 0.f;
+#pragma unroll
+            for (int i = 0; i < SIZE; ++i) sum = __builtin_fmaf(xr[i][v], xr[i][v], sum);
+            const float s = __builtin_fmaf(a_n, sum, k), p = pow_neg(s, beta);
+            pr[H1 - 1][v] = p;
+            rr[SIZE - 1][v] = inside ? gr[H1 - 1][v] * xr[HALF][v] * (p / s) : 0.f;
         }
-        const int j = m - HALF;   // the channel whose window is complete: x_j = xr[HALF]
-        if (j < 0) continue;
-        if (j < C) {
-            LrnIo<T, VEC, RAG>::load(dy + off + (size_t)j * HW, gr[H1 - 1]);
+    };
+    // before the first output: x from channel cb - 2 HALF, terms from cb - HALF
+    typename Io::VT head[4 * HALF + 1], ghead[2 * HALF + 1], ahead[LRN_AHEAD], gahead[LRN_AHEAD];
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                float sum = 0.f;
+    for (int i = 0; i < 4 * HALF; ++i) head[i] = Io::load(xp, cb - 2 * HALF + i, xend, HW);
 #pragma unroll
-                for (int i = 0; i < SIZE; ++i) sum = __builtin_fmaf(xr[i][v], xr[i][v], sum);
-                const float s = __builtin_fmaf(a_n, sum, k), p = pow_neg(s, beta);
-                pr[H1 - 1][v] = p;
-                rr[SIZE - 1][v] = gr[H1 - 1][v] * xr[HALF][v] * (p / s);
-            }
-        }
-        const int c = j - HALF;   // every r of its window is known: x_c = xr[0], dy_c = gr[0], s_c^(-beta) = pr[0]
-        if (c < cb) continue;
+    for (int i = 0; i < 2 * HALF; ++i) ghead[i] = Io::load(gp, cb - HALF + i, gend, HW);
+#pragma unroll
+    for (int i = 0; i < LRN_AHEAD; ++i) {
+        ahead[i] = Io::load(xp, cb + 2 * HALF + i, xend, HW);
+        gahead[i] = Io::load(gp, cb + HALF + i, gend, HW);
+    }
+#pragma unroll
+    for (int i = 0; i < 2 * HALF; ++i)   // the first window but its last channel, one place late: push moves it
+        Io::values(head[i], (unsigned)(cb - 2 * HALF + i) < (unsigned)C, RELU, xr[i + 1]);
+#pragma unroll
+    for (int i = 0; i < 2 * HALF; ++i) push(head[2 * HALF + i], ghead[i], cb - HALF + i);
+    const auto one = [&](int c, const typename Io::VT &xv, const typename Io::VT &gv) {
+        push(xv, gv, c + HALF);
+        // every r of channel c's window is known: x_c = xr[0], dy_c = gr[0], s_c^(-beta) = pr[0]
         float out[VEC];
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
@@ -1385,8 +1421,21 @@ lrn_bwd_kernel(const T *__restrict__ x, const T *__restrict__ dy, T *__restrict_
             out[v] = gr[0][v] * pr[0][v] - coef * xr[0][v] * acc;
             if (RELU && !(xr[0][v] > 0.f)) out[v] = 0.f;   // the ReLU's gate: x > 0 (xr holds max(x, 0))
         }
-        LrnIo<T, VEC, RAG>::store(dx + off + (size_t)c * HW, out);
+        Io::store(op + (size_t)c * HW, out);
+    };
+    int c = cb;
+    for (; c + LRN_AHEAD <= ce; c += LRN_AHEAD) {
+#pragma unroll
+        for (int i = 0; i < LRN_AHEAD; ++i) {
+            const typename Io::VT xv = ahead[i], gv = gahead[i];
+            ahead[i] = Io::load(xp, c + i + 2 * HALF + LRN_AHEAD, xend, HW);
+            gahead[i] = Io::load(gp, c + i + HALF + LRN_AHEAD, gend, HW);
+            one(c + i, xv, gv);
+        }
     }
+#pragma unroll
+    for (int i = 0; i < LRN_AHEAD; ++i)
+        if (c + i < ce) one(c + i, ahead[i], gahead[i]);
 }
 
 template <typename F> hipError_t by_dtype(int bf16, F f)

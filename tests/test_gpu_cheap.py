@@ -335,6 +335,14 @@ def test_maxpool3s2_row_ends(width, pad):
         test_maxpool(((2, 3, 9, width), (3, 3), (2, 2), (pad, pad)), dtype)
 
 
+@pytest.mark.parametrize("size", [1, 3, 5, 9])
+@pytest.mark.parametrize("channels", [1, 2, 4, 5, 9, 20, 33])
+def test_lrn_channel_ends(channels, size):
+    """Channels read ahead: fewer than the window or than are read ahead, parts of 8 channels, a part cut short."""
+    for dtype in ("bf16", "f32"):
+        test_relu_lrn_one_pass((2, channels, 5, 7), (size, 0.5, 0.75, 1.0), dtype)
+
+
 def test_measured_ceilings_are_sane():
     """sn_measure_ceiling: every kind runs, stays below the datasheet peak it is quoted beside, and the
     operand-fed MFMA loop does not beat the register-resident one; bad arguments are refused."""
