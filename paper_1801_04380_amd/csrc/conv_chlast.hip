@@ -29,7 +29,7 @@ const Tile kWTile[] = {{128, 128, 2, {NEVER, 0.279}, {NEVER, 0.210}},
                        {256, 256, 1, {NEVER, 0.689}, {NEVER, 0.080}}};
 constexpr int NWTILE = 4;
 // us: launches; bytes per us: copies in and out, partial sums written and read, results written
-constexpr double LAUNCH_US = 10.5, COPY_RATE = 5.0e6, PART_RATE = 4.6e6, OUT_RATE = 1.4e6;
+constexpr double LAUNCH_US = CHLAST_LEAST_US, COPY_RATE = 5.0e6, PART_RATE = 4.6e6, OUT_RATE = 1.4e6;
 
 double loop_us(const Tile &t, int bf16, double wgs, double steps)
 {

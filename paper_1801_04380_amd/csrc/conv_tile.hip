@@ -338,8 +338,8 @@ size_t tile_conv_packed_bytes(const ConvGeom &g, bool bwd_data)
 
 // What launch_tile_conv with a packed filter takes, in us, where that can compete with the channels-last product: 3x3
 // filters on planes whose patches are full (WIDE tilings, and everything the second-generation kernel takes), 1x1, and 5x5
-// filters with at most 64 output channels.  Per 16-channel chunk and workgroup the times below (measured over 100 shapes, 32 to
-// 512 channels, planes of 12x12 to 224x224); elsewhere the channels-last product was 1.2 to 10 times faster.
+// filters with at most 64 output channels, and 3x3 on short rows with few channels.  Per 16-channel chunk and workgroup the
+// times below (measured over 100 shapes, 32 to 512 channels, planes of 12x12 to 224x224); elsewhere the channels-last product was 1.2 to 10 times faster.
 double tile_conv_us(const ConvGeom &g, bool bwd_data)
 {
     constexpr double NEVER = 1e9;
@@ -353,7 +353,13 @@ double tile_conv_us(const ConvGeom &g, bool bwd_data)
     Plan pl2;
     const bool second = make_plan2(p, g.R, g.S, &pl2);
     if (second) pl = pl2;
-    else if (!pl.wide) return NEVER;
+    else if (!pl.wide) {
+        // Short rows: patches are cut out row by row.  2 x 16x16 to 32 x 16x16, any batch: 16 and 32 channels 11.5 us with the
+        // call (the product 12.7), 64 channels 14.5 (12.7), 128 22 (15.5), 14x14 rows 3 us more.
+        if (g.R != 3) return NEVER;
+        const double chunk = pl.KT == 64 ? 1.8 : 1.45;
+        return (g.Q % 4 == 0 ? 6 : 9) + chunk * pl.p.nchunks * std::max(1.0, (double)pl.p.nptiles * pl.p.nktiles / 256);
+    }
     double us = pl.KT == 64 ? (pl.NF == 1 ? 1.0 : pl.NF == 2 ? 1.7 : 3.0) * (second ? 0.68 : 1)
                             : (pl.NF == 1 ? 1.4 : pl.NF == 2 ? 2.0 : 3.0) * (second ? 0.80 : 1.15);
     us *= g.R * g.S / 9.0;

@@ -594,15 +594,23 @@ bool rows_wgrad_supported(const ConvGeom &g)
     return make_rplan(g, &pl);
 }
 
-// What launch_rows_wgrad with all its partial sums takes, in us, for 3x3 and 1x1 filters on rows of more than 16 pixels (measured
-// per chunk over 60 shapes); elsewhere the channels-last product was 1.2 to 6 times faster.
+// What launch_rows_wgrad takes, in the product's estimated us, for 3x3 and 1x1 filters (elsewhere the product was 1.2 to 6 times
+// faster): per chunk, and the launches.  3x3 on 13x13 to 32x32 planes, 64 to 512 channels: 10 to 12 us where the product
+// takes 8 (64 channels), 53 where it takes 75 (512 channels, 13x13).
 double rows_wgrad_us(const ConvGeom &g)
 {
     RPlan pl;
-    if (!make_rplan(g, &pl) || g.R != g.S || g.R > 3 || pl.TWP == 16) return 1e9;
+    if (!make_rplan(g, &pl) || g.R != g.S || g.R > 3 || (g.R == 1 && pl.TWP == 16)) return 1e9;
     const double wgs = (double)pl.p.ctiles * pl.p.ktiles * pl.nslices, rounds = std::ceil(wgs / 256);
-    const double chunk = g.R == 1 ? 1.2 : pl.TM == 1 && pl.TP == 2 ? 2.8 : 4.2;
-    return 10 + rounds * pl.p.cps * chunk + (double)g.R * g.S * g.C * g.K * 4 * pl.nslices / 4.3e6;
+    const double chunk = g.R == 1 ? 1.2 : pl.TWP == 16 || (pl.TM == 1 && pl.TP == 2) ? 2.8 : 2.5;
+    return (g.R == 1 ? 10 : 16) + rounds * pl.p.cps * chunk + (double)rows_wgrad_partial_bytes(g) / 4.3e6;
+}
+
+// All its partial sums.
+size_t rows_wgrad_partial_bytes(const ConvGeom &g)
+{
+    RPlan pl;
+    return make_rplan(g, &pl) ? (size_t)g.R * g.S * g.C * g.K * 4 * pl.nslices : 0;
 }
 
 int rows_wgrad_slices(const ConvGeom &g, int cap)

@@ -307,7 +307,11 @@ double other_us(const ConvGeom &g, sn_conv_dir dir)
     }
     if (dir == SN_CONV_BWD_DATA && scatter_bwd_data(g)) return 0;
     if (dir == SN_CONV_FWD && g.R == 1 && g.S == 1 && gather_fwd(g)) return 0;
-    if (g.sh > 1 || g.sw > 1 || !tile_conv_supported(g, dir == SN_CONV_BWD_DATA)) return general;
+    if (g.sh > 1 || g.sw > 1) return general;
+    // a workgroup's own chain over the reduction (8 x 8x8, 3x3: 32 channels forward 13, backward-data 44 us; 128 forward 26;
+    // the product 13 to 15)
+    if (!tile_conv_supported(g, dir == SN_CONV_BWD_DATA))
+        return std::max(general, dir == SN_CONV_FWD ? 8 + 0.0155 * g.C * g.R * g.S : 6 + 0.135 * g.K * g.R * g.S);
     return tile_conv_us(g, dir == SN_CONV_BWD_DATA);
 }
 
@@ -317,8 +321,10 @@ double other_us(const ConvGeom &g, sn_conv_dir dir)
 bool chlast_runs(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t ws_bytes, ChlastPlan *plan, double extra_us = 0)
 {
     if (ws_bytes == 0 || (algo != SN_ALGO_STAGED && algo != SN_ALGO_IM2COL_GEMM)) return false;
-    const double other = algo == SN_ALGO_IM2COL_GEMM ? 1e9 : other_us(g, dir);
-    if (other <= 0 || !chlast_plan(g, dir, ws_bytes, plan)) return false;
+    double other = algo == SN_ALGO_IM2COL_GEMM ? 1e9 : other_us(g, dir);
+    // less than half of the row-stationary kernel's partial sums: atomics (64 x 256 x 20x20 -> 128: 42 us, with them 15)
+    if (dir == SN_CONV_BWD_FILTER && g.R == 3 && rows_wgrad_supported(g) && rows_wgrad_partial_bytes(g) / 2 > ws_bytes) other += 30;
+    if (other <= CHLAST_LEAST_US + extra_us || !chlast_plan(g, dir, ws_bytes, plan)) return false;
     const bool alone = dir == SN_CONV_BWD_FILTER ? !tile_wgrad_supported(g) : dir == SN_CONV_FWD && !tile_conv_supported(g, false);
     return plan->passes <= (alone ? 8 : 2) && plan->us + extra_us < other;
 }

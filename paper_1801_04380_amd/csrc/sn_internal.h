@@ -76,6 +76,7 @@ hipError_t launch_tile_wgrad(const void *x, const void *dy, float *dw, const Con
 bool rows_wgrad_supported(const ConvGeom &g);
 int rows_wgrad_slices(const ConvGeom &g, int cap = 0);
 double rows_wgrad_us(const ConvGeom &g);   // estimate, as tile_conv_us
+size_t rows_wgrad_partial_bytes(const ConvGeom &g);
 hipError_t launch_rows_wgrad(const void *x, const void *dy, float *dw, const ConvGeom &g, float *partial,
                              hipStream_t st, int cap = 0);
 
@@ -160,6 +161,7 @@ struct ChlastPlan {
     int passes;
     double us;
 };
+constexpr double CHLAST_LEAST_US = 10.5;   // its launches alone: what runs in less needs no plan to compare with
 bool chlast_plan(const ConvGeom &g, int dir, size_t budget, ChlastPlan *plan);
 hipError_t launch_chlast(const void *a, const void *b, void *out, const ConvGeom &g, int dir, void *ws, ChlastPlan *plan, hipStream_t st);
 
