@@ -545,6 +545,7 @@ hipError_t direct_fwd(const void *x, const void *w, void *y, const ConvGeom &g, 
     if (smallc_supported(g)) return launch_smallc_fwd(x, w, y, g, st, nullptr);
     if (tile_conv_supported(g, false)) return launch_tile_conv(x, w, y, g, false, nullptr, st);
     if (g.R == 1 && g.S == 1 && gather_fwd(g)) return launch_gather_conv_fwd(x, w, y, g, nullptr, st);
+    if (small3x3_supported(g, false)) return launch_small3x3(x, w, y, g, false, st);
     return launch_generic_fwd(x, w, y, g, st);
 }
 
@@ -552,6 +553,7 @@ hipError_t direct_bwd_data(const void *dy, const void *w, void *dx, const ConvGe
 {
     if (scatter_bwd_data(g)) return launch_pointwise(dy, w, dx, g, true, st);
     if (tile_conv_supported(g, true)) return launch_tile_conv(dy, w, dx, g, true, nullptr, st);
+    if (small3x3_supported(g, true)) return launch_small3x3(dy, w, dx, g, true, st);
     return launch_generic_bwd_data(dy, w, dx, g, st);
 }
 

@@ -153,6 +153,12 @@ long long winograd_pass_tiles(const ConvGeom &g, bool bwd_data, size_t ws_bytes)
 hipError_t launch_winograd(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, void *ws,
                            size_t ws_bytes, hipStream_t st);
 
+// fp32 3x3 / stride-1 forward and backward-data of small problems (conv_small.hip), no workspace.  Up to 9e6 products it was 1.4 to 6
+// times faster than the general kernel; its time grows with the products, the general kernel's with the reduction alone.
+constexpr long long SMALL3X3_MACS = 1LL << 24;
+bool small3x3_supported(const ConvGeom &g, bool bwd_data);
+hipError_t launch_small3x3(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, hipStream_t st);
+
 // Any convolution as a product over a channels-last copy of its operands in the workspace (conv_chlast.h).  chlast_plan:
 // whether it runs with this budget; the bytes it uses of it, its passes over parts of the batch and its estimated time.
 struct ChlastPlan {
