@@ -317,16 +317,15 @@ double other_us(const ConvGeom &g, sn_conv_dir dir)
 
 // Whether the channels-last product is to run under this name with this workspace: where it is the faster one (against
 // unfolding always), in few passes over the batch (each is some launches) -- more where only the general kernels are left.
-// extra_us: what the choice costs elsewhere.
-bool chlast_runs(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t ws_bytes, ChlastPlan *plan, double extra_us = 0)
+bool chlast_runs(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t ws_bytes, ChlastPlan *plan)
 {
     if (ws_bytes == 0 || (algo != SN_ALGO_STAGED && algo != SN_ALGO_IM2COL_GEMM)) return false;
     double other = algo == SN_ALGO_IM2COL_GEMM ? 1e9 : other_us(g, dir);
     // less than half of the row-stationary kernel's partial sums: atomics (64 x 256 x 20x20 -> 128: 42 us, with them 15)
     if (dir == SN_CONV_BWD_FILTER && g.R == 3 && rows_wgrad_supported(g) && rows_wgrad_partial_bytes(g) / 2 > ws_bytes) other += 30;
-    if (other <= CHLAST_LEAST_US + extra_us || !chlast_plan(g, dir, ws_bytes, plan)) return false;
+    if (other <= CHLAST_LEAST_US || !chlast_plan(g, dir, ws_bytes, plan)) return false;
     const bool alone = dir == SN_CONV_BWD_FILTER ? !tile_wgrad_supported(g) : dir == SN_CONV_FWD && !tile_conv_supported(g, false);
-    return plan->passes <= (alone ? 8 : 2) && plan->us + extra_us < other;
+    return plan->passes <= (alone ? 8 : 2) && plan->us < other;
 }
 
 constexpr size_t ALL_BYTES = ~(size_t)0 / 2;
@@ -889,21 +888,18 @@ sn_status sn_conv2d_fwd_bn_stats(const void *x, const void *w, void *y, const sn
         if (launch_smallc_fwd(x, w, y, g, st, part) != hipSuccess) return SN_ERR_LAUNCH;
         return launch_status(launch_bn_finalize_tiles(part, g.K, smallc_fwd_stats_tiles(g), save_mean, save_invstd, eps, st));
     }
-    // (the channels-last product leaves the statistics to a pass over y)
+    // The kernel is the one run_fwd takes: y is sn_conv2d_fwd's, bit for bit.  (The channels-last product leaves the
+    // statistics to a pass over y.)
     ChlastPlan cl;
-    const bool copied = staged && chlast_runs(g, SN_CONV_FWD, algo, workspace_bytes, &cl, 6 + (double)g.N * g.K * g.P * g.Q * out_elem(g) / 4.5e6);
-    if (copied && launch_chlast(x, w, y, g, SN_CONV_FWD, workspace, &cl, st) != hipSuccess) return SN_ERR_LAUNCH;
-    if (!copied && tile_conv_supported(g, false) && (staged || algo == SN_ALGO_DIRECT)) {
+    if (tile_conv_supported(g, false) && (algo == SN_ALGO_DIRECT || (staged && !chlast_runs(g, SN_CONV_FWD, algo, workspace_bytes, &cl)))) {
         // the tile kernels take the statistics from their accumulators: y is not read again
         const int tiles = tile_conv_stats_tiles(g, staged, true);
         if (tiles <= 0) return SN_ERR_UNSUPPORTED;
         if (launch_tile_conv(x, w, y, g, false, staged ? workspace : nullptr, st, part) != hipSuccess) return SN_ERR_LAUNCH;
         return launch_status(launch_bn_finalize_tiles(part, g.K, tiles, save_mean, save_invstd, eps, st));
     }
-    if (!copied) {
-        s = run_fwd(x, w, y, g, algo, workspace, workspace_bytes, st);
-        if (s != SN_OK) return s;
-    }
+    s = run_fwd(x, w, y, g, algo, workspace, workspace_bytes, st);
+    if (s != SN_OK) return s;
     return launch_status(launch_bn_stats(y, part, save_mean, save_invstd, g.N, g.K, g.P * g.Q, eps, g.out_bf16, st));
 }
 
