@@ -457,7 +457,8 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
         if (budget == 0 || query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
         if (!chlast_runs(g, dir, SN_ALGO_STAGED, budget, &cl)) break;
         *algo = a;
-        *bytes = a == SN_ALGO_STAGED ? std::max(cl.bytes, std::min(pf, budget)) : cl.bytes;
+        // (never less than the least the name is accepted with, which for IM2COL_GEMM is one unfolded image)
+        *bytes = a == SN_ALGO_STAGED ? std::max(cl.bytes, std::min(pf, budget)) : std::max(cl.bytes, mn);
         if (ms_out) *ms_out = -1.f;
         return SN_OK;
     }

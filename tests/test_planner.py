@@ -128,3 +128,32 @@ def test_backward_filter_workspace_is_a_range():
     assert algo == sn.SN_ALGO_STAGED and used == half + per
     assert sn.sn_conv_plan(shape, sn.SN_CONV_BWD_FILTER, half - per)[0] == sn.SN_ALGO_DIRECT
     assert sn.sn_conv_plan(shape, sn.SN_CONV_BWD_FILTER, mn - 256)[0] == sn.SN_ALGO_DIRECT
+
+
+def _random_shape(rnd):
+    dt = rnd.choice((sn.SN_F32, sn.SN_BF16))
+    R, S = rnd.choice(((1, 1), (3, 3), (3, 3), (5, 5), (7, 7), (1, 7), (7, 1), (4, 3), (11, 11)))
+    stride = rnd.choice(((1, 1), (1, 1), (2, 2), (2, 2), (3, 2), (4, 4)))
+    pad = rnd.choice(((0, 0), ((R - 1) // 2, (S - 1) // 2)))
+    H, W = (rnd.randint(max(R, S), 64) for _ in range(2))
+    C, K = (rnd.choice((3, 8, 24, 64, 160, 288, rnd.randint(1, 400))) for _ in range(2))
+    return sn.conv_shape(rnd.choice((1, 2, 9, 32, 61)), C, H, W, K, R, S, stride, pad, dt, dt)
+
+
+def test_planned_calls_are_accepted_with_the_bytes_planned():
+    """What sn_conv_plan hands out can be called: bytes_used is at least the named algorithm's least workspace and at most
+    the budget, and planning again with it as the budget names the same algorithm with the same bytes."""
+    sn.sn_planner_clear()
+    rnd = random.Random(11)
+    named = {a: 0 for a in ALGOS}
+    for _ in range(4000):
+        shape, d = _random_shape(rnd), rnd.choice(DIRS)
+        budget = rnd.choice((1 << 18, 1 << 22, 32 << 20, 64 << 20, 512 << 20))
+        algo, used, _ = sn.sn_conv_plan(shape, d, budget)
+        mn, pf = sn.sn_conv_workspace_query(shape, d, algo)
+        case = ([getattr(shape, f) for f, _ in shape._fields_], d, budget, algo, used, mn, pf)
+        assert mn <= used <= budget and mn <= pf, case
+        again = sn.sn_conv_plan(shape, d, used)
+        assert again[:2] == (algo, used), case + again
+        named[algo] += 1
+    assert all(named.values()), named
