@@ -376,11 +376,11 @@ sn_status query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *m
         if (phase_plan(g, dir, &pp)) {
             *pref_b = phase_bytes(pp, dir, g.N);
             *min_b = pp.chunkable ? phase_bytes(pp, dir, 1) : *pref_b;
+            // backward-data also runs as the channels-last product: with less than the planes take, and, where it is the
+            // faster one, with all that it wants itself
             ChlastPlan all, one;
-            if (dir == SN_CONV_BWD_DATA && chlast_plan(g, dir, ALL_BYTES, &all) && chlast_least(g, dir, &one)) {
-                *pref_b = all.bytes;
-                *min_b = std::min(std::min(*min_b, one.bytes), all.bytes);
-            }
+            if (dir == SN_CONV_BWD_DATA && chlast_least(g, dir, &one)) *min_b = std::min(*min_b, one.bytes);
+            if (dir == SN_CONV_BWD_DATA && chlast_runs(g, dir, algo, ALL_BYTES, &all)) *pref_b = std::max(*min_b, all.bytes);
             return SN_OK;
         }
         if (dir == SN_CONV_BWD_FILTER) {

@@ -157,3 +157,14 @@ def test_planned_calls_are_accepted_with_the_bytes_planned():
         assert again[:2] == (algo, used), case + again
         named[algo] += 1
     assert all(named.values()), named
+
+
+def test_strided_backward_data_is_given_its_planes():
+    """Where the phase planes run (the channels-last product is not estimated to be faster), the workspace reported and
+    planned holds the planes of the whole batch -- dx once over -- so that they run in one pass."""
+    sn.sn_planner_clear()
+    for N, C, H, K in ((52, 240, 16, 64), (9, 96, 32, 64)):
+        shape = sn.conv_shape(N, C, H, H, K, 3, 3, (2, 2), (1, 1), sn.SN_BF16, sn.SN_BF16)
+        _, pf = sn.sn_conv_workspace_query(shape, sn.SN_CONV_BWD_DATA, sn.SN_ALGO_STAGED)
+        algo, used, _ = sn.sn_conv_plan(shape, sn.SN_CONV_BWD_DATA, 512 << 20)
+        assert algo == sn.SN_ALGO_STAGED and used == pf >= N * C * H * H * 2
