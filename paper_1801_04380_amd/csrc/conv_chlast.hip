@@ -10,6 +10,7 @@ namespace {
 
 constexpr size_t WS_ALIGN = 256;
 constexpr size_t COPY_MAX = (size_t)1 << 30;   // bytes of one pass's copy: 32-bit offsets, bit 31 marks "outside"
+constexpr size_t IMAGE_MAX = (size_t)1 << 31;  // below this, bytes of a source image: likewise (a stride may leave most of it out of the copy)
 
 // Tiles, and what they take: a workgroup alone on its compute unit needs `alone` us per stage of its reduction; with
 // more workgroups than compute units, a compute unit gets through one workgroup's stage in `busy` us (fp32 first, bf16
@@ -198,7 +199,7 @@ size_t fwd_bytes(FwdPlan *f, int nimg)
 // The plan under a budget: the fewest passes that fit (halving); false if not even one image does.
 bool fwd_plan(const ConvGeom &g, bool bwd, size_t budget, FwdPlan *f)
 {
-    if (!fwd_geometry(g, bwd, f)) return false;
+    if (!fwd_geometry(g, bwd, f) || (size_t)f->Cr * f->SH * f->SW * f->sz >= IMAGE_MAX) return false;
     const size_t per = (size_t)f->planes * f->Hp * f->Ws * f->Cp * f->sz;
     if (per > COPY_MAX) return false;
     const int cap = (int)std::min<size_t>(g.N, COPY_MAX / per);
@@ -376,7 +377,7 @@ size_t w_bytes(const ConvGeom &g, WPlan *f, int nimg)
 // for partial sums).
 bool w_plan(const ConvGeom &g, size_t budget, WPlan *f)
 {
-    if (!w_geometry(g, f)) return false;
+    if (!w_geometry(g, f) || std::max((size_t)g.C * g.H * g.W, (size_t)g.K * g.P * g.Q) * f->sz >= IMAGE_MAX) return false;
     const size_t per = (size_t)f->planes * f->Pp * f->Ws * f->Cp * f->sz, dper = (size_t)f->Pp * f->Qp * f->Kp * f->sz;
     if (std::max(per, dper) > COPY_MAX) return false;
     const int cap = (int)std::min<size_t>(g.N, COPY_MAX / std::max(per, dper)), bf16 = f->sz == 2;

@@ -79,7 +79,7 @@ __device__ void stage_block(const ClStage &s, int blk, char *lds)
     constexpr int PE = Elem<T>::PE;
     const T *src = static_cast<const T *>(s.src);
     T *dst = static_cast<T *>(s.dst);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int HpWs = s.Hp * s.Ws;
     int pt = blk % s.ptiles, rest = blk / s.ptiles;
     if (s.Cp <= PE) {   // few channels: a pixel is one store of Cp elements, no transposition
@@ -112,7 +112,8 @@ __device__ void stage_block(const ClStage &s, int blk, char *lds)
         const int i = pix / s.Ws, w = pix - i * s.Ws - s.pl, h = i * s.sh + a - s.pt;
         const bool in = pix < HpWs && (unsigned)h < (unsigned)s.H && (unsigned)w < (unsigned)s.W;
         // range-checked loads: pixels outside the image and channels past the last bring zeros, and all 16 (8) loads
-        // of a thread are on their way together
+        // of a thread are on their way together.  (An image of less than 2 GiB: the plans see to it.  A channel past the
+        // last reads behind the last channel's scalar offset, so that a lane's OUTSIDE never comes back into range.)
         const uint32_t HW = (uint32_t)s.H * s.W * sizeof(T);
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<T *>(src) + (size_t)n * s.C * s.H * s.W, 0, (uint32_t)s.C * HW, 0x00020000);
@@ -123,9 +124,9 @@ __device__ void stage_block(const ClStage &s, int blk, char *lds)
             const int c0 = (ct * 8 + wave + 4 * k) * PE;
 #pragma unroll
             for (int c = 0; c < PE; ++c) {
-                const uint32_t vo = c0 + c < s.C ? v0 : OUTSIDE;
-                if constexpr (sizeof(T) == 2) v[k][c] = (T)__builtin_amdgcn_raw_buffer_load_b16(rs, vo, (uint32_t)(c0 + c) * HW, 0);
-                else v[k][c] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, vo, (uint32_t)(c0 + c) * HW, 0));
+                const uint32_t vo = c0 + c < s.C ? v0 : OUTSIDE, so = (uint32_t)min(c0 + c, s.C - 1) * HW;
+                if constexpr (sizeof(T) == 2) v[k][c] = (T)__builtin_amdgcn_raw_buffer_load_b16(rs, vo, so, 0);
+                else v[k][c] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, vo, so, 0));
             }
         }
 #pragma unroll

@@ -59,3 +59,24 @@ def test_matches_oracle(name, dtype):
         want = ref()
         assert rel_l2(f64(got), want) <= TOL[dtype], (name, d)
         assert elementwise_excess(f64(got), want, TOL[dtype], t == torch.bfloat16) <= 0, (name, d)
+
+
+@pytest.mark.parametrize("C", [33, 64], ids=["past_2GiB", "4GiB"])
+def test_image_beyond_32_bit_offsets(C):
+    """A stride larger than the filter leaves most of an image out of the copy: the copy is small where the image itself is
+    beyond what 32-bit byte offsets address, and the call still answers (by unfolding)."""
+    K, H, stride = 8, 4096, 8
+    shape = sn.conv_shape(1, C, H, H, K, 1, 1, (stride, stride), (0, 0), sn.SN_F32, sn.SN_F32)
+    gen = torch.Generator(device="cuda").manual_seed(C)
+    x = torch.randn((1, C, H, H), generator=gen, device="cuda")
+    w = torch.randn((K, C, 1, 1), generator=gen, device="cuda")
+    dy = torch.randn((1, K, H // stride, H // stride), generator=gen, device="cuda")
+    y, dw = torch.full_like(dy, float("nan")), torch.full_like(w, float("nan"))
+    for d, fn, a, b, out in ((sn.SN_CONV_FWD, sn.sn_conv2d_fwd, x, w, y), (sn.SN_CONV_BWD_FILTER, sn.sn_conv2d_bwd_filter, x, dy, dw)):
+        ws = torch.empty(sn.sn_conv_workspace_query(shape, d, sn.SN_ALGO_IM2COL_GEMM)[0], dtype=torch.uint8, device="cuda")
+        print("C", C, "dir", d, flush=True)
+        fn(a, b, out, shape, sn.SN_ALGO_IM2COL_GEMM, ws)
+        torch.cuda.synchronize()
+    xs = f64(x[0, :, ::stride, ::stride].contiguous()).reshape(C, -1)
+    assert rel_l2(f64(y).reshape(K, -1), f64(w).reshape(K, C) @ xs) <= TOL["f32"]
+    assert rel_l2(f64(dw).reshape(K, C), f64(dy).reshape(K, -1) @ xs.T) <= TOL["f32"]
