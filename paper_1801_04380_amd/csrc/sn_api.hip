@@ -284,6 +284,17 @@ bool scatter_bwd_data(const ConvGeom &g) { return (g.sh > 1 || g.sw > 1) && poin
 // else, and every budget below that, takes the gathering kernel.
 bool phase_fwd_when_it_fits(const ConvGeom &g) { return g.R == 1 && g.S == 1 && g.K >= 512; }
 
+// Winograd pays four kernels per pass and streams 16 transformed values per 4 inputs: a guess in its favour only where a
+// pass has real work and the products outweigh the transforms (measured: 64 x 128 channels gain, 64 x 64 lose).
+bool winograd_guessed(const ConvGeom &g, sn_conv_dir dir, size_t budget)
+{
+    const bool bwd = dir == SN_CONV_BWD_DATA;
+    if (dir == SN_CONV_BWD_FILTER || !winograd_supported(g, bwd) || (long long)g.C * g.K < 8192) return false;
+    size_t mn = 0, pf = 0;
+    winograd_bytes(g, bwd, &mn, &pf);
+    return mn <= budget && (pf <= budget || winograd_pass_tiles(g, bwd, budget) >= 2048);
+}
+
 // ---- the channels-last product (conv_chlast.h) ---------------------------------------------------
 // It needs workspace for copies of whole tensors and runs every geometry, so it carries no name of its own: with enough
 // workspace it is what STAGED runs where it is faster than STAGED's other kernels, and what IM2COL_GEMM runs instead of
@@ -291,11 +302,12 @@ bool phase_fwd_when_it_fits(const ConvGeom &g) { return g.R == 1 && g.S == 1 && 
 
 // Estimated us of what runs instead (0: always keep that).  Kernels that read their operands where they are -- few input
 // channels, 1x1 layers, 1x1 / stride-2 layers written or gathered directly -- were faster on every shape measured.
-double other_us(const ConvGeom &g, sn_conv_dir dir)
+double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
 {
     // the general kernels at their best (they were never faster than the product given enough workspace)
     const double flops = 2.0 * g.N * g.K * g.C * g.R * g.S * g.P * g.Q, general = 10 + flops / (g.in_bf16 ? 1.5e8 : 7e7);
-    if (!g.in_bf16) return general;
+    // fp32: or WINOGRAD (8 x 256 x 56x56, 256 channels, 512 MiB: 230 us, the product 275; 16 x 144 x 32x17 -> 312, 64 MiB: 108 and 80)
+    if (!g.in_bf16) return winograd_guessed(g, dir, ws_bytes) ? std::min(general, winograd_us(g, dir == SN_CONV_BWD_DATA, ws_bytes)) : general;
     if (smallc_supported(g) && dir != SN_CONV_BWD_DATA) return 0;
     if (dir == SN_CONV_BWD_FILTER) {
         if (g.sh > 1 || g.sw > 1 || !tile_wgrad_supported(g)) return general;
@@ -320,7 +332,7 @@ double other_us(const ConvGeom &g, sn_conv_dir dir)
 bool chlast_runs(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t ws_bytes, ChlastPlan *plan)
 {
     if (ws_bytes == 0 || (algo != SN_ALGO_STAGED && algo != SN_ALGO_IM2COL_GEMM)) return false;
-    double other = algo == SN_ALGO_IM2COL_GEMM ? 1e9 : other_us(g, dir);
+    double other = algo == SN_ALGO_IM2COL_GEMM ? 1e9 : other_us(g, dir, ws_bytes);
     // less than half of the row-stationary kernel's partial sums: atomics (64 x 256 x 20x20 -> 128: 42 us, with them 15)
     if (dir == SN_CONV_BWD_FILTER && g.R == 3 && rows_wgrad_supported(g) && rows_wgrad_partial_bytes(g) / 2 > ws_bytes) other += 30;
     if (other <= CHLAST_LEAST_US || !chlast_plan(g, dir, ws_bytes, plan)) return false;
@@ -474,11 +486,7 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
         size_t mn = 0, pf = 0;
         if (query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
         if (a == SN_ALGO_STAGED && pf == 0) continue;   // nothing to stage: the same kernel runs as DIRECT
-        // Winograd pays four kernels per pass and streams 16 transformed values per 4 inputs: a guess in its
-        // favour only where a pass has real work and the products outweigh the transforms (measured: 64 x 128
-        // channels gain, 64 x 64 lose)
-        if (a == SN_ALGO_WINOGRAD && ((pf > budget && winograd_pass_tiles(g, dir == SN_CONV_BWD_DATA, budget) < 2048) ||
-                                      (long long)g.C * g.K < 8192)) continue;
+        if (a == SN_ALGO_WINOGRAD && !winograd_guessed(g, dir, budget)) continue;
         // The phase planes in passes: strided forward gains little over the zero-workspace kernel, so only
         // with the whole batch (below that STAGED forward is the gathering kernel, which needs the re-laid-out
         // filter alone); backward-data gains a quarter over the zero-workspace kernel, which works by residue

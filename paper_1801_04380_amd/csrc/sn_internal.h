@@ -150,6 +150,7 @@ hipError_t launch_phase_dw(const float *dwp, float *dw, const PhaseMap &m, const
 bool winograd_supported(const ConvGeom &g, bool bwd_data);
 void winograd_bytes(const ConvGeom &g, bool bwd_data, size_t *min_b, size_t *pref_b);
 long long winograd_pass_tiles(const ConvGeom &g, bool bwd_data, size_t ws_bytes);
+double winograd_us(const ConvGeom &g, bool bwd_data, size_t ws_bytes);   // estimate
 hipError_t launch_winograd(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, void *ws,
                            size_t ws_bytes, hipStream_t st);
 

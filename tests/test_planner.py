@@ -168,3 +168,15 @@ def test_strided_backward_data_is_given_its_planes():
         _, pf = sn.sn_conv_workspace_query(shape, sn.SN_CONV_BWD_DATA, sn.SN_ALGO_STAGED)
         algo, used, _ = sn.sn_conv_plan(shape, sn.SN_CONV_BWD_DATA, 512 << 20)
         assert algo == sn.SN_ALGO_STAGED and used == pf >= N * C * H * H * 2
+
+
+def test_cold_start_weighs_winograd_against_the_product():
+    """fp32 3x3: WINOGRAD's fewer products win on many channels and tiles (8 x 256 x 56x56, 512 MiB: 230 us against 275), the
+    product over channels-last copies, whose copies are cheaper than the transforms, on fewer (16 x 144 x 32x17 -> 312, 64 MiB:
+    80 us against 108)."""
+    sn.sn_planner_clear()
+    for N, C, H, W, K, mib, algo in ((8, 256, 56, 56, 256, 512, sn.SN_ALGO_WINOGRAD), (4, 512, 61, 61, 512, 256, sn.SN_ALGO_WINOGRAD),
+                                     (16, 144, 32, 17, 312, 64, sn.SN_ALGO_IM2COL_GEMM), (8, 64, 69, 69, 64, 512, sn.SN_ALGO_IM2COL_GEMM)):
+        shape = sn.conv_shape(N, C, H, W, K, 3, 3, (1, 1), (1, 1), sn.SN_F32, sn.SN_F32)
+        for d in (sn.SN_CONV_FWD, sn.SN_CONV_BWD_DATA):
+            assert sn.sn_conv_plan(shape, d, mib << 20)[0] == algo, (N, C, H, d)
