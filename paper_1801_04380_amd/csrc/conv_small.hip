@@ -6,7 +6,8 @@
 // layer is 32 workgroups without a barrier in the reduction: per channel a lane has its nine inputs in flight at once
 // and the filter taps come once per wave, and the partial sums meet in LDS in a fixed order.
 // Time of a call, general kernel -> this one: 2 x 16 x 16x16, 16 channels, forward 19 -> 8 us, backward-data 29 -> 9 us;
-// 4 x 32 x 16x16, 32 channels, 35 -> 9.6 and 55 -> 9.2 us.
+// 4 x 32 x 16x16, 32 channels, 35 -> 9.6 and 55 -> 9.2 us.  60 layers of 2.2e6 to 15.8e6 multiplications (1 to 8 images, 4 to 254
+// channels, planes of 4x4 to 63x63): forward 1.02 to 6.4 times faster, backward-data 1.65 to 9.3 times.
 #include "sn_internal.h"
 
 namespace sn {
@@ -19,12 +20,11 @@ struct Small3x3 {
     int IH, IW, OH, OW;
     int off_h, off_w;          // input row / column of output pixel (0, 0)'s first tap
     int w_so, w_sr;            // strides of an output / reduction channel in the filter
-    int out_bf16;
 };
 
 template <bool FLIP>
 __global__ void __launch_bounds__(64 * WAVES)
-small3x3_kernel(const float *__restrict__ in, const float *__restrict__ w, void *__restrict__ out, const Small3x3 p)
+small3x3_kernel(const float *__restrict__ in, const float *__restrict__ w, float *__restrict__ out, const Small3x3 p)
 {
     __shared__ float sums[WAVES][KO][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -64,9 +64,7 @@ small3x3_kernel(const float *__restrict__ in, const float *__restrict__ w, void 
     const int o = o0 + wave;   // wave k finishes output channel k
     if (pix >= p.npix || o >= p.M) return;
     const float v = (sums[0][wave][lane] + sums[1][wave][lane]) + (sums[2][wave][lane] + sums[3][wave][lane]);
-    const size_t to = ((size_t)n * p.M + o) * ohw + at;
-    if (p.out_bf16) static_cast<bf16_t *>(out)[to] = f32_to_bf16(v);
-    else static_cast<float *>(out)[to] = v;
+    out[((size_t)n * p.M + o) * ohw + at] = v;
 }
 
 }  // namespace
@@ -92,11 +90,11 @@ hipError_t launch_small3x3(const void *in, const void *w, void *out, const ConvG
     p.off_w = bwd ? g.pw - 2 : -g.pw;
     p.w_so = bwd ? 9 : g.C * 9;
     p.w_sr = bwd ? g.C * 9 : 9;
-    p.out_bf16 = g.out_bf16;
     const dim3 grid((p.npix + 63) / 64, (p.M + KO - 1) / KO), block(64 * WAVES);
     const float *a = static_cast<const float *>(in), *b = static_cast<const float *>(w);
-    if (bwd) hipLaunchKernelGGL(small3x3_kernel<true>, grid, block, 0, st, a, b, out, p);
-    else hipLaunchKernelGGL(small3x3_kernel<false>, grid, block, 0, st, a, b, out, p);
+    float *o = static_cast<float *>(out);
+    if (bwd) hipLaunchKernelGGL(small3x3_kernel<true>, grid, block, 0, st, a, b, o, p);
+    else hipLaunchKernelGGL(small3x3_kernel<false>, grid, block, 0, st, a, b, o, p);
     return hipGetLastError();
 }
 

@@ -154,8 +154,9 @@ double winograd_us(const ConvGeom &g, bool bwd_data, size_t ws_bytes);   // esti
 hipError_t launch_winograd(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, void *ws,
                            size_t ws_bytes, hipStream_t st);
 
-// fp32 3x3 / stride-1 forward and backward-data of small problems (conv_small.hip), no workspace.  Up to 9e6 products it was 1.4 to 6
-// times faster than the general kernel; its time grows with the products, the general kernel's with the reduction alone.
+// fp32 3x3 / stride-1 forward and backward-data of small problems (conv_small.hip), no workspace.  Up to this many products it was
+// never slower than the general kernel (60 layers timed, conv_small.hip) and mostly 2 to 8 times faster; its time grows with
+// the products, the general kernel's with the reduction alone, and beyond it is not measured.
 constexpr long long SMALL3X3_MACS = 1LL << 24;
 bool small3x3_supported(const ConvGeom &g, bool bwd_data);
 hipError_t launch_small3x3(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, hipStream_t st);

@@ -1,4 +1,5 @@
-"""The 3x3 / stride-1 kernel of small problems (csrc/conv_small.hip), forward and backward-data, against the oracle."""
+"""The fp32 3x3 / stride-1 kernel of small problems (csrc/conv_small.hip), forward and backward-data, against the oracle; the
+bf16 halves run the zero-workspace kernels that take the same layers in bf16."""
 import numpy as np
 import pytest
 import torch
