@@ -497,6 +497,19 @@ bool chlast_plan(const ConvGeom &g, int dir, size_t budget, ChlastPlan *plan)
     return true;
 }
 
+void chlast_config(const ChlastPlan &plan, int dir, int *tile_m, int *tile_n, int *threads, int *slices)
+{
+    const bool w = dir == SN_CONV_BWD_FILTER;
+    const WPlan &f = *reinterpret_cast<const WPlan *>(plan.mem);
+    const FwdPlan &d = *reinterpret_cast<const FwdPlan *>(plan.mem);
+    const int cfg = w ? f.cfg : d.cfg;
+    const Tile &t = w ? kWTile[cfg] : kTile[cfg];
+    *tile_m = t.bm;
+    *tile_n = t.bn;
+    *threads = cfg >= 3 ? 512 : 256;
+    *slices = w ? f.nsl : d.nsplit;
+}
+
 hipError_t launch_chlast(const void *a, const void *b, void *out, const ConvGeom &g, int dir, void *ws, ChlastPlan *plan, hipStream_t st)
 {
     if (dir == SN_CONV_BWD_FILTER) {

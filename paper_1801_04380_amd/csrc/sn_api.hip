@@ -765,6 +765,20 @@ sn_status sn_conv_workspace_query(const sn_conv_shape *shape, sn_conv_dir dir, s
     return query(g, dir, algo, min_bytes, preferred_bytes);
 }
 
+// For the tests (not in the header): whether the named call runs the channels-last product with this workspace, and as
+// what: tile, threads, reduction slices, passes over the batch, bytes it uses; its estimated time.
+int sn_chlast_inspect(const sn_conv_shape *shape, int dir, int algo, size_t workspace_bytes, int info[5], size_t *bytes, double *us)
+{
+    ConvGeom g;
+    ChlastPlan cl;
+    if (make_geom(shape, &g) != SN_OK || !chlast_runs(g, (sn_conv_dir)dir, (sn_conv_algo)algo, workspace_bytes, &cl)) return 0;
+    chlast_config(cl, dir, &info[0], &info[1], &info[2], &info[3]);
+    info[4] = cl.passes;
+    *bytes = cl.bytes;
+    *us = cl.us;
+    return 1;
+}
+
 sn_status sn_conv_plan(const sn_conv_shape *shape, sn_conv_dir dir, size_t budget_bytes, sn_conv_algo *algo,
                        size_t *bytes_used, float *predicted_ms)
 {

@@ -172,6 +172,7 @@ struct ChlastPlan {
 constexpr double CHLAST_LEAST_US = 10.5;   // its launches alone: what runs in less needs no plan to compare with
 bool chlast_plan(const ConvGeom &g, int dir, size_t budget, ChlastPlan *plan);
 hipError_t launch_chlast(const void *a, const void *b, void *out, const ConvGeom &g, int dir, void *ws, ChlastPlan *plan, hipStream_t st);
+void chlast_config(const ChlastPlan &plan, int dir, int *tile_m, int *tile_n, int *threads, int *slices);   // of a plan made
 
 // Cheap layers.
 hipError_t launch_relu_fwd(const void *x, void *y, size_t n, int bf16, hipStream_t st);

@@ -1,18 +1,22 @@
 """The channels-last product (conv_chlast): every geometry through IM2COL_GEMM with a workspace that holds the copies, at
 the sizes where it can go wrong -- filter runs that end inside a stage, output tiles with one row or pixel over, reduction
-slices, residue classes without taps, passes over parts of the batch -- against the fp64 oracle."""
+slices, residue classes without taps, passes over parts of the batch -- against the fp64 oracle; and every tile by name, with
+a row, a pixel or a column over, where the library's own plan says that it runs."""
+import ctypes
+
 import pytest
 import torch
 
 import oracle
 import paper_1801_04380_amd as sn
+from paper_1801_04380_amd import _lib
 from paper_1801_04380_amd import workloads as wl
-from _parity import TOL, elementwise_excess, f64, rel_l2, shape_of
+from _parity import CODE, TOL, elementwise_excess, f64, rel_l2, shape_of
 
 pytestmark = pytest.mark.gpu
 
 KiB, BIG = 1 << 10, 64 << 20
-# N, C, H, W, K, R, S, stride, pad, workspace
+# N, C, H, W, K, R, S, stride, pad, workspace (shapes; which tile takes them is the plan's: TILES below holds it to one)
 CASES = {
     "tile_64x64_one_over": (3, 24, 9, 7, 65, 3, 3, (1, 1), (1, 1), BIG),
     "reduction_slices": (2, 256, 14, 14, 96, 3, 3, (1, 1), (1, 1), BIG),
@@ -31,34 +35,106 @@ CASES = {
 }
 
 
+def _inspect(shape, d, ws_bytes):
+    """What the library would run for IM2COL_GEMM with this workspace: ((tile m, tile n, threads), slices, passes, bytes),
+    or None if not the product."""
+    info, used, us = (ctypes.c_int * 5)(), ctypes.c_size_t(), ctypes.c_double()
+    if not _lib.load().sn_chlast_inspect(ctypes.byref(shape), d, sn.SN_ALGO_IM2COL_GEMM, ctypes.c_size_t(ws_bytes), info,
+                                         ctypes.byref(used), ctypes.byref(us)):
+        return None
+    return tuple(info[:3]), info[3], info[4], used.value
+
+
+def _check(name, case, dtype, d, ws_bytes):
+    N, C, H, W, K, R, S, stride, pad = case
+    layer = wl.Layer(name, C, H, W, K, R, S, stride, pad, False, None, 1, False, None)
+    x, w, dy = wl.conv_inputs(layer, N, dtype, 4711)
+    shape = shape_of(layer, N, dtype, dtype)
+    t = torch.float32 if d == sn.SN_CONV_BWD_FILTER or dtype == "f32" else torch.bfloat16
+    P, Q = wl.out_hw(layer)
+    fn, a, b, dims, ref = {
+        sn.SN_CONV_FWD: (sn.sn_conv2d_fwd, x, w, (N, K, P, Q), lambda: oracle.conv2d_fwd(f64(x), f64(w), stride, pad)),
+        sn.SN_CONV_BWD_DATA: (sn.sn_conv2d_bwd_data, dy, w, (N, C, H, W),
+                              lambda: oracle.conv2d_bwd_data(f64(dy), f64(w), x.shape, stride, pad)),
+        sn.SN_CONV_BWD_FILTER: (sn.sn_conv2d_bwd_filter, x, dy, (K, C, R, S),
+                                lambda: oracle.conv2d_bwd_filter(f64(x), f64(dy), w.shape, stride, pad))}[d]
+    got = torch.full(dims, float("nan"), dtype=t, device="cuda")
+    ws = torch.full((ws_bytes,), 255, dtype=torch.uint8, device="cuda")   # NaNs: nothing unwritten may be used
+    print(name, dtype, "dir", d, "ws", ws_bytes, flush=True)
+    fn(a.cuda(), b.cuda(), got, shape, sn.SN_ALGO_IM2COL_GEMM, ws)
+    torch.cuda.synchronize()
+    want = ref()
+    assert rel_l2(f64(got), want) <= TOL[dtype], (name, d)
+    assert elementwise_excess(f64(got), want, TOL[dtype], t == torch.bfloat16) <= 0, (name, d)
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("name", list(CASES))
 def test_matches_oracle(name, dtype):
-    N, C, H, W, K, R, S, stride, pad, budget = CASES[name]
-    if dtype == "f32" and N * C * H * W * K > 1 << 28:
-        pytest.skip("the larger tiles are bf16 only")
-    layer = wl.Layer(name, C, H, W, K, R, S, stride, pad, False, None, 1, False, None)
-    x, w, dy = wl.conv_inputs(layer, N, dtype, 4711)
-    xo, wo, dyo = f64(x), f64(w), f64(dy)
-    shape = shape_of(layer, N, dtype, dtype)
-    out_t = torch.bfloat16 if dtype == "bf16" else torch.float32
-    P, Q = wl.out_hw(layer)
-    xd, wd, dyd = x.cuda(), w.cuda(), dy.cuda()
-    runs = [(sn.SN_CONV_FWD, sn.sn_conv2d_fwd, xd, wd, (N, K, P, Q), out_t, lambda: oracle.conv2d_fwd(xo, wo, stride, pad)),
-            (sn.SN_CONV_BWD_DATA, sn.sn_conv2d_bwd_data, dyd, wd, (N, C, H, W), out_t,
-             lambda: oracle.conv2d_bwd_data(dyo, wo, xo.shape, stride, pad)),
-            (sn.SN_CONV_BWD_FILTER, sn.sn_conv2d_bwd_filter, xd, dyd, (K, C, R, S), torch.float32,
-             lambda: oracle.conv2d_bwd_filter(xo, dyo, wo.shape, stride, pad))]
-    for d, fn, a, b, dims, t, ref in runs:
+    *case, budget = CASES[name]
+    N, C, H, W, K, R, S, stride, pad = case
+    shape = sn.conv_shape(N, C, H, W, K, R, S, stride, pad, CODE[dtype], CODE[dtype])
+    for d in (sn.SN_CONV_FWD, sn.SN_CONV_BWD_DATA, sn.SN_CONV_BWD_FILTER):
         ws_bytes = max(budget, sn.sn_conv_workspace_query(shape, d, sn.SN_ALGO_IM2COL_GEMM)[0])
-        got = torch.full(dims, float("nan"), dtype=t, device="cuda")
-        ws = torch.full((ws_bytes,), 255, dtype=torch.uint8, device="cuda")   # NaNs: nothing unwritten may be used
-        print(name, dtype, "dir", d, flush=True)
-        fn(a, b, got, shape, sn.SN_ALGO_IM2COL_GEMM, ws)
-        torch.cuda.synchronize()
-        want = ref()
-        assert rel_l2(f64(got), want) <= TOL[dtype], (name, d)
-        assert elementwise_excess(f64(got), want, TOL[dtype], t == torch.bfloat16) <= 0, (name, d)
+        assert _inspect(shape, d, ws_bytes), (name, d)
+        _check(name, case, dtype, d, ws_bytes)
+
+
+F, D, B = sn.SN_CONV_FWD, sn.SN_CONV_BWD_DATA, sn.SN_CONV_BWD_FILTER
+# (dtype, direction, (tile m, tile n, threads), sliced), N, C, H, W, K, R, S, stride, pad: output channels, pixels and columns that
+# are no whole number of tiles, planes of odd and even size, reductions longer than the ring of stages
+TILES = [
+    ("f32", F, (128, 128, 256), False, 7, 9, 99, 37, 65, 3, 3, (1, 1), (1, 1)),
+    ("f32", F, (128, 128, 256), True, 7, 17, 17, 69, 65, 5, 5, (1, 1), (2, 2)),
+    ("f32", F, (64, 64, 256), True, 2, 33, 11, 5, 65, 3, 3, (1, 1), (1, 1)),
+    ("f32", D, (128, 128, 256), True, 3, 65, 59, 47, 129, 3, 1, (1, 1), (1, 0)),
+    ("f32", D, (128, 128, 256), False, 7, 65, 75, 49, 193, 1, 1, (2, 2), (0, 0)),
+    ("f32", D, (64, 64, 256), False, 2, 65, 17, 5, 257, 1, 1, (2, 2), (0, 0)),
+    ("bf16", F, (128, 128, 256), False, 5, 17, 91, 93, 65, 3, 3, (1, 1), (1, 1)),
+    ("bf16", F, (128, 128, 256), False, 16, 17, 83, 81, 129, 3, 3, (2, 2), (1, 1)),
+    ("bf16", F, (128, 128, 512), False, 15, 17, 69, 25, 65, 3, 3, (1, 1), (1, 1)),
+    ("bf16", F, (128, 128, 512), True, 15, 257, 43, 49, 65, 3, 3, (2, 2), (1, 1)),
+    ("bf16", F, (256, 256, 512), False, 16, 17, 85, 37, 193, 3, 3, (1, 1), (1, 1)),
+    ("bf16", F, (64, 256, 256), False, 5, 17, 91, 79, 129, 3, 3, (1, 1), (1, 1)),
+    ("bf16", F, (64, 256, 256), True, 7, 257, 32, 55, 9, 3, 3, (1, 1), (1, 1)),
+    ("bf16", F, (64, 64, 256), True, 1, 65, 22, 6, 65, 5, 5, (2, 2), (2, 2)),
+    ("bf16", D, (128, 128, 256), False, 5, 65, 83, 99, 65, 3, 1, (1, 1), (1, 0)),
+    ("bf16", D, (128, 128, 512), False, 16, 65, 93, 85, 321, 1, 1, (2, 2), (0, 0)),
+    ("bf16", D, (128, 128, 512), True, 7, 65, 17, 69, 257, 3, 3, (1, 1), (1, 1)),
+    ("bf16", D, (256, 256, 512), False, 128, 256, 48, 52, 9, 1, 1, (2, 2), (0, 0)),
+    ("bf16", D, (64, 256, 256), False, 9, 129, 53, 71, 72, 3, 1, (1, 1), (1, 0)),
+    ("bf16", D, (64, 64, 256), False, 3, 65, 5, 5, 9, 5, 5, (1, 1), (2, 2)),
+    ("f32", B, (64, 64, 256), True, 1, 17, 57, 64, 129, 5, 5, (2, 2), (2, 2)),
+    ("bf16", B, (128, 128, 256), True, 7, 9, 61, 54, 129, 3, 3, (1, 1), (1, 1)),
+    ("bf16", B, (64, 128, 256), True, 16, 9, 46, 63, 9, 3, 3, (2, 2), (1, 1)),
+    ("bf16", B, (64, 64, 256), False, 1, 513, 24, 14, 129, 3, 3, (2, 2), (1, 1)),
+    ("bf16", B, (256, 256, 512), True, 33, 513, 13, 9, 129, 5, 5, (1, 1), (2, 2)),
+]
+
+
+@pytest.mark.parametrize("case", TILES, ids=lambda c: "%s-%s-%dx%dx%d%s-%d" % (c[0], "fdb"[c[1]], *c[2], "-sliced" * c[3], c[5]))
+def test_each_tile(case):
+    dtype, d, tile, sliced, *rest = case
+    N, C, H, W, K, R, S, stride, pad = rest
+    shape = sn.conv_shape(N, C, H, W, K, R, S, stride, pad, CODE[dtype], CODE[dtype])
+    ran = _inspect(shape, d, BIG)
+    assert ran and ran[0] == tile and (ran[1] > 1) == sliced and ran[2] == 1, ran
+    _check("tile", rest, dtype, d, BIG)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d", [F, D, B], ids=["fwd", "bwd_data", "bwd_filter"])
+def test_passes_over_the_batch(d, dtype):
+    """A byte less than one pass takes: two passes, the second of fewer images."""
+    case = (7, 24, 20, 21, 40, 3, 3, (2, 2), (1, 1))
+    shape = sn.conv_shape(*case, CODE[dtype], CODE[dtype])
+    whole = _inspect(shape, d, BIG)
+    ws_bytes = whole[3]
+    while _inspect(shape, d, ws_bytes)[2] == 1:
+        ws_bytes = _inspect(shape, d, ws_bytes)[3] - 256
+    assert whole[2] == 1 and _inspect(shape, d, ws_bytes)[2] == 2
+    assert ws_bytes >= sn.sn_conv_workspace_query(shape, d, sn.SN_ALGO_IM2COL_GEMM)[0]
+    _check("passes", case, dtype, d, ws_bytes)
 
 
 @pytest.mark.parametrize("C", [33, 64], ids=["past_2GiB", "4GiB"])
