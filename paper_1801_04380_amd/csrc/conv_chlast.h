@@ -95,7 +95,8 @@ struct ClWgrad {
     int in_sw, sh;
     int Ws;                     // columns of the x copy
     unsigned plane_bytes, x_bytes, d_bytes;
-    int nflat;                  // flat pixels
+    int P, Q, Pp, Qp;           // output plane, and its pitch in the copies
+    int holes, dp, dq;          // whether the pitch is larger; rows (mod Pp) and columns of the pitch that a stage's pixels are
     int steps, sps;             // reduction stages in all, per slice
     int ktiles, jtiles, nsl;    // tiles, slices of this launch
     int slice0;                 // first slice's number among all partial sums

@@ -231,11 +231,11 @@ ClStage stage_job(const void *src, void *dst, int C, int H, int W, int nimg, int
     return s;
 }
 
-template <typename T, int BM, int BN, int WM, int WN, int NST>
-hipError_t launch_gemm(const void *xs, const void *ap, void *y, float *part, const ClGemm &p, hipStream_t st)
+template <typename T, int BM, int BN, int WM, int WN, int NST, bool HALF>
+hipError_t launch_gemm_as(const void *xs, const void *ap, void *y, float *part, const ClGemm &p, hipStream_t st)
 {
     constexpr int lds = NST * (BM + BN) * 128;
-    auto kern = cl_gemm_kernel<T, BM, BN, WM, WN, NST>;
+    auto kern = cl_gemm_kernel<T, BM, BN, WM, WN, NST, HALF>;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL(kern, dim3(8 * p.ppx * p.mtiles, p.nsplit), dim3(64 * WM * WN), lds, st, static_cast<const T *>(xs),
@@ -243,15 +243,23 @@ hipError_t launch_gemm(const void *xs, const void *ap, void *y, float *part, con
     return hipGetLastError();
 }
 
-template <typename T>
-hipError_t launch_cfg(int cfg, const void *xs, const void *ap, void *y, float *part, const ClGemm &p, hipStream_t st)
+template <typename T, int BM, int BN, int WM, int WN, int NST>
+hipError_t launch_gemm(const void *xs, const void *ap, void *y, float *part, const ClGemm &p, int half, hipStream_t st)
 {
-    if (cfg == 0) return launch_gemm<T, 128, 128, 2, 2, 2>(xs, ap, y, part, p, st);
-    if (cfg == 2) return launch_gemm<T, 64, 64, 2, 2, 3>(xs, ap, y, part, p, st);
+    if constexpr (sizeof(T) == 2)
+        if (half) return launch_gemm_as<T, BM, BN, WM, WN, NST, true>(xs, ap, y, part, p, st);
+    return launch_gemm_as<T, BM, BN, WM, WN, NST, false>(xs, ap, y, part, p, st);
+}
+
+template <typename T>
+hipError_t launch_cfg(int cfg, const void *xs, const void *ap, void *y, float *part, const ClGemm &p, int half, hipStream_t st)
+{
+    if (cfg == 0) return launch_gemm<T, 128, 128, 2, 2, 2>(xs, ap, y, part, p, half, st);
+    if (cfg == 2) return launch_gemm<T, 64, 64, 2, 2, 3>(xs, ap, y, part, p, half, st);
     if constexpr (sizeof(T) == 2) {
-        if (cfg == 1) return launch_gemm<T, 64, 256, 1, 4, 2>(xs, ap, y, part, p, st);
-        if (cfg == 3) return launch_gemm<T, 256, 256, 2, 4, 2>(xs, ap, y, part, p, st);
-        if (cfg == 4) return launch_gemm<T, 128, 128, 2, 4, 4>(xs, ap, y, part, p, st);
+        if (cfg == 1) return launch_gemm<T, 64, 256, 1, 4, 2>(xs, ap, y, part, p, half, st);
+        if (cfg == 3) return launch_gemm<T, 256, 256, 2, 4, 2>(xs, ap, y, part, p, half, st);
+        if (cfg == 4) return launch_gemm<T, 128, 128, 2, 4, 4>(xs, ap, y, part, p, half, st);
     }
     return hipErrorInvalidValue;
 }
@@ -307,10 +315,12 @@ hipError_t run_fwd(const void *in, const void *w, void *out, const ConvGeom &g, 
         p.OH = f.OH; p.OW = f.OW; p.osh = f.osh; p.osw = f.osw;
         p.out_bf16 = g.out_bf16;
         p.pair = g.out_bf16 && f.ncls == 1 && f.osh == 1 && f.osw == 1 && (f.OH * f.OW) % 2 == 0;
+        int half = 0;   // a run ends half way through a piece (4 channels per pixel, bf16)
+        for (int i = 0; i < f.ncls; ++i) half |= f.pcls[i].St * f.Cp % (16 / f.sz) != 0;
         p.nsplit = f.nsplit;
         p.nptot = (int)np;
         char *o = static_cast<char *>(out) + n0 * dst_img;
-        e = launch_cfg<T>(f.cfg, copy, packed, o, part, p, st);
+        e = launch_cfg<T>(f.cfg, copy, packed, o, part, p, half, st);
         if (e != hipSuccess) return e;
         if (f.nsplit > 1) {
             const dim3 grid((unsigned)((np + 255) / 256), f.M);
@@ -452,7 +462,10 @@ hipError_t run_wgrad(const void *x, const void *dy, float *dw, const ConvGeom &g
         p.plane_bytes = (unsigned)(q.x_bytes / f.planes);
         p.x_bytes = (unsigned)q.x_all;
         p.d_bytes = (unsigned)q.d_all;
-        p.nflat = q.nflat; p.steps = q.steps; p.sps = q.sps; p.nsl = q.nsl;
+        p.P = g.P; p.Q = g.Q; p.Pp = f.Pp; p.Qp = f.Qp;
+        p.holes = f.Pp != g.P || f.Qp != g.Q;
+        p.dp = f.pix / f.Qp % f.Pp; p.dq = f.pix % f.Qp;
+        p.steps = q.steps; p.sps = q.sps; p.nsl = q.nsl;
         p.ktiles = ceil_div(g.K, kWTile[f.cfg].bm);
         p.jtiles = ceil_div(f.ncols, kWTile[f.cfg].bn);
         p.slice0 = slices;

@@ -65,6 +65,29 @@ __device__ inline uint32_t lds_address(const void *p)
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char *)p;
 }
 
+// Whether any thread of the workgroup holds an accumulator that is not finite.  `word` is LDS that nobody needs any more (of
+// the ring: a word beside it would cost the tiles that take half of a compute unit's LDS their second workgroup).
+template <int M, int N>
+__device__ inline bool any_not_finite(const f32x16 (&acc)[M][N], char *word)
+{
+    volatile int *found = reinterpret_cast<volatile int *>(word);
+    float s = 0.f;
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+        for (int f = 0; f < N; ++f)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) s = __builtin_fmaf(acc[i][f][v], 0.f, s);   // NaN from then on
+    __syncthreads();
+    if (threadIdx.x == 0) *found = 0;
+    __syncthreads();
+    if (s != s) *found = 1;
+    __syncthreads();
+    const bool any = *found;
+    __syncthreads();
+    return any;
+}
+
 // ---- preparation: the channels-last copies and the packed filter ---------------------------------------------
 template <typename T> struct Elem;
 template <> struct Elem<bf16_t> { static constexpr int PE = 8; };   // elements per 16-byte piece
@@ -198,7 +221,10 @@ __global__ void __launch_bounds__(256) cl_prep_kernel(ClPrep p)
 
 // ---- forward and backward-data -------------------------------------------------------------------------------
 // BM output channels x BN pixels per workgroup of WM x WN waves; NST stages of 128-byte runs.
-template <typename T, int BM, int BN, int WM, int WN, int NST>
+// HALF: the runs are an odd number of 4-channel pixels (bf16) and end half way through a 16-byte piece, whose other half is
+// the next pixel's.  It meets packed zeros, which is enough unless it is an Inf or a NaN: a tile with a result that is not
+// finite is done again with that half cleared (the look at the results costs such layers 1 %, clearing it always 4 %).
+template <typename T, int BM, int BN, int WM, int WN, int NST, bool HALF = false>
 __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2)))
 cl_gemm_kernel(const T *__restrict__ xs, const T *__restrict__ ap, void *__restrict__ y, float *__restrict__ part, ClGemm p)
 {
@@ -250,41 +276,7 @@ cl_gemm_kernel(const T *__restrict__ xs, const T *__restrict__ ap, void *__restr
     }
     const int n = s1 - s0;
 
-    // ---- the running position of the loads: channel block, row tap, run within it
-    const int ni = max(c.ni, 1), per_block = max(c.Rt * ni, 1);
-    int co = s0 / per_block, tap = (s0 - co * per_block) / ni, ri = s0 - co * per_block - tap * ni;
-    int mo = co, mleft = per_block - (s0 - co * per_block);   // and of the multiplications: block, stages left in it
-    int plane = tap % p.sh;
-    const uint32_t rowb = (uint32_t)p.Ws * psz;
-    uint32_t prow = (uint32_t)(tap / p.sh) * rowb;
-    uint32_t asoff = c.a_off + (uint32_t)s0 * p.Mpad * 128u;
-    const uint32_t lbase = lds_address(lds);
-    auto issue = [&](int buf) {
-        const uint32_t lb = lbase + buf * STG + wave * 1024;
-        const int ck = ri * c.no + co;
-        const uint32_t xsoff = plane * p.plane_bytes + prow + ck * 128u;
-        const uint32_t tm = ck == c.ncks - 1 ? tailmask : 0u;
-#pragma unroll
-        for (int k = 0; k < LA; ++k)
-            if (IA % NW == 0 || wave + NW * k < IA) load_lds16(lb + k * NW * 1024, va[k], ar, asoff);
-#pragma unroll
-        for (int k = 0; k < LB; ++k) load_lds16(lb + IA * 1024 + k * NW * 1024, vb[k] | tm, xr, xsoff);
-        asoff += p.Mpad * 128u;
-        if (++ri == ni) {
-            ri = 0;
-            if (++plane == p.sh) { plane = 0; prow += rowb; }
-            if (++tap == c.Rt) { tap = 0; plane = 0; prow = 0; ++co; }
-        }
-    };
-
     f32x16 acc[FM][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int f = 0; f < FN; ++f)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][f][v] = 0.f;
-
     // operand reads: row l32 of a 32-row block, piece 2t + g of eight, permuted as stored
     const uint32_t ra = (wm * FM * 32 + l32) * 128, rb = BM * 128 + (wn * FN * 32 + l32) * 128;
     const uint32_t q0 = (uint32_t)(g ^ ((l32 >> 1) & 7)) * 16;   // piece 2t + g is at q0 ^ 32 t
@@ -302,6 +294,13 @@ cl_gemm_kernel(const T *__restrict__ xs, const T *__restrict__ ap, void *__restr
 #pragma unroll
             for (int f = 0; f < FN; ++f) r.b[t][f] = *reinterpret_cast<const u32x4 *>(pb + f * 4096);
         }
+    };
+    auto clear_tail = [&](int half, Frags &r) {   // the second half of the run's last piece
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            if (half * 4 + 2 * t + g == c.tail - 1)
+#pragma unroll
+                for (int f = 0; f < FN; ++f) r.b[t][f][2] = r.b[t][f][3] = 0;
     };
     auto multiply = [&](const Frags &r) {
 #pragma unroll
@@ -327,33 +326,76 @@ cl_gemm_kernel(const T *__restrict__ xs, const T *__restrict__ ap, void *__restr
         }
     };
 
-    // Trip i, two halves: the second half of stage i is read while the first is multiplied; then, when stage i + 1
-    // has landed and everybody has read stage i, its buffer takes stage i + NST, and the first half of stage i + 1 is
-    // read while the second of stage i is multiplied (unless the run ends in the first half).
-    Frags f0, f1;
-    for (int i = 0; i < NST && i < n; ++i) issue(i);
-    if (n >= NST) stage_wait<(NST - 1) * LMIN>();
-    else stage_wait<0>();
-    fetch(0, 0, f0);
-    int buf = 0;
-    for (int i = 0; i < n; ++i) {
-        const bool both = c.tail > 4 || mo != c.no - 1;   // (a short run is its block's only one)
-        if (--mleft == 0) { mleft = per_block; ++mo; }
-        reads_done();
-        fetch(buf, 1, f1);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(f0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (i + NST - 1 < n) stage_wait<(NST - 2) * LMIN>();
+    auto accumulate = [&](auto clear) {
+        constexpr bool CUT = decltype(clear)::value;
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int f = 0; f < FN; ++f)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][f][v] = 0.f;
+
+        // ---- the running position of the loads: channel block, row tap, run within it
+        const int ni = max(c.ni, 1), per_block = max(c.Rt * ni, 1);
+        int co = s0 / per_block, tap = (s0 - co * per_block) / ni, ri = s0 - co * per_block - tap * ni;
+        int mo = co, mleft = per_block - (s0 - co * per_block);   // and of the multiplications: block, stages left in it
+        int plane = tap % p.sh;
+        const uint32_t rowb = (uint32_t)p.Ws * psz;
+        uint32_t prow = (uint32_t)(tap / p.sh) * rowb;
+        uint32_t asoff = c.a_off + (uint32_t)s0 * p.Mpad * 128u;
+        const uint32_t lbase = lds_address(lds);
+        auto issue = [&](int buf) {
+            const uint32_t lb = lbase + buf * STG + wave * 1024;
+            const int ck = ri * c.no + co;
+            const uint32_t xsoff = plane * p.plane_bytes + prow + ck * 128u;
+            const uint32_t tm = ck == c.ncks - 1 ? tailmask : 0u;
+#pragma unroll
+            for (int k = 0; k < LA; ++k)
+                if (IA % NW == 0 || wave + NW * k < IA) load_lds16(lb + k * NW * 1024, va[k], ar, asoff);
+#pragma unroll
+            for (int k = 0; k < LB; ++k) load_lds16(lb + IA * 1024 + k * NW * 1024, vb[k] | tm, xr, xsoff);
+            asoff += p.Mpad * 128u;
+            if (++ri == ni) {
+                ri = 0;
+                if (++plane == p.sh) { plane = 0; prow += rowb; }
+                if (++tap == c.Rt) { tap = 0; plane = 0; prow = 0; ++co; }
+            }
+        };
+
+        // Trip i, two halves: the second half of stage i is read while the first is multiplied; then, when stage i + 1
+        // has landed and everybody has read stage i, its buffer takes stage i + NST, and the first half of stage i + 1 is
+        // read while the second of stage i is multiplied (unless the run ends in the first half).
+        Frags f0, f1;
+        for (int i = 0; i < NST && i < n; ++i) issue(i);
+        if (n >= NST) stage_wait<(NST - 1) * LMIN>();
         else stage_wait<0>();
-        const int free = buf;
-        buf = buf + 1 == NST ? 0 : buf + 1;
-        fetch(buf, 0, f0);   // (past the last stage: whatever is there, not used)
-        if (i + NST < n) issue(free);
-        __builtin_amdgcn_sched_barrier(0);
-        if (both) multiply(f1);
-        __builtin_amdgcn_sched_barrier(0);
-    }
+        fetch(0, 0, f0);
+        int buf = 0;
+        for (int i = 0; i < n; ++i) {
+            const bool both = c.tail > 4 || mo != c.no - 1;   // (a short run is its block's only one)
+            const bool cut = CUT && mo == c.no - 1;
+            if (--mleft == 0) { mleft = per_block; ++mo; }
+            reads_done();
+            fetch(buf, 1, f1);
+            __builtin_amdgcn_sched_barrier(0);
+            if (cut) clear_tail(0, f0);
+            multiply(f0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i + NST - 1 < n) stage_wait<(NST - 2) * LMIN>();
+            else stage_wait<0>();
+            const int free = buf;
+            buf = buf + 1 == NST ? 0 : buf + 1;
+            fetch(buf, 0, f0);   // (past the last stage: whatever is there, not used)
+            if (i + NST < n) issue(free);
+            __builtin_amdgcn_sched_barrier(0);
+            if (cut) clear_tail(1, f1);
+            if (both) multiply(f1);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    accumulate(std::false_type());
+    if constexpr (HALF)
+        if (any_not_finite(acc, lds)) accumulate(std::true_type());
 
     // ---- epilogue: register v is output channel 8 * (v / 4) + 4 * g + v % 4 of its block, the lane is the pixel
     const size_t OHW = (size_t)p.OH * p.OW;
@@ -428,6 +470,9 @@ __global__ void __launch_bounds__(256) cl_reduce_kernel(const float *__restrict_
 
 // ---- backward-filter -----------------------------------------------------------------------------------------
 // BM output channels x BN columns (r, s, c) per workgroup; stages of 32 flat pixels (16 for fp32).
+// Where the copies' pitch leaves flat pixels that are no output pixel (p.holes), dy is zero, but x may hold a real pixel there.
+// Zero products, unless that pixel is an Inf or a NaN: a tile with a result that is not finite is done again without x's
+// loads at such pixels (the look at the results costs 1 %, leaving them out always 9 to 18 %).
 template <typename T, int BM, int BN, int WM, int WN, int NST>
 __global__ void __launch_bounds__(64 * WM * WN) __attribute__((amdgpu_waves_per_eu(2)))
 cl_wgrad_kernel(const T *__restrict__ ds, const T *__restrict__ xs, float *__restrict__ part, ClWgrad p)
@@ -480,28 +525,8 @@ cl_wgrad_kernel(const T *__restrict__ ds, const T *__restrict__ xs, float *__res
     }
     const int s0 = slice * p.sps, n = min(p.sps, p.steps - s0);
     const uint32_t dstep = (uint32_t)PIX * p.Kp * SZ, xstep = (uint32_t)PIX * p.in_sw * p.Cp * SZ;
-    uint32_t dsoff = s0 * dstep, xsoff = s0 * xstep;
     const uint32_t lbase = lds_address(lds);
-    auto issue = [&](int buf) {
-        const uint32_t lb = lbase + buf * STG + wave * 1024;
-#pragma unroll
-        for (int k = 0; k < LA; ++k)
-            if (IA % NW == 0 || wave + NW * k < IA) load_lds16(lb + k * NW * 1024, va[k], dr, dsoff);
-#pragma unroll
-        for (int k = 0; k < LB; ++k)
-            if (IB % NW == 0 || wave + NW * k < IB) load_lds16(lb + IA * 1024 + k * NW * 1024, vb[k], xr, xsoff);
-        dsoff += dstep;
-        xsoff += xstep;
-    };
-
     f32x16 acc[FM][FN];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int f = 0; f < FN; ++f)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][f][v] = 0.f;
-
     // operand reads.  bf16: lane i of 16 addresses row i / 4, columns 4 * (i % 4) .. + 3 and receives column i of the
     // four rows; rows 8g .. 8g + 3 and the four after them make the eight reduction elements of the lane's column.
     uint32_t ra[FM], rb[FN];
@@ -566,29 +591,72 @@ cl_wgrad_kernel(const T *__restrict__ ds, const T *__restrict__ xs, float *__res
                 }
     };
 
-    // the loop of cl_gemm_kernel
-    Frags fr[2];
-    for (int i = 0; i < NST && i < n; ++i) issue(i);
-    if (n >= NST) stage_wait<(NST - 1) * LMIN>();
-    else stage_wait<0>();
-    fetch(0, fr[0]);
-    int buf = 0;
-    auto trip = [&](int i, const Frags &cur, Frags &nxt) {
-        if (i + NST - 1 < n) stage_wait<(NST - 2) * LMIN>();
+    auto accumulate = [&](auto masked) {
+        constexpr bool MASK = decltype(masked)::value;
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int f = 0; f < FN; ++f)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][f][v] = 0.f;
+        int fq[LB], fp[LB];   // column and row of the pitch of each load's pixel
+#pragma unroll
+        for (int k = 0; k < LB; ++k) {
+            const int px = s0 * PIX + ((wave + NW * k) * 64 + lane) / PB, row = px / p.Qp;
+            fq[k] = px - row * p.Qp;
+            fp[k] = row % p.Pp;
+        }
+        uint32_t dsoff = s0 * dstep, xsoff = s0 * xstep;
+        auto issue = [&](int buf) {
+            const uint32_t lb = lbase + buf * STG + wave * 1024;
+            uint32_t vo[LB];
+#pragma unroll
+            for (int k = 0; k < LB; ++k) {
+                vo[k] = vb[k];
+                if (MASK) {
+                    if (fq[k] >= p.Q || fp[k] >= p.P) vo[k] = OUTSIDE;
+                    fq[k] += p.dq;
+                    fp[k] += p.dp;
+                    if (fq[k] >= p.Qp) { fq[k] -= p.Qp; ++fp[k]; }
+                    if (fp[k] >= p.Pp) fp[k] -= p.Pp;
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < LA; ++k)
+                if (IA % NW == 0 || wave + NW * k < IA) load_lds16(lb + k * NW * 1024, va[k], dr, dsoff);
+#pragma unroll
+            for (int k = 0; k < LB; ++k)
+                if (IB % NW == 0 || wave + NW * k < IB) load_lds16(lb + IA * 1024 + k * NW * 1024, vo[k], xr, xsoff);
+            dsoff += dstep;
+            xsoff += xstep;
+        };
+
+        // the loop of cl_gemm_kernel
+        Frags fr[2];
+        for (int i = 0; i < NST && i < n; ++i) issue(i);
+        if (n >= NST) stage_wait<(NST - 1) * LMIN>();
         else stage_wait<0>();
-        const int free = buf;
-        buf = buf + 1 == NST ? 0 : buf + 1;
-        reads_done();
-        fetch(buf, nxt);
-        if (i + NST < n) issue(free);
-        __builtin_amdgcn_sched_barrier(0);
-        multiply(cur);
-        __builtin_amdgcn_sched_barrier(0);
+        fetch(0, fr[0]);
+        int buf = 0;
+        auto trip = [&](int i, const Frags &cur, Frags &nxt) {
+            if (i + NST - 1 < n) stage_wait<(NST - 2) * LMIN>();
+            else stage_wait<0>();
+            const int free = buf;
+            buf = buf + 1 == NST ? 0 : buf + 1;
+            reads_done();
+            fetch(buf, nxt);
+            if (i + NST < n) issue(free);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply(cur);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        for (int i = 0; i < n; i += 2) {
+            trip(i, fr[0], fr[1]);
+            if (i + 1 < n) trip(i + 1, fr[1], fr[0]);
+        }
     };
-    for (int i = 0; i < n; i += 2) {
-        trip(i, fr[0], fr[1]);
-        if (i + 1 < n) trip(i + 1, fr[1], fr[0]);
-    }
+    accumulate(std::false_type());
+    if (p.holes && any_not_finite(acc, lds)) accumulate(std::true_type());
 
     float *o = part + (size_t)(p.slice0 + slice) * p.K * p.ncols;
 #pragma unroll

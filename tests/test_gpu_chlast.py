@@ -156,3 +156,37 @@ def test_image_beyond_32_bit_offsets(C):
     xs = f64(x[0, :, ::stride, ::stride].contiguous()).reshape(C, -1)
     assert rel_l2(f64(y).reshape(K, -1), f64(w).reshape(K, C) @ xs) <= TOL["f32"]
     assert rel_l2(f64(dw).reshape(K, C), f64(dy).reshape(K, -1) @ xs.T) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("case", [(2, 24, 13, 13, 40, 3, 3, (1, 1), (1, 1)), (2, 24, 14, 15, 40, 3, 3, (2, 2), (1, 1)),
+                                  (3, 9, 5, 6, 33, 5, 5, (1, 1), (2, 2)), (2, 3, 47, 45, 16, 11, 11, (4, 4), (0, 0)),
+                                  (2, 3, 30, 29, 24, 7, 7, (2, 2), (3, 3)), (2, 40, 17, 17, 32, 7, 1, (1, 1), (3, 0)),
+                                  (4, 128, 56, 56, 128, 3, 3, (1, 1), (1, 1))], ids=lambda c: "x".join(map(str, c[:7])))
+def test_infinite_inputs_stay_with_their_taps(case, dtype):
+    """An Inf in x reaches the outputs whose windows hold it (forward) and the taps that meet it (backward-filter), nothing
+    else: neither through the padding between the copies' rows nor through a piece shared with the next pixel."""
+    N, C, H, W, K, R, S, stride, pad = case
+    layer = wl.Layer("inf", *case[1:5], R, S, stride, pad, False, None, 1, False, None)
+    x, w, dy = wl.conv_inputs(layer, N, dtype, 815)
+    at = torch.zeros(x.shape, dtype=torch.bool)
+    for spot in ((0, 0, 0, 0), (N - 1, C - 1, H - 1, W - 1), (N // 2, C // 2, H // 2, W // 2), (0, C - 1, H - 1, 0)):
+        at[spot] = True
+    x0, hit = f64(x.masked_fill(at, 0)), f64(at)
+    xd = x.masked_fill(at, float("inf")).cuda()
+    shape = shape_of(layer, N, dtype, dtype)
+    for d, fn, b, t, touched, want in (
+            (F, sn.sn_conv2d_fwd, w, w.dtype, oracle.conv2d_fwd(hit, f64(torch.ones_like(w)), stride, pad),
+             oracle.conv2d_fwd(x0, f64(w), stride, pad)),
+            (B, sn.sn_conv2d_bwd_filter, dy, torch.float32, oracle.conv2d_bwd_filter(hit, f64(torch.ones_like(dy)), w.shape, stride, pad),
+             oracle.conv2d_bwd_filter(x0, f64(dy), w.shape, stride, pad))):
+        ws_bytes = max(BIG, sn.sn_conv_workspace_query(shape, d, sn.SN_ALGO_IM2COL_GEMM)[0])
+        assert _inspect(shape, d, ws_bytes)
+        out = torch.zeros(want.shape, dtype=t, device="cuda")
+        print("case", case, dtype, "dir", d, flush=True)
+        fn(xd, b.cuda(), out, shape, sn.SN_ALGO_IM2COL_GEMM, torch.empty(ws_bytes, dtype=torch.uint8, device="cuda"))
+        clean = touched < 0.5
+        got = f64(out)
+        assert (abs(got[clean]) < float("inf")).all(), (d, "reached outputs it does not belong to")
+        assert not (abs(got[~clean]) < float("inf")).any(), (d, "lost")
+        assert rel_l2(got[clean], want[clean]) <= TOL[dtype]
