@@ -142,7 +142,9 @@ int sn_out_dim(int in, int pad, int window, int stride);
 /* Workspace needs of one algorithm for one CONV step (Sec. 3.5: an algorithm is
  * memory-feasible iff its workspace fits the free bytes).
  *  min_bytes        least workspace with which the algorithm runs at all
- *  preferred_bytes  workspace beyond which it gets no faster
+ *  preferred_bytes  workspace beyond which it gets no faster, with one exception: STAGED's strided
+ *                   forward and its backward-filter report what their own kernels can use, and may
+ *                   still change to the channels-last product (about the tensors' own size) with more
  * Returns SN_ERR_UNSUPPORTED if the algorithm cannot run this shape. */
 sn_status sn_conv_workspace_query(const sn_conv_shape *shape, sn_conv_dir dir, sn_conv_algo algo,
                                   size_t *min_bytes, size_t *preferred_bytes);
@@ -151,9 +153,13 @@ sn_status sn_conv_workspace_query(const sn_conv_shape *shape, sn_conv_dir dir, s
  * the fastest.  "Fastest" comes from times recorded for this exact shape by
  * sn_planner_record / sn_conv_autotune (the paper benchmarks the feasible
  * algorithms at run time); a recorded time applies to budgets >= the workspace
- * it was measured with.  With no feasible record the choice falls back to a
- * built-in ranking (WINOGRAD where it applies, C * K >= 8192 and at least 2048 tiles fit a pass, STAGED,
- * then DIRECT; DIRECT first for forward on few-channel inputs).  Among records within 3 % of the fastest the one with the
+ * it was measured with, and a call with algo = AUTO runs the choice with just that
+ * workspace.  With no feasible record the choice falls back to estimates and a
+ * built-in ranking: first the channels-last product where the budget holds it and it is
+ * estimated to be faster than what would run instead, as STAGED or, where STAGED has no
+ * kernel for the shape or does not fit, as IM2COL_GEMM (bytes_used is then at least that algorithm's
+ * min_bytes); then WINOGRAD where it applies, C * K >= 8192 and at least 2048 tiles fit a pass, STAGED,
+ * DIRECT; DIRECT before these for forward on few-channel inputs.  Among records within 3 % of the fastest the one with the
  * smallest workspace wins (then the faster).  DIRECT needs 0 bytes, so a plan always exists.  bytes_used = the workspace the choice will use
  * (<= budget_bytes).  predicted_ms may be NULL; it receives the recorded time
  * or a negative value if the choice came from the built-in ranking. */
@@ -183,8 +189,9 @@ sn_status sn_conv2d_fwd(const void *x, const void *w, void *y, const sn_conv_sha
 
 /* sn_conv2d_fwd for callers that cannot allocate or pass device memory beyond the tensors
  * themselves: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
- * It is sn_conv2d_fwd with algo = SN_ALGO_STAGED (same kernels, bit-identical y) whose workspace
- * (the re-laid-out filter; the copies of small inputs) is a fixed array of SN_NOALLOC_SCRATCH_BYTES that the library's code
+ * It is sn_conv2d_fwd with algo = SN_ALGO_STAGED and a workspace of SN_NOALLOC_SCRATCH_BYTES (the same
+ * kernels and bits as that call; with more or less workspace STAGED may run other kernels, whose sums
+ * are in another order): the re-laid-out filter, or the copies of small inputs, in a fixed array that the library's code
  * object holds on every GPU it is loaded on until the process ends.  No hipMalloc / hipFree or
  * other allocating call is made.  The first call on a device looks up the array's address there
  * (make that call outside a graph capture).
@@ -192,8 +199,8 @@ sn_status sn_conv2d_fwd(const void *x, const void *w, void *y, const sn_conv_sha
  *    SN_ERR_WORKSPACE_TOO_SMALL if its min_bytes exceed SN_NOALLOC_SCRATCH_BYTES (filters of
  *    more than about 4 M elements); nothing is launched then.
  *  - Every call on a GPU uses that GPU's one array: calls that overlap on a GPU (different
- *    streams, or host threads without ordering) race on it; calls on one stream are safe.  The
- *    array keeps the last call's packed filter; each call rewrites all of what it reads. */
+ *    streams, or host threads without ordering) race on it; calls on one stream are safe.  Each
+ *    call writes all of what it reads there: nothing of an earlier call's contents counts. */
 #define SN_NOALLOC_SCRATCH_BYTES (8u << 20)
 sn_status sn_conv2d_fwd_noalloc(const void *x, const void *w, void *y, const sn_conv_shape *shape,
                                 sn_stream stream);

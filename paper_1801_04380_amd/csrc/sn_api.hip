@@ -350,7 +350,8 @@ bool chlast_least(const ConvGeom &g, sn_conv_dir dir, ChlastPlan *plan)
     return chlast_plan(one, dir, ALL_BYTES, plan);
 }
 
-sn_status query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *min_b, size_t *pref_b)
+// What the algorithm's own kernels need (the channels-last product aside).
+sn_status own_query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *min_b, size_t *pref_b)
 {
     switch (algo) {
     case SN_ALGO_DIRECT:
@@ -388,11 +389,6 @@ sn_status query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *m
         if (phase_plan(g, dir, &pp)) {
             *pref_b = phase_bytes(pp, dir, g.N);
             *min_b = pp.chunkable ? phase_bytes(pp, dir, 1) : *pref_b;
-            // backward-data also runs as the channels-last product: with less than the planes take, and, where it is the
-            // faster one, with all that it wants itself
-            ChlastPlan all, one;
-            if (dir == SN_CONV_BWD_DATA && chlast_least(g, dir, &one)) *min_b = std::min(*min_b, one.bytes);
-            if (dir == SN_CONV_BWD_DATA && chlast_runs(g, dir, algo, ALL_BYTES, &all)) *pref_b = std::max(*min_b, all.bytes);
             return SN_OK;
         }
         if (dir == SN_CONV_BWD_FILTER) {
@@ -402,13 +398,28 @@ sn_status query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *m
         }
         if (!tile_conv_supported(g, dir == SN_CONV_BWD_DATA)) return SN_ERR_UNSUPPORTED;
         *min_b = *pref_b = tile_conv_packed_bytes(g, dir == SN_CONV_BWD_DATA);
-        ChlastPlan cl;
-        if (chlast_runs(g, dir, algo, ALL_BYTES, &cl)) *pref_b = std::max(*pref_b, cl.bytes);
         return SN_OK;
     }
     default:
         return SN_ERR_BAD_ARG;
     }
+}
+
+// With the product where it is the one that runs with enough workspace: for forward and backward-data at stride 1, for
+// backward-data at any stride, and for IM2COL_GEMM.  (Strided forward and backward-filter report their own kernels' need, a
+// fraction of the copies': what the product takes beyond it is in the plan's bytes.)  Strided backward-data also runs as
+// the product with less than the phase planes take.
+sn_status query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *min_b, size_t *pref_b)
+{
+    const sn_status s = own_query(g, dir, algo, min_b, pref_b);
+    const bool strided = g.sh > 1 || g.sw > 1;
+    ChlastPlan cl;
+    if (s != SN_OK || *pref_b == 0) return s;
+    if (algo == SN_ALGO_IM2COL_GEMM && chlast_runs(g, dir, algo, ALL_BYTES, &cl)) *pref_b = std::max(*pref_b, cl.bytes);
+    if (algo != SN_ALGO_STAGED || dir == SN_CONV_BWD_FILTER || (strided && dir == SN_CONV_FWD)) return SN_OK;
+    if (strided && chlast_least(g, dir, &cl)) *min_b = std::min(*min_b, cl.bytes);
+    if (chlast_runs(g, dir, algo, ALL_BYTES, &cl)) *pref_b = std::max(strided ? *min_b : *pref_b, cl.bytes);
+    return SN_OK;
 }
 
 // ---- planner table ------------------------------------------------------------
@@ -423,10 +434,10 @@ std::vector<Record> g_table;
 
 bool same_shape(const sn_conv_shape &a, const sn_conv_shape &b) { return std::memcmp(&a, &b, sizeof(a)) == 0; }
 
-// Built-in ranking used when nothing has been measured for the shape: lower is
-// tried first.  The workspace-staged implicit GEMM, then the direct one; the
-// explicit unfold pays a write and a read of a buffer R*S times the input, so it
-// is picked on measurement only.
+// Built-in ranking used when nothing has been measured for the shape and the channels-last
+// product is not estimated to be the fastest: lower is tried first.  The workspace-staged
+// implicit GEMM, then the direct one; the explicit unfold pays a write and a read of a
+// buffer R*S times the input, so it is picked on measurement only.
 const sn_conv_algo kRanking[] = {SN_ALGO_WINOGRAD, SN_ALGO_STAGED, SN_ALGO_DIRECT};
 
 sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, size_t budget,
@@ -469,8 +480,7 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
         if (budget == 0 || query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
         if (!chlast_runs(g, dir, SN_ALGO_STAGED, budget, &cl)) break;
         *algo = a;
-        // (never less than the least the name is accepted with, which for IM2COL_GEMM is one unfolded image)
-        *bytes = a == SN_ALGO_STAGED ? std::max(cl.bytes, std::min(pf, budget)) : std::max(cl.bytes, mn);
+        *bytes = std::max(cl.bytes, mn);   // (mn: the least the name is accepted with; for IM2COL_GEMM one unfolded image)
         if (ms_out) *ms_out = -1.f;
         return SN_OK;
     }
@@ -484,7 +494,7 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
     }
     for (sn_conv_algo a : kRanking) {
         size_t mn = 0, pf = 0;
-        if (query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
+        if (own_query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
         if (a == SN_ALGO_STAGED && pf == 0) continue;   // nothing to stage: the same kernel runs as DIRECT
         if (a == SN_ALGO_WINOGRAD && !winograd_guessed(g, dir, budget)) continue;
         // The phase planes in passes: strided forward gains little over the zero-workspace kernel, so only
@@ -861,8 +871,8 @@ sn_status sn_conv2d_fwd_noalloc(const void *x, const void *w, void *y, const sn_
     void *ws = nullptr;
     s = scratch_of_current_device(&ws);
     if (s != SN_OK) return s;
-    // the packing kernel rewrites every item of the packed filter, padding included: nothing of an
-    // earlier call's contents is read
+    // the packing and copying kernels write every item of what is read, padding included: nothing of an
+    // earlier call's contents is
     return run_fwd(x, w, y, g, SN_ALGO_STAGED, ws, SN_NOALLOC_SCRATCH_BYTES, static_cast<hipStream_t>(stream));
 }
 

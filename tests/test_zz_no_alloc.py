@@ -1,6 +1,6 @@
 """sn_conv2d_fwd_noalloc, the forward CONV for callers that cannot allocate: its workspace is a
-fixed array inside the library.  It runs the kernels of sn_conv2d_fwd with SN_ALGO_STAGED, so the
-outputs must be bit-identical; two calls in a row, the second on a smaller problem, share the array.
+fixed array inside the library.  It runs the kernels of sn_conv2d_fwd with SN_ALGO_STAGED and a
+workspace of the array's size, so the outputs must be bit-identical; two calls in a row, the second on a smaller problem, share the array.
 Also checked against the fp64 oracle (relative L2 <= 5e-3, bf16 inputs)."""
 import ctypes
 
@@ -47,6 +47,25 @@ def test_two_calls_in_a_row_match_the_workspace_entry_point():
         assert torch.equal(got, want), "call %d differs from sn_conv2d_fwd(STAGED)" % i
         ref = oracle.conv2d_fwd(f64(x), f64(w), (1, 1), pad)
         assert rel_l2(f64(got), ref) <= 5e-3
+
+
+@pytest.mark.parametrize("case", [(2, 256, 17, 17, 256, 5, 5, (2, 2)), (6, 448, 40, 40, 288, 3, 3, (1, 1)), (2, 256, 14, 14, 256, 3, 3, (1, 1))],
+                         ids=lambda c: "x".join(map(str, c[:7])))
+def test_shapes_that_would_use_more_than_the_array(case):
+    """Whatever STAGED would run with its preferred workspace, the call is STAGED with the array's size of it."""
+    N, C, H, W, K, R, S, pad = case
+    layer = wl.Layer("t", C, H, W, K, R, S, (1, 1), pad, True, None, 1, False, None)
+    x, w, _ = wl.conv_inputs(layer, N, "bf16", 99)
+    shape = sn.conv_shape(N, C, H, W, K, R, S, (1, 1), pad, sn.SN_BF16, sn.SN_BF16)
+    ws = torch.empty(sn.SN_NOALLOC_SCRATCH_BYTES, dtype=torch.uint8, device="cuda")
+    want = torch.full((N, K, H, W), float("nan"), dtype=torch.bfloat16, device="cuda")
+    xd, wd = x.cuda(), w.cuda()
+    sn.sn_conv2d_fwd(xd, wd, want, shape, sn.SN_ALGO_STAGED, ws)
+    got = torch.full_like(want, float("nan"))
+    assert _raw_call(xd, wd, got, shape) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    assert rel_l2(f64(got), oracle.conv2d_fwd(f64(x), f64(w), (1, 1), pad)) <= 5e-3
 
 
 def test_sizes_beyond_the_array_are_refused():
