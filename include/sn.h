@@ -102,9 +102,9 @@ typedef enum { SN_CONV_FWD = 0, SN_CONV_BWD_DATA = 1, SN_CONV_BWD_FILTER = 2 } s
  *               workspace holds (min_bytes: one image).
  *               Where the product over channels-last copies (see IM2COL_GEMM) is
  *               estimated to be faster than these kernels and the workspace given
- *               holds it, STAGED runs that; sn_conv_plan's bytes_used then says how
- *               much of the budget it takes (preferred_bytes includes it for
- *               stride-1 forward and backward-data and for strided backward-data).
+ *               holds it, STAGED runs that (which of them ran is a matter of the
+ *               order of the sums only); sn_conv_plan's bytes_used then says how
+ *               much of the budget it takes, and sn_conv_autotune times both.
  *  WINOGRAD     F(2x2, 3x3) for the fp32 path (3x3 filters, stride 1, forward and
  *               backward-data): the transformed filter, the transformed input
  *               tiles and the 16 products per tile live in the workspace, for as
@@ -174,14 +174,15 @@ void sn_planner_clear(void);
 /* Benchmark every algorithm that fits workspace_bytes on the caller's own
  * buffers (same arguments as the matching sn_conv2d_* call: a, b are its two
  * inputs, out its output) and record the times: per algorithm one untimed launch, then
- * `iters` launches timed one by one, of which the median counts.  Synchronises the stream. */
+ * `iters` launches timed one by one, of which the median counts; STAGED, where it runs as the
+ * channels-last product, a second time with what its own kernels need.  Synchronises the stream. */
 sn_status sn_conv_autotune(sn_conv_dir dir, const void *a, const void *b, void *out,
                            const sn_conv_shape *shape, void *workspace, size_t workspace_bytes,
                            int iters, sn_stream stream);
 
 /* CONV forward:  y[n,k,p,q] = sum_{c,r,s} x[n,c,p*sh+r-ph,q*sw+s-pw] * w[k,c,r,s]
  * (out-of-image taps contribute 0).  x, w of in_dtype; y of out_dtype.
- * algo = AUTO plans with workspace_bytes as the budget.  A named algorithm whose
+ * algo = AUTO plans with workspace_bytes as the budget and uses the planned bytes of it.  A named algorithm whose
  * min_bytes exceeds workspace_bytes returns SN_ERR_WORKSPACE_TOO_SMALL.
  * workspace may be NULL iff workspace_bytes == 0. */
 sn_status sn_conv2d_fwd(const void *x, const void *w, void *y, const sn_conv_shape *shape,

@@ -531,18 +531,18 @@ sn_status check_ws(const void *ws, size_t bytes)
 
 sn_status launch_status(hipError_t e) { return e == hipSuccess ? SN_OK : SN_ERR_LAUNCH; }
 
-// Resolve AUTO and check the budget for a named algorithm.
-sn_status resolve(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, sn_conv_algo *algo,
-                  size_t ws_bytes)
+// Resolve AUTO -- into the planned algorithm with the planned bytes: which of an algorithm's kernels runs depends on its
+// workspace, and a record's time is that of the workspace it was measured with -- and check the budget for a named algorithm.
+sn_status resolve(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, sn_conv_algo *algo, size_t *ws_bytes)
 {
     if (*algo == SN_ALGO_AUTO) {
-        size_t used;
-        return plan(shape, g, dir, ws_bytes, algo, &used, nullptr);
+        const size_t budget = *ws_bytes;
+        return plan(shape, g, dir, budget, algo, ws_bytes, nullptr);
     }
     size_t mn = 0, pf = 0;
     sn_status s = query(g, dir, *algo, &mn, &pf);
     if (s != SN_OK) return s;
-    if (mn > ws_bytes) return SN_ERR_WORKSPACE_TOO_SMALL;
+    if (mn > *ws_bytes) return SN_ERR_WORKSPACE_TOO_SMALL;
     return SN_OK;
 }
 
@@ -842,7 +842,7 @@ static sn_status conv_call(sn_conv_dir dir, const void *a, const void *b, void *
     if (algo < SN_ALGO_AUTO || algo >= SN_ALGO_COUNT) return SN_ERR_BAD_ARG;
     s = check_ws(ws, ws_bytes);
     if (s != SN_OK) return s;
-    s = resolve(shape, g, dir, &algo, ws_bytes);
+    s = resolve(shape, g, dir, &algo, &ws_bytes);
     if (s != SN_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
     switch (dir) {
@@ -911,7 +911,7 @@ sn_status sn_conv2d_fwd_bn_stats(const void *x, const void *w, void *y, const sn
     s = check_ws(workspace, workspace_bytes);
     if (s != SN_OK) return s;
     if (scratch_bytes < conv_bn_stats_need(g)) return SN_ERR_WORKSPACE_TOO_SMALL;
-    s = resolve(shape, g, SN_CONV_FWD, &algo, workspace_bytes);
+    s = resolve(shape, g, SN_CONV_FWD, &algo, &workspace_bytes);
     if (s != SN_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
     float *part = static_cast<float *>(scratch);
@@ -960,21 +960,36 @@ sn_status sn_conv_autotune(sn_conv_dir dir, const void *a, const void *b, void *
     if (hipEventCreate(&e0) != hipSuccess) return SN_ERR_LAUNCH;
     if (hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); return SN_ERR_LAUNCH; }
     sn_status result = SN_OK;
-    for (int algo = 0; algo < SN_ALGO_COUNT && result == SN_OK; ++algo) {
-        size_t mn = 0, pf = 0;
-        if (query(g, dir, (sn_conv_algo)algo, &mn, &pf) != SN_OK || mn > workspace_bytes) continue;
-        size_t used = std::min(pf, workspace_bytes);
+    // What to time: every algorithm with the most it can use of the workspace; and STAGED, where that is the channels-last
+    // product, also with what its own kernels need, so that the records decide between them (the product is estimated to
+    // be faster, within some 10 %).
+    struct Candidate { sn_conv_algo algo; size_t ws; };
+    std::vector<Candidate> todo;
+    for (int a = 0; a < SN_ALGO_COUNT; ++a) {
+        const sn_conv_algo algo = (sn_conv_algo)a;
+        size_t mn = 0, pf = 0, own_mn = 0, own_pf = 0;
+        if (query(g, dir, algo, &mn, &pf) != SN_OK || mn > workspace_bytes) continue;
         ChlastPlan cl;
-        if (chlast_runs(g, dir, (sn_conv_algo)algo, workspace_bytes, &cl)) used = std::max(used, cl.bytes);
+        const bool product = chlast_runs(g, dir, algo, workspace_bytes, &cl);
+        todo.push_back({algo, product ? std::max(cl.bytes, mn) : std::min(pf, workspace_bytes)});
+        if (!product || algo != SN_ALGO_STAGED || own_query(g, dir, algo, &own_mn, &own_pf) != SN_OK) continue;
+        for (size_t own : {own_pf, own_mn})
+            if (own <= workspace_bytes && !chlast_runs(g, dir, algo, own, &cl)) {
+                todo.push_back({algo, own});
+                break;
+            }
+    }
+    for (const Candidate &c : todo) {
+        if (result != SN_OK) break;
         // one untimed run, then `iters` runs timed one by one: the median is recorded (a mean of a
         // few back-to-back launches follows whatever else disturbs one of them)
-        s = conv_call(dir, a, b, out, shape, (sn_conv_algo)algo, workspace, used, stream);
+        s = conv_call(dir, a, b, out, shape, c.algo, workspace, c.ws, stream);
         if (s != SN_OK) { result = s; break; }
         std::vector<float> times;
         for (int i = 0; i < iters; ++i) {
             float ms = 0.f;
             if (hipEventRecord(e0, st) != hipSuccess) { result = SN_ERR_LAUNCH; break; }
-            s = conv_call(dir, a, b, out, shape, (sn_conv_algo)algo, workspace, used, stream);
+            s = conv_call(dir, a, b, out, shape, c.algo, workspace, c.ws, stream);
             if (s != SN_OK) { result = s; break; }
             if (hipEventRecord(e1, st) != hipSuccess || hipEventSynchronize(e1) != hipSuccess ||
                 hipEventElapsedTime(&ms, e0, e1) != hipSuccess) {
@@ -985,7 +1000,7 @@ sn_status sn_conv_autotune(sn_conv_dir dir, const void *a, const void *b, void *
         }
         if (result != SN_OK) break;
         std::sort(times.begin(), times.end());
-        result = sn_planner_record(shape, dir, (sn_conv_algo)algo, used, times[times.size() / 2]);
+        result = sn_planner_record(shape, dir, c.algo, c.ws, times[times.size() / 2]);
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

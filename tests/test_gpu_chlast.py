@@ -35,11 +35,11 @@ CASES = {
 }
 
 
-def _inspect(shape, d, ws_bytes):
-    """What the library would run for IM2COL_GEMM with this workspace: ((tile m, tile n, threads), slices, passes, bytes),
+def _inspect(shape, d, ws_bytes, algo=sn.SN_ALGO_IM2COL_GEMM):
+    """What the library would run under this name with this workspace: ((tile m, tile n, threads), slices, passes, bytes),
     or None if not the product."""
     info, used, us = (ctypes.c_int * 5)(), ctypes.c_size_t(), ctypes.c_double()
-    if not _lib.load().sn_chlast_inspect(ctypes.byref(shape), d, sn.SN_ALGO_IM2COL_GEMM, ctypes.c_size_t(ws_bytes), info,
+    if not _lib.load().sn_chlast_inspect(ctypes.byref(shape), d, algo, ctypes.c_size_t(ws_bytes), info,
                                          ctypes.byref(used), ctypes.byref(us)):
         return None
     return tuple(info[:3]), info[3], info[4], used.value
@@ -190,3 +190,33 @@ def test_infinite_inputs_stay_with_their_taps(case, dtype):
         assert (abs(got[clean]) < float("inf")).all(), (d, "reached outputs it does not belong to")
         assert not (abs(got[~clean]) < float("inf")).any(), (d, "lost")
         assert rel_l2(got[clean], want[clean]) <= TOL[dtype]
+
+
+def test_measurements_choose_between_staged_kernels():
+    """Where STAGED with enough workspace is the product, autotuning also times STAGED's own kernel (with the workspace that
+    runs it), and AUTO runs what was measured, with the workspace it was measured with."""
+    layer, N = wl.Layer("w14", 64, 14, 14, 128, 3, 3, (1, 1), (1, 1), True, None, 1, False, None), 4
+    x, w, _ = (t.cuda() for t in wl.conv_inputs(layer, N, "bf16", 16))
+    shape = shape_of(layer, N, "bf16", "bf16")
+    mn, pf = sn.sn_conv_workspace_query(shape, F, sn.SN_ALGO_STAGED)
+    assert _inspect(shape, F, pf, sn.SN_ALGO_STAGED) and not _inspect(shape, F, mn, sn.SN_ALGO_STAGED)
+    ws = torch.empty(4 << 20, dtype=torch.uint8, device="cuda")
+
+    def run(algo, ws):
+        y = torch.full((N, 128, 14, 14), float("nan"), dtype=torch.bfloat16, device="cuda")
+        sn.sn_conv2d_fwd(x, w, y, shape, algo, ws)
+        return y
+
+    own, product = run(sn.SN_ALGO_STAGED, ws[:mn]), run(sn.SN_ALGO_STAGED, ws[:pf])
+    assert not torch.equal(own, product)   # (another order of the sums: what tells them apart below)
+    sn.sn_planner_clear()
+    sn.sn_conv_autotune(F, x, w, torch.empty_like(own), shape, ws, iters=2)
+    sn.sn_planner_record(shape, F, sn.SN_ALGO_DIRECT, 0, 1e6)
+    algo, used, ms = sn.sn_conv_plan(shape, F, mn)
+    assert (algo, used) == (sn.SN_ALGO_STAGED, mn) and 0 < ms < 1e6
+    sn.sn_planner_record(shape, F, sn.SN_ALGO_STAGED, mn, 1e-6)
+    assert torch.equal(run(sn.SN_ALGO_AUTO, ws), own)
+    sn.sn_planner_record(shape, F, sn.SN_ALGO_STAGED, mn, 1e6)
+    sn.sn_planner_record(shape, F, sn.SN_ALGO_STAGED, pf, 1e-6)
+    assert torch.equal(run(sn.SN_ALGO_AUTO, ws), product)
+    sn.sn_planner_clear()
