@@ -320,6 +320,7 @@ double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
     if (dir == SN_CONV_BWD_DATA && scatter_bwd_data(g)) return 0;
     if (dir == SN_CONV_FWD && g.R == 1 && g.S == 1 && gather_fwd(g)) return 0;
     if (g.sh > 1 || g.sw > 1) return general;
+    if (pointwise_supported(g, dir == SN_CONV_BWD_DATA)) return 0;
     // a workgroup's own chain over the reduction (8 x 8x8, 3x3: 32 channels forward 13, backward-data 44 us; 128 forward 26;
     // the product 13 to 15)
     if (!tile_conv_supported(g, dir == SN_CONV_BWD_DATA))
@@ -474,11 +475,11 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
         return SN_OK;
     }
     // The channels-last product where it is the fastest, under the name that runs it with this budget.
+    ChlastPlan cl;
+    const bool product = chlast_runs(g, dir, SN_ALGO_STAGED, budget, &cl);
     for (sn_conv_algo a : {SN_ALGO_STAGED, SN_ALGO_IM2COL_GEMM}) {
         size_t mn = 0, pf = 0;
-        ChlastPlan cl;
-        if (budget == 0 || query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
-        if (!chlast_runs(g, dir, SN_ALGO_STAGED, budget, &cl)) break;
+        if (!product || query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
         *algo = a;
         *bytes = std::max(cl.bytes, mn);   // (mn: the least the name is accepted with; for IM2COL_GEMM one unfolded image)
         if (ms_out) *ms_out = -1.f;
