@@ -336,34 +336,42 @@ size_t tile_conv_packed_bytes(const ConvGeom &g, bool bwd_data)
     return align_up((size_t)pl.p.nchunks * g.R * g.S * pl.p.Mpad * 16 * sizeof(bf16_t), 256);
 }
 
-// What launch_tile_conv with a packed filter takes, in us, where that can compete with the channels-last product: 3x3
-// filters on planes whose patches are full (WIDE tilings, and everything the second-generation kernel takes), 1x1, and 5x5
-// filters with at most 64 output channels, and 3x3 on short rows with few channels.  Per 16-channel chunk and workgroup the
-// times below (measured over 100 shapes, 32 to 512 channels, planes of 12x12 to 224x224); elsewhere the channels-last product was 1.2 to 10 times faster.
+// What launch_tile_conv with a packed filter takes, in us, for the choice between it and the channels-last product:
+// base + rounds * (chunk * 16-channel chunks + tile), rounds = workgroups over 256 compute units in halves (two share one),
+// at least 1.  Fitted per filter, generation, tiling and tile to 1600 timings (2 to 128 images, 16 to 640 channels, planes of 7x7 to
+// 224x224), which it reproduces to 5 to 13 % (rms; the few 1x1 layers without a kernel of their own: 20 %).
+struct TileCost {
+    int taps;         // R * S
+    bool second, wide, kt64;
+    int NF;
+    double base, chunk, tile;
+};
+const TileCost kTileCost[] = {
+    {9, false, false, false, 1, 10.2, 1.55, 0},  {9, false, false, false, 2, 12.5, 1.95, 0},  {9, false, false, false, 4, 15.5, 2.4, 3.2},
+    {9, false, false, true, 2, 10.4, 1.86, 0},   {9, false, true, false, 1, 10.4, 1.2, 0},    {9, false, true, false, 2, 13.3, 1.38, 0},
+    {9, false, true, false, 4, 15.4, 2.17, 4.1}, {9, false, true, true, 2, 10.7, 1.31, 1.2},  {9, true, false, false, 2, 10, 1.16, 2.2},
+    {9, true, false, false, 4, 14.5, 1.85, 2.5}, {9, true, true, false, 2, 9, 1.0, 1.5},      {9, true, true, false, 4, 8.8, 1.63, 2.6},
+    {9, true, true, true, 2, 7.5, 1.03, 0},
+    {25, false, false, false, 4, 20.7, 7.15, 0}, {25, false, true, false, 4, 0, 10.5, 18},    {25, false, false, true, 2, 12.4, 3.56, 0.3},
+    {25, false, true, true, 2, 6.6, 3.42, 3.2},
+    {7, false, false, false, 4, 10.5, 4.15, 8.4}, {7, false, true, false, 4, 10.4, 2.26, 7.4}, {7, false, false, true, 4, 8.4, 2.6, 7},
+    {7, false, true, true, 4, 12.5, 2.86, 0},
+    {1, false, false, false, 1, 10.1, 0.77, 0},  {1, false, false, false, 2, 13.1, 0.45, 0},  {1, false, false, false, 4, 4.4, 1.0, 5},
+    {1, false, true, false, 1, 10.7, 0.41, 0},   {1, false, true, false, 2, 10.7, 0.28, 1.0}, {1, false, true, false, 4, 4.4, 0.44, 4.3},
+    {1, false, false, true, 1, 9.8, 0.64, 0},    {1, false, true, true, 1, 11.5, 0.21, 0},    {1, false, true, true, 4, 14.4, 0.6, 2.7}};
+
 double tile_conv_us(const ConvGeom &g, bool bwd_data)
 {
-    constexpr double NEVER = 1e9;
     TileProblem p;
-    Plan pl;
-    if (!tile_conv_supported(g, bwd_data) || !problem_of(g, bwd_data, &p) || !make_plan(p, g.R, g.S, true, &pl)) return NEVER;
-    if (pointwise_supported(g, bwd_data)) return 0;
-    if (g.R == 1 && g.S == 1)
-        return 5 + (pl.NF == 4 ? 1.3 : 1.0) * pl.p.nchunks * std::max(1.0, (double)pl.p.nptiles * pl.p.nktiles / 256);
-    if (!(g.R == 3 && g.S == 3) && !(g.R == 5 && g.S == 5 && pl.KT == 64 && pl.NF <= 2)) return NEVER;
-    Plan pl2;
+    Plan pl, pl2;
+    if (!filter_supported(g.R, g.S) || !problem_of(g, bwd_data, &p) || !make_plan(p, g.R, g.S, true, &pl)) return 1e9;
     const bool second = make_plan2(p, g.R, g.S, &pl2);
     if (second) pl = pl2;
-    else if (!pl.wide) {
-        // Short rows: patches are cut out row by row.  2 x 16x16 to 32 x 16x16, any batch: 16 and 32 channels 11.5 us with the
-        // call (the product 12.7), 64 channels 14.5 (12.7), 128 22 (15.5), 14x14 rows 3 us more.
-        if (g.R != 3) return NEVER;
-        const double chunk = pl.KT == 64 ? 1.8 : 1.45;
-        return (g.Q % 4 == 0 ? 6 : 9) + chunk * pl.p.nchunks * std::max(1.0, (double)pl.p.nptiles * pl.p.nktiles / 256);
-    }
-    double us = pl.KT == 64 ? (pl.NF == 1 ? 1.0 : pl.NF == 2 ? 1.7 : 3.0) * (second ? 0.68 : 1)
-                            : (pl.NF == 1 ? 1.4 : pl.NF == 2 ? 2.0 : 3.0) * (second ? 0.80 : 1.15);
-    us *= g.R * g.S / 9.0;
-    return 5 + us * pl.p.nchunks * std::max(1.0, (double)pl.p.nptiles * pl.p.nktiles / 256);
+    const double rounds = std::max(1.0, std::ceil((double)pl.p.nptiles * pl.p.nktiles / 128) / 2);
+    for (const TileCost &t : kTileCost)
+        if (t.taps == g.R * g.S && t.second == second && t.wide == pl.wide && t.kt64 == (pl.KT == 64) && t.NF == pl.NF)
+            return t.base + rounds * (t.chunk * pl.p.nchunks + t.tile);
+    return 1e9;   // not measured; the product was 1.2 to 10 times faster elsewhere
 }
 
 // Pixel tiles of the plan launch_tile_conv would use (forward); 0 if the kernels do not apply.

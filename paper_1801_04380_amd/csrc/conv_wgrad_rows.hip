@@ -594,16 +594,26 @@ bool rows_wgrad_supported(const ConvGeom &g)
     return make_rplan(g, &pl);
 }
 
-// What launch_rows_wgrad takes, in the product's estimated us, for 3x3 and 1x1 filters (elsewhere the product was 1.2 to 6 times
-// faster): per chunk, and the launches.  3x3 on 13x13 to 32x32 planes, 64 to 512 channels: 10 to 12 us where the product
-// takes 8 (64 channels), 53 where it takes 75 (512 channels, 13x13).
+// What launch_rows_wgrad takes, in us, for the choice between it and the channels-last product: base + rounds * (chunk * chunks per
+// slice + tile) + the partial sums' bytes, rounds = workgroups over 256 compute units, rounded up.  Fitted per row width and tile
+// to 270 timings of 3x3 layers (16 to 640 channels, planes of 7x7 to 224x224), which it reproduces to 3 to 11 % (rms; on
+// rows of at most 16 pixels, or of 33 to 64 with 64-channel tiles, 20 %).
+struct RowsCost { int TWP, TM, TP; bool wide; double base, chunk, tile, per_mb; };
+const RowsCost kRowsCost[] = {{16, 1, 1, false, 19.8, 2.24, 2.3, 0.44},  {32, 1, 1, false, 12.4, 2.06, 10.1, 0.61}, {32, 1, 2, false, 20.1, 1.5, 0, 0.42},
+                              {32, 1, 2, true, 14.7, 1.68, 0, 0.76},     {32, 2, 1, false, 21.8, 2.71, 9.7, 0.24},  {32, 2, 1, true, 15.9, 2.42, 7.7, 0.56},
+                              {64, 1, 1, false, 6.5, 1.85, 17, 0.42},    {64, 2, 1, false, 23.3, 3.09, 8.4, 0.11},  {32, 1, 1, true, 12.4, 2.06, 10.1, 0.61}};
+
 double rows_wgrad_us(const ConvGeom &g)
 {
     RPlan pl;
     if (!make_rplan(g, &pl) || g.R != g.S || g.R > 3 || (g.R == 1 && pl.TWP == 16)) return 1e9;
-    const double wgs = (double)pl.p.ctiles * pl.p.ktiles * pl.nslices, rounds = std::ceil(wgs / 256);
-    const double chunk = g.R == 1 ? 1.2 : pl.TWP == 16 || (pl.TM == 1 && pl.TP == 2) ? 2.8 : 2.5;
-    return (g.R == 1 ? 10 : 16) + rounds * pl.p.cps * chunk + (double)rows_wgrad_partial_bytes(g) / 4.3e6;
+    const double rounds = std::ceil((double)pl.p.ctiles * pl.p.ktiles * pl.nslices / 256);
+    const double mb = (double)rows_wgrad_partial_bytes(g) / 1e6;
+    if (g.R == 1) return 10 + rounds * pl.p.cps * 1.2 + mb / 4.3;
+    for (const RowsCost &t : kRowsCost)
+        if (t.TWP == pl.TWP && t.TM == pl.TM && t.TP == pl.TP && t.wide == pl.wide)
+            return t.base + rounds * (t.chunk * pl.p.cps + t.tile) + t.per_mb * mb;
+    return 1e9;
 }
 
 // All its partial sums.

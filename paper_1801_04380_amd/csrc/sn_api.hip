@@ -312,9 +312,9 @@ double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
     if (dir == SN_CONV_BWD_FILTER) {
         if (g.sh > 1 || g.sw > 1 || !tile_wgrad_supported(g)) return general;
         // 1x1 on planes of odd sizes or short rows: bound by memory up to 256 channels on either side, where copies are a
-        // second pass; with more the product's larger tiles win
+        // second pass; with more the product's larger tiles win, but for the smallest planes
         if (pointwise_wgrad_supported(g))
-            return std::min(g.C, g.K) > 256 ? 1e9 : 7 + (double)g.N * g.P * g.Q * (g.C + g.K) * 2 / 1.5e6;
+            return std::min(g.C, g.K) > 256 ? (g.P * g.Q <= 64 ? 8 + flops / 2e8 : 1e9) : 7 + (double)g.N * g.P * g.Q * (g.C + g.K) * 2 / 1.5e6;
         return rows_wgrad_us(g);
     }
     if (dir == SN_CONV_BWD_DATA && scatter_bwd_data(g)) return 0;

@@ -59,7 +59,7 @@ size_t tile_conv_packed_bytes(const ConvGeom &g, bool bwd_data);
 hipError_t launch_tile_conv(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data,
                             void *packed, hipStream_t st, float *stats = nullptr);
 int tile_conv_stats_tiles(const ConvGeom &g, bool staged, bool in_aligned16);
-double tile_conv_us(const ConvGeom &g, bool bwd_data);   // estimate; 0: nothing is faster, very large: everything is
+double tile_conv_us(const ConvGeom &g, bool bwd_data);   // estimate; very large: everything is faster
 
 // Stride-1 bf16 backward-filter fast path.  partial == nullptr: the slices of the
 // (n,p,q) sum combine with atomics into a zero-filled dw; otherwise slice z writes
