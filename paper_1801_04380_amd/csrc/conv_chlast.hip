@@ -25,7 +25,7 @@ const Tile kTile[] = {{128, 128, 2, {0.08, 0.708}, {1.96, 0.432}},
                       {128, 128, 1, {NEVER, 0.543}, {NEVER, 0.117}}};
 constexpr int NTILE = 5;
 const Tile kWTile[] = {{128, 128, 2, {NEVER, 0.279}, {NEVER, 0.210}},
-                       {64, 128, 2, {0.022, 0.011}, {0.554, 0.183}},
+                       {64, 128, 2, {NEVER, 0.011}, {NEVER, 0.183}},   // (fp32: 0.55 busy, more than two 64 x 64)
                        {64, 64, 3, {0.304, 0.154}, {0.257, 0.103}},
                        {256, 256, 1, {NEVER, 0.689}, {NEVER, 0.080}}};
 constexpr int NWTILE = 4;
@@ -471,10 +471,10 @@ hipError_t run_wgrad(const void *x, const void *dy, float *dw, const ConvGeom &g
         p.slice0 = slices;
         slices += q.nsl;
         e = hipErrorInvalidValue;
-        if (f.cfg == 1) e = launch_wgemm<T, 64, 128, 2, 2, 4>(ds, xs, part, p, st);
-        else if (f.cfg == 2) e = launch_wgemm<T, 64, 64, 2, 2, 4>(ds, xs, part, p, st);
+        if (f.cfg == 2) e = launch_wgemm<T, 64, 64, 2, 2, 4>(ds, xs, part, p, st);
         if constexpr (sizeof(T) == 2) {
-            if (f.cfg == 0) e = launch_wgemm<T, 128, 128, 2, 2, 4>(ds, xs, part, p, st);
+            if (f.cfg == 1) e = launch_wgemm<T, 64, 128, 2, 2, 4>(ds, xs, part, p, st);
+            else if (f.cfg == 0) e = launch_wgemm<T, 128, 128, 2, 2, 4>(ds, xs, part, p, st);
             else if (f.cfg == 3) e = launch_wgemm<T, 256, 256, 2, 4, 4>(ds, xs, part, p, st);
         }
         if (e != hipSuccess) return e;
