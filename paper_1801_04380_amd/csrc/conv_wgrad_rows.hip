@@ -595,25 +595,36 @@ bool rows_wgrad_supported(const ConvGeom &g)
 }
 
 // What launch_rows_wgrad takes, in us, for the choice between it and the channels-last product: base + rounds * (chunk * chunks per
-// slice + tile) + the partial sums' bytes, rounds = workgroups over 256 compute units, rounded up.  Fitted per row width and tile
-// to 270 timings of 3x3 layers (16 to 640 channels, planes of 7x7 to 224x224), which it reproduces to 3 to 11 % (rms; on
-// rows of at most 16 pixels, or of 33 to 64 with 64-channel tiles, 20 %).
-struct RowsCost { int TWP, TM, TP; bool wide; double base, chunk, tile, per_mb; };
-const RowsCost kRowsCost[] = {{16, 1, 1, false, 19.8, 2.24, 2.3, 0.44},  {32, 1, 1, false, 12.4, 2.06, 10.1, 0.61}, {32, 1, 2, false, 20.1, 1.5, 0, 0.42},
-                              {32, 1, 2, true, 14.7, 1.68, 0, 0.76},     {32, 2, 1, false, 21.8, 2.71, 9.7, 0.24},  {32, 2, 1, true, 15.9, 2.42, 7.7, 0.56},
-                              {64, 1, 1, false, 6.5, 1.85, 17, 0.42},    {64, 2, 1, false, 23.3, 3.09, 8.4, 0.11},  {32, 1, 1, true, 12.4, 2.06, 10.1, 0.61}};
+// slice + tile) + the partial sums' bytes, rounds = workgroups over 256 compute units, rounded up.  Fitted per filter, row width,
+// tile and whether the last 64-channel tile is whole to 800 timings of 3x3, 1x7 and 7x1 layers (16 to 640 channels, planes of 7x7
+// to 224x224), which it reproduces to 3 to 13 % (rms).
+struct RowsCost { int taps, TWP, TM, TP; bool wide, whole; double base, chunk, tile, per_mb; };
+const RowsCost kRowsCost[] = {
+    {9, 16, 1, 1, false, false, 10.5, 1.54, 14.2, 0.72}, {9, 16, 1, 1, false, true, 8.1, 1.38, 6.4, 0.38},
+    {9, 16, 2, 1, false, false, 22.7, 2.77, 9.1, 0.20},  {9, 16, 2, 1, false, true, 8.9, 2.94, 0, 0.32},
+    {9, 32, 1, 1, false, false, 11.9, 1.86, 11.1, 0.68}, {9, 32, 1, 1, false, true, 9.8, 1.29, 4.8, 0.32},
+    {9, 32, 1, 1, true, false, 13, 1.9, 8, 0.70},        {9, 32, 1, 1, true, true, 11.1, 1.63, 4.4, 0.29},
+    {9, 32, 1, 2, false, false, 20.1, 1.62, 0, 0.37},    {9, 32, 1, 2, false, true, 8.1, 1.59, 7.3, 0.23},
+    {9, 32, 1, 2, true, false, 14.5, 1.72, 0, 0.76},     {9, 32, 1, 2, true, true, 19, 2.23, 0, 0.07},
+    {9, 32, 2, 1, false, false, 22.7, 2.77, 9.1, 0.20},  {9, 32, 2, 1, false, true, 8.9, 2.94, 0, 0.32},
+    {9, 32, 2, 1, true, false, 16.8, 2.43, 7.4, 0.51},   {9, 32, 2, 1, true, true, 13.1, 3.04, 0, 0.27},
+    {9, 64, 1, 1, false, false, 9.2, 1.8, 13.1, 0.75},   {9, 64, 1, 1, false, true, 14.5, 1.64, 0, 0.33},
+    {9, 64, 2, 1, false, false, 22.1, 3.01, 2.9, 0.46},  {9, 64, 2, 1, false, true, 9.9, 3.62, 0, 0.24},
+    {7, 16, 1, 1, false, false, 11.6, 1.92, 10, 0.71},   {7, 16, 1, 1, false, true, 10.9, 1.59, 1.1, 0.46},
+    {7, 32, 1, 1, false, false, 10.2, 1.56, 8.6, 0.86},  {7, 32, 1, 1, false, true, 12.9, 1.52, 0, 0.33},
+    {7, 64, 1, 1, false, false, 21.6, 1.51, 0, 0.65}};
 
 double rows_wgrad_us(const ConvGeom &g)
 {
     RPlan pl;
-    if (!make_rplan(g, &pl) || g.R != g.S || g.R > 3 || (g.R == 1 && pl.TWP == 16)) return 1e9;
+    if (!make_rplan(g, &pl) || (g.R * g.S == 1 && pl.TWP == 16)) return 1e9;
     const double rounds = std::ceil((double)pl.p.ctiles * pl.p.ktiles * pl.nslices / 256);
     const double mb = (double)rows_wgrad_partial_bytes(g) / 1e6;
-    if (g.R == 1) return 10 + rounds * pl.p.cps * 1.2 + mb / 4.3;
+    if (g.R * g.S == 1) return 10 + rounds * pl.p.cps * 1.2 + mb / 4.3;
     for (const RowsCost &t : kRowsCost)
-        if (t.TWP == pl.TWP && t.TM == pl.TM && t.TP == pl.TP && t.wide == pl.wide)
+        if (t.taps == g.R * g.S && t.TWP == pl.TWP && t.TM == pl.TM && t.TP == pl.TP && t.wide == pl.wide && t.whole == (g.C % CTB == 0))
             return t.base + rounds * (t.chunk * pl.p.cps + t.tile) + t.per_mb * mb;
-    return 1e9;
+    return 1e9;   // (5x5: the product was 1.2 to 6 times faster)
 }
 
 // All its partial sums.

@@ -328,9 +328,9 @@ double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
     return tile_conv_us(g, dir == SN_CONV_BWD_DATA);
 }
 
-// Whether the channels-last product is to run under this name with this workspace: where it is the faster one (against
-// unfolding always), in few passes over the batch (each is some launches) -- more where only the general kernels are left.
-bool chlast_runs(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t ws_bytes, ChlastPlan *plan)
+// Whether the channels-last product is the faster one with this workspace (against unfolding always), in few passes over the
+// batch (each is some launches) -- more where only the general kernels are left.
+bool chlast_faster(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t ws_bytes, ChlastPlan *plan)
 {
     if (ws_bytes == 0 || (algo != SN_ALGO_STAGED && algo != SN_ALGO_IM2COL_GEMM)) return false;
     double other = algo == SN_ALGO_IM2COL_GEMM ? 1e9 : other_us(g, dir, ws_bytes);
@@ -339,6 +339,29 @@ bool chlast_runs(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t w
     if (other <= CHLAST_LEAST_US || !chlast_plan(g, dir, ws_bytes, plan)) return false;
     const bool alone = dir == SN_CONV_BWD_FILTER ? !tile_wgrad_supported(g) : dir == SN_CONV_FWD && !tile_conv_supported(g, false);
     return plan->passes <= (alone ? 8 : 2) && plan->us < other;
+}
+
+sn_status own_query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *min_b, size_t *pref_b);
+
+// With exactly the bytes its own kernels can use, STAGED backward-filter runs those: they take no less than the product does, so
+// that no other workspace would say which is meant (forward's and backward-data's own kernels take less).
+bool own_bytes(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t ws_bytes)
+{
+    size_t mn = 0, pf = 0;
+    return dir == SN_CONV_BWD_FILTER && algo == SN_ALGO_STAGED && own_query(g, dir, algo, &mn, &pf) == SN_OK && ws_bytes == pf;
+}
+
+// Whether the call of this name runs it with this workspace.
+bool chlast_runs(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t ws_bytes, ChlastPlan *plan)
+{
+    return chlast_faster(g, dir, algo, ws_bytes, plan) && !own_bytes(g, dir, algo, ws_bytes);
+}
+
+// The workspace that names it: what it uses, at least what the name is accepted with (for IM2COL_GEMM one unfolded image).
+size_t chlast_bytes(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, const ChlastPlan &plan, size_t min_bytes)
+{
+    const size_t b = std::max(plan.bytes, min_bytes);
+    return own_bytes(g, dir, algo, b) ? b + WS_ALIGN : b;
 }
 
 constexpr size_t ALL_BYTES = ~(size_t)0 / 2;
@@ -476,12 +499,14 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
     }
     // The channels-last product where it is the fastest, under the name that runs it with this budget.
     ChlastPlan cl;
-    const bool product = chlast_runs(g, dir, SN_ALGO_STAGED, budget, &cl);
+    const bool product = chlast_faster(g, dir, SN_ALGO_STAGED, budget, &cl);
     for (sn_conv_algo a : {SN_ALGO_STAGED, SN_ALGO_IM2COL_GEMM}) {
         size_t mn = 0, pf = 0;
         if (!product || query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
+        const size_t need = chlast_bytes(g, dir, a, cl, mn);
+        if (need > budget) continue;
         *algo = a;
-        *bytes = std::max(cl.bytes, mn);   // (mn: the least the name is accepted with; for IM2COL_GEMM one unfolded image)
+        *bytes = need;
         if (ms_out) *ms_out = -1.f;
         return SN_OK;
     }
@@ -972,7 +997,7 @@ sn_status sn_conv_autotune(sn_conv_dir dir, const void *a, const void *b, void *
         if (query(g, dir, algo, &mn, &pf) != SN_OK || mn > workspace_bytes) continue;
         ChlastPlan cl;
         const bool product = chlast_runs(g, dir, algo, workspace_bytes, &cl);
-        todo.push_back({algo, product ? std::max(cl.bytes, mn) : std::min(pf, workspace_bytes)});
+        todo.push_back({algo, product ? std::min(chlast_bytes(g, dir, algo, cl, mn), workspace_bytes) : std::min(pf, workspace_bytes)});
         if (!product || algo != SN_ALGO_STAGED || own_query(g, dir, algo, &own_mn, &own_pf) != SN_OK) continue;
         for (size_t own : {own_pf, own_mn})
             if (own <= workspace_bytes && !chlast_runs(g, dir, algo, own, &cl)) {

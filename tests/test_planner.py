@@ -1,10 +1,12 @@
 """CPU-only property tests of the planner against brute force on made-up timing
 tables (Sec. 3.5: skip the algorithms that need more memory than is free, take
 the fastest of the rest; more workspace never makes the plan slower)."""
+import ctypes
 import itertools
 import random
 
 import paper_1801_04380_amd as sn
+from paper_1801_04380_amd import _lib
 
 DIRS = (sn.SN_CONV_FWD, sn.SN_CONV_BWD_DATA, sn.SN_CONV_BWD_FILTER)
 ALGOS = (sn.SN_ALGO_DIRECT, sn.SN_ALGO_IM2COL_GEMM, sn.SN_ALGO_STAGED, sn.SN_ALGO_WINOGRAD)
@@ -180,3 +182,20 @@ def test_cold_start_weighs_winograd_against_the_product():
         shape = sn.conv_shape(N, C, H, W, K, 3, 3, (1, 1), (1, 1), sn.SN_F32, sn.SN_F32)
         for d in (sn.SN_CONV_FWD, sn.SN_CONV_BWD_DATA):
             assert sn.sn_conv_plan(shape, d, mib << 20)[0] == algo, (N, C, H, d)
+
+
+def test_backward_filter_with_its_own_kernels_bytes_runs_them():
+    """STAGED backward-filter's own kernels can be named (and so measured) by workspace: with exactly preferred_bytes they run,
+    whatever the estimates say, and a plan that names the product never has just those bytes."""
+    lib = _lib.load()
+    info, used, us = (ctypes.c_int * 5)(), ctypes.c_size_t(), ctypes.c_double()
+    rnd = random.Random(23)
+    beyond = 0
+    for _ in range(1000):
+        shape = _random_shape(rnd)
+        _, pf = sn.sn_conv_workspace_query(shape, sn.SN_CONV_BWD_FILTER, sn.SN_ALGO_STAGED)
+        runs = [lib.sn_chlast_inspect(ctypes.byref(shape), sn.SN_CONV_BWD_FILTER, sn.SN_ALGO_STAGED, ctypes.c_size_t(b), info,
+                                      ctypes.byref(used), ctypes.byref(us)) for b in (pf, 1 << 32)]
+        assert not runs[0]
+        beyond += runs[1]
+    assert beyond > 100   # (shapes whose STAGED is the product with more)
