@@ -143,9 +143,8 @@ int sn_out_dim(int in, int pad, int window, int stride);
  * memory-feasible iff its workspace fits the free bytes).
  *  min_bytes        least workspace with which the algorithm runs at all
  *  preferred_bytes  workspace beyond which it gets no faster, with one exception: STAGED's strided
- *                   forward and its backward-filter report what their own kernels can use (and run
- *                   those with it), and may change to the channels-last product (about the tensors' own
- *                   size) with more
+ *                   forward and its backward-filter report what their own kernels can use, and
+ *                   may change to the channels-last product (about the tensors' own size) with more
  * Returns SN_ERR_UNSUPPORTED if the algorithm cannot run this shape. */
 sn_status sn_conv_workspace_query(const sn_conv_shape *shape, sn_conv_dir dir, sn_conv_algo algo,
                                   size_t *min_bytes, size_t *preferred_bytes);

@@ -343,12 +343,12 @@ bool chlast_faster(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t
 
 sn_status own_query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *min_b, size_t *pref_b);
 
-// With exactly the bytes its own kernels can use, STAGED backward-filter runs those: they take no less than the product does, so
-// that no other workspace would say which is meant (forward's and backward-data's own kernels take less).
+// STAGED backward-filter's own kernels may take more workspace than the product does, so that no amount of it would say that they
+// are meant (forward's and backward-data's own kernels take less): this one does, one unit beyond what they can use.
 bool own_bytes(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t ws_bytes)
 {
     size_t mn = 0, pf = 0;
-    return dir == SN_CONV_BWD_FILTER && algo == SN_ALGO_STAGED && own_query(g, dir, algo, &mn, &pf) == SN_OK && ws_bytes == pf;
+    return dir == SN_CONV_BWD_FILTER && algo == SN_ALGO_STAGED && own_query(g, dir, algo, &mn, &pf) == SN_OK && ws_bytes == pf + WS_ALIGN;
 }
 
 // Whether the call of this name runs it with this workspace.
@@ -999,7 +999,7 @@ sn_status sn_conv_autotune(sn_conv_dir dir, const void *a, const void *b, void *
         const bool product = chlast_runs(g, dir, algo, workspace_bytes, &cl);
         todo.push_back({algo, product ? std::min(chlast_bytes(g, dir, algo, cl, mn), workspace_bytes) : std::min(pf, workspace_bytes)});
         if (!product || algo != SN_ALGO_STAGED || own_query(g, dir, algo, &own_mn, &own_pf) != SN_OK) continue;
-        for (size_t own : {own_pf, own_mn})
+        for (size_t own : {dir == SN_CONV_BWD_FILTER ? own_pf + WS_ALIGN : own_pf, own_mn})
             if (own <= workspace_bytes && !chlast_runs(g, dir, algo, own, &cl)) {
                 todo.push_back({algo, own});
                 break;

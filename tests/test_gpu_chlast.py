@@ -220,3 +220,29 @@ def test_measurements_choose_between_staged_kernels():
     sn.sn_planner_record(shape, F, sn.SN_ALGO_STAGED, pf, 1e-6)
     assert torch.equal(run(sn.SN_ALGO_AUTO, ws), product)
     sn.sn_planner_clear()
+
+
+def test_measurements_reach_the_backward_filter_kernel():
+    """The same for backward-filter, whose own kernel takes more workspace than the product: its time is recorded under the bytes
+    that name it, and AUTO runs it where that is the fastest record."""
+    layer, N = wl.Layer("w14", 64, 14, 14, 64, 3, 3, (1, 1), (1, 1), True, None, 1, False, None), 16
+    x, _, dy = (t.cuda() for t in wl.conv_inputs(layer, N, "bf16", 17))
+    shape = shape_of(layer, N, "bf16", "bf16")
+    assert _inspect(shape, B, 64 << 20, sn.SN_ALGO_STAGED)
+    ws = torch.empty(64 << 20, dtype=torch.uint8, device="cuda")
+    sn.sn_planner_clear()
+    sn.sn_conv_autotune(B, x, dy, torch.empty((64, 64, 3, 3), device="cuda"), shape, ws, iters=2)
+    slow = [(sn.SN_ALGO_DIRECT, 0)]
+    algo, used, _ = sn.sn_conv_plan(shape, B, 64 << 20)
+    while _inspect(shape, B, used, algo) or algo == sn.SN_ALGO_DIRECT:   # put what is not STAGED's own kernel out of the way
+        sn.sn_planner_record(shape, B, algo, used, 1e6 + len(slow))
+        slow.append((algo, used))
+        algo, used, ms = sn.sn_conv_plan(shape, B, 64 << 20)
+        assert len(slow) < 8 and ms < 1e6, slow
+    assert algo == sn.SN_ALGO_STAGED
+    out = [torch.full((64, 64, 3, 3), float("nan"), device="cuda") for _ in range(2)]
+    sn.sn_conv2d_bwd_filter(x, dy, out[0], shape, sn.SN_ALGO_STAGED, ws[:used])
+    sn.sn_conv2d_bwd_filter(x, dy, out[1], shape, sn.SN_ALGO_AUTO, ws)
+    assert torch.equal(out[0], out[1])
+    assert rel_l2(f64(out[0]), oracle.conv2d_bwd_filter(f64(x), f64(dy), (64, 64, 3, 3), (1, 1), (1, 1))) <= TOL["bf16"]
+    sn.sn_planner_clear()
