@@ -10,6 +10,7 @@ namespace {
 
 constexpr size_t WS_ALIGN = 256;
 constexpr size_t COPY_MAX = (size_t)1 << 30;   // bytes of one pass's copy: 32-bit offsets, bit 31 marks "outside"
+constexpr int GRID_Y = 65535;                  // output channels of the kernels that add up slices are rows of their grid
 constexpr size_t IMAGE_MAX = (size_t)1 << 31;  // below this, bytes of a source image: likewise (a stride may leave most of it out of the copy)
 
 // Tiles, and what they take: a workgroup alone on its compute unit needs `alone` us per stage of its reduction; with
@@ -178,7 +179,7 @@ void choose(FwdPlan *f, int nimg, size_t part_limit)
         }
         const double copy = (double)nimg * (f->Cr * (double)f->SH * f->SW + (double)f->planes * f->Hp * f->Ws * f->Cp) * f->sz;
         for (int s = 1; s <= 16; s = s < 4 ? s + 1 : s * 2) {
-            if (s > 1 && (f->ncls > 1 || most / s < 4)) break;
+            if (s > 1 && (f->ncls > 1 || most / s < 4 || f->M > GRID_Y)) break;
             const double pb = s > 1 ? (double)s * f->M * npix * 4 : 0;
             if (pb > part_limit) break;
             double t = std::max(loop_us(k, bf16, wgs * s, work / wgs / s), 0.9 * longest / s * k.alone[bf16]);
@@ -387,7 +388,7 @@ size_t w_bytes(const ConvGeom &g, WPlan *f, int nimg)
 // for partial sums).
 bool w_plan(const ConvGeom &g, size_t budget, WPlan *f)
 {
-    if (!w_geometry(g, f) || std::max((size_t)g.C * g.H * g.W, (size_t)g.K * g.P * g.Q) * f->sz >= IMAGE_MAX) return false;
+    if (g.K > GRID_Y || !w_geometry(g, f) || std::max((size_t)g.C * g.H * g.W, (size_t)g.K * g.P * g.Q) * f->sz >= IMAGE_MAX) return false;
     const size_t per = (size_t)f->planes * f->Pp * f->Ws * f->Cp * f->sz, dper = (size_t)f->Pp * f->Qp * f->Kp * f->sz;
     if (std::max(per, dper) > COPY_MAX) return false;
     const int cap = (int)std::min<size_t>(g.N, COPY_MAX / std::max(per, dper)), bf16 = f->sz == 2;

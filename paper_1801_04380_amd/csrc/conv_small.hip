@@ -74,7 +74,7 @@ bool small3x3_supported(const ConvGeom &g, bool bwd)
     if (g.in_bf16 || g.R != 3 || g.S != 3 || g.sh != 1 || g.sw != 1 || g.P < 1 || g.Q < 1) return false;
     const long long M = bwd ? g.C : g.K, red = bwd ? g.K : g.C, npix = (long long)g.N * (bwd ? g.H * (long long)g.W : g.P * (long long)g.Q);
     const long long inputs = (long long)g.N * red * (bwd ? g.P * (long long)g.Q : g.H * (long long)g.W);
-    return M * red * npix * 9 <= SMALL3X3_MACS && inputs < (1LL << 31);
+    return M * red * npix * 9 <= SMALL3X3_MACS && M <= 65535LL * KO && inputs < (1LL << 31);   // (KO output channels per grid row)
 }
 
 hipError_t launch_small3x3(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd, hipStream_t st)

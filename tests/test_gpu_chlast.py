@@ -246,3 +246,15 @@ def test_measurements_reach_the_backward_filter_kernel():
     assert torch.equal(out[0], out[1])
     assert rel_l2(f64(out[0]), oracle.conv2d_bwd_filter(f64(x), f64(dy), (64, 64, 3, 3), (1, 1), (1, 1))) <= TOL["bf16"]
     sn.sn_planner_clear()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d", [F, D, B], ids=["fwd", "bwd_data", "bwd_filter"])
+def test_more_output_channels_than_a_grid_has_rows(d, dtype):
+    case = (1, 8, 5, 5, 70000, 1, 1, (1, 1), (0, 0)) if d != D else (1, 70000, 5, 5, 8, 1, 1, (1, 1), (0, 0))
+    shape = sn.conv_shape(*case, CODE[dtype], CODE[dtype])
+    try:
+        least = sn.sn_conv_workspace_query(shape, d, sn.SN_ALGO_IM2COL_GEMM)[0]
+    except sn.SnError:   # (unfolding 70000 input channels is refused; the name with it)
+        return
+    _check("channels", case, dtype, d, max(BIG, least))

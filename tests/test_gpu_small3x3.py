@@ -34,3 +34,19 @@ def test_small3x3(shape, dtype):
     for got, ref in ((y, oracle.conv2d_fwd(xo, wo, (1, 1), (p, p))), (dx, oracle.conv2d_bwd_data(dyo, wo, x.shape, (1, 1), (p, p)))):
         err = np.linalg.norm(got.double().cpu().numpy() - ref) / np.linalg.norm(ref)
         assert err <= TOL[dtype], err
+
+
+@pytest.mark.parametrize("backward", [False, True], ids=["fwd", "bwd_data"])
+def test_more_output_channels_than_a_grid_has_rows(backward):
+    """Four output channels per row of the grid, of which there are 65535: beyond, the general kernel answers."""
+    M, red = 300000, 2
+    K, C = (red, M) if backward else (M, red)
+    a = wl.activation((1, red, 1, 1), "f32", 3)
+    w = wl.activation((K, C, 3, 3), "f32", 4)
+    sh = sn.conv_shape(1, C, 1, 1, K, 3, 3, (1, 1), (1, 1), sn.SN_F32, sn.SN_F32)
+    out = torch.full((1, M, 1, 1), float("nan"), device="cuda")
+    (sn.sn_conv2d_bwd_data if backward else sn.sn_conv2d_fwd)(a.cuda(), w.cuda(), out, sh, sn.SN_ALGO_DIRECT)
+    torch.cuda.synchronize()
+    taps = w[:, :, 1, 1].double().numpy()   # one pixel: the centre tap alone
+    ref = a.double().numpy().reshape(red) @ (taps if backward else taps.T)
+    assert np.linalg.norm(out.double().cpu().numpy().reshape(M) - ref) / np.linalg.norm(ref) <= TOL["f32"]

@@ -199,3 +199,17 @@ def test_backward_filters_own_kernels_have_a_workspace_that_names_them():
         assert not runs[0]
         beyond += runs[1]
     assert beyond > 100   # (shapes whose STAGED is the product with more)
+
+
+def test_more_output_channels_than_a_grid_has_rows():
+    """The product's slice sums give every output channel a row of the grid, of which there are 65535: with more channels there
+    are no slices, and no product for backward-filter."""
+    lib = _lib.load()
+    info, used, us = (ctypes.c_int * 5)(), ctypes.c_size_t(), ctypes.c_double()
+    for K, R, dt in ((65535, 1, sn.SN_BF16), (65536, 1, sn.SN_BF16), (70000, 3, sn.SN_BF16), (70000, 3, sn.SN_F32)):
+        shape = sn.conv_shape(1, 512, 5, 5, K, R, R, (1, 1), (R // 2, R // 2), dt, dt)
+        for d in (sn.SN_CONV_FWD, sn.SN_CONV_BWD_FILTER):
+            runs = lib.sn_chlast_inspect(ctypes.byref(shape), d, sn.SN_ALGO_IM2COL_GEMM, ctypes.c_size_t(1 << 34), info, ctypes.byref(used),
+                                         ctypes.byref(us))
+            assert runs == (d == sn.SN_CONV_FWD or K <= 65535), (K, d)
+            assert not runs or K <= 65535 or info[3] == 1, (K, d, list(info))
