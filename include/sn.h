@@ -104,7 +104,9 @@ typedef enum { SN_CONV_FWD = 0, SN_CONV_BWD_DATA = 1, SN_CONV_BWD_FILTER = 2 } s
  *               estimated to be faster than these kernels and the workspace given
  *               holds it, STAGED runs that (which of them ran is a matter of the
  *               order of the sums only); sn_conv_plan's bytes_used then says how
- *               much of the budget it takes, and sn_conv_autotune times both.
+ *               much of the budget it takes, and sn_conv_autotune times both
+ *               (backward-filter's own kernels under preferred_bytes + 256, with exactly
+ *               which they run whatever the estimates say).
  *  WINOGRAD     F(2x2, 3x3) for the fp32 path (3x3 filters, stride 1, forward and
  *               backward-data): the transformed filter, the transformed input
  *               tiles and the 16 products per tile live in the workspace, for as
