@@ -5,6 +5,7 @@
 // workgroups for 256 compute units, and fixed-order wavefront reductions for
 // the BN statistics.  Storage is fp32 or bf16; arithmetic is fp32.
 #include "sn_internal.h"
+#include <climits>
 #include <type_traits>
 
 namespace sn {
@@ -49,7 +50,7 @@ template <> struct Vec<bf16_t> {
         uint32_t w[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            w[i] = (uint32_t)f32_to_bf16(f[2 * i]) | ((uint32_t)f32_to_bf16(f[2 * i + 1]) << 16);
+            w[i] = f32x2_to_bf16x2(f[2 * i], f[2 * i + 1]);
         *reinterpret_cast<uint4 *>(p) = make_uint4(w[0], w[1], w[2], w[3]);
     }
 };
@@ -207,7 +208,7 @@ template <typename T, int VB> __device__ inline typename RawVec<VB>::type pack(c
     if (sizeof(T) == 2) {
 #pragma unroll
         for (int i = 0; i < VB / 4; ++i)
-            w[i] = (uint32_t)f32_to_bf16(f[2 * i]) | ((uint32_t)f32_to_bf16(f[2 * i + 1]) << 16);
+            w[i] = f32x2_to_bf16x2(f[2 * i], f[2 * i + 1]);
     } else {
 #pragma unroll
         for (int i = 0; i < VB / 4; ++i) w[i] = __float_as_uint(f[i]);
@@ -1166,72 +1167,136 @@ maxpool3s2_fwd_kernel(const T *__restrict__ x, T *__restrict__ y, int32_t *__res
 }
 
 // 3x3 windows, stride 2 (the overlapping pool of the AlexNet- and Inception-style workloads),
-// backward: a thread owns 8 neighbouring columns of one input row.  At most 2 window rows and
-// 5 window columns cover them; their indices and gradients are read as one run per window row, both
-// rows before either is used (a loop over the windows waits for memory once per window), and
-// added, in ascending (p, q) order -- the order of the one-thread-per-element kernel -- to
-// the column the index names, and the row piece leaves in one store (the last one of a row moved
-// back to end with it).  128 x 96 x 55x55 bf16: 82 -> 60 us; the ten compares of eight columns bound it now.
+// backward.  In coordinates of the padded image window (p, q) covers rows 2p .. 2p + 2 and columns
+// 2q .. 2q + 2, so a piece of rows (2m, 2m + 1) x columns 8g .. 8g + 7 meets windows p = m - 1, m and
+// q = 4g - 1 .. 4g + 3 only, and which of them can reach an element is known from the element's place in
+// the piece: an even row meets both p, an odd one the second; an even column e meets j = e/2 and
+// e/2 + 1, an odd one the latter.  A thread owns such a piece: 36 compares for its 16 elements, where
+// pieces that start anywhere need ten per element.  Gradients are added in ascending (p, q) order, the
+// order of the one-thread-per-element kernel.  A piece at the end of a row also looks at windows of the row
+// beside it: with two or more windows a row (Q >= 2, else the general kernel) none of those reaches a
+// column that it is compared with.
+// Rows of dx, and the window rows that reach them, are runs of memory that start anywhere; accesses of 16
+// bytes at such addresses cost more than aligned ones, so a workgroup brings its run of idx and dy to LDS,
+// and takes its run of dx from there, in aligned 16-byte pieces (each lies at the same offset from a 16-byte
+// boundary in LDS as in memory).  128 x 96 x 55x55 bf16: 59 -> 35 us
+// (pieces alone 67, dx through LDS 48, idx and dy too 44, all loads issued before the first wait 35); compulsory
+// bytes at the copy rate 23.
+template <typename T> __device__ inline int misplaced(const T *p) { return (int)((uintptr_t)p % 16 / sizeof(T)); }
+
+// A thread's 16-byte piece of a run of count elements, shift = misplaced(run), that goes to lds[i]: the i-th on of
+// the run moved up by shift.  A piece over either end is loaded whole where it lies inside the tensor [begin, end).
+template <typename T> __device__ inline uint4 run_piece(const T *run, int i, int count, int shift, const T *begin, const T *end)
+{
+    constexpr int EPV = 16 / (int)sizeof(T);
+    uint4 v = make_uint4(0, 0, 0, 0);
+    const T *p = run + (i - shift);
+    if (i >= shift + count) return v;
+    if (p >= begin && p + EPV <= end) return *reinterpret_cast<const uint4 *>(p);
+    T e[EPV];
+#pragma unroll
+    for (int j = 0; j < EPV; ++j) e[j] = p + j >= begin && p + j < end ? p[j] : T(0);
+    __builtin_memcpy(&v, e, 16);
+    return v;
+}
+template <typename T> __device__ inline void run_from_lds(T *run, const T *lds, int count, int shift)
+{
+    constexpr int EPV = 16 / (int)sizeof(T);
+    run -= shift;
+    for (int i = threadIdx.x * EPV; i < shift + count; i += 256 * EPV) {
+        if (i >= shift && i + EPV <= shift + count)
+            *reinterpret_cast<uint4 *>(run + i) = *reinterpret_cast<const uint4 *>(lds + i);
+        else
+            for (int j = max(i, shift); j < min(i + EPV, shift + count); ++j) run[j] = lds[j];
+    }
+}
+
+// LDS: 256 pieces of 16 elements of dx, and 8 for what lies outside; the windows of 256 >> lg row pairs and of one row more (at most 4 << lg a row:
+// W + pw <= 8 << lg and pw <= 2); each with room for its shift, and the windows for a piece that looks past either end.
+constexpr int POOL3_PAD = 16, POOL3_SPARE = 256 * 16 + 8;   // (SPARE: 8 elements behind the run and its shift)
+template <typename T> inline int pool3_bwd_lds(int lg)
+{
+    const int windows = 1024 + (4 << lg) + 2 * POOL3_PAD;
+    return (256 * 16 + POOL3_PAD) * (int)sizeof(T) + windows * (int)(sizeof(T) + sizeof(int32_t));
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256)
-maxpool3s2_bwd_kernel(const T *__restrict__ dy, const int32_t *__restrict__ idx, T *__restrict__ dx, unsigned rows,
-                      int H, int W, int P, int Q, int ph, int pw, int lg)
+maxpool3s2_bwd_kernel(const T *__restrict__ dy, const int32_t *__restrict__ idx, T *__restrict__ dx, unsigned planes,
+                      unsigned pairs, int M, int H, int W, int P, int Q, int ph, int pw, int lg)
 {
-    const unsigned row = blockIdx.x * (256u >> lg) + (threadIdx.x >> lg);
+    extern __shared__ __align__(16) char pool3_lds[];
+    T *tile = reinterpret_cast<T *>(pool3_lds);
+    int32_t *widx = reinterpret_cast<int32_t *>(tile + 256 * 16 + POOL3_PAD) + POOL3_PAD;
+    T *wdy = reinterpret_cast<T *>(widx + 1024 + (4 << lg) + POOL3_PAD) + POOL3_PAD;
+    const unsigned pair0 = blockIdx.x * (256u >> lg), pair1 = min(pairs, pair0 + (256u >> lg)) - 1;   // first and last pair
+    const unsigned nc0 = pair0 / (unsigned)M, nc1 = pair1 / (unsigned)M;
+    const int m0 = (int)(pair0 - nc0 * M), m1 = (int)(pair1 - nc1 * M);
+    const size_t row0 = (size_t)nc0 * P + min(max(m0 - 1, 0), P - 1);   // first window row, of all planes'
+    const int nwin = (int)((size_t)nc1 * P + min(m1, P - 1) + 1 - row0) * Q;
+    const int ishift = misplaced(idx + row0 * Q), gshift = misplaced(dy + row0 * Q);
+    // all of a thread's loads before the first is waited for (at most 1024 + (4 << lg) windows)
+    constexpr int GV = 16 / (int)sizeof(T), NI = 3, NG = sizeof(T) == 2 ? 2 : 3;
+    const int32_t *iend = idx + (size_t)planes * P * Q;
+    const T *gend = dy + (size_t)planes * P * Q;
+    uint4 vi[NI], vg[NG];
+#pragma unroll
+    for (int k = 0; k < NI; ++k) vi[k] = run_piece(idx + row0 * Q, (threadIdx.x + 256 * k) * 4, nwin, ishift, idx, iend);
+#pragma unroll
+    for (int k = 0; k < NG; ++k) vg[k] = run_piece(dy + row0 * Q, (threadIdx.x + 256 * k) * GV, nwin, gshift, dy, gend);
+#pragma unroll
+    for (int k = 0; k < NI; ++k) {
+        const int i = (threadIdx.x + 256 * k) * 4;
+        if (i >= ishift + nwin + 5) continue;
+        // what a piece reads before the first and past the last window names no element
+        const auto keep = [&](uint32_t v, int j) { return (unsigned)(i + j - ishift) < (unsigned)nwin ? v : (uint32_t)(INT_MIN / 2); };
+        *reinterpret_cast<uint4 *>(widx + i) = make_uint4(keep(vi[k].x, 0), keep(vi[k].y, 1), keep(vi[k].z, 2), keep(vi[k].w, 3));
+    }
+    if (threadIdx.x == 0) widx[-1] = INT_MIN / 2;
+#pragma unroll
+    for (int k = 0; k < NG; ++k) {
+        const int i = (threadIdx.x + 256 * k) * GV;
+        if (i < gshift + nwin) *reinterpret_cast<uint4 *>(wdy + i) = vg[k];
+    }
+    const unsigned pair = min(pair0 + (threadIdx.x >> lg), pair1);
     const int g = threadIdx.x & ((1 << lg) - 1);
-    if (row >= rows || g * 8 >= W) return;
-    const unsigned nc = row / (unsigned)H;
-    const int h = (int)(row - nc * (unsigned)H), v0 = max(0, min(8 * g, W - 8));   // the last piece ends with the row
-    const int ncol = min(8, W - v0);
-    // windows p with 2p - ph <= h <= 2p - ph + 2, windows q that reach one of the columns
-    const int p0 = max(0, (h + ph - 1) >> 1), p1 = min((h + ph) >> 1, P - 1);
-    const int q0 = max(0, (v0 + pw - 1) >> 1), q1 = min((v0 + ncol - 1 + pw) >> 1, Q - 1);
-    const T *gp = dy + (size_t)nc * P * Q;
-    const int32_t *ip = idx + (size_t)nc * P * Q;
-    const int first = h * W + v0;
-    float acc[8];
+    const bool live = pair0 + (threadIdx.x >> lg) <= pair1;
+    const unsigned nc = pair / (unsigned)M;
+    const int m = (int)(pair - nc * (unsigned)M);
+    const int h = 2 * m - ph, v0 = 8 * g - pw;   // the piece's first element; rows h, h + 1 and columns v0 .. v0 + 7
+    const size_t out0 = ((size_t)nc0 * H + max(0, 2 * m0 - ph)) * W;   // the workgroup's run of dx
+    const int count = (int)(((size_t)nc1 * H + min(H, 2 * m1 - ph + 2)) * W - out0);
+    const int shift = misplaced(dx + out0);
+    __syncthreads();
+    float acc[2][8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] = 0.f;
-    if (Q >= 5) {
-        const int qb = min(q0, Q - 5);   // windows qb .. qb + 4 hold q0 .. q1
-        Pack<int32_t, 5> wi[2];
-        Pack<T, 5> wg[2];
+    for (int c = 0; c < 8; ++c) acc[0][c] = acc[1][c] = 0.f;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int at = min(p0 + i, P - 1) * Q + qb;
-            wi[i] = *reinterpret_cast<const Pack<int32_t, 5> *>(ip + at);
-            wg[i] = *reinterpret_cast<const Pack<T, 5> *>(gp + at);
+    for (int i = 0; i < 2; ++i) {
+        const int p = m - 1 + i, at = (int)((size_t)nc * P + min(max(p, 0), P - 1) - row0) * Q + min(4 * g - 1, Q - 1);
+        // the index of the piece's first element; of a window row outside the output nothing is used
+        const int first = (unsigned)p < (unsigned)P ? h * W + v0 : INT_MAX / 2;
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            const int rel = widx[ishift + at + j] - first;
+            const float d = ld<T>(&wdy[gshift + at + j]);
+#pragma unroll
+            for (int c = max(0, 2 * j - 2); c <= min(7, 2 * j); ++c) {
+                acc[0][c] += rel == c ? d : 0.f;
+                if (i == 1) acc[1][c] += rel == W + c ? d : 0.f;
+            }
         }
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 5; ++j) {
-                const bool use = p0 + i <= p1 && qb + j >= q0 && qb + j <= q1;
-                const int rel = use ? wi[i].e[j] - first : -1;
-                const float d = ld<T>(&wg[i].e[j]);
-#pragma unroll
-                for (int c = 0; c < 8; ++c) acc[c] += rel == c ? d : 0.f;
-            }
-    } else {
-        for (int p = p0; p <= p1; ++p)
-            for (int q = q0; q <= q1; ++q) {
-                const int rel = ip[p * Q + q] - first;
-                const float d = ld<T>(gp + p * Q + q);
-#pragma unroll
-                for (int c = 0; c < 8; ++c) acc[c] += rel == c ? d : 0.f;
-            }
     }
-    T *o = dx + (size_t)row * W + v0;
-    if (ncol == 8) {
-        Pack<T, 8> out;
+    const int o = (int)((long long)((size_t)nc * H + h) * W + v0 - (long long)out0) + shift;
+    const int o0 = live && h >= 0 ? o : POOL3_SPARE, o1 = live && (unsigned)(h + 1) < (unsigned)H ? o + W : POOL3_SPARE;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) st(&out.e[c], acc[c]);
-        *reinterpret_cast<Pack<T, 8> *>(o) = out;
-    } else {
-#pragma unroll
-        for (int c = 0; c < 8; ++c)
-            if (c < ncol) st(o + c, acc[c]);
-    }
+    for (int c = 0; c < 8; ++c)
+        if ((unsigned)(v0 + c) < (unsigned)W) {
+            st(tile + o0 + c, acc[0][c]);
+            st(tile + o1 + c, acc[1][c]);
+        }
+    __syncthreads();
+    run_from_lds(dx + out0, tile, count, shift);
 }
 
 // ------------------------------------------------------------------ LRN
@@ -1243,9 +1308,10 @@ maxpool3s2_bwd_kernel(const T *__restrict__ dy, const int32_t *__restrict__ idx,
 // it, each of which needs the window around j: the loop runs HALF channels ahead for s_j and
 // another HALF ahead for x, with r, s^(-beta) and dy of the channels in between in registers;
 // x and dy are read once, the forward output is not needed.  Nothing but loads of several channels
-// in flight hides their latency: each channel's x and dy are loaded LRN_AHEAD channels before they
-// are pushed into the window, with no branch around a load (channels outside the tensor load the
-// nearest one inside and count as zero).  128 x 96 x 55x55 bf16: backward 82 -> 67 us, forward 34 -> 33 us (4.5 TB/s).
+// in flight hides their latency: each channel's x and dy are loaded LRN_AHEAD channels (backward: a turn
+// of its rings) before they are pushed into the window, with no branch around a load (channels outside the
+// tensor load the nearest one inside and count as zero).  128 x 96 x 55x55 bf16: forward 33 us (4.5 TB/s); backward
+// 65 -> 56 us, of which vector instructions issue for 31 (registers renamed instead of moved, no division).
 // RAG: planes that are no whole number of vectors (55x55, 27x27): a plane is ceil(HW / VEC) vectors at the
 // element's own alignment, the last one moved back so that it ends with the plane; the positions it shares
 // with the vector before are computed and written twice, with the same values.
@@ -1357,85 +1423,81 @@ lrn_bwd_kernel(const T *__restrict__ x, const T *__restrict__ dy, T *__restrict_
     const size_t n = t / vpp;
     const size_t off = n * (size_t)C * HW + (RAG ? min((int)(t - n * vpp) * VEC, HW - VEC) : (int)(t - n * vpp) * VEC);
     const float coef = 2.f * a_n * beta;
-    float xr[SIZE][VEC], rr[SIZE][VEC];   // x of channels m - 2 HALF .. m; r of channels j - 2 HALF .. j (j = m - HALF)
-    float pr[H1][VEC], gr[H1][VEC];       // s^(-beta) and dy of channels j - HALF .. j
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) {
-#pragma unroll
-        for (int i = 0; i < SIZE; ++i) xr[i][v] = rr[i][v] = 0.f;
-#pragma unroll
-        for (int i = 0; i < H1; ++i) pr[i][v] = gr[i][v] = 0.f;
-    }
+    // Rings of registers, U = 2 H1 steps to a turn, so that the loop below, a turn per trip, names every
+    // register and moves none: after step i of a turn (channel m = j + HALF of x has arrived)
+    // xr[(i + t) % U] = x of channel m - 2 HALF + t, rr the same for r of channels j - 2 HALF .. j,
+    // pr[(i + t) % H1], gr[(i + t) % H1] = s^(-beta), dy of channel j - HALF + t.
+    constexpr int U = 2 * H1;
+    float xr[U][VEC], rr[U][VEC], pr[H1][VEC], gr[H1][VEC];
     typedef LrnIo<T, VEC, RAG> Io;
     const T *xp = x + off, *gp = dy + off;
     T *op = dx + off;
     const int xend = min(C, ce + 2 * HALF), gend = min(C, ce + HALF);   // channels read: up to here
-    // channel j + HALF of x arrives: channel j's window is complete (x_j = xr[HALF]) and its dy arrives with it
-    const auto push = [&](const typename Io::VT &xv, const typename Io::VT &gv, int j) {
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-#pragma unroll
-            for (int i = 0; i + 1 < SIZE; ++i) { xr[i][v] = xr[i + 1][v]; rr[i][v] = rr[i + 1][v]; }
-#pragma unroll
-            for (int i = 0; i + 1 < H1; ++i) { pr[i][v] = pr[i + 1][v]; gr[i][v] = gr[i + 1][v]; }
-        }
+    // step i: channel j + HALF of x arrives: channel j's window is complete (x_j in its middle) and its dy arrives with it
+    // (EDGE: channels j or j + HALF may lie outside the tensor)
+    const auto push = [&](const typename Io::VT &xv, const typename Io::VT &gv, int j, int i, auto edge) {
+        constexpr bool EDGE = decltype(edge)::value;
         // LRN saw max(x, 0) with RELU: negative and zero x both count as 0, and their dx is 0 below
-        Io::values(xv, (unsigned)(j + HALF) < (unsigned)C, RELU, xr[SIZE - 1]);
-        const bool inside = (unsigned)j < (unsigned)C;
-        Io::values(gv, inside, 0, gr[H1 - 1]);
+        Io::values(xv, !EDGE || (unsigned)(j + HALF) < (unsigned)C, RELU, xr[(i + SIZE - 1) % U]);
+        const bool inside = !EDGE || (unsigned)j < (unsigned)C;
+        Io::values(gv, inside, 0, gr[(i + HALF) % H1]);
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
             float sum = 0.f;
 #pragma unroll
-            for (int i = 0; i < SIZE; ++i) sum = __builtin_fmaf(xr[i][v], xr[i][v], sum);
+            for (int t_ = 0; t_ < SIZE; ++t_) sum = __builtin_fmaf(xr[(i + t_) % U][v], xr[(i + t_) % U][v], sum);
             const float s = __builtin_fmaf(a_n, sum, k), p = pow_neg(s, beta);
-            pr[H1 - 1][v] = p;
-            rr[SIZE - 1][v] = inside ? gr[H1 - 1][v] * xr[HALF][v] * (p / s) : 0.f;
+            pr[(i + HALF) % H1][v] = p;
+            // s^(-beta-1): the reciprocal instruction (1 ulp) against ten for a division; the two powers' own errors are larger
+            rr[(i + SIZE - 1) % U][v] = inside ? gr[(i + HALF) % H1][v] * xr[(i + HALF) % U][v] * (p * __builtin_amdgcn_rcpf(s)) : 0.f;
         }
     };
     // before the first output: x from channel cb - 2 HALF, terms from cb - HALF
-    typename Io::VT head[4 * HALF + 1], ghead[2 * HALF + 1], ahead[LRN_AHEAD], gahead[LRN_AHEAD];
+    typename Io::VT head[4 * HALF + 1], ghead[2 * HALF + 1], ahead[U], gahead[U];
 #pragma unroll
     for (int i = 0; i < 4 * HALF; ++i) head[i] = Io::load(xp, cb - 2 * HALF + i, xend, HW);
 #pragma unroll
     for (int i = 0; i < 2 * HALF; ++i) ghead[i] = Io::load(gp, cb - HALF + i, gend, HW);
 #pragma unroll
-    for (int i = 0; i < LRN_AHEAD; ++i) {
+    for (int i = 0; i < U; ++i) {
         ahead[i] = Io::load(xp, cb + 2 * HALF + i, xend, HW);
         gahead[i] = Io::load(gp, cb + HALF + i, gend, HW);
     }
+    // the 2 HALF steps before the first turn: steps U - 2 HALF .. U - 1
 #pragma unroll
-    for (int i = 0; i < 2 * HALF; ++i)   // the first window but its last channel, one place late: push moves it
-        Io::values(head[i], (unsigned)(cb - 2 * HALF + i) < (unsigned)C, RELU, xr[i + 1]);
+    for (int i = 0; i < 2 * HALF; ++i)   // the first window but its last channel
+        Io::values(head[i], (unsigned)(cb - 2 * HALF + i) < (unsigned)C, RELU, xr[(U - 2 * HALF + i) % U]);
 #pragma unroll
-    for (int i = 0; i < 2 * HALF; ++i) push(head[2 * HALF + i], ghead[i], cb - HALF + i);
-    const auto one = [&](int c, const typename Io::VT &xv, const typename Io::VT &gv) {
-        push(xv, gv, c + HALF);
-        // every r of channel c's window is known: x_c = xr[0], dy_c = gr[0], s_c^(-beta) = pr[0]
+    for (int i = 0; i < 2 * HALF; ++i) push(head[2 * HALF + i], ghead[i], cb - HALF + i, U - 2 * HALF + i, std::true_type());
+    const auto one = [&](int c, int i, const typename Io::VT &xv, const typename Io::VT &gv, auto edge) {
+        push(xv, gv, c + HALF, i, edge);
+        // every r of channel c's window is known: x_c, dy_c and s_c^(-beta) are the oldest of their rings
         float out[VEC];
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
-            float acc = 0.f;
+            float acc = rr[i % U][v];
 #pragma unroll
-            for (int i = 0; i < SIZE; ++i) acc += rr[i][v];
-            out[v] = gr[0][v] * pr[0][v] - coef * xr[0][v] * acc;
-            if (RELU && !(xr[0][v] > 0.f)) out[v] = 0.f;   // the ReLU's gate: x > 0 (xr holds max(x, 0))
+            for (int t_ = 1; t_ < SIZE; ++t_) acc += rr[(i + t_) % U][v];
+            out[v] = gr[i % H1][v] * pr[i % H1][v] - coef * xr[i % U][v] * acc;
+            if (RELU && !(xr[i % U][v] > 0.f)) out[v] = 0.f;   // the ReLU's gate: x > 0 (xr holds max(x, 0))
         }
         Io::store(op + (size_t)c * HW, out);
     };
     int c = cb;
-    for (; c + LRN_AHEAD <= ce; c += LRN_AHEAD) {
+    const auto turn = [&](auto edge) {
 #pragma unroll
-        for (int i = 0; i < LRN_AHEAD; ++i) {
+        for (int i = 0; i < U; ++i) {
             const typename Io::VT xv = ahead[i], gv = gahead[i];
-            ahead[i] = Io::load(xp, c + i + 2 * HALF + LRN_AHEAD, xend, HW);
-            gahead[i] = Io::load(gp, c + i + HALF + LRN_AHEAD, gend, HW);
-            one(c + i, xv, gv);
+            ahead[i] = Io::load(xp, c + i + 2 * HALF + U, xend, HW);
+            gahead[i] = Io::load(gp, c + i + HALF + U, gend, HW);
+            one(c + i, i, xv, gv, edge);
         }
-    }
+    };
+    for (; c + U <= ce && c + U + 2 * HALF <= C; c += U) turn(std::false_type());
+    for (; c + U <= ce; c += U) turn(std::true_type());
 #pragma unroll
-    for (int i = 0; i < LRN_AHEAD; ++i)
-        if (c + i < ce) one(c + i, ahead[i], gahead[i]);
+    for (int i = 0; i < U; ++i)
+        if (c + i < ce) one(c + i, i, ahead[i], gahead[i], std::true_type());
 }
 
 template <typename F> hipError_t by_dtype(int bf16, F f)
@@ -1732,7 +1794,10 @@ hipError_t lrn_launch(bool bwd, const void *x, const void *dy, void *out, int N,
     // A thread walks its channels one after the other: with few positions the channels are split over
     // blockIdx.y (each part re-reads the HALF or 2 HALF channels beside it) until there are enough threads.
     // (measured on 128 x 256 x 27 x 27: 5 parts of 52 channels 3.1 TB/s forward, 1 part 0.9, 6 parts of 43 2.4)
+    // Backward, whose registers leave a SIMD six waves, takes as many parts as run at once: 128 x 96 x 55 x 55,
+    // 5 parts (a round and a half of waves, 28 channels read for 20) 63 us, 3 or 4 parts 56.
     long long parts = total >= 400000 ? 1 : (450000 + (long long)total - 1) / (long long)total;
+    if (bwd) parts = 6 * 1024 * 64 / (long long)total;
     if (parts > (C + 7) / 8) parts = (C + 7) / 8;
     if (parts < 1) parts = 1;
     const int cc = (int)((C + parts - 1) / parts + 3) / 4 * 4, ny = (C + cc - 1) / cc;
@@ -1826,14 +1891,14 @@ hipError_t launch_maxpool_bwd(const void *dy, const int32_t *idx, void *dx, int 
                                idx, (T *)dx, rows, H, W, P, Q, lg);
         });
     }
-    if (kh == 3 && kw == 3 && sh == 2 && sw == 2 && ph >= 0 && ph <= 2 && pw >= 0 && pw <= 2 && P > 0 && Q > 0 &&
-        (long long)NC * H <= 0x7fffffffLL && log2_groups((W + 7) / 8) >= 0) {
-        const int lg = log2_groups((W + 7) / 8);
-        const unsigned rows = (unsigned)NC * H, rpb = 256u >> lg;
+    if (kh == 3 && kw == 3 && sh == 2 && sw == 2 && ph >= 0 && ph <= 2 && pw >= 0 && pw <= 2 && P > 0 && Q >= 2 &&
+        (long long)NC * (H + 2) <= 0x7fffffffLL && (long long)H * W <= 0x40000000LL && log2_groups((W + pw + 7) / 8) >= 0) {
+        const int lg = log2_groups((W + pw + 7) / 8), M = (H + ph + 1) / 2;   // row pairs of the padded image that hold image rows
+        const unsigned pairs = (unsigned)NC * M, rpb = 256u >> lg;
         return by_dtype(bf16, [&](auto *tag) {
             typedef typename std::remove_pointer<decltype(tag)>::type T;
-            hipLaunchKernelGGL(maxpool3s2_bwd_kernel<T>, dim3((rows + rpb - 1) / rpb), dim3(256), 0, s, (const T *)dy,
-                               idx, (T *)dx, rows, H, W, P, Q, ph, pw, lg);
+            hipLaunchKernelGGL(maxpool3s2_bwd_kernel<T>, dim3((pairs + rpb - 1) / rpb), dim3(256), pool3_bwd_lds<T>(lg), s,
+                               (const T *)dy, idx, (T *)dx, (unsigned)NC, pairs, M, H, W, P, Q, ph, pw, lg);
         });
     }
     const unsigned bpp = (unsigned)(((long long)H * W + 255) / 256);

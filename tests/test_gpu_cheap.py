@@ -335,6 +335,25 @@ def test_maxpool3s2_row_ends(width, pad):
         test_maxpool(((2, 3, 9, width), (3, 3), (2, 2), (pad, pad)), dtype)
 
 
+@pytest.mark.parametrize("pad", [(0, 0), (1, 2), (2, 1)])
+@pytest.mark.parametrize("shape", [(7, 9, 13, 13), (3, 7, 5, 4), (1, 3, 6, 2046), (2, 65, 27, 27), (1, 2, 3, 2047)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_maxpool3s2_bwd_runs(shape, pad):
+    """3x3 / stride-2 backward moves runs of rows that cross planes, through LDS: planes per workgroup from many to a
+    fraction, the widest rows it takes and one wider.  The routing is exact: against the oracle on values whose sums
+    are exact in either type."""
+    N, C, H, W = shape
+    x = wl.activation(shape, "f32", seed=W, relu=True)
+    po, io = oracle.maxpool_fwd(f64(torch.round(x * 4.0)), (3, 3), (2, 2), pad)
+    idx = torch.from_numpy(np.ascontiguousarray(io)).int().cuda()
+    for dtype in ("bf16", "f32"):
+        dy = torch.randint(-8, 9, po.shape, generator=torch.Generator().manual_seed(W)).to(DT[dtype])
+        dx = torch.full(shape, float("nan"), dtype=DT[dtype], device="cuda")
+        sn.sn_maxpool_bwd(dy.cuda(), idx, dx, (3, 3), (2, 2), pad)
+        torch.cuda.synchronize()
+        assert np.array_equal(f64(dx), oracle.maxpool_bwd(f64(dy), io, shape))
+
+
 @pytest.mark.parametrize("size", [1, 3, 5, 9])
 @pytest.mark.parametrize("channels", [1, 2, 4, 5, 9, 20, 33])
 def test_lrn_channel_ends(channels, size):
