@@ -698,47 +698,34 @@ hipError_t launch_bwd_filter_px(const void *dy, const void *x, float *dw, float 
     return hipGetLastError();
 }
 
-__global__ void reduce_partials_kernel(const float *__restrict__ partial, float *__restrict__ dw, size_t n,
-                                       int splits, bool accumulate)
-{
-    size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    float s = accumulate ? dw[i] : 0.f;
-    for (int z = 0; z < splits; ++z) s += partial[(size_t)z * n + i];
-    dw[i] = s;
-}
-
-// The same sum for n a multiple of 4, 16 bytes per load: a workgroup of TX x TY threads (256 in all)
-// takes TX consecutive float4; thread (tx, ty) adds slices ty, ty + TY, ... of its element in
+// dw[i] (or 0) + the sum over the slices, V = float4 where n is a multiple of 4 and both start on 16 bytes, else float (one
+// thread per element was 130 us for 512 slices of 38 x 147, this 12): a workgroup of TX x TY threads (256 in all)
+// takes TX consecutive V; thread (tx, ty) adds slices ty, ty + TY, ... of its element in
 // ascending order, and the TY sums are added in the order of ty.  The order is fixed, so the result
 // is the same from run to run.  Few slices: TY = 4, so that a thread still has several loads in
 // flight and a row of lanes reads 1 KB at a stretch; many slices: TY = 16.
-template <int TY>
+__device__ inline void add_to(float &a, float b) { a += b; }
+__device__ inline void add_to(float4 &a, const float4 &b) { a.x += b.x; a.y += b.y; a.z += b.z; a.w += b.w; }
+
+template <typename V, int TY>
 __global__ void __launch_bounds__(256)
-reduce_partials4_kernel(const float4 *__restrict__ partial, float4 *__restrict__ dw, size_t n4, int splits,
-                        bool accumulate)
+reduce_partials_kernel(const V *__restrict__ partial, V *__restrict__ dw, size_t n4, int splits, bool accumulate)
 {
     constexpr int TX = 256 / TY;
-    __shared__ float4 part[TY][TX];
+    __shared__ V part[TY][TX];
     const int tx = threadIdx.x % TX, ty = threadIdx.x / TX;
     const size_t i = (size_t)blockIdx.x * TX + tx;
-    float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+    V s = V();
     if (i < n4) {
 #pragma unroll 4
-        for (int z = ty; z < splits; z += TY) {
-            const float4 v = partial[(size_t)z * n4 + i];
-            s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-        }
+        for (int z = ty; z < splits; z += TY) add_to(s, partial[(size_t)z * n4 + i]);
     }
     part[ty][tx] = s;
     __syncthreads();
     if (ty == 0 && i < n4) {
-        float4 t = accumulate ? dw[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+        V t = accumulate ? dw[i] : V();
         const int ny = splits < TY ? splits : TY;
-        for (int y = 0; y < ny; ++y) {
-            const float4 v = part[y][tx];
-            t.x += v.x; t.y += v.y; t.z += v.z; t.w += v.w;
-        }
+        for (int y = 0; y < ny; ++y) add_to(t, part[y][tx]);
         dw[i] = t;
     }
 }
@@ -855,21 +842,19 @@ hipError_t launch_fill_zero(float *p, size_t n, hipStream_t st)
 hipError_t launch_reduce_partials(const float *partial, float *dw, size_t n, int splits, bool accumulate,
                                   hipStream_t st)
 {
-    if (n % 4 == 0 && reinterpret_cast<uintptr_t>(partial) % 16 == 0 && reinterpret_cast<uintptr_t>(dw) % 16 == 0) {
-        const size_t n4 = n / 4;
-        const float4 *p4 = reinterpret_cast<const float4 *>(partial);
-        float4 *d4 = reinterpret_cast<float4 *>(dw);
+    const auto go = [&](auto *p, auto *d, size_t nv) {
+        typedef typename std::remove_pointer<decltype(d)>::type V;
         if (splits >= 64)
-            hipLaunchKernelGGL(reduce_partials4_kernel<16>, dim3((unsigned)((n4 + 15) / 16)), dim3(256), 0, st, p4, d4,
-                               n4, splits, accumulate);
+            hipLaunchKernelGGL((reduce_partials_kernel<V, 16>), dim3((unsigned)((nv + 15) / 16)), dim3(256), 0, st, p, d, nv,
+                               splits, accumulate);
         else
-            hipLaunchKernelGGL(reduce_partials4_kernel<4>, dim3((unsigned)((n4 + 63) / 64)), dim3(256), 0, st, p4, d4,
-                               n4, splits, accumulate);
+            hipLaunchKernelGGL((reduce_partials_kernel<V, 4>), dim3((unsigned)((nv + 63) / 64)), dim3(256), 0, st, p, d, nv,
+                               splits, accumulate);
         return hipGetLastError();
-    }
-    dim3 grid((unsigned)((n + 255) / 256)), block(256);
-    hipLaunchKernelGGL(reduce_partials_kernel, grid, block, 0, st, partial, dw, n, splits, accumulate);
-    return hipGetLastError();
+    };
+    if (n % 4 == 0 && reinterpret_cast<uintptr_t>(partial) % 16 == 0 && reinterpret_cast<uintptr_t>(dw) % 16 == 0)
+        return go(reinterpret_cast<const float4 *>(partial), reinterpret_cast<float4 *>(dw), n / 4);
+    return go(partial, dw, n);
 }
 
 }  // namespace sn

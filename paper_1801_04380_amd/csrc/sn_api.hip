@@ -101,27 +101,30 @@ ConvGeom gemm_geom_1x1(const ConvGeom &g, int nimg)
 size_t staged_bwd_filter_bytes(const ConvGeom &g, int *splits_out)
 {
     int splits = smallc_supported(g) ? smallc_wgrad_slices(g)
+               : image_wgrad_supported(g) ? image_wgrad_slices(g)
                : tile_wgrad_supported(g) ? tile_wgrad_slices(g)
                : gather_wgrad_supported(g) ? gather_wgrad_slices(g) : generic_bwd_filter_splits(g);
     if (splits_out) *splits_out = splits;
     return align_up((size_t)splits * g.K * g.C * g.R * g.S * sizeof(float), WS_ALIGN);
 }
 
-// The row-stationary kernel also runs with fewer slices than fill the chip (fewer, longer workgroups): a
+// The row-stationary and the image layer's kernel also run with fewer slices than fill the chip (fewer, longer workgroups): a
 // quarter of them is the least STAGED backward-filter takes, so its workspace is a range (Sec. 3.5: more
 // workspace, more speed).  Whether the shape has that range, and its least workspace.
 bool staged_bwd_filter_ranged(const ConvGeom &g)
 {
-    return !smallc_supported(g) && tile_wgrad_supported(g) && tile_wgrad_cappable(g);
+    return !smallc_supported(g) && (image_wgrad_supported(g) || (tile_wgrad_supported(g) && tile_wgrad_cappable(g)));
 }
 
 size_t staged_bwd_filter_min_bytes(const ConvGeom &g)
 {
-    const int full = tile_wgrad_slices(g), least = tile_wgrad_slices(g, (full + 3) / 4);
+    const bool image = image_wgrad_supported(g);
+    const int full = image ? image_wgrad_slices(g) : tile_wgrad_slices(g);
+    const int least = image ? image_wgrad_slices(g, (full + 3) / 4) : tile_wgrad_slices(g, (full + 3) / 4);
     return align_up((size_t)least * g.K * g.C * g.R * g.S * sizeof(float), WS_ALIGN);
 }
 
-// Slices the row-stationary kernel may use with ws_bytes of workspace (0: all it wants).
+// Slices such a kernel may use with ws_bytes of workspace (0: all it wants).
 int staged_bwd_filter_cap(const ConvGeom &g, size_t ws_bytes)
 {
     if (!staged_bwd_filter_ranged(g) || ws_bytes >= staged_bwd_filter_bytes(g, nullptr)) return 0;
@@ -310,6 +313,7 @@ double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
     if (!g.in_bf16) return winograd_guessed(g, dir, ws_bytes) ? std::min(general, winograd_us(g, dir == SN_CONV_BWD_DATA, ws_bytes)) : general;
     if (smallc_supported(g) && dir != SN_CONV_BWD_DATA) return 0;
     if (dir == SN_CONV_BWD_FILTER) {
+        if (image_wgrad_supported(g)) return 0;   // 11x11 / 4 on 227x227 images: 69 + 7 us, the product with 300 MiB 140
         if (g.sh > 1 || g.sw > 1 || !tile_wgrad_supported(g)) return general;
         // 1x1 on planes of odd sizes or short rows: bound by memory up to 256 channels on either side, where copies are a
         // second pass; with more the product's larger tiles win, but for the smallest planes
@@ -394,8 +398,9 @@ sn_status own_query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_
         return SN_OK;
     case SN_ALGO_STAGED: {
         PhasePlan pp;
-        if (dir == SN_CONV_BWD_FILTER && smallc_supported(g)) {
+        if (dir == SN_CONV_BWD_FILTER && (smallc_supported(g) || image_wgrad_supported(g))) {
             *min_b = *pref_b = staged_bwd_filter_bytes(g, nullptr);
+            if (staged_bwd_filter_ranged(g)) *min_b = staged_bwd_filter_min_bytes(g);
             return SN_OK;
         }
         if (dir == SN_CONV_BWD_DATA && scatter_bwd_data(g)) {
@@ -701,6 +706,9 @@ sn_status run_bwd_filter(const void *x, const void *dy, void *dw, const ConvGeom
     const bool tile = tile_wgrad_supported(g);
     if (smallc_supported(g) && (algo == SN_ALGO_DIRECT || algo == SN_ALGO_STAGED))
         return launch_status(launch_smallc_wgrad(x, dy, dwf, g, algo == SN_ALGO_STAGED ? static_cast<float *>(ws) : nullptr, st));
+    if (image_wgrad_supported(g) && (algo == SN_ALGO_DIRECT || algo == SN_ALGO_STAGED))
+        return launch_status(launch_image_wgrad(x, dy, dwf, g, algo == SN_ALGO_STAGED ? static_cast<float *>(ws) : nullptr, st,
+                                                staged_bwd_filter_cap(g, ws_bytes)));
     if (algo == SN_ALGO_DIRECT) {
         if (tile) return launch_status(launch_tile_wgrad(x, dy, dwf, g, nullptr, st));
         if (gather_wgrad_supported(g)) return launch_status(launch_gather_wgrad(x, dy, dwf, g, nullptr, st));

@@ -106,6 +106,12 @@ int smallc_wgrad_slices(const ConvGeom &g);
 hipError_t launch_smallc_wgrad(const void *x, const void *dy, float *dw, const ConvGeom &g, float *partial,
                                hipStream_t st);
 
+// Backward-filter of the image layer: up to four input channels under a filter of 33 to 384 products of up to 12
+// columns (bf16, any stride and padding; conv_image.hip); contract of launch_rows_wgrad, any number of slices up to image_wgrad_slices(g).
+bool image_wgrad_supported(const ConvGeom &g);
+int image_wgrad_slices(const ConvGeom &g, int cap = 0);
+hipError_t launch_image_wgrad(const void *x, const void *dy, float *dw, const ConvGeom &g, float *partial, hipStream_t st, int cap = 0);
+
 // 1x1 / stride-1 / unpadded layers with bf16 operands and channel counts that are multiples of 8
 // (conv_pointwise.hip): forward or backward-data without workspace; launch_tile_conv prefers it
 // when no statistics are asked for.
