@@ -360,7 +360,7 @@ const TileCost kTileCost[] = {
     {1, false, true, false, 1, 10.7, 0.41, 0},   {1, false, true, false, 2, 10.7, 0.28, 1.0}, {1, false, true, false, 4, 4.4, 0.44, 4.3},
     {1, false, false, true, 1, 9.8, 0.64, 0},    {1, false, true, true, 1, 11.5, 0.21, 0},    {1, false, true, true, 4, 14.4, 0.6, 2.7}};
 
-double tile_conv_us(const ConvGeom &g, bool bwd_data)
+static double packed_tile_us(const ConvGeom &g, bool bwd_data)
 {
     TileProblem p;
     Plan pl, pl2;
@@ -374,12 +374,23 @@ double tile_conv_us(const ConvGeom &g, bool bwd_data)
     return 1e9;   // not measured; the product was 1.2 to 10 times faster elsewhere
 }
 
+// Few reduction channels: the streaming kernel where it is estimated to be faster than the tiles with or without workspace
+// (it wins from about eight rows a band on; on smaller layers its start, the filter into registers, is what counts).
+static bool band_runs(const ConvGeom &g, bool bwd_data, bool staged)
+{
+    const double us = band_conv_us(g, bwd_data);
+    return us < (staged ? packed_tile_us(g, bwd_data) : band_conv_direct_us(g, bwd_data));
+}
+
+double tile_conv_us(const ConvGeom &g, bool bwd_data) { return std::min(packed_tile_us(g, bwd_data), band_conv_us(g, bwd_data)); }
+
 // Pixel tiles of the plan launch_tile_conv would use (forward); 0 if the kernels do not apply.
 int tile_conv_stats_tiles(const ConvGeom &g, bool staged, bool in_aligned16)
 {
     TileProblem p;
     Plan pl, pl2;
     if (!tile_conv_supported(g, false) || !problem_of(g, false, &p) || !make_plan(p, g.R, g.S, staged, &pl)) return 0;
+    if (in_aligned16 && band_runs(g, false, staged)) return band_conv_stats_tiles(g);
     if (staged && in_aligned16 && make_plan2(p, g.R, g.S, &pl2)) return pl2.p.nptiles;
     return pl.p.nptiles;
 }
@@ -394,6 +405,7 @@ hipError_t launch_tile_conv(const void *in, const void *w, void *out, const Conv
         return hipErrorInvalidValue;
     if (stats && bwd_data) return hipErrorInvalidValue;
     if (!stats && pointwise_supported(g, bwd_data)) return launch_pointwise(in, w, out, g, bwd_data, st);
+    if (reinterpret_cast<uintptr_t>(in) % 16 == 0 && band_runs(g, bwd_data, packed != nullptr)) return launch_band_conv(in, w, out, g, bwd_data, st, stats);
     pl.p.stats = stats;
     const bf16_t *wsrc = static_cast<const bf16_t *>(w);
     if (packed) {

@@ -823,6 +823,18 @@ int sn_chlast_inspect(const sn_conv_shape *shape, int dir, int algo, size_t work
     return 1;
 }
 
+// For the tests (not in the header): the streaming 3x3 kernel (conv_band.hip) on a shape that the estimates may leave to another;
+// with `part` (256 triples of floats per output channel) forward with statistics.
+sn_status sn_band_conv(const void *in, const void *w, void *out, const sn_conv_shape *shape, int bwd_data, float *part, float *mean, float *invstd,
+                       float eps, sn_stream stream)
+{
+    ConvGeom g;
+    if (make_geom(shape, &g) != SN_OK || band_conv_us(g, bwd_data != 0) >= 1e9 || (part && bwd_data)) return SN_ERR_UNSUPPORTED;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (launch_band_conv(in, w, out, g, bwd_data != 0, st, part) != hipSuccess) return SN_ERR_LAUNCH;
+    return part ? launch_status(launch_bn_finalize_tiles(part, g.K, band_conv_stats_tiles(g), mean, invstd, eps, st)) : SN_OK;
+}
+
 sn_status sn_conv_plan(const sn_conv_shape *shape, sn_conv_dir dir, size_t budget_bytes, sn_conv_algo *algo,
                        size_t *bytes_used, float *predicted_ms)
 {

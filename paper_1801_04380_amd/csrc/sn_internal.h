@@ -74,6 +74,13 @@ size_t tile_conv_packed_bytes(const ConvGeom &g, bool bwd_data);
 hipError_t launch_tile_conv(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data,
                             void *packed, hipStream_t st, float *stats = nullptr);
 int tile_conv_stats_tiles(const ConvGeom &g, bool staged, bool in_aligned16);
+// 3x3 / stride-1 over at most 64 reduction channels (conv_band.hip): the image streamed past a filter held in registers, no
+// workspace; launch_tile_conv takes it where the estimates favour it (very large: the shape has none of it).  stats: as
+// there, band_conv_stats_tiles(g) triples per channel.
+double band_conv_us(const ConvGeom &g, bool bwd_data);
+double band_conv_direct_us(const ConvGeom &g, bool bwd_data);   // of conv_tile_kernel without workspace
+int band_conv_stats_tiles(const ConvGeom &g);
+hipError_t launch_band_conv(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, hipStream_t st, float *stats);
 double tile_conv_us(const ConvGeom &g, bool bwd_data);   // estimate; very large: everything is faster
 
 // Stride-1 bf16 backward-filter fast path.  partial == nullptr: the slices of the
