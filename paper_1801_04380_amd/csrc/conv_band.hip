@@ -364,6 +364,7 @@ band3x3_kernel(const bf16_t *__restrict__ in, const bf16_t *__restrict__ w, bf16
     finish_half(std::integral_constant<int, 0>{});
     finish_half(std::integral_constant<int, 1>{});
     if constexpr (STATS) finish_stats();
+    wait_loads<0>();   // rows past the last one are on their way into LDS: not past the workgroup's end
 
     if constexpr (STATS) {
         TileMoments m;
