@@ -250,8 +250,12 @@ size_t phase_plane_bytes(const PhasePlan &pp, sn_conv_dir dir, int nimg)
 
 size_t phase_bytes(const PhasePlan &pp, sn_conv_dir dir, int nimg)
 {
-    if (dir == SN_CONV_BWD_FILTER)
-        return phase_plane_bytes(pp, dir, pp.inner.N) + pp.dwprime_bytes + staged_bwd_filter_bytes(pp.inner, nullptr);
+    if (dir == SN_CONV_BWD_FILTER) {
+        // the slices of launch_tile_wgrad, which runs the inner shape; as a layer of its own another kernel may take that (few
+        // input channels, the image layer's), with fewer of them
+        const ConvGeom &u = pp.inner;
+        return phase_plane_bytes(pp, dir, u.N) + pp.dwprime_bytes + align_up((size_t)tile_wgrad_slices(u) * u.K * u.C * u.R * u.S * sizeof(float), WS_ALIGN);
+    }
     return phase_fixed_bytes(pp, dir) + phase_plane_bytes(pp, dir, nimg);
 }
 

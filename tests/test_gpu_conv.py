@@ -328,3 +328,26 @@ def test_conv_random_geometries(case):
             assert err <= TOL["bf16"], (layer, N, direction, sn.ALGO_NAMES[algo], err)
             assert elementwise_excess(f64(got), ref, TOL["bf16"], got.dtype == torch.bfloat16) <= 0, \
                 (layer, N, direction, sn.ALGO_NAMES[algo], "element")
+
+
+# N, C, H, W, K, stride: few input channels under a stride on one axis or both, over phase planes
+PHASED = [(8, 1, 225, 225, 64, (2, 2)), (1, 1, 29, 255, 128, (1, 2)), (2, 2, 64, 61, 40, (2, 1))]
+
+
+@pytest.mark.parametrize("shape", PHASED, ids=lambda s: "x".join(map(str, s[:5])))
+def test_phased_bwd_filter_stays_in_its_workspace(shape):
+    """With exactly the queried bytes: what lies behind them is left alone, and the result is the oracle's."""
+    N, C, H, W, K, stride = shape
+    P, Q = (H - 1) // stride[0] + 1, (W - 1) // stride[1] + 1
+    x, dy = wl.activation((N, C, H, W), "bf16", 3), wl.activation((N, K, P, Q), "bf16", 5)
+    sh = sn.conv_shape(N, C, H, W, K, 3, 3, stride, (1, 1), sn.SN_BF16, sn.SN_BF16)
+    ref = oracle.conv2d_bwd_filter(f64(x), f64(dy), (K, C, 3, 3), stride, (1, 1))
+    mn, pf = sn.sn_conv_workspace_query(sh, sn.SN_CONV_BWD_FILTER, sn.SN_ALGO_STAGED)
+    for b in sorted({mn, pf}):
+        print("case", shape, "ws", b, flush=True)
+        ws = torch.full((b + (4 << 20),), 0xA5, dtype=torch.uint8, device="cuda")
+        dw = torch.full((K, C, 3, 3), float("nan"), device="cuda")
+        sn.sn_conv2d_bwd_filter(x.cuda(), dy.cuda(), dw, sh, sn.SN_ALGO_STAGED, ws[:b])
+        torch.cuda.synchronize()
+        assert bool((ws[b:] == 0xA5).all())
+        assert rel_l2(f64(dw), ref) <= TOL["f32"]   # bf16 products are exact in fp32: only the sums round

@@ -1,0 +1,71 @@
+"""What the library's host code launches, recorded without a GPU (tests/launches/recorder.cpp): the sums over slices stay inside the
+workspace that the query and the plan asked for."""
+import os
+import random
+import re
+import subprocess
+
+import pytest
+
+import paper_1801_04380_amd as sn
+from paper_1801_04380_amd import _lib
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HERE = os.path.join(ROOT, "tests", "launches")
+FIELDS = [n for n, _ in _lib.ConvShape._fields_]
+
+
+@pytest.fixture(scope="session")
+def recorded():
+    """calls -> [(status, [(kernel, grid, threads, lds, limit, reach)])], a call being (direction, algorithm, workspace bytes, shape)."""
+    os.makedirs(os.path.join(HERE, "_build"), exist_ok=True)
+    exe = os.path.join(HERE, "_build", "recorder")
+    _lib.load()
+    subprocess.run(["g++", "-O1", "-std=c++17", "-rdynamic", "-I", os.path.join(ROOT, "include"), "-o", exe, os.path.join(HERE, "recorder.cpp"),
+                    _lib.LIB_PATH, "-Wl,-rpath," + os.path.dirname(_lib.LIB_PATH), "-Wl,--allow-shlib-undefined"], check=True)
+
+    def run(calls):
+        lines = "\n".join(" ".join(map(str, (d, a, b) + tuple(getattr(s, f) for f in FIELDS))) for d, a, b, s in calls)
+        env = dict(os.environ, LD_LIBRARY_PATH="/opt/rocm/lib:" + os.environ.get("LD_LIBRARY_PATH", ""))
+        out = subprocess.run([exe], input=lines, stdout=subprocess.PIPE, text=True, check=True, env=env).stdout
+        res, launches = [], []
+        for line in out.splitlines():
+            w = line.split()
+            if w[0] == "call":
+                res.append((int(w[1]), launches))
+                launches = []
+            else:
+                v = list(map(int, w[2:]))
+                launches.append((re.sub(r"^_ZN2sn(12_GLOBAL__N_1)?", "", w[1]), tuple(v[:3])) + tuple(v[3:]))
+        assert len(res) == len(calls)
+        return res
+
+    return run
+
+
+def test_partial_sums_stay_in_the_workspace(recorded):
+    """STAGED backward-filter under the least, the preferred and the planned bytes.  Most shapes have few channels and a stride on
+    one axis or both: over their phase planes they run as a stride-1 shape that as a layer of its own would run another kernel."""
+    sn.sn_planner_clear()
+    rnd, calls = random.Random(7), []
+    for i in range(6000):
+        few = i % 4 != 0
+        R, S = rnd.choice([(3, 3), (3, 3), (1, 1), (2, 2), (5, 5), (3, 1), (1, 7), (4, 3)])
+        stride = rnd.choice([(1, 2), (2, 1), (2, 2)] if few else [(1, 1), (2, 2), (3, 2), (4, 4)])
+        C = rnd.randint(1, 4) if few else rnd.choice([8, 16, 24, 64, 100])
+        H, W = (rnd.randint(max(R, S), 256 if few else 64) for _ in range(2))
+        pad = rnd.choice([(0, 0), (R // 2, S // 2)])
+        s = sn.conv_shape(rnd.choice([1, 2, 8, 32]), C, H, W, rnd.choice([8, 16, 33, 64, 128]), R, S, stride, pad, sn.SN_BF16, sn.SN_BF16)
+        mn, pf = sn.sn_conv_workspace_query(s, sn.SN_CONV_BWD_FILTER, sn.SN_ALGO_STAGED)
+        algo, used, _ = sn.sn_conv_plan(s, sn.SN_CONV_BWD_FILTER, 256 << 20)
+        calls += [(sn.SN_CONV_BWD_FILTER, a, b, s) for a, b in ((sn.SN_ALGO_STAGED, mn), (sn.SN_ALGO_STAGED, pf), (algo, used))]
+    sums = over = 0
+    worst = None
+    for (d, a, b, s), (status, launches) in zip(calls, recorded(calls)):
+        assert status == 0
+        for k, *_, reach in launches:
+            sums += reach >= 0
+            if reach > b:
+                over += 1
+                worst = worst or ([getattr(s, f) for f in FIELDS], a, b, reach)
+    assert sums > 5000 and over == 0, (sums, over, worst)
