@@ -203,19 +203,19 @@ image_wgrad_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ dy, 
             }
         }
         if (s.step < 0) return;
-        const uint64_t rmask = PER == 1 || s.step * PER + sub < p.P ? dmask : 0ull;
         const bool dends = s.n == p.N - 1 && (p.P - (s.step + 1) * PER) * p.Q < 4;
 #pragma unroll
         for (int m = 0; m < NG; ++m) {
             const int row = m * (THREADS / 16) + (t >> 4);
             uint64_t d = gv[m];
             if (dends) d >>= 16 * min(max(dy_of(s, m) - (p.dyn - 4), 0), 3);
-            d = k0 + row < p.K ? d & rmask : 0ull;
+            d = k0 + row < p.K ? d & dmask : 0ull;
             if (NG * (THREADS / 16) == 32 * MT || row < 32 * MT) *reinterpret_cast<uint64_t *>(dyb + buf * DYB + row * DPITCH + run * 2) = d;
         }
     };
-    // groups slot - G + 1 .. slot of the ring, dy buffer buf
-    const auto multiply = [&](int slot, int buf) {
+    // groups slot - G + 1 .. slot of the ring, dy buffer buf, `rows` output rows of the step: one past the image's last is left out --
+    // dy is another row's there, and x is inside the image (an Inf times zero is no zero either)
+    const auto multiply = [&](int slot, int buf, int rows) {
         const char *a = dyb + buf * DYB + a_off;
         const char *b[PER];
 #pragma unroll
@@ -226,6 +226,7 @@ image_wgrad_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ dy, 
         }
 #pragma unroll
         for (int ks = 0; ks < 4; ks += KS) {   // (+ part)
+            if (PX == 32 && (KS == 4 ? part >> 1 : ks / 2) >= rows) break;
             const bf16x8 bv = *reinterpret_cast<const bf16x8 *>(PX == 64 ? b[0] + ks * 32 : b[KS == 4 ? 0 : ks / 2] + (ks & 1) * 32);
             bf16x8 av[MT];
 #pragma unroll
@@ -249,7 +250,7 @@ image_wgrad_kernel(const bf16_t *__restrict__ x, const bf16_t *__restrict__ dy, 
             l2 = walk.live();
             if (l2) s2 = walk.next(p, PX);
             load(s2, xr[u], gr[u]);
-            if (l0 && s0.step >= 0 && tile < ntiles) multiply(slot, u);
+            if (l0 && s0.step >= 0 && tile < ntiles) multiply(slot, u, p.P - s0.step * PER);
             slot = slot + 1 == nring ? 0 : slot + 1;
             if (l1) store(s1, xr[u ^ 1], gr[u ^ 1], slot, u ^ 1);
             __syncthreads();

@@ -37,3 +37,27 @@ def test_image_bwd_filter(shape):
         assert algo == sn.SN_ALGO_DIRECT or torch.equal(dw[0], dw[1])
         # products of bf16 values are exact in fp32, so only the sums round, in fp32
         assert np.linalg.norm(dw[0].double().cpu().numpy() - ref) / np.linalg.norm(ref) <= 1e-5
+
+
+@pytest.mark.parametrize("H,W,stride,pad", [(23, 30, 2, 0), (22, 29, 2, 2), (41, 131, 4, 3), (24, 25, 3, 1)])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_an_infinity_stays_with_the_products_it_belongs_to(H, W, stride, pad, value):
+    """Steps of two output rows of which the second is past the end, columns of the last block past the row's end, rows and columns
+    of x that no output reaches: an Inf or NaN there touches the products that read it and no others."""
+    N, C, K, R = 2, 3, 40, 7
+    P, Q = (H + 2 * pad - R) // stride + 1, (W + 2 * pad - R) // stride + 1
+    sh = sn.conv_shape(N, C, H, W, K, R, R, (stride, stride), (pad, pad), sn.SN_BF16, sn.SN_BF16)
+    dy = wl.activation((N, K, P, Q), "bf16", 5)
+    last = (P - 1) * stride - pad + R   # the first row that no output reaches, if the image has it
+    for h, w in {(min(P * stride - pad, H - 1), W // 2), (H - 1, W - 1), (min(last, H - 1), 0), (0, 0)}:
+        x = wl.activation((N, C, H, W), "bf16", 3)
+        x[1, 1, h, w] = value
+        ref = oracle.conv2d_bwd_filter(x.double().numpy(), dy.double().numpy(), (K, C, R, R), (stride, stride), (pad, pad))
+        for algo in (sn.SN_ALGO_DIRECT, sn.SN_ALGO_STAGED):
+            b = sn.sn_conv_workspace_query(sh, sn.SN_CONV_BWD_FILTER, algo)[1]
+            dw = torch.full((K, C, R, R), 7.0, device="cuda")
+            sn.sn_conv2d_bwd_filter(x.cuda(), dy.cuda(), dw, sh, algo, torch.empty(b, dtype=torch.uint8, device="cuda") if b else None)
+            torch.cuda.synchronize()
+            got, fine = dw.double().cpu().numpy(), np.isfinite(ref)
+            assert np.array_equal(np.isfinite(got), fine), (algo, h, w)
+            assert np.linalg.norm(got[fine] - ref[fine]) <= 1e-5 * np.linalg.norm(ref[fine])
