@@ -1274,7 +1274,8 @@ maxpool3s2_bwd_kernel(const T *__restrict__ dy, const int32_t *__restrict__ idx,
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
         const int p = m - 1 + i, at = (int)((size_t)nc * P + min(max(p, 0), P - 1) - row0) * Q + min(4 * g - 1, Q - 1);
-        // the index of the piece's first element; of a window row outside the output nothing is used
+        // the index of the piece's first element; of a window row outside the output nothing is used: INT_MAX / 2 is no
+        // element's index (planes of fewer than 2^30)
         const int first = (unsigned)p < (unsigned)P ? h * W + v0 : INT_MAX / 2;
 #pragma unroll
         for (int j = 0; j < 5; ++j) {
@@ -1892,7 +1893,7 @@ hipError_t launch_maxpool_bwd(const void *dy, const int32_t *idx, void *dx, int 
         });
     }
     if (kh == 3 && kw == 3 && sh == 2 && sw == 2 && ph >= 0 && ph <= 2 && pw >= 0 && pw <= 2 && P > 0 && Q >= 2 &&
-        (long long)NC * (H + 2) <= 0x7fffffffLL && (long long)H * W <= 0x40000000LL && log2_groups((W + pw + 7) / 8) >= 0) {
+        (long long)NC * (H + 2) <= 0x7fffffffLL && (long long)H * W < 0x40000000LL && log2_groups((W + pw + 7) / 8) >= 0) {
         const int lg = log2_groups((W + pw + 7) / 8), M = (H + ph + 1) / 2;   // row pairs of the padded image that hold image rows
         const unsigned pairs = (unsigned)NC * M, rpb = 256u >> lg;
         return by_dtype(bf16, [&](auto *tag) {

@@ -354,6 +354,27 @@ def test_maxpool3s2_bwd_runs(shape, pad):
         assert np.array_equal(f64(dx), oracle.maxpool_bwd(f64(dy), io, shape))
 
 
+@pytest.mark.parametrize("W", [1024, 1023])
+def test_maxpool3s2_bwd_largest_plane(W):
+    """A plane of 2^30 elements, the first that the kernel for smaller ones does not take, and one of a row's elements less: the last
+    elements get each gradient once."""
+    H = 1 << 20
+    P, Q = (H + 2 - 3) // 2 + 1, (W + 2 - 3) // 2 + 1
+    # every window's winner is the last of its elements inside the image
+    h = (2 * torch.arange(P, device="cuda") + 1).clamp(max=H - 1)
+    w = (2 * torch.arange(Q, device="cuda") + 1).clamp(max=W - 1)
+    idx = (h[:, None] * W + w[None, :]).to(torch.int32).view(1, 1, P, Q)
+    dy = torch.ones((1, 1, P, Q), dtype=torch.bfloat16, device="cuda")
+    dx = torch.full((1, 1, H, W), float("nan"), dtype=torch.bfloat16, device="cuda")
+    sn.sn_maxpool_bwd(dy, idx, dx, (3, 3), (2, 2), (1, 1))
+    torch.cuda.synchronize()
+    hits, cols = torch.zeros(H, device="cuda"), torch.zeros(W, device="cuda")
+    hits.index_add_(0, h, torch.ones(P, device="cuda"))
+    cols.index_add_(0, w, torch.ones(Q, device="cuda"))
+    for r in (0, H // 2, H - 4096):
+        assert torch.equal(dx[0, 0, r:r + 4096].float(), hits[r:r + 4096, None] * cols[None, :]), r
+
+
 @pytest.mark.parametrize("size", [1, 3, 5, 9])
 @pytest.mark.parametrize("channels", [1, 2, 4, 5, 9, 20, 33])
 def test_lrn_channel_ends(channels, size):
