@@ -1449,8 +1449,7 @@ lrn_bwd_kernel(const T *__restrict__ x, const T *__restrict__ dy, T *__restrict_
             for (int t_ = 0; t_ < SIZE; ++t_) sum = __builtin_fmaf(xr[(i + t_) % U][v], xr[(i + t_) % U][v], sum);
             const float s = __builtin_fmaf(a_n, sum, k), p = pow_neg(s, beta);
             pr[(i + HALF) % H1][v] = p;
-            // s^(-beta-1): the reciprocal instruction (1 ulp) against ten for a division; the two powers' own errors are larger
-            rr[(i + SIZE - 1) % U][v] = inside ? gr[(i + HALF) % H1][v] * xr[(i + HALF) % U][v] * (p * __builtin_amdgcn_rcpf(s)) : 0.f;
+            rr[(i + SIZE - 1) % U][v] = inside ? gr[(i + HALF) % H1][v] * xr[(i + HALF) % U][v] * (p / s) : 0.f;
         }
     };
     // before the first output: x from channel cb - 2 HALF, terms from cb - HALF

@@ -58,6 +58,28 @@ def test_band(shape, backward):
     assert err <= 5e-3, err   # one rounding to bf16
 
 
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("backward", [False, True], ids=["fwd", "bwd_data"])
+def test_an_infinity_reaches_its_own_outputs(backward, value):
+    """Without padding around it: the nine outputs over an Inf or NaN, in their own image and every output channel, and no others --
+    beside a band's edge, in the last row and column, in the last channel of a class."""
+    N, red, H, W, out = 3, 40, 23, 72, 72
+    pad = (1, 1)
+    K, C = (red, out) if backward else (out, red)
+    sh = sn.conv_shape(N, C, H, W, K, 3, 3, (1, 1), pad, sn.SN_BF16, sn.SN_BF16)
+    w = wl.activation((K, C, 3, 3), "bf16", 4, scale=0.06)
+    w[w == 0] = 0.01
+    for n, c, h, x in ((1, 39, 11, 31), (1, 0, 22, 71), (0, 17, 0, 32), (2, 8, 1, 64)):
+        a = wl.activation((N, red, H, W), "bf16", 3)
+        a[n, c, h, x] = value
+        got = torch.full((N, out, H, W), 7.0, dtype=torch.bfloat16, device="cuda")
+        _band(a.cuda(), w.cuda(), got, sh, backward)
+        torch.cuda.synchronize()
+        reached = torch.zeros((N, out, H, W), dtype=torch.bool)
+        reached[n, :, max(0, h - 1):h + 2, max(0, x - 1):x + 2] = True
+        assert torch.equal(~torch.isfinite(got.cpu().float()), reached), (n, c, h, x)
+
+
 def test_band_stats():
     """(count, mean, M2) over bands whose last columns and rows are not there, the mean far from 0."""
     N, C, H, W, K = 9, 64, 37, 48, 72

@@ -375,6 +375,23 @@ def test_maxpool3s2_bwd_largest_plane(W):
         assert torch.equal(dx[0, 0, r:r + 4096].float(), hits[r:r + 4096, None] * cols[None, :]), r
 
 
+@pytest.mark.parametrize("size", [3, 5, 7, 9])
+def test_lrn_bwd_divides(size):
+    """dx of a channel whose own gradient is zero, beside one whose gradient is one: with beta so small that s^(-beta) is one, -coef / s_j,
+    and with coef a power of two that is the correctly rounded quotient 1 / s_j, bit for bit."""
+    M, half = 4096, size // 2
+    x, dy = torch.zeros((1, 2 + 2 * half, 64, M // 64)), torch.zeros((1, 2 + 2 * half, 64, M // 64))
+    x[0, 0] = x[0, 1] = dy[0, 1] = 1.0
+    # in the window of channel 1 and not in that of channel 0; squares of 8-bit values, so that the window's sum is exact
+    x[0, 1 + half] = (torch.arange(M) % 256 / 64.0 + (torch.arange(M) // 256) * 4.0).view(64, M // 64)
+    alpha, beta, k = size * 0.5, 2.0 ** -100, 1.0
+    s = (k + 0.5 * (x[0].double() ** 2).sum(0)).float()   # one rounding, as of a fused multiply-add
+    dx = torch.full_like(x, float("nan"), device="cuda")
+    sn.sn_lrn_bwd(x.cuda(), dy.cuda(), dx, size, alpha, beta, k)
+    torch.cuda.synchronize()
+    assert torch.equal(dx[0, 0].cpu(), -(2.0 * 0.5 * beta) * (1.0 / s))
+
+
 @pytest.mark.parametrize("size", [1, 3, 5, 9])
 @pytest.mark.parametrize("channels", [1, 2, 4, 5, 9, 20, 33])
 def test_lrn_channel_ends(channels, size):
