@@ -1310,9 +1310,9 @@ maxpool3s2_bwd_kernel(const T *__restrict__ dy, const int32_t *__restrict__ idx,
 // another HALF ahead for x, with r, s^(-beta) and dy of the channels in between in registers;
 // x and dy are read once, the forward output is not needed.  Nothing but loads of several channels
 // in flight hides their latency: each channel's x and dy are loaded LRN_AHEAD channels (backward: a turn
-// of its rings) before they are pushed into the window, with no branch around a load (channels outside the
-// tensor load the nearest one inside and count as zero).  128 x 96 x 55x55 bf16: forward 33 us (4.5 TB/s); backward
-// 65 -> 56 us, of which vector instructions issue for 31 (registers renamed instead of moved, no division).
+// of its rings, from size 7 on half a turn) before they are pushed into the window, with no branch around a load (channels outside the
+// tensor load the nearest one inside and count as zero).  128 x 96 x 55x55 bf16, size 5: forward 33 us (4.5 TB/s); backward
+// with the ReLU 57 -> 48 us (registers renamed instead of moved), size 9 77 -> 56, fp32 size 9 108 -> 98.
 // RAG: planes that are no whole number of vectors (55x55, 27x27): a plane is ceil(HW / VEC) vectors at the
 // element's own alignment, the last one moved back so that it ends with the plane; the positions it shares
 // with the vector before are computed and written twice, with the same values.
@@ -1428,7 +1428,9 @@ lrn_bwd_kernel(const T *__restrict__ x, const T *__restrict__ dy, T *__restrict_
     // register and moves none: after step i of a turn (channel m = j + HALF of x has arrived)
     // xr[(i + t) % U] = x of channel m - 2 HALF + t, rr the same for r of channels j - 2 HALF .. j,
     // pr[(i + t) % H1], gr[(i + t) % H1] = s^(-beta), dy of channel j - HALF + t.
-    constexpr int U = 2 * H1;
+    // Loads run A channels ahead.  A whole turn of size 7 or 9 is 16 or 20 vectors more in registers: 177 and 213 of them for bf16, 210 and
+    // over 256 for fp32, two waves or one on a SIMD; half a turn takes 131, 159, 150 and 184.
+    constexpr int U = 2 * H1, A = HALF >= 3 ? H1 : U;
     float xr[U][VEC], rr[U][VEC], pr[H1][VEC], gr[H1][VEC];
     typedef LrnIo<T, VEC, RAG> Io;
     const T *xp = x + off, *gp = dy + off;
@@ -1453,13 +1455,13 @@ lrn_bwd_kernel(const T *__restrict__ x, const T *__restrict__ dy, T *__restrict_
         }
     };
     // before the first output: x from channel cb - 2 HALF, terms from cb - HALF
-    typename Io::VT head[4 * HALF + 1], ghead[2 * HALF + 1], ahead[U], gahead[U];
+    typename Io::VT head[4 * HALF + 1], ghead[2 * HALF + 1], ahead[A], gahead[A];
 #pragma unroll
     for (int i = 0; i < 4 * HALF; ++i) head[i] = Io::load(xp, cb - 2 * HALF + i, xend, HW);
 #pragma unroll
     for (int i = 0; i < 2 * HALF; ++i) ghead[i] = Io::load(gp, cb - HALF + i, gend, HW);
 #pragma unroll
-    for (int i = 0; i < U; ++i) {
+    for (int i = 0; i < A; ++i) {
         ahead[i] = Io::load(xp, cb + 2 * HALF + i, xend, HW);
         gahead[i] = Io::load(gp, cb + HALF + i, gend, HW);
     }
@@ -1484,20 +1486,18 @@ lrn_bwd_kernel(const T *__restrict__ x, const T *__restrict__ dy, T *__restrict_
         Io::store(op + (size_t)c * HW, out);
     };
     int c = cb;
-    const auto turn = [&](auto edge) {
+    const auto turn = [&](auto edge, int end) {
 #pragma unroll
         for (int i = 0; i < U; ++i) {
-            const typename Io::VT xv = ahead[i], gv = gahead[i];
-            ahead[i] = Io::load(xp, c + i + 2 * HALF + U, xend, HW);
-            gahead[i] = Io::load(gp, c + i + HALF + U, gend, HW);
+            if (c + i >= end) break;
+            const typename Io::VT xv = ahead[i % A], gv = gahead[i % A];
+            ahead[i % A] = Io::load(xp, c + i + 2 * HALF + A, xend, HW);
+            gahead[i % A] = Io::load(gp, c + i + HALF + A, gend, HW);
             one(c + i, i, xv, gv, edge);
         }
     };
-    for (; c + U <= ce && c + U + 2 * HALF <= C; c += U) turn(std::false_type());
-    for (; c + U <= ce; c += U) turn(std::true_type());
-#pragma unroll
-    for (int i = 0; i < U; ++i)
-        if (c + i < ce) one(c + i, i, ahead[i], gahead[i], std::true_type());
+    for (; c + U <= ce && c + U + 2 * HALF <= C; c += U) turn(std::false_type(), INT_MAX);
+    for (; c < ce; c += U) turn(std::true_type(), ce);
 }
 
 template <typename F> hipError_t by_dtype(int bf16, F f)
@@ -1794,10 +1794,12 @@ hipError_t lrn_launch(bool bwd, const void *x, const void *dy, void *out, int N,
     // A thread walks its channels one after the other: with few positions the channels are split over
     // blockIdx.y (each part re-reads the HALF or 2 HALF channels beside it) until there are enough threads.
     // (measured on 128 x 256 x 27 x 27: 5 parts of 52 channels 3.1 TB/s forward, 1 part 0.9, 6 parts of 43 2.4)
-    // Backward, whose registers leave a SIMD six waves, takes as many parts as run at once: 128 x 96 x 55 x 55,
-    // 5 parts (a round and a half of waves, 28 channels read for 20) 63 us, 3 or 4 parts 56.
+    // Backward, whose registers leave a SIMD three waves (size 1: eight, size 3: four or five, fp32 size 9: two), takes as many parts
+    // as make three (size 1: seven): more is another round of waves and more channels read twice.  128 x 96 x 55 x 55 bf16, size 5:
+    // 1 part 60 us, 2 parts 48, 4 parts 50; size 9 70, 56, 63; fp32 size 9 104, 98, 101; 128 x 256 x 27 x 27 fp32 size 9: 5 parts
+    // (two waves) 59, 8 parts 63, 16 parts 76.
     long long parts = total >= 400000 ? 1 : (450000 + (long long)total - 1) / (long long)total;
-    if (bwd) parts = 6 * 1024 * 64 / (long long)total;
+    if (bwd) parts = (half == 0 ? 7 : 3) * 1024 * 64 / (long long)total;
     if (parts > (C + 7) / 8) parts = (C + 7) / 8;
     if (parts < 1) parts = 1;
     const int cc = (int)((C + parts - 1) / parts + 3) / 4 * 4, ny = (C + cc - 1) / cc;
