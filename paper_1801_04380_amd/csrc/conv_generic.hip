@@ -789,19 +789,37 @@ hipError_t launch_generic_bwd_data(const void *dy, const void *w, void *dx, cons
     return launch_any<DIR_BWD_DATA>(w, dy, dx, nullptr, g, d, 1, st);
 }
 
+// Tiles of a backward-filter launch.
+long long bwd_filter_tiles(const ConvGeom &g)
+{
+    const int M = g.K, Ncols = g.C * g.R * g.S;
+    return (long long)((M <= 64) ? (M + 63) / 64 : (M + 127) / 128) * ((Ncols + BN - 1) / BN);
+}
+
 // Slices of the (n,p,q) sum so that a backward-filter launch has enough
 // workgroups to fill 256 compute units; each slice keeps at least 8 steps.
 int generic_bwd_filter_splits(const ConvGeom &g)
 {
-    const int M = g.K, Ncols = g.C * g.R * g.S;
-    const long long Kred = (long long)g.N * g.P * g.Q;
-    const long long tiles = (long long)((M <= 64) ? (M + 63) / 64 : (M + 127) / 128) * ((Ncols + BN - 1) / BN);
+    const long long Kred = (long long)g.N * g.P * g.Q, tiles = bwd_filter_tiles(g);
     long long want = (1024 + tiles - 1) / tiles;
     long long most = Kred / (8 * bk_of(g));
     if (want > most) want = most;
     if (want < 1) want = 1;
     if (want > 4096) want = 4096;
     return (int)want;
+}
+
+// Against the image layer's kernel: steps of a workgroup, rounds of workgroups, partial sums or atomics; fitted to those of 390 layers
+// of 1 to 4 channels where the two are close (with partial sums 130, to 9 %; with atomics 66, to 11 % (rms); elsewhere up to four times slower
+// than this says).
+double generic_bwd_filter_us(const ConvGeom &g, bool partial)
+{
+    const int bk = bk_of(g);
+    const long long Kred = (long long)g.N * g.P * g.Q, splits = generic_bwd_filter_splits(g);
+    const long long steps = ((Kred + splits - 1) / splits + bk - 1) / bk, slices = (Kred + steps * bk - 1) / (steps * bk);
+    const double rounds = bwd_filter_tiles(g) * slices / 256.0, mb = slices > 1 ? (double)slices * g.K * g.C * g.R * g.S * 4e-6 : 0;
+    if (partial) return 11 + (slices > 1 ? 3.7 : 0) + steps * (g.K > 64 ? 1.45 : 0.89) * std::max(1.0, rounds / 1.64) + 0.4 * mb;
+    return 8.5 + (slices > 1 ? 3.1 : 0) + steps * (g.K > 64 ? 1.62 : 1.15) * std::max(1.0, rounds / 1.5) + 0.97 * mb;
 }
 
 hipError_t launch_generic_bwd_filter(const void *x, const void *dy, float *dw, const ConvGeom &g, int splits,

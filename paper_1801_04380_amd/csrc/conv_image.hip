@@ -17,6 +17,7 @@
 // twice that.  128 x 3 x 227x227, 96 channels 11x11 / 4 (27 GFLOP): general kernel 203 -> 69 us, the channels-last product
 // with 300 MiB 140; 22 x 3 x 82x66, 38 channels 7x7 / 2: forward and backward-filter 64 -> 36 us.
 #include <algorithm>
+#include <cmath>
 
 #include "sn_internal.h"
 
@@ -330,9 +331,22 @@ bool make_problem(const ConvGeom &g, ImageLaunch *l)
     return l->lds <= LDS_MAX;
 }
 
-int slices_of(const ImageLaunch &l, int cap)
+// us of a stage, and of a slice's way into dw: with partial sums fitted to 1900 timings (1100 layers of 1 to 4 channels, 33 to 384 products,
+// strides 1 to 4, planes of 16 to 300 on a side, 8 to 1024 channels of dy; 400 of them over their slices), which they reproduce to 8 % (rms); atomics
+// to 13 % of 400 layers'.
+double stage_us(const ImageLaunch &l, bool partial)
+{
+    return partial ? 0.41 + 0.035 * l.mt / l.ks + 0.16 * l.nl * l.nrow + 0.047 * (l.mt - 2) : 0.42 + 0.09 * l.mt / l.ks + 0.15 * l.nl * l.nrow;
+}
+double slice_us(const ImageLaunch &l, bool partial) { return (double)l.p.K * l.p.CRS * 4e-6 * (partial ? 0.51 : 0.8); }
+
+// Slices of the sum: with partial sums a workgroup per compute unit, or as many as the workspace holds.  Atomics cost more than a
+// reduction reads, so without them as many as balance the two terms above (2 x 3 x 97x91, 1024 channels 11x11 / 4: 23 slices 44 us, 6
+// 32; 6 x 3 x 44x44, 256 channels 11x11: 85 slices 52, 21 42; 400 layers: 7 % on average).
+int slices_of(const ImageLaunch &l, int cap, bool partial)
 {
     const int most = std::max(1, std::min(l.p.rows, 256 / l.ktiles));   // a workgroup per compute unit
+    if (!partial) return std::max(1, std::min(most, (int)std::sqrt(l.p.rows * stage_us(l, false) / slice_us(l, false))));
     return cap > 0 ? std::min(most, cap) : most;
 }
 
@@ -347,14 +361,25 @@ bool image_wgrad_supported(const ConvGeom &g)
 int image_wgrad_slices(const ConvGeom &g, int cap)
 {
     ImageLaunch l;
-    return make_problem(g, &l) ? slices_of(l, cap) : 0;
+    return make_problem(g, &l) ? slices_of(l, cap, true) : 0;
+}
+
+double image_wgrad_us(const ConvGeom &g, bool partial, int cap)
+{
+    ImageLaunch l;
+    if (!make_problem(g, &l)) return 1e9;
+    const int slices = slices_of(l, cap, partial), steps = (l.p.rows + slices - 1) / slices;
+    const int strips = (steps + l.p.steps - 1) / l.p.steps;   // each starts with G - 1 groups that no step ends with
+    const int ntiles = (l.p.CRS + 31) / 32;
+    const double base = partial ? 9.7 + 2.4 * (l.mt - 2) + 0.03 * ntiles * l.mt / l.ks : 9.8 + 0.8e-5 * l.p.K * l.p.CRS;
+    return base + (steps + (l.p.G - 1.0) * strips + 2) * stage_us(l, partial) + slices * slice_us(l, partial);
 }
 
 hipError_t launch_image_wgrad(const void *x, const void *dy, float *dw, const ConvGeom &g, float *partial, hipStream_t st, int cap)
 {
     ImageLaunch l;
     if (!make_problem(g, &l)) return hipErrorInvalidValue;
-    const int slices = slices_of(l, partial ? cap : 0);
+    const int slices = slices_of(l, cap, partial != nullptr);
     const size_t nw = (size_t)g.K * l.p.CRS;
     const bool alone = slices == 1;   // no sum over workgroups: straight into dw
     if (!partial && !alone) {

@@ -97,11 +97,23 @@ ConvGeom gemm_geom_1x1(const ConvGeom &g, int nimg)
     return u;
 }
 
+// Backward-filter of the image layer by its own kernel, with partial sums or atomics, where its estimate is below that of what runs
+// instead.  It has its start against it -- a workgroup's first group of rows, the filter's height of them, before its first step: 6 x 3 x 44x44,
+// 256 channels 11x11 as STAGED 41 us, the general kernel 31; 46 x 4 x 100x22, 1024 channels 6x6 / 4 50 and 32 -- and wins from some work on (128 x 3 x
+// 227x227, 96 channels 11x11 / 4: 69 and 203).  5x5 "same" layers are 3 to 15 times faster than on the stride-1 kernels.
+bool image_runs(const ConvGeom &g, bool partial)
+{
+    if (smallc_supported(g) || !image_wgrad_supported(g)) return false;
+    const double other = !tile_wgrad_supported(g) ? generic_bwd_filter_us(g, partial)
+                       : partial && g.R == 3 && rows_wgrad_supported(g) ? rows_wgrad_us(g) : 1e9;
+    return image_wgrad_us(g, partial) < 1.05 * other;   // the margin that lost least of 1100 layers
+}
+
 // STAGED backward-filter: fp32 partial dw per slice of the (n,p,q) sum.
 size_t staged_bwd_filter_bytes(const ConvGeom &g, int *splits_out)
 {
     int splits = smallc_supported(g) ? smallc_wgrad_slices(g)
-               : image_wgrad_supported(g) ? image_wgrad_slices(g)
+               : image_runs(g, true) ? image_wgrad_slices(g)
                : tile_wgrad_supported(g) ? tile_wgrad_slices(g)
                : gather_wgrad_supported(g) ? gather_wgrad_slices(g) : generic_bwd_filter_splits(g);
     if (splits_out) *splits_out = splits;
@@ -113,12 +125,12 @@ size_t staged_bwd_filter_bytes(const ConvGeom &g, int *splits_out)
 // workspace, more speed).  Whether the shape has that range, and its least workspace.
 bool staged_bwd_filter_ranged(const ConvGeom &g)
 {
-    return !smallc_supported(g) && (image_wgrad_supported(g) || (tile_wgrad_supported(g) && tile_wgrad_cappable(g)));
+    return !smallc_supported(g) && (image_runs(g, true) || (tile_wgrad_supported(g) && tile_wgrad_cappable(g)));
 }
 
 size_t staged_bwd_filter_min_bytes(const ConvGeom &g)
 {
-    const bool image = image_wgrad_supported(g);
+    const bool image = image_runs(g, true);
     const int full = image ? image_wgrad_slices(g) : tile_wgrad_slices(g);
     const int least = image ? image_wgrad_slices(g, (full + 3) / 4) : tile_wgrad_slices(g, (full + 3) / 4);
     return align_up((size_t)least * g.K * g.C * g.R * g.S * sizeof(float), WS_ALIGN);
@@ -317,7 +329,9 @@ double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
     if (!g.in_bf16) return winograd_guessed(g, dir, ws_bytes) ? std::min(general, winograd_us(g, dir == SN_CONV_BWD_DATA, ws_bytes)) : general;
     if (smallc_supported(g) && dir != SN_CONV_BWD_DATA) return 0;
     if (dir == SN_CONV_BWD_FILTER) {
-        if (image_wgrad_supported(g)) return 0;   // 11x11 / 4 on 227x227 images: 69 + 7 us, the product with 300 MiB 140
+        // (11x11 / 4 on 227x227 images: 69 + 7 us, the product with 300 MiB 140; 6 x 3 x 38x59, 96 channels 5x5: 22 and 16.  The product's three
+        // launches on a small layer are 2 to 3 us more than its estimate says)
+        if (image_runs(g, true)) return image_wgrad_us(g, true, staged_bwd_filter_cap(g, ws_bytes)) - 2;
         if (g.sh > 1 || g.sw > 1 || !tile_wgrad_supported(g)) return general;
         // 1x1 on planes of odd sizes or short rows: bound by memory up to 256 channels on either side, where copies are a
         // second pass; with more the product's larger tiles win, but for the smallest planes
@@ -402,7 +416,7 @@ sn_status own_query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_
         return SN_OK;
     case SN_ALGO_STAGED: {
         PhasePlan pp;
-        if (dir == SN_CONV_BWD_FILTER && (smallc_supported(g) || image_wgrad_supported(g))) {
+        if (dir == SN_CONV_BWD_FILTER && (smallc_supported(g) || image_runs(g, true))) {
             *min_b = *pref_b = staged_bwd_filter_bytes(g, nullptr);
             if (staged_bwd_filter_ranged(g)) *min_b = staged_bwd_filter_min_bytes(g);
             return SN_OK;
@@ -710,16 +724,16 @@ sn_status run_bwd_filter(const void *x, const void *dy, void *dw, const ConvGeom
     const bool tile = tile_wgrad_supported(g);
     if (smallc_supported(g) && (algo == SN_ALGO_DIRECT || algo == SN_ALGO_STAGED))
         return launch_status(launch_smallc_wgrad(x, dy, dwf, g, algo == SN_ALGO_STAGED ? static_cast<float *>(ws) : nullptr, st));
-    if (image_wgrad_supported(g) && (algo == SN_ALGO_DIRECT || algo == SN_ALGO_STAGED))
-        return launch_status(launch_image_wgrad(x, dy, dwf, g, algo == SN_ALGO_STAGED ? static_cast<float *>(ws) : nullptr, st,
-                                                staged_bwd_filter_cap(g, ws_bytes)));
     if (algo == SN_ALGO_DIRECT) {
+        if (image_runs(g, false)) return launch_status(launch_image_wgrad(x, dy, dwf, g, nullptr, st));
         if (tile) return launch_status(launch_tile_wgrad(x, dy, dwf, g, nullptr, st));
         if (gather_wgrad_supported(g)) return launch_status(launch_gather_wgrad(x, dy, dwf, g, nullptr, st));
         return launch_status(launch_generic_bwd_filter(x, dy, dwf, g, generic_bwd_filter_splits(g), nullptr, false, st));
     }
     ChlastPlan cl;
     if (chlast_runs(g, SN_CONV_BWD_FILTER, algo, ws_bytes, &cl)) return launch_status(launch_chlast(x, dy, dw, g, SN_CONV_BWD_FILTER, ws, &cl, st));
+    if (algo == SN_ALGO_STAGED && image_runs(g, true))
+        return launch_status(launch_image_wgrad(x, dy, dwf, g, static_cast<float *>(ws), st, staged_bwd_filter_cap(g, ws_bytes)));
     PhasePlan pp;
     if (algo == SN_ALGO_STAGED && phase_plan(g, SN_CONV_BWD_FILTER, &pp)) {
         // workspace: phase planes of x | dw of the inner convolution | its partial sums

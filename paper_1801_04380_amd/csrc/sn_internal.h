@@ -62,6 +62,7 @@ hipError_t launch_generic_bwd_data(const void *dy, const void *w, void *dx, cons
 hipError_t launch_generic_bwd_filter(const void *x, const void *dy, float *dw, const ConvGeom &g,
                                      int splits, float *partial, bool accumulate, hipStream_t st);
 int generic_bwd_filter_splits(const ConvGeom &g);
+double generic_bwd_filter_us(const ConvGeom &g, bool partial);   // estimate for few input channels, bf16
 
 // Stride-1 bf16 fast path (forward, or backward-data when bwd_data is set).
 // `packed` = workspace for the re-laid-out filter (tile_conv_packed_bytes), or
@@ -117,6 +118,7 @@ hipError_t launch_smallc_wgrad(const void *x, const void *dy, float *dw, const C
 // columns (bf16, any stride and padding; conv_image.hip); contract of launch_rows_wgrad, any number of slices up to image_wgrad_slices(g).
 bool image_wgrad_supported(const ConvGeom &g);
 int image_wgrad_slices(const ConvGeom &g, int cap = 0);
+double image_wgrad_us(const ConvGeom &g, bool partial, int cap = 0);   // estimate, with partial sums or atomics
 hipError_t launch_image_wgrad(const void *x, const void *dy, float *dw, const ConvGeom &g, float *partial, hipStream_t st, int cap = 0);
 
 // 1x1 / stride-1 / unpadded layers with bf16 operands and channel counts that are multiples of 8

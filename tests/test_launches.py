@@ -69,3 +69,23 @@ def test_partial_sums_stay_in_the_workspace(recorded):
                 over += 1
                 worst = worst or ([getattr(s, f) for f in FIELDS], a, b, reach)
     assert sums > 5000 and over == 0, (sums, over, worst)
+
+
+def test_image_layers_take_the_faster_kernel(recorded):
+    """Backward-filter of few input channels under a large filter: its own kernel where there is work for it, the general one where its
+    start would be most of the time, and without partial sums fewer slices than compute units where the
+    atomics of more would cost more than their rows."""
+    sn.sn_planner_clear()
+    D, S = sn.SN_ALGO_DIRECT, sn.SN_ALGO_STAGED
+    want = [((128, 3, 227, 227, 96, 11, 4, 0), True, True), ((64, 3, 224, 224, 64, 7, 2, 3), True, True), ((32, 3, 32, 32, 64, 5, 1, 2), True, True),
+            ((2, 3, 20, 20, 512, 11, 4, 5), False, False), ((6, 3, 44, 44, 256, 11, 1, 0), False, False), ((5, 1, 18, 18, 8, 7, 4, 0), False, True)]
+    calls = []
+    for (N, C, H, W, K, R, st, pad), _, _ in want:
+        s = sn.conv_shape(N, C, H, W, K, R, R, (st, st), (pad, pad), sn.SN_BF16, sn.SN_BF16)
+        calls += [(sn.SN_CONV_BWD_FILTER, D, 0, s), (sn.SN_CONV_BWD_FILTER, S, sn.sn_conv_workspace_query(s, sn.SN_CONV_BWD_FILTER, S)[1] + 256, s)]
+    res = recorded(calls)
+    for i, (shape, direct, staged) in enumerate(want):
+        for image, (status, launches) in zip((direct, staged), res[2 * i:2 * i + 2]):
+            assert status == 0 and any("image_wgrad" in k[0] for k in launches) == image, (shape, launches)
+    grid = [next(k[1] for k in launches if "image_wgrad" in k[0]) for _, launches in res[4:6]]
+    assert grid[0][0] < grid[1][0] <= 256
