@@ -389,17 +389,16 @@ hipError_t launch_image_wgrad(const void *x, const void *dy, float *dw, const Co
     float *out = partial && !alone ? partial : dw;
     const int atomics = !partial && !alone;
     auto go = [&](auto kern) -> hipError_t {
-        static const hipError_t attr =   // one per instantiation of the lambda's call operator
-            hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_MAX);
+        const hipError_t attr = kern.enable_lds(LDS_MAX);
         if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL(kern, dim3(slices, l.ktiles), dim3(THREADS), l.lds, st, static_cast<const bf16_t *>(x),
+        hipLaunchKernelGGL(kern.call, dim3(slices, l.ktiles), dim3(THREADS), l.lds, st, static_cast<const bf16_t *>(x),
                            static_cast<const bf16_t *>(dy), out, atomics, l.p);
         return hipGetLastError();
     };
     hipError_t e = hipErrorInvalidValue;
 #define SN_IMG_K(MT_, NL_, PX_, NR_) \
-    (l.ks == 1 ? go(image_wgrad_kernel<MT_, NL_, PX_, NR_, 1>) : l.ks == 2 ? go(image_wgrad_kernel<MT_, NL_, PX_, NR_, 2>) \
-                                                                           : go(image_wgrad_kernel<MT_, NL_, PX_, NR_, 4>))
+    (l.ks == 1 ? go(Kernel<image_wgrad_kernel<MT_, NL_, PX_, NR_, 1>>()) : l.ks == 2 ? go(Kernel<image_wgrad_kernel<MT_, NL_, PX_, NR_, 2>>()) \
+                                                                           : go(Kernel<image_wgrad_kernel<MT_, NL_, PX_, NR_, 4>>()))
 #define SN_IMG_R(MT_, NL_, PX_) (l.nrow == 1 ? SN_IMG_K(MT_, NL_, PX_, 1) : SN_IMG_K(MT_, NL_, PX_, 2))
 #define SN_IMG_P(MT_, NL_) (l.px == 64 ? SN_IMG_R(MT_, NL_, 64) : SN_IMG_R(MT_, NL_, 32))
 #define SN_IMG(MT_) (l.nl == 2 ? SN_IMG_P(MT_, 2) : SN_IMG_P(MT_, 3))

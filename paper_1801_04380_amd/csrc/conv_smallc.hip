@@ -559,12 +559,6 @@ bool make_problem(const ConvGeom &g, bool wgrad, SmallProblem *p, dim3 *grid, si
     return true;
 }
 
-template <typename Kern>
-hipError_t enable_lds(Kern kern)
-{
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-}
-
 }  // namespace
 
 bool smallc_supported(const ConvGeom &g)
@@ -592,17 +586,17 @@ hipError_t launch_smallc_fwd(const void *x, const void *w, void *y, const ConvGe
     p.stats = stats;
     const bf16_t *xs = static_cast<const bf16_t *>(x), *wsrc = static_cast<const bf16_t *>(w);
     auto go = [&](auto kern) -> hipError_t {
-        static const hipError_t attr = enable_lds(kern);   // one per instantiation of the lambda's call operator
+        const hipError_t attr = kern.enable_lds(160 * 1024);
         if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL(kern, grid, dim3(WAVES * 64), lds, st, xs, wsrc, y, p);
+        hipLaunchKernelGGL(kern.call, grid, dim3(WAVES * 64), lds, st, xs, wsrc, y, p);
         return hipGetLastError();
     };
     const bool q8 = g.Q % 8 == 0;
     if (g.out_bf16) {
-        if (q8) return stats ? go(smallc_fwd_kernel<true, true, true>) : go(smallc_fwd_kernel<true, false, true>);
-        return stats ? go(smallc_fwd_kernel<true, true, false>) : go(smallc_fwd_kernel<true, false, false>);
+        if (q8) return stats ? go(Kernel<smallc_fwd_kernel<true, true, true>>()) : go(Kernel<smallc_fwd_kernel<true, false, true>>());
+        return stats ? go(Kernel<smallc_fwd_kernel<true, true, false>>()) : go(Kernel<smallc_fwd_kernel<true, false, false>>());
     }
-    return stats ? go(smallc_fwd_kernel<false, true, false>) : go(smallc_fwd_kernel<false, false, false>);
+    return stats ? go(Kernel<smallc_fwd_kernel<false, true, false>>()) : go(Kernel<smallc_fwd_kernel<false, false, false>>());
 }
 
 int smallc_wgrad_slices(const ConvGeom &g)
@@ -631,12 +625,12 @@ hipError_t launch_smallc_wgrad(const void *x, const void *dy, float *dw, const C
     float *out = partial ? partial : dw;
     const int atomics = (!partial && !direct_store) ? 1 : 0;
     auto go = [&](auto kern) -> hipError_t {
-        static const hipError_t attr = enable_lds(kern);
+        const hipError_t attr = kern.enable_lds(160 * 1024);
         if (attr != hipSuccess) return attr;
-        hipLaunchKernelGGL(kern, grid, dim3(WAVES * 64), lds, st, xs, ds, out, atomics, p);
+        hipLaunchKernelGGL(kern.call, grid, dim3(WAVES * 64), lds, st, xs, ds, out, atomics, p);
         return hipSuccess;
     };
-    hipError_t e0 = g.Q % 8 == 0 ? go(smallc_wgrad_kernel<true>) : go(smallc_wgrad_kernel<false>);
+    hipError_t e0 = g.Q % 8 == 0 ? go(Kernel<smallc_wgrad_kernel<true>>()) : go(Kernel<smallc_wgrad_kernel<false>>());
     if (e0 != hipSuccess) return e0;
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

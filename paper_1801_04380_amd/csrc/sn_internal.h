@@ -47,6 +47,17 @@ __device__ inline uint32_t f32x2_to_bf16x2(float lo, float hi)
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, b2));
 }
 
+// A kernel as a type of its own (those of one family share the type of their pointers), and its dynamic LDS beyond 64 KB, enabled once
+// per kernel (thread-safe initialisation).
+template <auto K> struct Kernel {
+    static constexpr auto call = K;
+    static hipError_t enable_lds(int bytes)
+    {
+        static const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(K), hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+        return e;
+    }
+};
+
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // ---- launchers implemented in the .hip files (all enqueue on `st`, return hipError_t) ----

@@ -89,3 +89,25 @@ def test_image_layers_take_the_faster_kernel(recorded):
             assert status == 0 and any("image_wgrad" in k[0] for k in launches) == image, (shape, launches)
     grid = [next(k[1] for k in launches if "image_wgrad" in k[0]) for _, launches in res[4:6]]
     assert grid[0][0] < grid[1][0] <= 256
+
+
+def test_every_kernel_is_given_the_lds_that_it_is_launched_with(recorded):
+    """Beyond 64 KB dynamic LDS is enabled kernel by kernel, not for the first one of a family that a process runs."""
+    sn.sn_planner_clear()
+    rnd, calls = random.Random(3), []
+    for _ in range(4000):
+        few = rnd.random() < 0.7
+        R, S = rnd.choice([(11, 11), (7, 7), (5, 5), (3, 3), (9, 12), (7, 3), (4, 8)] if few else [(3, 3), (1, 1), (5, 5), (1, 7), (7, 1)])
+        st = rnd.choice([1, 2, 4])
+        s = sn.conv_shape(rnd.choice([1, 8, 64]), rnd.randint(1, 4) if few else rnd.choice([16, 64, 128]), rnd.randint(R, 200), rnd.randint(S, 200),
+                          rnd.choice([8, 64, 96, 200]), R, S, (st, st), rnd.choice([(0, 0), (R // 2, S // 2)]), sn.SN_BF16, sn.SN_BF16)
+        for d in (sn.SN_CONV_FWD, sn.SN_CONV_BWD_DATA, sn.SN_CONV_BWD_FILTER):
+            algo, used, _ = sn.sn_conv_plan(s, d, rnd.choice([0, 64 << 20]))
+            calls.append((d, algo, used, s))
+    large = {}
+    for status, launches in recorded(calls):
+        assert status == 0
+        for kernel, _, _, lds, limit, _ in launches:
+            if lds > 64 << 10:
+                large[kernel] = min(limit - lds, large.get(kernel, 0))
+    assert len(large) > 40 and all(room >= 0 for room in large.values()), [k for k, room in large.items() if room < 0]
