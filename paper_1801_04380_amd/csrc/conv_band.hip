@@ -85,14 +85,18 @@ __device__ inline uint32_t lds_address(const void *p)
     return (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) const void *)p);
 }
 
-// 16 bytes a lane from memory to LDS, lane l's at lds + 16 l.
+// 16 bytes a lane from memory to LDS, lane l's at lds + 16 l.  (m0 is one of the registers that the compiler reserves: that it is not
+// preserved here, which it warns of, is what the clobber says.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ inline void load_lds16(uint32_t lds, uint32_t voff, i32x4 rsrc)
 {
     asm volatile("s_mov_b32 m0, %0\n\t"
                  "s_nop 0\n\t"
                  "buffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(lds), "v"(voff), "s"(rsrc) : "memory");
+                 :: "s"(lds), "v"(voff), "s"(rsrc) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // All but the last N of the wave's loads and stores are done.
 template <int N>

@@ -37,16 +37,18 @@ __device__ inline i32x4 make_rsrc(const void *p, uint32_t bytes)
 }
 
 // 16 bytes per lane from the buffer straight into LDS: lane l's at lds + 16 * l.  In assembly, so that the compiler
-// neither counts these loads nor waits for them before LDS reads that do not depend on them: stage_wait does.  (m0 is a
-// reserved register that the compiler sets before each use of its own, of which these kernels have none; as a clobber it is
-// warned about.)
+// neither counts these loads nor waits for them before LDS reads that do not depend on them: stage_wait does.  (m0 is one
+// of the registers that the compiler reserves: that it is not preserved here, which it warns of, is what the clobber says.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 __device__ inline void load_lds16(uint32_t lds, uint32_t voff, i32x4 rsrc, uint32_t soff)
 {
     asm volatile("s_mov_b32 m0, %0\n\t"
                  "s_nop 0\n\t"
                  "buffer_load_dwordx4 %1, %2, %3 offen lds"
-                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory");
+                 :: "s"(lds), "v"(voff), "s"(rsrc), "s"(soff) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 // All but the last N of the wave's loads have landed and its LDS reads are done; then the workgroup's barrier.
 template <int N>
