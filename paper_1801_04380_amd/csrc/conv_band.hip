@@ -421,17 +421,22 @@ bool band_plan(const ConvGeom &g, bool bwd_data, BandPlan *pl)
     p.nkt = (p.Kout + 63) / 64;
     p.per_xcd = std::max(1, 32 / p.nkt);
     p.nub = 8 * p.per_xcd;
-    // bands of a strip: the rows that a workgroup's bands walk, two of them halo
+    // Bands of a strip, of four rows at least, so that the rounds of bands that the workgroups' slots take have the fewest steps in all.
+    // For a number of rounds that is as many bands as fit; more rounds, with two rows of halo each, only make up for rows that do
+    // not divide evenly, and none can do with fewer steps than all rows over the slots and its halos.
+    const long long each = (long long)p.N * p.strips, at = (long long)p.nub * WG_BANDS;
+    const long long most = std::min<long long>(std::max(1, p.Pout / 4), 0x3fffffff / each);
     long long best = -1;
-    for (int b = 1; b <= std::max(1, p.Pout / 4); ++b) {
-        const int rows = (p.Pout + b - 1) / b, bands = (p.Pout + rows - 1) / rows;
-        const long long units = (long long)p.N * p.strips * bands, at = (long long)p.nub * WG_BANDS;
-        if (units > 0x3fffffff) break;
-        const long long steps = (units + at - 1) / at * (rows + 2);
+    for (long long rounds = (each + at - 1) / at, b = 0; most > 0; rounds = std::max(rounds + 1, ((b + 1) * each + at - 1) / at)) {
+        if (best >= 0 && (p.Pout * each + at - 1) / at + 2 * rounds >= best) break;
+        b = std::min(most, rounds * at / each);
+        const int rows = (int)((p.Pout + b - 1) / b), bands = (p.Pout + rows - 1) / rows;
+        const long long units = each * bands, steps = (units + at - 1) / at * (rows + 2);
         if (best < 0 || steps < best) {
             best = steps;
             p.bands = bands; p.rows = rows; p.units = (int)units;
         }
+        if (b == most) break;
     }
     if (best < 0 || best > 0x3fffffff) return false;
     p.nub = std::min(p.nub, (p.units + WG_BANDS - 1) / WG_BANDS);

@@ -4,6 +4,7 @@ the fastest of the rest; more workspace never makes the plan slower)."""
 import ctypes
 import itertools
 import random
+import time
 
 import paper_1801_04380_amd as sn
 from paper_1801_04380_amd import _lib
@@ -213,3 +214,19 @@ def test_more_output_channels_than_a_grid_has_rows():
                                          ctypes.byref(us))
             assert runs == (d == sn.SN_CONV_FWD or K <= 65535), (K, d)
             assert not runs or K <= 65535 or info[3] == 1, (K, d, list(info))
+
+
+def test_planning_a_tall_layer_takes_no_longer():
+    """3x3 layers of few reduction channels: the rows are split into bands without trying every number of them."""
+    sn.sn_planner_clear()
+    us = {}
+    for H, W in ((224, 224), (65536, 8)):
+        shape = sn.conv_shape(1, 64, H, W, 64, 3, 3, (1, 1), (1, 1), sn.SN_BF16, sn.SN_BF16)
+        runs = []
+        for _ in range(9):
+            t = time.perf_counter()
+            for _ in range(50):
+                sn.sn_conv_plan(shape, sn.SN_CONV_FWD, 64 << 20)
+            runs.append(time.perf_counter() - t)
+        us[H] = min(runs)
+    assert us[65536] < 8 * us[224], us
