@@ -842,12 +842,16 @@ int sn_chlast_inspect(const sn_conv_shape *shape, int dir, int algo, size_t work
 }
 
 // For the tests (not in the header): the streaming 3x3 kernel (conv_band.hip) on a shape that the estimates may leave to another;
-// with `part` (256 triples of floats per output channel) forward with statistics.
+// with `part` (256 triples of floats per output channel: a launch has no more workgroups) forward with statistics.
 sn_status sn_band_conv(const void *in, const void *w, void *out, const sn_conv_shape *shape, int bwd_data, float *part, float *mean, float *invstd,
                        float eps, sn_stream stream)
 {
     ConvGeom g;
-    if (make_geom(shape, &g) != SN_OK || band_conv_us(g, bwd_data != 0) >= 1e9 || (part && bwd_data)) return SN_ERR_UNSUPPORTED;
+    const sn_status s = make_geom(shape, &g);
+    if (s != SN_OK) return s;
+    if (!in || !w || !out || !aligned(in, 16) || !aligned(w, 16) || !aligned(out, 16) || !aligned(part, 16)) return SN_ERR_BAD_ARG;
+    if (part && (!mean || !invstd || !aligned(mean, 4) || !aligned(invstd, 4) || !(eps >= 0.f))) return SN_ERR_BAD_ARG;
+    if (band_conv_us(g, bwd_data != 0) >= 1e9 || (part && bwd_data)) return SN_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (launch_band_conv(in, w, out, g, bwd_data != 0, st, part) != hipSuccess) return SN_ERR_LAUNCH;
     return part ? launch_status(launch_bn_finalize_tiles(part, g.K, band_conv_stats_tiles(g), mean, invstd, eps, st)) : SN_OK;

@@ -105,6 +105,19 @@ def test_bad_arguments_are_refused_before_any_launch():
     assert lib.sn_bn_relu_pool2_bwd(one, two, three, one, one, one, one, ctypes.c_void_p(1024), one, one, 1, 1, 4, 6, 1, None) == 2
 
 
+def test_the_streaming_kernels_entry_for_tests_checks_what_it_is_given():
+    lib = _lib.load()
+    s = sn.conv_shape(2, 64, 16, 16, 64, 3, 3, (1, 1), (1, 1), sn.SN_BF16, sn.SN_BF16)
+    wide = sn.conv_shape(2, 128, 16, 16, 64, 3, 3, (1, 1), (1, 1), sn.SN_BF16, sn.SN_BF16)
+    one, odd, eps = ctypes.c_void_p(256), ctypes.c_void_p(264), ctypes.c_float(1e-5)
+    for args, status in (((None, one, one, s, 0, None, None, None), 1), ((one, odd, one, s, 0, None, None, None), 1),
+                         ((one, one, odd, s, 0, None, None, None), 1), ((one, one, one, s, 0, odd, one, one), 1),
+                         ((one, one, one, s, 0, one, None, one), 1), ((one, one, one, s, 1, one, one, one), 2),
+                         ((one, one, one, wide, 0, None, None, None), 2)):
+        a, w, out, shape, back, part, mean, invstd = args
+        assert lib.sn_band_conv(a, w, out, ctypes.byref(shape), back, part, mean, invstd, eps, None) == status, args
+
+
 def test_workspace_query():
     s = sn.conv_shape(2, 16, 16, 16, 16, 3, 3, (1, 1), (1, 1))
     assert sn.sn_conv_workspace_query(s, sn.SN_CONV_FWD, sn.SN_ALGO_DIRECT) == (0, 0)
