@@ -67,7 +67,14 @@ typedef enum { SN_CONV_FWD = 0, SN_CONV_BWD_DATA = 1, SN_CONV_BWD_FILTER = 2 } s
  *               so does backward-data of 1x1 / stride-2 layers on planes of even
  *               size, whose kernel writes each 2x2 cell of dx (one value, three
  *               zeros) itself: sn_conv_workspace_query reports STAGED there with
- *               0 bytes and sn_conv_plan names DIRECT.  Every other strided
+ *               0 bytes and sn_conv_plan names DIRECT.  So do forward and
+ *               backward-data of 3x3 / stride-1 layers over at most 64 reduction
+ *               channels (bf16, multiples of 8, as are the rows) from some size on,
+ *               whose kernel streams the image past a filter in registers; and
+ *               backward-filter of up to four input channels under 33 to 384
+ *               products (C * R * S; a network's first layer with a large filter) has
+ *               a kernel of its own under DIRECT and STAGED where that is
+ *               estimated to be the faster one.  Every other strided
  *               backward-data works by residue classes of the input pixels
  *               (h mod stride_h, w mod stride_w): a class shares its taps, so only
  *               the taps that meet an output pixel are multiplied.
@@ -82,7 +89,8 @@ typedef enum { SN_CONV_FWD = 0, SN_CONV_BWD_DATA = 1, SN_CONV_BWD_FILTER = 2 } s
  *               workspace: the filter packed tap-major for forward and
  *               backward-data; per-slice partial sums of dw (reduced in a fixed
  *               order, so the result is run-to-run identical) for
- *               backward-filter (3x3, 1x1, 5x5, 1x7 and 7x1 "same" layers take from a
+ *               backward-filter (3x3, 1x1, 5x5, 1x7 and 7x1 "same" layers, and those of
+ *               few input channels that run the kernel of their own above, take from a
  *               quarter of the slices they want, min_bytes, up to all of them,
  *               preferred_bytes: fewer slices are fewer, longer workgroups).  On strided shapes (bf16; 1x1 filters without
  *               padding, and filters whose taps reach at most one row / column

@@ -376,7 +376,7 @@ static double packed_tile_us(const ConvGeom &g, bool bwd_data)
 
 // Few reduction channels: the streaming kernel where it is estimated to be faster than the tiles with or without workspace
 // (it wins from about eight rows a band on; on smaller layers its start, the filter into registers, is what counts).
-static bool band_runs(const ConvGeom &g, bool bwd_data, bool staged)
+bool band_conv_runs(const ConvGeom &g, bool bwd_data, bool staged)
 {
     const double us = band_conv_us(g, bwd_data);
     return us < (staged ? packed_tile_us(g, bwd_data) : band_conv_direct_us(g, bwd_data));
@@ -390,7 +390,7 @@ int tile_conv_stats_tiles(const ConvGeom &g, bool staged, bool in_aligned16)
     TileProblem p;
     Plan pl, pl2;
     if (!tile_conv_supported(g, false) || !problem_of(g, false, &p) || !make_plan(p, g.R, g.S, staged, &pl)) return 0;
-    if (in_aligned16 && band_runs(g, false, staged)) return band_conv_stats_tiles(g);
+    if (in_aligned16 && band_conv_runs(g, false, staged)) return band_conv_stats_tiles(g);
     if (staged && in_aligned16 && make_plan2(p, g.R, g.S, &pl2)) return pl2.p.nptiles;
     return pl.p.nptiles;
 }
@@ -405,7 +405,7 @@ hipError_t launch_tile_conv(const void *in, const void *w, void *out, const Conv
         return hipErrorInvalidValue;
     if (stats && bwd_data) return hipErrorInvalidValue;
     if (!stats && pointwise_supported(g, bwd_data)) return launch_pointwise(in, w, out, g, bwd_data, st);
-    if (reinterpret_cast<uintptr_t>(in) % 16 == 0 && band_runs(g, bwd_data, packed != nullptr)) return launch_band_conv(in, w, out, g, bwd_data, st, stats);
+    if (reinterpret_cast<uintptr_t>(in) % 16 == 0 && band_conv_runs(g, bwd_data, packed != nullptr)) return launch_band_conv(in, w, out, g, bwd_data, st, stats);
     pl.p.stats = stats;
     const bf16_t *wsrc = static_cast<const bf16_t *>(w);
     if (packed) {

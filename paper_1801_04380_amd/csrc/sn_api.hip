@@ -445,6 +445,8 @@ sn_status own_query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_
         }
         if (!tile_conv_supported(g, dir == SN_CONV_BWD_DATA)) return SN_ERR_UNSUPPORTED;
         *min_b = *pref_b = tile_conv_packed_bytes(g, dir == SN_CONV_BWD_DATA);
+        // the streaming kernel writes no packed filter
+        if (band_conv_runs(g, dir == SN_CONV_BWD_DATA, true) && band_conv_runs(g, dir == SN_CONV_BWD_DATA, false)) *min_b = *pref_b = 0;
         return SN_OK;
     }
     default:
@@ -461,7 +463,7 @@ sn_status query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *m
     const sn_status s = own_query(g, dir, algo, min_b, pref_b);
     const bool strided = g.sh > 1 || g.sw > 1;
     ChlastPlan cl;
-    if (s != SN_OK || *pref_b == 0) return s;
+    if (s != SN_OK) return s;
     if (algo == SN_ALGO_IM2COL_GEMM && chlast_runs(g, dir, algo, ALL_BYTES, &cl)) *pref_b = std::max(*pref_b, cl.bytes);
     if (algo != SN_ALGO_STAGED || dir == SN_CONV_BWD_FILTER || (strided && dir == SN_CONV_FWD)) return SN_OK;
     if (strided && chlast_least(g, dir, &cl)) *min_b = std::min(*min_b, cl.bytes);

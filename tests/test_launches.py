@@ -111,3 +111,17 @@ def test_every_kernel_is_given_the_lds_that_it_is_launched_with(recorded):
             if lds > 64 << 10:
                 large[kernel] = min(limit - lds, large.get(kernel, 0))
     assert len(large) > 40 and all(room >= 0 for room in large.values()), [k for k, room in large.items() if room < 0]
+
+
+def test_the_streaming_kernel_is_given_no_workspace(recorded):
+    """Few reduction channels: where the kernel that writes no packed filter runs, none is asked for under either name."""
+    sn.sn_planner_clear()
+    calls = []
+    for N, C, H, W, K in ((64, 64, 56, 56, 64), (32, 64, 224, 224, 64), (32, 32, 112, 112, 64)):
+        s = sn.conv_shape(N, C, H, W, K, 3, 3, (1, 1), (1, 1), sn.SN_BF16, sn.SN_BF16)
+        assert sn.sn_conv_workspace_query(s, sn.SN_CONV_FWD, sn.SN_ALGO_STAGED) == (0, 0)
+        assert sn.sn_conv_plan(s, sn.SN_CONV_FWD, 256 << 20)[:2] == (sn.SN_ALGO_DIRECT, 0)
+        calls += [(sn.SN_CONV_FWD, a, b, s) for a, b in ((sn.SN_ALGO_DIRECT, 0), (sn.SN_ALGO_STAGED, 0), (sn.SN_ALGO_STAGED, 1 << 20),
+                                                         (sn.SN_ALGO_AUTO, 0), (sn.SN_ALGO_AUTO, 256 << 20))]
+    for status, launches in recorded(calls):
+        assert status == 0 and [re.sub(r"^\d+", "", k[0])[:15] for k in launches] == ["band3x3_kernelI"], launches
