@@ -8,8 +8,9 @@
 // that are open; the first of them is then complete and stored.  An operand read from LDS serves three matrix products,
 // each input row is read once per band, and there are no vertical halos but the two rows at a band's ends.
 //   A workgroup is 8 waves: 4 bands x 2 halves of 64 output channels; the two waves of a band share its rows in LDS, laid out
-// [pixel][channel] (a pixel's pitch is an odd number of 16-byte units: no bank conflicts).  Rows come from memory straight into
-// LDS three steps ahead, and a step ahead of their use they are turned with byte permutes, 8 channels x 4 pixels a lane.  All this,
+// [pixel][channel] (a pixel's pitch is an odd number of 16-byte units: neither operands read nor turned pixels written meet in a bank,
+// measured alone).  Rows come from memory straight into LDS three steps ahead, and a step ahead of their use they are turned with byte
+// permutes, 8 channels x 4 pixels a lane; the reads for that, 8 bytes at strides of 192, are what conflicts: 29 % of the kernel's LDS cycles.  All this,
 // and storing the row completed before, is cut into pieces between the matrix products: done before and after them it cost
 // 10 to 15 % (54 steps: 139 us, like this 125).  One barrier a step.  BN statistics are summed as rows are stored, a triple per
 // workgroup and channel.
@@ -175,7 +176,7 @@ band3x3_kernel(const bf16_t *__restrict__ in, const bf16_t *__restrict__ w, bf16
     constexpr int QUADS = NC * 2;   // channel quads of a wave
     const int blk = lane % 6, quad = kh * QUADS + lane % (6 * QUADS) / 6;   // lanes left over repeat another's
     unsigned char *const mine = lds + band * 2 * ROW;
-    // turned: a lane takes 8 channels x 4 pixels of the columns 4 .. 43, neighbours the next channels (no bank conflicts either way)
+    // turned: a lane takes 8 channels x 4 pixels of the columns 4 .. 43, neighbours the next channels (written without bank conflicts)
     const int turn = lane % (10 * NC), tcol = 4 + turn / NC * 4, oct = turn % NC;
     const uint32_t tsrc = (oct * 12 + tcol / 8) * 16 + tcol % 8 * 2;
     const uint32_t wr = tcol * PITCH + (kh * NC + oct) * 16;

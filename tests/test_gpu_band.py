@@ -98,6 +98,24 @@ def test_band_stats():
     assert np.linalg.norm(invstd.cpu().numpy() - s) / np.linalg.norm(s) <= 1e-5
 
 
+@pytest.mark.parametrize("shape", [(9, 32, 37, 48, 72), (3, 48, 29, 40, 33), (2, 40, 62, 72, 130), (70, 16, 40, 32, 64)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_band_stats_of_fewer_channels(shape):
+    """The kernels for up to 32 and up to 48 channels, remainders of output channels and columns, many bands a workgroup."""
+    N, C, H, W, K = shape
+    x = wl.activation((N, C, H, W), "bf16", 3)
+    w = (wl.activation((K, C, 3, 3), "bf16", 4, scale=0.06).float() + 0.03).bfloat16()
+    sh = sn.conv_shape(N, C, H, W, K, 3, 3, (1, 1), (1, 1), sn.SN_BF16, sn.SN_BF16)
+    y = torch.full((N, K, H, W), float("nan"), dtype=torch.bfloat16, device="cuda")
+    mean, invstd = (torch.empty(K, device="cuda") for _ in range(2))
+    part = torch.full((K, 256, 3), float("nan"), device="cuda")
+    _band(x.cuda(), w.cuda(), y, sh, False, (part, mean, invstd))
+    torch.cuda.synchronize()
+    v = y.double()
+    m, s = v.mean((0, 2, 3)), (v.var((0, 2, 3), correction=0) + 1e-5).rsqrt()
+    assert (mean - m).norm() / m.norm() <= 1e-5 and (invstd - s).norm() / s.norm() <= 1e-5
+
+
 @pytest.mark.parametrize("algo", [sn.SN_ALGO_DIRECT, sn.SN_ALGO_STAGED], ids=["direct", "staged"])
 def test_calls_take_it_where_it_is_faster(algo):
     """From some size on: the same bits as the kernel itself, with and without statistics."""

@@ -1,5 +1,5 @@
-"""Backward-filter of image layers (csrc/conv_image.hip) against the oracle: every column stride and tile count, strips of one
-pixel and one over 64, one output row and workgroups whose rows cross strips and images, rows of padding alone; by atomics,
+"""Backward-filter of image layers (csrc/conv_image.hip) against the oracle: every instantiation of the kernel, column strides 1 to 7,
+strips of one pixel and one over 64, one output row and workgroups whose rows cross strips and images, rows of padding alone; by atomics,
 with the least and with all the partial sums it can use."""
 import numpy as np
 import pytest
@@ -16,6 +16,36 @@ SHAPES = [(2, 3, 227, 227, 96, 11, 11, (4, 4), (0, 0)), (3, 3, 60, 131, 64, 7, 7
           (2, 3, 30, 90, 40, 7, 7, (2, 2), (3, 3)), (1, 4, 9, 9, 5, 9, 9, (1, 1), (0, 0)), (5, 1, 40, 67, 33, 6, 9, (3, 3), (2, 4)),
           (2, 2, 21, 300, 130, 5, 7, (1, 4), (4, 0)), (7, 3, 16, 64, 16, 5, 5, (1, 1), (2, 2)),
           (1, 4, 70, 30, 97, 8, 12, (4, 1), (3, 11)), (2, 3, 13, 259, 200, 4, 3, (2, 4), (5, 7))]
+# small layers that between them run every kernel of the family, under either name: tiles of channels, runs of a filter row, 32 or 64 pixels
+# a step, passes over the rows of a group, waves that share a column tile (test_launches.py holds them to it)
+EVERY = [(2, 3, 15, 28, 5, 12, 6, (4, 1), (2, 1)), (3, 2, 26, 45, 5, 7, 7, (4, 7), (0, 3)), (1, 2, 33, 40, 5, 4, 6, (6, 3), (0, 3)),
+         (1, 4, 95, 46, 5, 10, 5, (6, 4), (1, 1)), (2, 3, 49, 31, 5, 6, 6, (6, 5), (0, 3)), (5, 3, 23, 27, 5, 4, 3, (8, 4), (1, 1)),
+         (2, 4, 16, 69, 5, 9, 7, (3, 2), (0, 3)), (1, 3, 15, 113, 5, 10, 4, (2, 3), (2, 0)),
+         (1, 1, 16, 130, 5, 8, 5, (6, 4), (2, 2)), (1, 3, 44, 244, 5, 11, 7, (8, 7), (5, 1)),
+         (1, 4, 15, 242, 5, 4, 8, (6, 7), (1, 4)), (1, 4, 25, 205, 5, 3, 3, (6, 5), (0, 0)),
+         (3, 2, 24, 76, 5, 12, 9, (6, 7), (3, 2)), (3, 1, 38, 21, 5, 11, 9, (5, 4), (5, 3)),
+         (1, 1, 13, 226, 5, 3, 11, (3, 7), (0, 4)), (3, 4, 81, 16, 5, 5, 12, (5, 4), (1, 3)),
+         (1, 3, 33, 72, 5, 3, 12, (6, 3), (1, 4)), (3, 2, 38, 51, 5, 3, 12, (8, 5), (1, 5)),
+         (1, 3, 14, 54, 5, 8, 11, (4, 1), (2, 4)), (3, 1, 13, 104, 5, 12, 9, (5, 2), (1, 0)),
+         (1, 1, 16, 188, 5, 4, 10, (5, 5), (1, 1)), (1, 3, 11, 197, 5, 7, 11, (6, 2), (2, 4)),
+         (1, 2, 13, 117, 5, 6, 9, (8, 1), (3, 0)), (3, 2, 11, 221, 5, 3, 11, (8, 5), (0, 1)),
+         (9, 4, 14, 96, 70, 11, 7, (2, 3), (0, 0)), (1, 2, 22, 37, 70, 7, 8, (4, 2), (0, 3)),
+         (1, 1, 84, 20, 70, 5, 7, (8, 7), (2, 1)), (64, 3, 104, 170, 70, 10, 7, (6, 7), (1, 0)),
+         (1, 3, 14, 114, 70, 5, 7, (6, 5), (2, 2)), (2, 2, 22, 45, 70, 6, 3, (8, 3), (3, 1)),
+         (1, 4, 14, 192, 70, 11, 5, (2, 1), (0, 0)), (1, 2, 18, 84, 70, 10, 7, (6, 2), (1, 1)),
+         (1, 3, 5, 228, 70, 3, 4, (4, 5), (0, 2)), (1, 3, 14, 151, 70, 11, 6, (8, 3), (5, 1)),
+         (2, 4, 6, 168, 70, 4, 7, (6, 4), (1, 2)), (1, 2, 15, 239, 96, 6, 4, (8, 7), (3, 1)),
+         (3, 2, 11, 166, 97, 10, 11, (5, 7), (2, 1)), (1, 2, 19, 148, 70, 6, 9, (6, 7), (3, 2)),
+         (3, 1, 15, 57, 96, 5, 9, (6, 5), (0, 3)), (3, 2, 26, 33, 70, 12, 10, (8, 1), (0, 1)),
+         (2, 4, 12, 176, 97, 3, 9, (5, 7), (0, 2)), (1, 2, 26, 91, 130, 3, 10, (8, 3), (1, 5)),
+         (3, 2, 11, 172, 96, 10, 10, (6, 5), (1, 1)), (3, 2, 5, 173, 97, 5, 12, (6, 5), (2, 5)),
+         (1, 1, 7, 35, 70, 4, 11, (3, 1), (1, 5)), (33, 2, 109, 198, 97, 12, 9, (8, 5), (0, 1)),
+         (1, 3, 7, 111, 97, 4, 9, (8, 1), (0, 0)), (1, 2, 49, 193, 70, 4, 9, (8, 5), (1, 1))]
+
+
+@pytest.mark.parametrize("shape", EVERY, ids=lambda s: "x".join(str(v) for v in s[:7]))
+def test_every_image_kernel(shape):
+    test_image_bwd_filter(shape)
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(str(v) for v in s[:7]))

@@ -8,6 +8,7 @@ import subprocess
 import pytest
 
 import paper_1801_04380_amd as sn
+import test_gpu_image
 from paper_1801_04380_amd import _lib
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -89,6 +90,18 @@ def test_image_layers_take_the_faster_kernel(recorded):
             assert status == 0 and any("image_wgrad" in k[0] for k in launches) == image, (shape, launches)
     grid = [next(k[1] for k in launches if "image_wgrad" in k[0]) for _, launches in res[4:6]]
     assert grid[0][0] < grid[1][0] <= 256
+
+
+def test_the_image_tests_run_every_kernel(recorded):
+    sn.sn_planner_clear()
+    calls = []
+    for N, C, H, W, K, R, S, stride, pad in test_gpu_image.EVERY:
+        s = sn.conv_shape(N, C, H, W, K, R, S, stride, pad, sn.SN_BF16, sn.SN_BF16)
+        calls += [(sn.SN_CONV_BWD_FILTER, a, b, s) for a, b in
+                  ((sn.SN_ALGO_DIRECT, 0), (sn.SN_ALGO_STAGED, sn.sn_conv_workspace_query(s, sn.SN_CONV_BWD_FILTER, sn.SN_ALGO_STAGED)[1]))]
+    res = recorded(calls)
+    for one in (res[0::2], res[1::2]):
+        assert len({k[0] for _, launches in one for k in launches if "image_wgrad_kernel" in k[0]}) == 48
 
 
 def test_every_kernel_is_given_the_lds_that_it_is_launched_with(recorded):
