@@ -47,9 +47,12 @@ MEASURED_TRAFFIC = {("cfg3_vgg16_n32", 2 << 30, "conv_bwd_filter"): 262e6,
                     # forward and backward-data run the same kernels: one figure for the 25 launches of both
                     ("cfg3_vgg16_n32", 2 << 30, "conv_fwd"): 146e6,
                     ("cfg3_vgg16_n32", 2 << 30, "conv_bwd_data"): 146e6}
-KERNELS = {"conv_fwd": "conv_tile2_kernel / conv_tile_kernel (+ pack_filter9_kernel), smallc_fwd_kernel, pointwise_kernel (1x1), cl_gemm_kernel (+ cl_prep_kernel)",
-           "conv_bwd_data": "conv_tile2_kernel / conv_tile_kernel (+ pack_filter9_kernel), pointwise_kernel (1x1), cl_gemm_kernel (+ cl_prep_kernel)",
-           "conv_bwd_filter": "wgrad_rows_kernel / smallc_wgrad_kernel / pointwise_wgrad_kernel + reduce_partials4_kernel (STAGED) or fill_zero_kernel (DIRECT), "
+KERNELS = {"conv_fwd": "conv_tile2_kernel / conv_tile_kernel (+ pack_filter9_kernel), band3x3_kernel (3x3 over 64 channels), smallc_fwd_kernel, "
+                       "pointwise_kernel (1x1), cl_gemm_kernel (+ cl_prep_kernel)",
+           "conv_bwd_data": "conv_tile2_kernel / conv_tile_kernel (+ pack_filter9_kernel), band3x3_kernel (3x3 over 64 channels), pointwise_kernel (1x1), "
+                            "cl_gemm_kernel (+ cl_prep_kernel)",
+           "conv_bwd_filter": "wgrad_rows_kernel / smallc_wgrad_kernel / image_wgrad_kernel / pointwise_wgrad_kernel + reduce_partials_kernel (STAGED) or "
+                              "fill_zero_kernel (DIRECT), "
                               "cl_wgrad_kernel + cl_wgrad_reduce_kernel (+ cl_prep_kernel)"}
 
 
@@ -88,13 +91,13 @@ class Op:
 
 
 def kernel_set_id():
-    """A short hash of the sources of the kernels the traffic figures are about (the stride-1 tile,
-    few-channel, backward-filter and channels-last kernels): tells a stale counter figure from a current one."""
+    """A short hash of the sources of the kernels the traffic figures are about (the stride-1 tile, streaming, few-channel, image,
+    backward-filter and channels-last kernels, the reduction of partial sums): tells a stale counter figure from a current one."""
     import hashlib
     h = hashlib.sha256()
     d = os.path.join(ROOT, "paper_1801_04380_amd", "csrc")
     for name in sorted(os.listdir(d)):
-        if name.startswith(("conv_tile", "conv_wgrad", "conv_smallc", "conv_chlast")) and name.endswith((".hip", ".h")):
+        if name.startswith(("conv_tile", "conv_band", "conv_wgrad", "conv_smallc", "conv_image", "conv_generic", "conv_chlast")) and name.endswith((".hip", ".h")):
             with open(os.path.join(d, name), "rb") as f:
                 h.update(name.encode() + b"\0" + f.read())
     return h.hexdigest()[:12]

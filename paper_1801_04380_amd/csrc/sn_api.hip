@@ -357,7 +357,7 @@ bool chlast_faster(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t
     if (ws_bytes == 0 || (algo != SN_ALGO_STAGED && algo != SN_ALGO_IM2COL_GEMM)) return false;
     double other = algo == SN_ALGO_IM2COL_GEMM ? 1e9 : other_us(g, dir, ws_bytes);
     // less than half of the row-stationary kernel's partial sums: atomics (64 x 256 x 20x20 -> 128: 42 us, with them 15)
-    if (dir == SN_CONV_BWD_FILTER && g.R == 3 && rows_wgrad_supported(g) && rows_wgrad_partial_bytes(g) / 2 > ws_bytes) other += 30;
+    if (dir == SN_CONV_BWD_FILTER && g.R == 3 && !image_runs(g, true) && rows_wgrad_supported(g) && rows_wgrad_partial_bytes(g) / 2 > ws_bytes) other += 30;
     if (other <= CHLAST_LEAST_US || !chlast_plan(g, dir, ws_bytes, plan)) return false;
     const bool alone = dir == SN_CONV_BWD_FILTER ? !tile_wgrad_supported(g) : dir == SN_CONV_FWD && !tile_conv_supported(g, false);
     return plan->passes <= (alone ? 8 : 2) && plan->us < other;
