@@ -19,6 +19,7 @@
 // 222 and 238 (backward-data) -> 145 and 138 without; 64 x 64 x 56x56 -> 64: 32 -> 25 and 33 -> 26; 32 x 32 x 112x112 -> 64:
 // 35 -> 28 and 41 -> 28.  A launch starts with the filter's way into registers: small layers stay with the tiles.
 #include <algorithm>
+#include <cmath>
 
 #include "conv_tile.h"
 
@@ -468,25 +469,16 @@ hipError_t launch_nc(const void *in, const void *w, void *out, const BandProblem
 
 }  // namespace
 
-// Estimates in us, of this kernel and of conv_tile_kernel without workspace, which it replaces where it is the faster one.  Steps
-// of a workgroup: 6 (8 x 64 x 56x56 -> 64) 15.6 us, 9 (64 x 64 x 56x56 -> 64) 25, 30 (32 x 64 x 112x112 -> 128) 64, 54
-// (32 x 64 x 224x224 -> 64) 130; 16 of 32 channels 28.
+// Estimate in us: steps of a workgroup, rounds of workgroups, bytes; fitted to 1600 layers (1 to 64 images, 8 to 64 reduction and 8 to 520
+// output channels, planes of 7x7 to 230x224, either direction), which it reproduces to 8 % (rms).
 double band_conv_us(const ConvGeom &g, bool bwd_data)
 {
     BandPlan pl;
     if (!band_plan(g, bwd_data, &pl)) return 1e9;
     const BandProblem &p = pl.p;
     const long long at = (long long)p.nub * WG_BANDS, steps = (p.units + at - 1) / at * (p.rows + 2);
-    return 5 + steps * (0.75 + 0.35 * pl.NC) * std::max(1.0, p.nub * p.nkt / 256.0);
-}
-
-// Per 256 tiles of 512 pixels (fractions count: two workgroups share a compute unit): the layers above 10.4, 32, 84, 222 and 41 us.
-double band_conv_direct_us(const ConvGeom &g, bool bwd_data)
-{
-    BandPlan pl;
-    if (!band_plan(g, bwd_data, &pl)) return 1e9;
-    const BandProblem &p = pl.p;
-    return 8 + (double)p.N * p.Pout * p.Qout * p.nkt / (512 * 256) * (6 + 2.25 * pl.NC);
+    const double share = p.nub * p.nkt / 256.0;
+    return 6.8 + steps * (0.204 + 0.337 * pl.NC + 0.14 * std::min(1.0, share)) * std::max(1.0, std::ceil(share)) + 0.058e-6 * ((double)p.in_bytes + p.out_bytes);
 }
 
 int band_conv_stats_tiles(const ConvGeom &g)

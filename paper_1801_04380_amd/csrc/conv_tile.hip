@@ -374,15 +374,55 @@ static double packed_tile_us(const ConvGeom &g, bool bwd_data)
     return 1e9;   // not measured; the product was 1.2 to 10 times faster elsewhere
 }
 
-// Few reduction channels: the streaming kernel where it is estimated to be faster than the tiles with or without workspace
-// (it wins from about eight rows a band on; on smaller layers its start, the filter into registers, is what counts).
+// The same over at most 64 reduction channels, 3x3, with a term for the tensors' bytes, for the choice between the tiles and the streaming kernel:
+// 960 layers with a packed filter, which these reproduce to 7 % (rms) ...
+struct FewChannelsCost {
+    bool second, wide, kt64;
+    int NF;
+    double base, chunk, tile, per_mb;
+};
+const FewChannelsCost kFewChannels[] = {
+    {false, false, false, 1, 9.0, 1.0, 0, 0.278},    {false, false, true, 2, 7.8, 1.48, 1.6, 0.121}, {false, true, false, 1, 7.9, 1.06, 1.3, 0.05},
+    {false, true, true, 2, 9.2, 0.83, 0.9, 0.146},   {true, false, false, 2, 8.9, 1.39, 0, 0.056},   {true, false, false, 4, 9.1, 1.7, 1.4, 0.074},
+    {true, true, false, 2, 8.5, 1.19, 0, 0.118},     {true, true, false, 4, 9.0, 1.54, 0.9, 0.121}};
+// ... and 1580 without, to 10 %, where a chunk of the filter that is gathered in runs costs 0.69 (forward) or 1.0 (backward-data) of this, one
+// gathered element by element (channels no multiple of 16) 1.9.
+const FewChannelsCost kFewChannelsDirect[] = {
+    {false, false, true, 1, 4.9, 1.8, 0.15, 0.213},  {false, true, true, 1, 4.9, 1.46, 0, 0.213},    {false, false, true, 2, 4.9, 1.72, 1.0, 0.213},
+    {false, true, true, 2, 4.9, 1.48, 0.8, 0.213},   {false, false, true, 4, 4.9, 1.13, 5.9, 0.213}, {false, true, true, 4, 4.9, 1.46, 3.5, 0.213},
+    {false, false, false, 1, 4.9, 2.47, 0, 0.213},   {false, true, false, 1, 4.9, 2.28, 0, 0.213},   {false, false, false, 2, 4.9, 2.78, 0.4, 0.213},
+    {false, true, false, 2, 4.9, 2.47, 0.4, 0.213},  {false, false, false, 4, 4.9, 3.11, 3.0, 0.213}, {false, true, false, 4, 4.9, 2.43, 2.0, 0.213}};
+
+// Few reduction channels: the streaming kernel where its estimate is below that of the tiles with or without workspace.  Of 590 layers that the
+// estimates were not fitted to, without workspace: 13 % faster on average than on the tiles, more than 5 % slower on 15 (at most 17 %), 0.5 % from
+// the better of the two each time; of 345 with workspace 5 %, 12 (29 %) and 0.9 %.  It wins from about eight rows a band on; on smaller layers its
+// start, the filter into registers, is what counts.
 bool band_conv_runs(const ConvGeom &g, bool bwd_data, bool staged)
 {
     const double us = band_conv_us(g, bwd_data);
-    return us < (staged ? packed_tile_us(g, bwd_data) : band_conv_direct_us(g, bwd_data));
+    TileProblem p;
+    Plan pl, pl2;
+    if (us >= 1e9 || !problem_of(g, bwd_data, &p) || !make_plan(p, g.R, g.S, staged, &pl)) return false;
+    const bool second = staged && make_plan2(p, g.R, g.S, &pl2);
+    if (second) pl = pl2;
+    const double rounds = std::max(1.0, std::ceil((double)pl.p.nptiles * pl.p.nktiles / 128) / 2);
+    const double gather = staged ? 1 : p.Cin % 16 ? 1.9 : bwd_data ? 1 : 0.69;
+    const double mb = 2e-6 * p.N * ((double)p.Cin * p.Hin * p.Win + (double)p.Kout * p.Pout * p.Qout);
+    double other = packed_tile_us(g, bwd_data);   // (a tiling that none of these layers had)
+    const auto tiles = [&](const FewChannelsCost &t) {
+        if (t.second == second && t.wide == pl.wide && t.kt64 == (pl.KT == 64) && t.NF == pl.NF)
+            other = t.base + rounds * (t.chunk * gather * pl.p.nchunks + t.tile) + t.per_mb * mb;
+    };
+    if (staged) for (const FewChannelsCost &t : kFewChannels) tiles(t);
+    else for (const FewChannelsCost &t : kFewChannelsDirect) tiles(t);
+    return us < other;
 }
 
-double tile_conv_us(const ConvGeom &g, bool bwd_data) { return std::min(packed_tile_us(g, bwd_data), band_conv_us(g, bwd_data)); }
+double tile_conv_us(const ConvGeom &g, bool bwd_data)
+{
+    const double us = packed_tile_us(g, bwd_data);
+    return band_conv_runs(g, bwd_data, true) ? std::min(us, band_conv_us(g, bwd_data)) : us;
+}
 
 // Pixel tiles of the plan launch_tile_conv would use (forward); 0 if the kernels do not apply.
 int tile_conv_stats_tiles(const ConvGeom &g, bool staged, bool in_aligned16)

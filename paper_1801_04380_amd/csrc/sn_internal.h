@@ -90,7 +90,6 @@ int tile_conv_stats_tiles(const ConvGeom &g, bool staged, bool in_aligned16);
 // workspace; launch_tile_conv takes it where the estimates favour it (very large: the shape has none of it).  stats: as
 // there, band_conv_stats_tiles(g) triples per channel.
 double band_conv_us(const ConvGeom &g, bool bwd_data);
-double band_conv_direct_us(const ConvGeom &g, bool bwd_data);   // of conv_tile_kernel without workspace
 bool band_conv_runs(const ConvGeom &g, bool bwd_data, bool staged);   // launch_tile_conv with or without `packed`, `in` on 16 bytes
 int band_conv_stats_tiles(const ConvGeom &g);
 hipError_t launch_band_conv(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, hipStream_t st, float *stats);
