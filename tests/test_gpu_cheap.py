@@ -131,6 +131,32 @@ def test_bn(shape, dtype):
         assert np.linalg.norm(f64(dx) - dxo) <= tol * np.linalg.norm(terms)
 
 
+@pytest.mark.parametrize("shape,dtype", [((64, 256, 57, 57), "bf16"), ((33, 64, 111, 113), "f32")], ids=["57x57_bf16", "111x113_f32"])
+def test_bn_stores_past_the_cache(shape, dtype):
+    """Calls that move more than 192 MiB store past the caches: forward the same bits as on halves of the batch, which do
+    not, backward against the formula in fp32 (odd planes: scalar ends beside the vectors)."""
+    N, C, H, W = shape
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn(shape, generator=g, device="cuda").to(DT[dtype])
+    dy = torch.randn(shape, generator=g, device="cuda").to(DT[dtype])
+    assert 2 * x.numel() * x.element_size() > 192 << 20 >= (N // 2 + 1) * 2 * x[0].numel() * x.element_size()
+    gamma, beta = (t.cuda() for t in wl.bn_params(C, 3))
+    y, half, dx = (torch.full_like(x, float("nan")) for _ in range(3))
+    mean, invstd, dgamma, dbeta = (torch.empty(C, device="cuda") for _ in range(4))
+    sn.sn_bn_relu_fwd(x, gamma, beta, y, mean, invstd)
+    for part in (slice(0, N // 2), slice(N // 2, N)):
+        sn.sn_bn_apply(x[part], gamma, beta, mean, invstd, half[part], relu=True)
+    torch.cuda.synchronize()
+    assert torch.equal(y, half)
+    sn.sn_bn_relu_bwd(x, dy, gamma, beta, mean, invstd, dx, dgamma, dbeta)
+    c = lambda t: t.view(1, C, 1, 1)
+    xhat = (x.float() - c(mean)) * c(invstd)
+    gr = torch.where(y > 0, dy.float(), 0.)
+    ref = c(gamma * invstd) * (gr - gr.mean((0, 2, 3), keepdim=True) - xhat * (gr * xhat).mean((0, 2, 3), keepdim=True))
+    torch.cuda.synchronize()
+    assert float((dx.float() - ref).norm() / ref.norm()) <= TOL[dtype]
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("N,H", [(4, 16), (40, 64)], ids=["one_pass", "two_pass"])
 def test_bn_relu_bwd_gate_edges(N, H, dtype):
