@@ -321,6 +321,13 @@ bool winograd_guessed(const ConvGeom &g, sn_conv_dir dir, size_t budget)
 // workspace it is what STAGED runs where it is faster than STAGED's other kernels, and what IM2COL_GEMM runs instead of
 // unfolding.
 
+// Small bf16 3x3 / stride-1 layers: one launch, which DIRECT and STAGED take instead of their other kernels (the product is
+// weighed against it, see other_us).
+bool small_bf16_runs(const ConvGeom &g, sn_conv_dir dir)
+{
+    return dir != SN_CONV_BWD_FILTER && !(dir == SN_CONV_FWD && smallc_supported(g)) && small_bf16_us(g, dir == SN_CONV_BWD_DATA) < SMALL_BF16_US;
+}
+
 // Estimated us of what runs instead (0: always keep that).  Kernels that read their operands where they are -- few input
 // channels, 1x1 layers, 1x1 / stride-2 layers written or gathered directly -- were faster on every shape measured.
 double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
@@ -341,6 +348,7 @@ double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
             return std::min(g.C, g.K) > 256 ? (g.P * g.Q <= 64 ? 8 + flops / 2e8 : 1e9) : 7 + (double)g.N * g.P * g.Q * (g.C + g.K) * 2 / 1.5e6;
         return rows_wgrad_us(g);
     }
+    if (small_bf16_runs(g, dir)) return small_bf16_us(g, dir == SN_CONV_BWD_DATA);
     if (dir == SN_CONV_BWD_DATA && scatter_bwd_data(g)) return 0;
     if (dir == SN_CONV_FWD && g.R == 1 && g.S == 1 && gather_fwd(g)) return 0;
     if (g.sh > 1 || g.sw > 1) return general;
@@ -548,7 +556,7 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
     for (sn_conv_algo a : kRanking) {
         size_t mn = 0, pf = 0;
         if (own_query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
-        if (a == SN_ALGO_STAGED && pf == 0) continue;   // nothing to stage: the same kernel runs as DIRECT
+        if (a == SN_ALGO_STAGED && (pf == 0 || small_bf16_runs(g, dir))) continue;   // nothing to stage: the same kernel runs as DIRECT
         if (a == SN_ALGO_WINOGRAD && !winograd_guessed(g, dir, budget)) continue;
         // The phase planes in passes: strided forward gains little over the zero-workspace kernel, so only
         // with the whole batch (below that STAGED forward is the gathering kernel, which needs the re-laid-out
@@ -614,6 +622,7 @@ size_t out_elem(const ConvGeom &g) { return g.out_bf16 ? 2 : 4; }
 hipError_t direct_fwd(const void *x, const void *w, void *y, const ConvGeom &g, hipStream_t st)
 {
     if (smallc_supported(g)) return launch_smallc_fwd(x, w, y, g, st, nullptr);
+    if (small_bf16_runs(g, SN_CONV_FWD)) return launch_small_bf16(x, w, y, g, false, st);
     if (tile_conv_supported(g, false)) return launch_tile_conv(x, w, y, g, false, nullptr, st);
     if (g.R == 1 && g.S == 1 && gather_fwd(g)) return launch_gather_conv_fwd(x, w, y, g, nullptr, st);
     if (small3x3_supported(g, false)) return launch_small3x3(x, w, y, g, false, st);
@@ -623,6 +632,7 @@ hipError_t direct_fwd(const void *x, const void *w, void *y, const ConvGeom &g, 
 hipError_t direct_bwd_data(const void *dy, const void *w, void *dx, const ConvGeom &g, hipStream_t st)
 {
     if (scatter_bwd_data(g)) return launch_pointwise(dy, w, dx, g, true, st);
+    if (small_bf16_runs(g, SN_CONV_BWD_DATA)) return launch_small_bf16(dy, w, dx, g, true, st);
     if (tile_conv_supported(g, true)) return launch_tile_conv(dy, w, dx, g, true, nullptr, st);
     if (small3x3_supported(g, true)) return launch_small3x3(dy, w, dx, g, true, st);
     return launch_generic_bwd_data(dy, w, dx, g, st);
@@ -635,6 +645,7 @@ sn_status run_fwd(const void *x, const void *w, void *y, const ConvGeom &g, sn_c
     if (algo == SN_ALGO_WINOGRAD) return launch_status(launch_winograd(x, w, y, g, false, ws, ws_bytes, st));
     ChlastPlan cl;
     if (chlast_runs(g, SN_CONV_FWD, algo, ws_bytes, &cl)) return launch_status(launch_chlast(x, w, y, g, SN_CONV_FWD, ws, &cl, st));
+    if (algo == SN_ALGO_STAGED && small_bf16_runs(g, SN_CONV_FWD)) return launch_status(launch_small_bf16(x, w, y, g, false, st));
     PhasePlan pp;
     if (algo == SN_ALGO_STAGED && gather_fwd(g)) {
         const bool planes = phase_fwd_when_it_fits(g) && phase_plan(g, SN_CONV_FWD, &pp);
@@ -681,6 +692,7 @@ sn_status run_bwd_data(const void *dy, const void *w, void *dx, const ConvGeom &
     if (algo == SN_ALGO_STAGED && scatter_bwd_data(g)) return launch_status(launch_pointwise(dy, w, dx, g, true, st));
     ChlastPlan cl;
     if (chlast_runs(g, SN_CONV_BWD_DATA, algo, ws_bytes, &cl)) return launch_status(launch_chlast(dy, w, dx, g, SN_CONV_BWD_DATA, ws, &cl, st));
+    if (algo == SN_ALGO_STAGED && small_bf16_runs(g, SN_CONV_BWD_DATA)) return launch_status(launch_small_bf16(dy, w, dx, g, true, st));
     PhasePlan pp;
     const bool phases = algo == SN_ALGO_STAGED && phase_plan(g, SN_CONV_BWD_DATA, &pp);
     if (phases && ws_bytes < phase_bytes(pp, SN_CONV_BWD_DATA, pp.chunkable ? 1 : g.N)) {   // less than the phase planes need: many passes
@@ -996,7 +1008,7 @@ sn_status sn_conv2d_fwd_bn_stats(const void *x, const void *w, void *y, const sn
     // The kernel is the one run_fwd takes: y is sn_conv2d_fwd's, bit for bit.  (The channels-last product leaves the
     // statistics to a pass over y.)
     ChlastPlan cl;
-    if (tile_conv_supported(g, false) && (algo == SN_ALGO_DIRECT || (staged && !chlast_runs(g, SN_CONV_FWD, algo, workspace_bytes, &cl)))) {
+    if (tile_conv_supported(g, false) && !small_bf16_runs(g, SN_CONV_FWD) && (algo == SN_ALGO_DIRECT || (staged && !chlast_runs(g, SN_CONV_FWD, algo, workspace_bytes, &cl)))) {
         // the tile kernels take the statistics from their accumulators: y is not read again
         const int tiles = tile_conv_stats_tiles(g, staged, true);
         if (tiles <= 0) return SN_ERR_UNSUPPORTED;

@@ -202,6 +202,13 @@ constexpr long long SMALL3X3_MACS = 1LL << 24;
 bool small3x3_supported(const ConvGeom &g, bool bwd_data);
 hipError_t launch_small3x3(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, hipStream_t st);
 
+// bf16 3x3 / stride-1 forward and backward-data of small layers in one launch (conv_small_bf16.hip), no workspace.  Of 400 layers of
+// 1 to 8 images all with an estimate below SMALL_BF16_US were faster on it than on the other kernels that take no workspace (up to
+// 12 times) but for one, 1.06 times slower; above it the tiles' larger operands win, one layer after the other.
+constexpr double SMALL_BF16_US = 16;
+double small_bf16_us(const ConvGeom &g, bool bwd_data);   // estimate; very large: not supported
+hipError_t launch_small_bf16(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, hipStream_t st);
+
 // Any convolution as a product over a channels-last copy of its operands in the workspace (conv_chlast.h).  chlast_plan:
 // whether it runs with this budget; the bytes it uses of it, its passes over parts of the batch and its estimated time.
 struct ChlastPlan {
