@@ -321,8 +321,10 @@ bool winograd_guessed(const ConvGeom &g, sn_conv_dir dir, size_t budget)
 // workspace it is what STAGED runs where it is faster than STAGED's other kernels, and what IM2COL_GEMM runs instead of
 // unfolding.
 
-// Small bf16 3x3 / stride-1 layers: one launch, which DIRECT and STAGED take instead of their other kernels (the product is
-// weighed against it, see other_us).
+// Small 3x3 / stride-1 layers: one launch, which DIRECT and STAGED take instead of their other kernels (the product is weighed against
+// it, see other_us).  Image layers keep the kernels of their own.
+bool small_wgrad_runs(const ConvGeom &g) { return g.C > 4 && small_wgrad_us(g) < SMALL_WGRAD_US; }
+
 bool small_bf16_runs(const ConvGeom &g, sn_conv_dir dir)
 {
     return dir != SN_CONV_BWD_FILTER && !(dir == SN_CONV_FWD && smallc_supported(g)) && small_bf16_us(g, dir == SN_CONV_BWD_DATA) < SMALL_BF16_US;
@@ -334,6 +336,7 @@ double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
 {
     // the general kernels at their best (they were never faster than the product given enough workspace)
     const double flops = 2.0 * g.N * g.K * g.C * g.R * g.S * g.P * g.Q, general = 10 + flops / (g.in_bf16 ? 1.5e8 : 7e7);
+    if (dir == SN_CONV_BWD_FILTER && small_wgrad_runs(g)) return small_wgrad_us(g);
     // fp32: or WINOGRAD (8 x 256 x 56x56, 256 channels, 512 MiB: 230 us, the product 275; 16 x 144 x 32x17 -> 312, 64 MiB: 108 and 80)
     if (!g.in_bf16) return winograd_guessed(g, dir, ws_bytes) ? std::min(general, winograd_us(g, dir == SN_CONV_BWD_DATA, ws_bytes)) : general;
     if (smallc_supported(g) && dir != SN_CONV_BWD_DATA) return 0;
@@ -556,7 +559,7 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
     for (sn_conv_algo a : kRanking) {
         size_t mn = 0, pf = 0;
         if (own_query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
-        if (a == SN_ALGO_STAGED && (pf == 0 || small_bf16_runs(g, dir))) continue;   // nothing to stage: the same kernel runs as DIRECT
+        if (a == SN_ALGO_STAGED && (pf == 0 || small_bf16_runs(g, dir) || (dir == SN_CONV_BWD_FILTER && small_wgrad_runs(g)))) continue;   // nothing to stage: the same kernel runs as DIRECT
         if (a == SN_ALGO_WINOGRAD && !winograd_guessed(g, dir, budget)) continue;
         // The phase planes in passes: strided forward gains little over the zero-workspace kernel, so only
         // with the whole batch (below that STAGED forward is the gathering kernel, which needs the re-laid-out
@@ -741,6 +744,7 @@ sn_status run_bwd_filter(const void *x, const void *dy, void *dw, const ConvGeom
     if (smallc_supported(g) && (algo == SN_ALGO_DIRECT || algo == SN_ALGO_STAGED))
         return launch_status(launch_smallc_wgrad(x, dy, dwf, g, algo == SN_ALGO_STAGED ? static_cast<float *>(ws) : nullptr, st));
     if (algo == SN_ALGO_DIRECT) {
+        if (small_wgrad_runs(g)) return launch_status(launch_small_wgrad(x, dy, dwf, g, st));
         if (image_runs(g, false)) return launch_status(launch_image_wgrad(x, dy, dwf, g, nullptr, st));
         if (tile) return launch_status(launch_tile_wgrad(x, dy, dwf, g, nullptr, st));
         if (gather_wgrad_supported(g)) return launch_status(launch_gather_wgrad(x, dy, dwf, g, nullptr, st));
@@ -748,6 +752,7 @@ sn_status run_bwd_filter(const void *x, const void *dy, void *dw, const ConvGeom
     }
     ChlastPlan cl;
     if (chlast_runs(g, SN_CONV_BWD_FILTER, algo, ws_bytes, &cl)) return launch_status(launch_chlast(x, dy, dw, g, SN_CONV_BWD_FILTER, ws, &cl, st));
+    if (algo == SN_ALGO_STAGED && small_wgrad_runs(g)) return launch_status(launch_small_wgrad(x, dy, dwf, g, st));
     if (algo == SN_ALGO_STAGED && image_runs(g, true))
         return launch_status(launch_image_wgrad(x, dy, dwf, g, static_cast<float *>(ws), st, staged_bwd_filter_cap(g, ws_bytes)));
     PhasePlan pp;
