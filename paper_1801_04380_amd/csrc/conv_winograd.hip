@@ -126,7 +126,10 @@ wino_gemm_kernel(const float *__restrict__ U, const float *__restrict__ V, float
     __shared__ __attribute__((aligned(16))) float Bs[2][BK][BN];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, g = lane >> 5;
     const int wm = wave >> 1, wn = wave & 1;
-    const int t0 = blockIdx.x * BN, m0 = blockIdx.y * BM, xi = blockIdx.z;
+    const int mtiles = Mp / BM, ttiles = Tp / BN;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, mt = slot % mtiles, job = slot / mtiles * 8 + xcd;
+    if (job >= 16 * ttiles) return;
+    const int xi = job / ttiles, t0 = (job - xi * ttiles) * BN, m0 = mt * BM;
     const float *Ux = U + (size_t)xi * REDp * Mp + m0;
     const float *Vx = V + (size_t)xi * REDp * Tp + t0;
     // a thread copies two float4 of each tile: rows tid / 32 and tid / 32 + 8, columns 4 * (tid % 32)
@@ -334,7 +337,7 @@ hipError_t launch_winograd(const void *in, const void *w, void *out, const ConvG
         hipLaunchKernelGGL(wino_input_kernel, dim3(Tp / 256 + (Tp % 256 != 0), p.REDp), dim3(256), 0, st,
                            static_cast<const float *>(in), V, p, n0, T, Tp);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(wino_gemm_kernel, dim3(Tp / BN, p.Mp / BM, 16), dim3(256), 0, st, U, V, Mo, p.REDp, p.Mp, Tp);
+        hipLaunchKernelGGL(wino_gemm_kernel, dim3(8 * ((16 * (Tp / BN) + 7) / 8) * (p.Mp / BM)), dim3(256), 0, st, U, V, Mo, p.REDp, p.Mp, Tp);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(wino_output_kernel<float>, dim3((T + 255) / 256, p.M), dim3(256), 0, st, Mo,
                            static_cast<float *>(out), p, n0, T, Tp);
