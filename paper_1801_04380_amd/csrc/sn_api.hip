@@ -321,8 +321,8 @@ bool winograd_guessed(const ConvGeom &g, sn_conv_dir dir, size_t budget)
 // workspace it is what STAGED runs where it is faster than STAGED's other kernels, and what IM2COL_GEMM runs instead of
 // unfolding.
 
-// Small 3x3 / stride-1 layers: one launch, which DIRECT and STAGED take instead of their other kernels (the product is weighed against
-// it, see other_us).  Image layers keep the kernels of their own.
+// Small 3x3 / stride-1 layers in one launch without workspace, which DIRECT takes instead of its other kernels and AUTO where the
+// estimate is below the product's.  Image layers keep the kernels of their own.
 bool small_wgrad_runs(const ConvGeom &g) { return g.C > 4 && small_wgrad_us(g) < SMALL_WGRAD_US; }
 
 bool small_bf16_runs(const ConvGeom &g, sn_conv_dir dir)
@@ -330,15 +330,24 @@ bool small_bf16_runs(const ConvGeom &g, sn_conv_dir dir)
     return dir != SN_CONV_BWD_FILTER && !(dir == SN_CONV_FWD && smallc_supported(g)) && small_bf16_us(g, dir == SN_CONV_BWD_DATA) < SMALL_BF16_US;
 }
 
+// Its estimate; very large: it does not run.
+double small_us(const ConvGeom &g, sn_conv_dir dir)
+{
+    if (dir == SN_CONV_BWD_FILTER) return small_wgrad_runs(g) ? small_wgrad_us(g) : 1e9;
+    return small_bf16_runs(g, dir) ? small_bf16_us(g, dir == SN_CONV_BWD_DATA) : 1e9;
+}
+
 // Estimated us of what runs instead (0: always keep that).  Kernels that read their operands where they are -- few input
 // channels, 1x1 layers, 1x1 / stride-2 layers written or gathered directly -- were faster on every shape measured.
 double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
 {
     // the general kernels at their best (they were never faster than the product given enough workspace)
-    const double flops = 2.0 * g.N * g.K * g.C * g.R * g.S * g.P * g.Q, general = 10 + flops / (g.in_bf16 ? 1.5e8 : 7e7);
-    if (dir == SN_CONV_BWD_FILTER && small_wgrad_runs(g)) return small_wgrad_us(g);
-    // fp32: or WINOGRAD (8 x 256 x 56x56, 256 channels, 512 MiB: 230 us, the product 275; 16 x 144 x 32x17 -> 312, 64 MiB: 108 and 80)
-    if (!g.in_bf16) return winograd_guessed(g, dir, ws_bytes) ? std::min(general, winograd_us(g, dir == SN_CONV_BWD_DATA, ws_bytes)) : general;
+    const double flops = 2.0 * g.N * g.K * g.C * g.R * g.S * g.P * g.Q;
+    double general = 10 + flops / (g.in_bf16 ? 1.5e8 : 7e7);
+    if (!g.in_bf16) {
+        // or WINOGRAD (8 x 256 x 56x56, 256 channels, 512 MiB: 230 us, the product 275; 16 x 144 x 32x17 -> 312, 64 MiB: 108 and 80)
+        return winograd_guessed(g, dir, ws_bytes) ? std::min(general, winograd_us(g, dir == SN_CONV_BWD_DATA, ws_bytes)) : general;
+    }
     if (smallc_supported(g) && dir != SN_CONV_BWD_DATA) return 0;
     if (dir == SN_CONV_BWD_FILTER) {
         // (11x11 / 4 on 227x227 images: 69 + 7 us, the product with 300 MiB 140; 6 x 3 x 38x59, 96 channels 5x5: 22 and 16.  The product's three
@@ -351,7 +360,6 @@ double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
             return std::min(g.C, g.K) > 256 ? (g.P * g.Q <= 64 ? 8 + flops / 2e8 : 1e9) : 7 + (double)g.N * g.P * g.Q * (g.C + g.K) * 2 / 1.5e6;
         return rows_wgrad_us(g);
     }
-    if (small_bf16_runs(g, dir)) return small_bf16_us(g, dir == SN_CONV_BWD_DATA);
     if (dir == SN_CONV_BWD_DATA && scatter_bwd_data(g)) return 0;
     if (dir == SN_CONV_FWD && g.R == 1 && g.S == 1 && gather_fwd(g)) return 0;
     if (g.sh > 1 || g.sw > 1) return general;
@@ -372,6 +380,15 @@ bool chlast_faster(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t
     // less than half of the row-stationary kernel's partial sums: atomics (64 x 256 x 20x20 -> 128: 42 us, with them 15)
     if (dir == SN_CONV_BWD_FILTER && g.R == 3 && !image_runs(g, true) && rows_wgrad_supported(g) && rows_wgrad_partial_bytes(g) / 2 > ws_bytes) other += 30;
     if (other <= CHLAST_LEAST_US || !chlast_plan(g, dir, ws_bytes, plan)) return false;
+    // STAGED's forward and backward-data run the small layers' kernel, too, in place of its others and of the product where that is at
+    // its worst: reduction slices (a third launch) or channels that fill no whole runs (2 x 256 x 14x14, 256 channels: 17 us, the kernel 9; 2 x 24 x
+    // 14x14 -> 40: 12 and 3.5).  On the rest (4 x 64 x 14x14 -> 128: 13 and 5) the name keeps the product, so that measurements have both to
+    // choose from: AUTO without any takes the kernel, as DIRECT.
+    if (algo == SN_ALGO_STAGED && dir != SN_CONV_BWD_FILTER && small_us(g, dir) < plan->us) {
+        int m, n, threads, slices;
+        chlast_config(*plan, dir, &m, &n, &threads, &slices);
+        if (slices > 1 || (dir == SN_CONV_FWD ? g.C : g.K) % 64 != 0) return false;
+    }
     const bool alone = dir == SN_CONV_BWD_FILTER ? !tile_wgrad_supported(g) : dir == SN_CONV_FWD && !tile_conv_supported(g, false);
     return plan->passes <= (alone ? 8 : 2) && plan->us < other;
 }
@@ -537,7 +554,7 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
     }
     // The channels-last product where it is the fastest, under the name that runs it with this budget.
     ChlastPlan cl;
-    const bool product = chlast_faster(g, dir, SN_ALGO_STAGED, budget, &cl);
+    const bool product = chlast_faster(g, dir, SN_ALGO_STAGED, budget, &cl) && cl.us <= small_us(g, dir);
     for (sn_conv_algo a : {SN_ALGO_STAGED, SN_ALGO_IM2COL_GEMM}) {
         size_t mn = 0, pf = 0;
         if (!product || query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
@@ -559,7 +576,7 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
     for (sn_conv_algo a : kRanking) {
         size_t mn = 0, pf = 0;
         if (own_query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
-        if (a == SN_ALGO_STAGED && (pf == 0 || small_bf16_runs(g, dir) || (dir == SN_CONV_BWD_FILTER && small_wgrad_runs(g)))) continue;   // nothing to stage: the same kernel runs as DIRECT
+        if (a == SN_ALGO_STAGED && (pf == 0 || small_us(g, dir) < 1e9)) continue;   // nothing to stage: the same kernel runs as DIRECT
         if (a == SN_ALGO_WINOGRAD && !winograd_guessed(g, dir, budget)) continue;
         // The phase planes in passes: strided forward gains little over the zero-workspace kernel, so only
         // with the whole batch (below that STAGED forward is the gathering kernel, which needs the re-laid-out
@@ -752,7 +769,6 @@ sn_status run_bwd_filter(const void *x, const void *dy, void *dw, const ConvGeom
     }
     ChlastPlan cl;
     if (chlast_runs(g, SN_CONV_BWD_FILTER, algo, ws_bytes, &cl)) return launch_status(launch_chlast(x, dy, dw, g, SN_CONV_BWD_FILTER, ws, &cl, st));
-    if (algo == SN_ALGO_STAGED && small_wgrad_runs(g)) return launch_status(launch_small_wgrad(x, dy, dwf, g, st));
     if (algo == SN_ALGO_STAGED && image_runs(g, true))
         return launch_status(launch_image_wgrad(x, dy, dwf, g, static_cast<float *>(ws), st, staged_bwd_filter_cap(g, ws_bytes)));
     PhasePlan pp;
