@@ -654,10 +654,36 @@ cl_wgrad_kernel(const T *__restrict__ ds, const T *__restrict__ xs, float *__res
             multiply(cur);
             __builtin_amdgcn_sched_barrier(0);
         };
+        // fp32: a chain of 256 pixels at a time, the chains' sums added up (one long chain's roundings made the result up to 1.7 times
+        // further from the exact one than the general kernel's slices did; 16 additions in 16 stages cost nothing measurable)
+        f32x16 whole[FM][FN];
+        constexpr int CHAIN = 8;
+        auto add_up = [&](bool last) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int f = 0; f < FN; ++f)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) {
+                        whole[i][f][v] += acc[i][f][v];
+                        acc[i][f][v] = last ? whole[i][f][v] : 0.f;
+                    }
+        };
+        if constexpr (SZ == 4) {
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int f = 0; f < FN; ++f)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) whole[i][f][v] = 0.f;
+        }
         for (int i = 0; i < n; i += 2) {
             trip(i, fr[0], fr[1]);
             if (i + 1 < n) trip(i + 1, fr[1], fr[0]);
+            if constexpr (SZ == 4)
+                if (i % CHAIN == CHAIN - 2) add_up(false);
         }
+        if constexpr (SZ == 4) add_up(true);
     };
     accumulate(std::false_type());
     if (p.holes && any_not_finite(acc, lds)) accumulate(std::true_type());

@@ -822,6 +822,28 @@ double generic_bwd_filter_us(const ConvGeom &g, bool partial)
     return 8.5 + (slices > 1 ? 3.1 : 0) + steps * (g.K > 64 ? 1.62 : 1.15) * std::max(1.0, rounds / 1.5) + 0.97 * mb;
 }
 
+// fp32, in us: base + the reduction steps of a workgroup x the rounds that its tiles take of the chip (+ partial sums), per direction and
+// tile height.  Fitted to 450 timings (2 to 128 images, 32 to 2048 channels, 1x1 and 3x3, planes of 7x7 to 112x112), which it
+// reproduces to 2 to 9 % (rms; backward-filter of 3x3 over more than 64 channels 15 %).  Strided backward-data has a kernel of its own: 0.
+double generic_f32_us(const ConvGeom &g, int dir)
+{
+    const int bk = TileCfg<float>::BK, one = g.R * g.S == 1;
+    if (dir == DIR_BWD_FILTER) {
+        const long long Kred = (long long)g.N * g.P * g.Q, splits = generic_bwd_filter_splits(g);
+        const long long steps = ((Kred + splits - 1) / splits + bk - 1) / bk, slices = (Kred + steps * bk - 1) / (steps * bk);
+        const double rounds = bwd_filter_tiles(g) * slices / 256.0, mb = slices > 1 ? (double)slices * g.K * g.C * g.R * g.S * 4e-6 : 0;
+        if (g.K <= 64) return one ? 14.5 + 0.47 * steps * std::max(1.0, rounds / 1.75) + 1.4 * mb : 6 + 1.39 * steps * std::max(1.0, rounds / 1.8) + mb;
+        return one ? 16 + 1.2 * steps * std::max(1.0, rounds / 0.8) + 0.8 * mb : 10 + 2.1 * steps * std::max(1.0, rounds / 0.7);
+    }
+    if (dir == DIR_BWD_DATA && (g.sh > 1 || g.sw > 1)) return 0;
+    const bool bwd = dir == DIR_BWD_DATA;
+    const long long M = bwd ? g.C : g.K, cols = (long long)g.N * (bwd ? (long long)g.H * g.W : (long long)g.P * g.Q);
+    const double steps = (double)((bwd ? g.K : g.C) * (long long)g.R * g.S + bk - 1) / bk;
+    const double rounds = (double)((M <= 64 ? 1 : (M + 127) / 128) * ((cols + BN - 1) / BN)) / 256;
+    if (M <= 64) return 5 + (bwd ? 2.83 : 1.75) * steps * std::max(1.0, rounds / (bwd ? 1.5 : 1.3));
+    return bwd ? 6 + 3.65 * steps * std::max(1.0, rounds / 1.1) : 8 + 2.35 * steps * std::max(1.0, rounds / 1.05);
+}
+
 hipError_t launch_generic_bwd_filter(const void *x, const void *dy, float *dw, const ConvGeom &g, int splits,
                                      float *partial, bool accumulate, hipStream_t st)
 {

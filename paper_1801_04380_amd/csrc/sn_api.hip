@@ -345,6 +345,8 @@ double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
     const double flops = 2.0 * g.N * g.K * g.C * g.R * g.S * g.P * g.Q;
     double general = 10 + flops / (g.in_bf16 ? 1.5e8 : 7e7);
     if (!g.in_bf16) {
+        // (8 x 256 x 28x28 -> 512, 1x1: backward-data 123 us, the product 34; 8 x 100 x 30x30 -> 72, 3x3: forward 143 and 30)
+        if (dir == SN_CONV_BWD_FILTER || !small3x3_supported(g, dir == SN_CONV_BWD_DATA)) general = std::max(general, generic_f32_us(g, dir));
         // or WINOGRAD (8 x 256 x 56x56, 256 channels, 512 MiB: 230 us, the product 275; 16 x 144 x 32x17 -> 312, 64 MiB: 108 and 80)
         return winograd_guessed(g, dir, ws_bytes) ? std::min(general, winograd_us(g, dir == SN_CONV_BWD_DATA, ws_bytes)) : general;
     }

@@ -74,6 +74,7 @@ hipError_t launch_generic_bwd_filter(const void *x, const void *dy, float *dw, c
                                      int splits, float *partial, bool accumulate, hipStream_t st);
 int generic_bwd_filter_splits(const ConvGeom &g);
 double generic_bwd_filter_us(const ConvGeom &g, bool partial);   // estimate for few input channels, bf16
+double generic_f32_us(const ConvGeom &g, int dir);               // estimate, fp32; 0: none
 
 // Stride-1 bf16 fast path (forward, or backward-data when bwd_data is set).
 // `packed` = workspace for the re-laid-out filter (tile_conv_packed_bytes), or
