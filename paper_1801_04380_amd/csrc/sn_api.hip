@@ -337,6 +337,13 @@ double small_us(const ConvGeom &g, sn_conv_dir dir)
     return small_bf16_runs(g, dir) ? small_bf16_us(g, dir == SN_CONV_BWD_DATA) : 1e9;
 }
 
+// The kernels without workspace that DIRECT takes in place of its others: of small layers, and the image layer's forward.
+double direct_us(const ConvGeom &g, sn_conv_dir dir)
+{
+    const double us = small_us(g, dir);
+    return dir == SN_CONV_FWD ? std::min(us, image_fwd_us(g)) : us;
+}
+
 // Estimated us of what runs instead (0: always keep that).  Kernels that read their operands where they are -- few input
 // channels, 1x1 layers, 1x1 / stride-2 layers written or gathered directly -- were faster on every shape measured.
 double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
@@ -556,7 +563,7 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
     }
     // The channels-last product where it is the fastest, under the name that runs it with this budget.
     ChlastPlan cl;
-    const bool product = chlast_faster(g, dir, SN_ALGO_STAGED, budget, &cl) && cl.us <= small_us(g, dir);
+    const bool product = chlast_faster(g, dir, SN_ALGO_STAGED, budget, &cl) && cl.us <= direct_us(g, dir);
     for (sn_conv_algo a : {SN_ALGO_STAGED, SN_ALGO_IM2COL_GEMM}) {
         size_t mn = 0, pf = 0;
         if (!product || query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
@@ -578,7 +585,7 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
     for (sn_conv_algo a : kRanking) {
         size_t mn = 0, pf = 0;
         if (own_query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
-        if (a == SN_ALGO_STAGED && (pf == 0 || small_us(g, dir) < 1e9)) continue;   // nothing to stage: the same kernel runs as DIRECT
+        if (a == SN_ALGO_STAGED && (pf == 0 || direct_us(g, dir) < 1e9)) continue;   // nothing to stage: the same kernel runs as DIRECT
         if (a == SN_ALGO_WINOGRAD && !winograd_guessed(g, dir, budget)) continue;
         // The phase planes in passes: strided forward gains little over the zero-workspace kernel, so only
         // with the whole batch (below that STAGED forward is the gathering kernel, which needs the re-laid-out
@@ -645,6 +652,7 @@ hipError_t direct_fwd(const void *x, const void *w, void *y, const ConvGeom &g, 
 {
     if (smallc_supported(g)) return launch_smallc_fwd(x, w, y, g, st, nullptr);
     if (small_bf16_runs(g, SN_CONV_FWD)) return launch_small_bf16(x, w, y, g, false, st);
+    if (image_fwd_us(g) < 1e9) return launch_image_fwd(x, w, y, g, st);
     if (tile_conv_supported(g, false)) return launch_tile_conv(x, w, y, g, false, nullptr, st);
     if (g.R == 1 && g.S == 1 && gather_fwd(g)) return launch_gather_conv_fwd(x, w, y, g, nullptr, st);
     if (small3x3_supported(g, false)) return launch_small3x3(x, w, y, g, false, st);

@@ -126,6 +126,10 @@ int smallc_wgrad_slices(const ConvGeom &g);
 hipError_t launch_smallc_wgrad(const void *x, const void *dy, float *dw, const ConvGeom &g, float *partial,
                                hipStream_t st);
 
+// Forward of the image layer, up to 96 output channels, an even column stride (bf16; conv_image_fwd.hip), no workspace.
+double image_fwd_us(const ConvGeom &g);   // estimate; very large: not supported
+hipError_t launch_image_fwd(const void *x, const void *w, void *y, const ConvGeom &g, hipStream_t st);
+
 // Backward-filter of the image layer: up to four input channels under a filter of 33 to 384 products of up to 12
 // columns (bf16, any stride and padding; conv_image.hip); contract of launch_rows_wgrad, any number of slices up to image_wgrad_slices(g).
 bool image_wgrad_supported(const ConvGeom &g);
