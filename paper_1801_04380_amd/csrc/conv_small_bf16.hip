@@ -14,7 +14,7 @@
 //     waves, the loads in flight spill: 400 layers 1.05 to 1.5 times slower.)
 // Neighbouring workgroups are neighbouring channel tiles of one patch: with eight of them each XCD keeps one slice of the filter.
 // us a call, the kernels that took these layers before (with 8 MiB of workspace; without) -> this one: 2 x 256 x 14x14, 256 channels,
-// forward 17.2 (34.6) -> 9.1, backward-data 17.0 (45) -> 10.1; 1 x 512 x 7x7, 512 channels 24 (65) -> 10.5 and 25 (87) -> 11.2;
+// forward 17.2 (34.6) -> 7.3, backward-data 17.0 (45) -> 10.1; 1 x 512 x 7x7, 512 channels 24 (65) -> 10.5 and 25 (87) -> 11.2;
 // 8 x 16 x 16x16, 16 channels 13 (7.7) -> 3.4 and 13 (7.7) -> 3.6.
 #include <algorithm>
 
@@ -35,7 +35,8 @@ struct SmallConv {
     int out_bf16;
 };
 
-template <bool BWD, int MT>
+// TOGETHER: how the filter is loaded, see below.
+template <bool BWD, int MT, bool TOGETHER>
 __global__ void __launch_bounds__(64 * MAXWAVES)
 small3x3_bf16_kernel(const bf16_t *__restrict__ in, const bf16_t *__restrict__ w, void *__restrict__ out, const SmallConv p)
 {
@@ -58,18 +59,36 @@ small3x3_bf16_kernel(const bf16_t *__restrict__ in, const bf16_t *__restrict__ w
         const bool ok = lane < SLOTS && (unsigned)h < (unsigned)p.IH && (unsigned)v < (unsigned)p.IW;
         xoff = ok ? (uint32_t)(h * p.IW + v) * 2 : FAR;
     }
-    constexpr int WCD = BWD ? 40 : 36;
+    // Forward, the lane loads its run, 64 cache lines a load; or (TOGETHER) its neighbours do: of the tile's rows, a step's channels are PPR 16-byte
+    // pieces each, neighbouring lanes load neighbouring pieces, 12 lines a load, and the pieces change lanes through LDS.
+    constexpr int WCD = BWD ? 40 : 36, PPR = 9 * NOCT;
+    uint32_t woff[TOGETHER ? 9 : 1];
+    if constexpr (TOGETHER) {
+#pragma unroll
+        for (int j = 0; j < 9; ++j) {
+            const int r = (j * 64 + lane) / PPR, pc = (j * 64 + lane) - r * PPR;
+            woff[j] = mt * MT + r < p.M ? (uint32_t)(mt * MT + r) * p.Red * 18 + pc * 16 : FAR;
+        }
+    }
     struct Step { uint32_t a[WCD]; bf16_t x[RED]; };
     auto load = [&](int c0, Step &s) {
-        const int red0 = c0 + 8 * g;
-        if constexpr (!BWD) {
-            const uint32_t o = m < p.M && red0 < p.Red ? ((uint32_t)m * p.Red + red0) * 18 : FAR;
+        if constexpr (TOGETHER) {
+#pragma unroll
+            for (int j = 0; j < 9; ++j) {
+                // (a last step of fewer channels: the pieces past them are the next row's)
+                const bool in = c0 + RED <= p.Red || ((j * 64 + lane) % PPR) * 16 < (p.Red - c0) * 18;
+                const u32x4 d = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, in ? woff[j] : FAR, (uint32_t)c0 * 18, 0));
+                s.a[4 * j] = d.x; s.a[4 * j + 1] = d.y; s.a[4 * j + 2] = d.z; s.a[4 * j + 3] = d.w;
+            }
+        } else if constexpr (!BWD) {
+            const uint32_t o = m < p.M && c0 + 8 * g < p.Red ? ((uint32_t)m * p.Red + c0 + 8 * g) * 18 : FAR;
 #pragma unroll
             for (int j = 0; j < 9; ++j) {
                 const u32x4 d = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(wr, o + 16 * j, 0, 0));
                 s.a[4 * j] = d.x; s.a[4 * j + 1] = d.y; s.a[4 * j + 2] = d.z; s.a[4 * j + 3] = d.w;
             }
         } else {
+            const int red0 = c0 + 8 * g;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const bool ok = m < p.M && red0 + i < p.Red;
@@ -91,9 +110,15 @@ small3x3_bf16_kernel(const bf16_t *__restrict__ in, const bf16_t *__restrict__ w
     Acc acc;
 #pragma unroll
     for (int v = 0; v < NACC; ++v) acc[v] = 0.f;
-    char *patch = lds + wave * NOCT * OCTET;
+    constexpr int FILTER = TOGETHER ? 9 * 1024 : 0;   // bytes of a wave's pieces of the filter
+    char *patch = lds + wave * (NOCT * OCTET + FILTER);
     const char *mine = patch + g * OCTET + (row / TW * LW + row % TW) * 16;   // the lane's pixel under tap (0, 0)
-    auto multiply = [&](const Step &s) {
+    auto multiply = [&](Step &s) {
+        if constexpr (TOGETHER) {
+#pragma unroll
+            for (int j = 0; j < 9; ++j)
+                *reinterpret_cast<u32x4 *>(patch + NOCT * OCTET + (j * 64 + lane) * 16) = u32x4{s.a[4 * j], s.a[4 * j + 1], s.a[4 * j + 2], s.a[4 * j + 3]};
+        }
 #pragma unroll
         for (int h = 0; h < NOCT; ++h) {
             u32x4 d;
@@ -102,6 +127,13 @@ small3x3_bf16_kernel(const bf16_t *__restrict__ in, const bf16_t *__restrict__ w
             *reinterpret_cast<u32x4 *>(patch + h * OCTET + lane * 16) = d;
         }
         __builtin_amdgcn_wave_barrier();   // (the wave's own LDS, in order: no more than the compiler has to know)
+        if constexpr (TOGETHER) {
+#pragma unroll
+            for (int j = 0; j < 9; ++j) {
+                const u32x4 d = *reinterpret_cast<const u32x4 *>(patch + NOCT * OCTET + (row * PPR + g * 9 + j) * 16);
+                s.a[4 * j] = d.x; s.a[4 * j + 1] = d.y; s.a[4 * j + 2] = d.z; s.a[4 * j + 3] = d.w;
+            }
+        }
 #pragma unroll
         for (int tap = 0; tap < 9; ++tap) {
             u32x4 a;
@@ -206,17 +238,33 @@ double tile_us(const ConvGeom &g, bool bwd, int MT)
            c.filter * 18e-6 * p.M * p.Red;
 }
 
+// Long reductions, whose loads add up, load the filter together; in short ones the way through LDS is what counts (350 layers: up to eight steps
+// 0.91 to 1.03 of the speed, from nine on 1.0 to 1.22 times; 2 x 256 x 14x14, 256 channels 8.8 -> 7.3 us).
+constexpr int TOGETHER_STEPS = 9;
+
+template <bool BWD, int MT, bool TOGETHER>
+hipError_t launch_as(const void *in, const void *w, void *out, const ConvGeom &g, const SmallConv &p, hipStream_t st)
+{
+    const long long wgs = workgroups(g, p);
+    const int waves = waves_of(wgs, steps_of(p, MT));
+    // LDS, a wave: its patch (MT = 32: two octets of channels, 16: four) and its pieces of the filter, then its sums (4 KB, 1 KB)
+    constexpr int each = std::max(4096, 65536 / MT + (TOGETHER ? 9216 : 0));
+    typedef Kernel<small3x3_bf16_kernel<BWD, MT, TOGETHER>> K;
+    const hipError_t e = K::enable_lds(MAXWAVES * each);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(K::call, dim3((unsigned)wgs), dim3(64 * waves), waves * each, st, static_cast<const bf16_t *>(in),
+                       static_cast<const bf16_t *>(w), out, p);
+    return hipGetLastError();
+}
+
 template <bool BWD, int MT>
 hipError_t launch(const void *in, const void *w, void *out, const ConvGeom &g, hipStream_t st)
 {
     SmallConv p;
     if (!problem_of(g, BWD, MT, &p)) return hipErrorInvalidValue;
-    const long long wgs = workgroups(g, p);
-    const int waves = waves_of(wgs, steps_of(p, MT));
-    // LDS, a wave: its patch (MT = 32: two octets of channels, 16: four), then its sums (16 registers, four)
-    hipLaunchKernelGGL((small3x3_bf16_kernel<BWD, MT>), dim3((unsigned)wgs), dim3(64 * waves), waves * 4096, st,
-                       static_cast<const bf16_t *>(in), static_cast<const bf16_t *>(w), out, p);
-    return hipGetLastError();
+    if constexpr (!BWD)
+        if (steps_of(p, MT) >= TOGETHER_STEPS) return launch_as<BWD, MT, true>(in, w, out, g, p, st);
+    return launch_as<BWD, MT, false>(in, w, out, g, p, st);
 }
 
 }  // namespace
