@@ -221,8 +221,8 @@ int waves_of(long long wgs, int steps)
 }
 
 // us = start + chain * steps of a wave + turn * (rounds of workgroups, each its waves' steps and one) + work * steps on a compute unit
-// + filter MB.  Fitted to 400 layers each (1 to 8 images, 8 to 512 channels, planes of 7x7 to 56x56), which they reproduce to 11 to
-// 13 % (rms).
+// + filter MB.  Fitted to 400 layers each (1 to 8 images, 8 to 512 channels, planes of 7x7 to 56x56), which they reproduce to 9 to
+// 14 % (rms).
 struct Cost { double start, chain, turn, work, filter; };
 const Cost kCost[2][2] = {{{1.34, 1.11, 1.07, 0.19, 0.48}, {1.16, 1.26, 0.53, 0.26, 0.73}},    // forward: MT = 32, 16
                           {{0.05, 1.58, 1.82, 0.24, 0.29}, {0.74, 1.44, 0.86, 0.36, 0.78}}};   // backward-data
