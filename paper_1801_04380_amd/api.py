@@ -56,13 +56,10 @@ def _ptr(t):
     return t.data_ptr()
 
 
-# The current stream of the current device as the number that the C side takes: torch.cuda.current_stream() makes a Python object of
-# it first, a third of what a call costs the host (a small layer's pass of seven calls is bound by that).
-_raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
-
-
 def _stream():
-    return _raw_stream(_device())
+    # the number that the C side takes: torch.cuda.current_stream() makes a Python object of it first, a third of what a call
+    # cost the host (a small layer's pass of seven calls was bound by that)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def conv_shape(N, C, H, W, K, R, S, stride=(1, 1), pad=(0, 0), in_dtype=SN_F32, out_dtype=None):
