@@ -168,8 +168,8 @@ sn_status sn_conv_workspace_query(const sn_conv_shape *shape, sn_conv_dir dir, s
  * built-in ranking: first the channels-last product where the budget holds it and it is
  * estimated to be faster than what would run instead, as STAGED or, where STAGED has no
  * kernel for the shape or does not fit, as IM2COL_GEMM (bytes_used is then at least that algorithm's
- * min_bytes); then WINOGRAD where it applies, C * K >= 8192 and at least 2048 tiles fit a pass, STAGED,
- * DIRECT; DIRECT before these for forward on few-channel inputs.  Among records within 3 % of the fastest the one with the
+ * min_bytes); then WINOGRAD where it applies, C * K >= 8192 and at least 2048 tiles (or the whole batch) fit a pass, but for
+ * small layers, which are one launch as DIRECT; STAGED, DIRECT; DIRECT before these for forward on few-channel inputs.  Among records within 3 % of the fastest the one with the
  * smallest workspace wins (then the faster).  DIRECT needs 0 bytes, so a plan always exists.  bytes_used = the workspace the choice will use
  * (<= budget_bytes).  predicted_ms may be NULL; it receives the recorded time
  * or a negative value if the choice came from the built-in ranking. */

@@ -306,11 +306,12 @@ bool scatter_bwd_data(const ConvGeom &g) { return (g.sh > 1 || g.sw > 1) && poin
 bool phase_fwd_when_it_fits(const ConvGeom &g) { return g.R == 1 && g.S == 1 && g.K >= 512; }
 
 // Winograd pays four kernels per pass and streams 16 transformed values per 4 inputs: a guess in its favour only where a
-// pass has real work and the products outweigh the transforms (measured: 64 x 128 channels gain, 64 x 64 lose).
+// pass has real work and the products outweigh the transforms (measured: 64 x 128 channels gain, 64 x 64 lose).  Never over the small
+// layers' kernel: on 151 of them that these conditions let through its four launches took 4 times as long (geometric mean; at least 2.5).
 bool winograd_guessed(const ConvGeom &g, sn_conv_dir dir, size_t budget)
 {
     const bool bwd = dir == SN_CONV_BWD_DATA;
-    if (dir == SN_CONV_BWD_FILTER || !winograd_supported(g, bwd) || (long long)g.C * g.K < 8192) return false;
+    if (dir == SN_CONV_BWD_FILTER || !winograd_supported(g, bwd) || (long long)g.C * g.K < 8192 || small3x3_supported(g, bwd)) return false;
     size_t mn = 0, pf = 0;
     winograd_bytes(g, bwd, &mn, &pf);
     return mn <= budget && (pf <= budget || winograd_pass_tiles(g, bwd, budget) >= 2048);

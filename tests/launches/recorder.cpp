@@ -1,7 +1,8 @@
 // Runs the library's host code on a machine without a GPU and prints what it would launch: this program defines the runtime
 // calls that the library makes, and the dynamic linker finds them here before the HIP runtime's.  No kernel runs.
 //
-// stdin, a line per call: dir algo workspace_bytes, then the 13 fields of sn_conv_shape.  stdout per call: a line per launch
+// stdin, a line per call: dir (3: forward with statistics, 4: the forward that allocates nothing) algo workspace_bytes, then the 13 fields
+// of sn_conv_shape.  stdout per call: a line per launch
 //   launch <kernel> <grid x y z> <threads> <dynamic LDS> <LDS limit set for the kernel, or -1> <workspace bytes it reaches, or -1>
 // and `call <status>`.  What a launch reaches is known for the sum over slices (reduce_partials_kernel): the end of its slices.
 #include <cstdint>
@@ -69,7 +70,11 @@ int main()
         void *const w = ws_bytes ? const_cast<char *>(ws) : nullptr;
         const auto tensor = [](uintptr_t i) { return reinterpret_cast<void *>(i << 40); };
         const auto call = dir == SN_CONV_FWD ? sn_conv2d_fwd : dir == SN_CONV_BWD_DATA ? sn_conv2d_bwd_data : sn_conv2d_bwd_filter;
-        const int status = call(tensor(1), tensor(2), tensor(3), &s, (sn_conv_algo)algo, w, ws_bytes, nullptr);
+        float *const stats = static_cast<float *>(tensor(4));
+        const int status = dir == 3 ? sn_conv2d_fwd_bn_stats(tensor(1), tensor(2), tensor(3), &s, (sn_conv_algo)algo, w, ws_bytes, stats, stats, 1e-5f,
+                                                             tensor(5), sn_conv_bn_stats_scratch_bytes(&s), nullptr)
+                           : dir == 4 ? sn_conv2d_fwd_noalloc(tensor(1), tensor(2), tensor(3), &s, nullptr)
+                                      : call(tensor(1), tensor(2), tensor(3), &s, (sn_conv_algo)algo, w, ws_bytes, nullptr);
         std::printf("call %d\n", status);
     }
     return 0;

@@ -138,3 +138,15 @@ def test_the_streaming_kernel_is_given_no_workspace(recorded):
                                                          (sn.SN_ALGO_AUTO, 0), (sn.SN_ALGO_AUTO, 256 << 20))]
     for status, launches in recorded(calls):
         assert status == 0 and [re.sub(r"^\d+", "", k[0])[:15] for k in launches] == ["band3x3_kernelI"], launches
+
+
+def test_small_fp32_layers_keep_their_kernel_with_workspace(recorded):
+    """3x3 layers that one launch takes without workspace: no amount of it makes AUTO run WINOGRAD's four instead."""
+    sn.sn_planner_clear()
+    calls = []
+    for N, C, H, W, K in ((1, 128, 7, 7, 128), (2, 96, 8, 8, 96), (1, 256, 7, 7, 128), (1, 512, 4, 4, 200), (1, 1024, 5, 5, 8)):
+        s = sn.conv_shape(N, C, H, W, K, 3, 3, (1, 1), (1, 1), sn.SN_F32, sn.SN_F32)
+        calls += [(d, sn.SN_ALGO_AUTO, b, s) for d in (sn.SN_CONV_FWD, sn.SN_CONV_BWD_DATA) for b in (0, 32 << 20, 512 << 20)]
+    for (d, _, b, s), (status, launches) in zip(calls, recorded(calls)):
+        kernel = "small3x3_mfma_kernel" if (s.C if d == sn.SN_CONV_FWD else s.K) >= 16 else "small3x3_kernel"
+        assert status == 0 and [kernel in k[0] for k in launches] == [True], (d, b, [getattr(s, f) for f in FIELDS], launches)
