@@ -12,6 +12,7 @@
 // us a call, before (without workspace; planned with 32 MiB) -> now: 2 x 16 x 16x16, 16 channels fp32 16.6 (17.2) -> 6.5, bf16 21.9
 // (15.6) -> 4.4; 1 x 64 x 8x8, 64 channels 10.5 -> 3.6 and 12.1 -> 4.1; 2 x 80 x 24x24, 77 channels 26.7 -> 11.6 and 30.4 (15.5) -> 6.7.
 #include <algorithm>
+#include <cmath>
 
 #include "sn_internal.h"
 
@@ -164,15 +165,14 @@ bool problem_of(const ConvGeom &g, SmallWgrad *p)
 
 }  // namespace
 
-// us = 2.6 + turn * steps of a wave (times the rounds of workgroups beyond one a compute unit) + 0.03 * steps on a compute unit: 300
-// layers each (1 to 8 images, 4 to 256 channels, planes of 4x4 to 64x64) to 8 % (rms).
+// us = start + work * steps on the chip + unit * steps on one compute unit + turn * its workgroups, a step being four units of 16 bytes of a
+// row: 4600 layers (1 to 16 images, 8 to 512 channels, planes of 4x4 to 64x64) to 6 % in bf16 and 4 % in fp32 (rms).
 double small_wgrad_us(const ConvGeom &g)
 {
     SmallWgrad p;
     if (!problem_of(g, &p)) return 1e9;
-    const double steps = (p.units + 3) / 4, wgs = 3.0 * p.ktiles * ((g.C + 15) / 16);
-    const double waves = std::min<double>(MAXWAVES, steps);
-    return 2.6 + (g.in_bf16 ? 1.42 : 1.73) * std::max(1.0, wgs / 256) * (double)(long long)((steps + waves - 1) / waves) + 0.03 * steps * wgs / 256;
+    const double steps = (p.units + 3) / 4, wgs = 3.0 * p.ktiles * ((g.C + 15) / 16), each = std::ceil(wgs / 256);
+    return g.in_bf16 ? 3.6 + 0.033 * steps * wgs / 256 + (0.088 * steps + 0.91) * each : 3.5 + 0.033 * steps * wgs / 256 + (0.109 * steps + 0.68) * each;
 }
 
 hipError_t launch_small_wgrad(const void *x, const void *dy, float *dw, const ConvGeom &g, hipStream_t st)

@@ -214,10 +214,10 @@ constexpr double SMALL_BF16_US = 16;
 double small_bf16_us(const ConvGeom &g, bool bwd_data);   // estimate; very large: not supported
 hipError_t launch_small_bf16(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, hipStream_t st);
 
-// 3x3 / stride-1 backward-filter of small layers, either type, in one launch (conv_small_wgrad.hip), no workspace.  Of 600 layers all
-// with an estimate below SMALL_WGRAD_US were faster on it, at most 0.71 of the time without workspace and 0.80 with; from 16 us on
-// the other kernels, which fill the chip, begin to win.
-constexpr double SMALL_WGRAD_US = 14;
+// 3x3 / stride-1 backward-filter of small layers, either type, in one launch (conv_small_wgrad.hip), no workspace.  Of 4600 layers those
+// with an estimate below small_wgrad_most were no slower on it than on the other kernels without workspace (at most 1.05 times); from
+// there on those, which fill the chip, begin to win.
+inline double small_wgrad_most(const ConvGeom &g) { return g.in_bf16 ? 22 : 19; }
 double small_wgrad_us(const ConvGeom &g);   // estimate; very large: not supported
 hipError_t launch_small_wgrad(const void *x, const void *dy, float *dw, const ConvGeom &g, hipStream_t st);
 

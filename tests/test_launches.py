@@ -150,3 +150,18 @@ def test_small_fp32_layers_keep_their_kernel_with_workspace(recorded):
     for (d, _, b, s), (status, launches) in zip(calls, recorded(calls)):
         kernel = "small3x3_mfma_kernel" if (s.C if d == sn.SN_CONV_FWD else s.K) >= 16 else "small3x3_kernel"
         assert status == 0 and [kernel in k[0] for k in launches] == [True], (d, b, [getattr(s, f) for f in FIELDS], launches)
+
+
+def test_small_layers_backward_filter_takes_the_faster_kernel(recorded):
+    """With workspace: the one launch where the layer is small, the product over copies where it is the faster one (by 1.4 times on the
+    shapes here: long sums on few compute units, or many workgroups on each)."""
+    sn.sn_planner_clear()
+    small = [(2, 16, 16, 16, 16, "f32"), (2, 16, 16, 16, 16, "bf16"), (1, 64, 8, 8, 64, "bf16"), (2, 80, 24, 24, 77, "bf16"), (4, 112, 5, 5, 240, "f32")]
+    product = [(10, 16, 11, 26, 16, "bf16"), (3, 51, 26, 26, 384, "bf16"), (13, 40, 10, 10, 464, "bf16"), (1, 16, 38, 38, 64, "f32")]
+    calls = []
+    for N, C, H, W, K, dtype in small + product:
+        t = sn.SN_BF16 if dtype == "bf16" else sn.SN_F32
+        calls.append((sn.SN_CONV_BWD_FILTER, sn.SN_ALGO_AUTO, 64 << 20, sn.conv_shape(N, C, H, W, K, 3, 3, (1, 1), (1, 1), t, t)))
+    for i, (status, launches) in enumerate(recorded(calls)):
+        one = [k[0] for k in launches if "small3x3_wgrad" in k[0]]
+        assert status == 0 and (len(launches) == len(one) == 1 if i < len(small) else not one), ((small + product)[i], launches)
