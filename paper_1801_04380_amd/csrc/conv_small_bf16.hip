@@ -220,22 +220,23 @@ int waves_of(long long wgs, int steps)
     return waves;
 }
 
-// us = start + chain * steps of a wave + turn * (rounds of workgroups, each its waves' steps and one) + work * steps on a compute unit
-// + filter MB.  Fitted to 400 layers each (1 to 8 images, 8 to 512 channels, planes of 7x7 to 56x56), which they reproduce to 9 to
-// 14 % (rms).
-struct Cost { double start, chain, turn, work, filter; };
-const Cost kCost[2][2] = {{{1.34, 1.11, 1.07, 0.19, 0.48}, {1.16, 1.26, 0.53, 0.26, 0.73}},    // forward: MT = 32, 16
-                          {{0.05, 1.58, 1.82, 0.24, 0.29}, {0.74, 1.44, 0.86, 0.36, 0.78}}};   // backward-data
+// us = start + chain * a wave's steps, times the rounds of workgroups + work * steps on the chip + unit * steps on one compute unit + MB written and
+// read.  A SIMD holds three of these waves, so that a workgroup of five to seven leaves no place for a second.  6500 layers each (1 to 16 images, 8 to 512
+// channels, planes of 4x4 to 64x64, either tile) to 6 to 8 % (rms).
+struct Cost { double start, chain, work, unit, out, in; };
+const Cost kCost[2][2] = {{{4.62, 0.47, 0.068, 0.142, 0.63, 0.16}, {3.88, 0.20, 0.072, 0.224, 0, 0.465}},    // forward: MT = 32, 16
+                          {{4.37, 0.83, 0.082, 0.28, 0.35, 0.06}, {3.77, 0.29, 0.047, 0.403, 0, 0.47}}};   // backward-data
 
 double tile_us(const ConvGeom &g, bool bwd, int MT)
 {
     SmallConv p;
     if (!problem_of(g, bwd, MT, &p)) return 1e9;
     const Cost &c = kCost[bwd][MT == 16];
-    const long long wgs = workgroups(g, p);
+    const long long wgs = workgroups(g, p), each = (wgs + 255) / 256;
     const int steps = steps_of(p, MT), waves = waves_of(wgs, steps);
-    return c.start + c.chain * ((steps + waves - 1) / waves) + c.turn * rounds_cost(wgs, steps, waves) + c.work * wgs * steps / 256 +
-           c.filter * 18e-6 * p.M * p.Red;
+    const long long fit = 256 * (MAXWAVES / 4 / ((waves + 3) / 4));
+    const double out = (p.out_bf16 ? 2e-6 : 4e-6) * g.N * p.M * p.OH * p.OW, in = 2e-6 * g.N * p.Red * p.IH * p.IW;
+    return c.start + c.chain * ((wgs + fit - 1) / fit * ((steps + waves - 1) / waves)) + c.work * wgs * steps / 256 + c.unit * each * steps + c.out * out + c.in * in;
 }
 
 // Long reductions, whose loads add up, load the filter together; in short ones the way through LDS is what counts (350 layers: up to eight steps

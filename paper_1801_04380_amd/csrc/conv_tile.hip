@@ -393,6 +393,27 @@ const FewChannelsCost kFewChannelsDirect[] = {
     {false, false, false, 1, 4.9, 2.47, 0, 0.213},   {false, true, false, 1, 4.9, 2.28, 0, 0.213},   {false, false, false, 2, 4.9, 2.78, 0.4, 0.213},
     {false, true, false, 2, 4.9, 2.47, 0.4, 0.213},  {false, false, false, 4, 4.9, 3.11, 3.0, 0.213}, {false, true, false, 4, 4.9, 2.43, 2.0, 0.213}};
 
+// The tiles by these tables, what they do not hold as packed_tile_us has it; 0: no tile takes the shape.
+static double tiles_us(const ConvGeom &g, bool bwd_data, bool staged)
+{
+    TileProblem p;
+    Plan pl, pl2;
+    if (!problem_of(g, bwd_data, &p) || !make_plan(p, g.R, g.S, staged, &pl)) return 0;
+    const bool second = staged && make_plan2(p, g.R, g.S, &pl2);
+    if (second) pl = pl2;
+    const double rounds = std::max(1.0, std::ceil((double)pl.p.nptiles * pl.p.nktiles / 128) / 2);
+    const double gather = staged ? 1 : p.Cin % 16 ? 1.9 : bwd_data ? 1 : 0.69;
+    const double mb = 2e-6 * p.N * ((double)p.Cin * p.Hin * p.Win + (double)p.Kout * p.Pout * p.Qout);
+    double us = packed_tile_us(g, bwd_data);
+    const auto tiles = [&](const FewChannelsCost &t) {
+        if (t.second == second && t.wide == pl.wide && t.kt64 == (pl.KT == 64) && t.NF == pl.NF)
+            us = t.base + rounds * (t.chunk * gather * pl.p.nchunks + t.tile) + t.per_mb * mb;
+    };
+    if (staged) for (const FewChannelsCost &t : kFewChannels) tiles(t);
+    else for (const FewChannelsCost &t : kFewChannelsDirect) tiles(t);
+    return us;
+}
+
 // Few reduction channels: the streaming kernel where its estimate is below that of the tiles with or without workspace.  Of 590 layers that the
 // estimates were not fitted to, without workspace: 13 % faster on average than on the tiles, more than 5 % slower on 15 (at most 17 %), 0.5 % from
 // the better of the two each time; of 345 with workspace 5 %, 12 (29 %) and 0.9 %.  It wins from about eight rows a band on; on smaller layers its
@@ -400,22 +421,13 @@ const FewChannelsCost kFewChannelsDirect[] = {
 bool band_conv_runs(const ConvGeom &g, bool bwd_data, bool staged)
 {
     const double us = band_conv_us(g, bwd_data);
-    TileProblem p;
-    Plan pl, pl2;
-    if (us >= 1e9 || !problem_of(g, bwd_data, &p) || !make_plan(p, g.R, g.S, staged, &pl)) return false;
-    const bool second = staged && make_plan2(p, g.R, g.S, &pl2);
-    if (second) pl = pl2;
-    const double rounds = std::max(1.0, std::ceil((double)pl.p.nptiles * pl.p.nktiles / 128) / 2);
-    const double gather = staged ? 1 : p.Cin % 16 ? 1.9 : bwd_data ? 1 : 0.69;
-    const double mb = 2e-6 * p.N * ((double)p.Cin * p.Hin * p.Win + (double)p.Kout * p.Pout * p.Qout);
-    double other = packed_tile_us(g, bwd_data);   // (a tiling that none of these layers had)
-    const auto tiles = [&](const FewChannelsCost &t) {
-        if (t.second == second && t.wide == pl.wide && t.kt64 == (pl.KT == 64) && t.NF == pl.NF)
-            other = t.base + rounds * (t.chunk * gather * pl.p.nchunks + t.tile) + t.per_mb * mb;
-    };
-    if (staged) for (const FewChannelsCost &t : kFewChannels) tiles(t);
-    else for (const FewChannelsCost &t : kFewChannelsDirect) tiles(t);
-    return us < other;
+    return us < 1e9 && us < tiles_us(g, bwd_data, staged);
+}
+
+double tile_conv3x3_us(const ConvGeom &g, bool bwd_data, bool staged)
+{
+    const double us = tiles_us(g, bwd_data, staged);
+    return us > 0 ? std::min(us, band_conv_us(g, bwd_data)) : 1e9;
 }
 
 double tile_conv_us(const ConvGeom &g, bool bwd_data)

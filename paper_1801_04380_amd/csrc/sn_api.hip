@@ -322,27 +322,50 @@ bool winograd_guessed(const ConvGeom &g, sn_conv_dir dir, size_t budget)
 // workspace it is what STAGED runs where it is faster than STAGED's other kernels, and what IM2COL_GEMM runs instead of
 // unfolding.
 
-// Small 3x3 / stride-1 layers in one launch without workspace, which DIRECT takes instead of its other kernels and AUTO where the
-// estimate is below the product's.  Image layers keep the kernels of their own.
+// Small 3x3 / stride-1 layers in one launch without workspace, which DIRECT takes in place of its other kernels and AUTO where the
+// estimate is below the product's too.  Image layers keep the kernels of their own.
 bool small_wgrad_runs(const ConvGeom &g) { return g.C > 4 && small_wgrad_us(g) < small_wgrad_most(g); }
 
-bool small_bf16_runs(const ConvGeom &g, sn_conv_dir dir)
+double small_conv_us(const ConvGeom &g, sn_conv_dir dir)
 {
-    return dir != SN_CONV_BWD_FILTER && !(dir == SN_CONV_FWD && smallc_supported(g)) && small_bf16_us(g, dir == SN_CONV_BWD_DATA) < SMALL_BF16_US;
+    if (dir == SN_CONV_BWD_FILTER || (dir == SN_CONV_FWD && smallc_supported(g))) return 1e9;
+    const double us = small_bf16_us(g, dir == SN_CONV_BWD_DATA);
+    return us < SMALL_BF16_US ? us : 1e9;
 }
 
-// Its estimate; very large: it does not run.
+// The tiles (and the streaming kernel), as they are estimated for other choices, on the scale of the estimate above, which was fitted to other
+// timings: both of 3200 layers forward and 3500 backward-data, to 9 to 10 % (rms) without and 14 % with a packed filter.
+double small_tiles_us(const ConvGeom &g, sn_conv_dir dir, bool staged)
+{
+    const bool bwd = dir == SN_CONV_BWD_DATA;
+    const double us = tile_conv3x3_us(g, bwd, staged);
+    return staged ? (bwd ? 1.04 * us + 1.7 : 1.06 * us + 0.6) : (bwd ? 0.97 * us + 2.0 : 1.13 * us + 0.8);
+}
+
+// Whether DIRECT (STAGED) takes it in place of its tiles.  Of those 6700 layers DIRECT is more than 5 % slower than on the tiles on 18 (at most 1.25
+// times, as 5 * 16 * 33 x 33, 240 channels); without the comparison it was on 86 (1.46 times).  (No tile is estimated below 6.)
+bool small_bf16_runs(const ConvGeom &g, sn_conv_dir dir, bool staged)
+{
+    const double us = small_conv_us(g, dir);
+    return us < 1e9 && (us < 6 || us < (staged ? 1.15 : 1.05) * small_tiles_us(g, dir, staged));
+}
+
+// Its estimate; very large: DIRECT does not run it.
 double small_us(const ConvGeom &g, sn_conv_dir dir)
 {
     if (dir == SN_CONV_BWD_FILTER) return small_wgrad_runs(g) ? small_wgrad_us(g) : 1e9;
-    return small_bf16_runs(g, dir) ? small_bf16_us(g, dir == SN_CONV_BWD_DATA) : 1e9;
+    return small_bf16_runs(g, dir, false) ? small_conv_us(g, dir) : 1e9;
 }
 
-// The kernels without workspace that DIRECT takes in place of its others: of small layers, and the image layer's forward.
-double direct_us(const ConvGeom &g, sn_conv_dir dir)
+// Whether there is nothing to stage: DIRECT's kernels are the faster ones, the small layers' or the tiles that such a layer takes without workspace
+// (12 x 48 x 42x42 -> 16, backward-data: the tiles 9.3 us, with a packed filter 13.6), or the image layer's forward.
+bool direct_faster(const ConvGeom &g, sn_conv_dir dir)
 {
-    const double us = small_us(g, dir);
-    return dir == SN_CONV_FWD ? std::min(us, image_fwd_us(g)) : us;
+    if (dir == SN_CONV_BWD_FILTER) return small_wgrad_runs(g);
+    if (dir == SN_CONV_FWD && image_fwd_us(g) < 1e9) return true;
+    const double us = small_conv_us(g, dir);
+    if (us >= 1e9) return false;
+    return (small_bf16_runs(g, dir, false) ? us : small_tiles_us(g, dir, false)) < 1.15 * small_tiles_us(g, dir, true);
 }
 
 // Estimated us of what runs instead (0: always keep that).  Kernels that read their operands where they are -- few input
@@ -381,6 +404,11 @@ double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
     return tile_conv_us(g, dir == SN_CONV_BWD_DATA);
 }
 
+// The product's estimate as it counts against the small layers' kernels: it is too high on the least work (its launches) and too low where the filter is
+// large (packed, or summed from parts).  Of 4600 layers' backward-filter this leaves 28 more than 5 % slower than without the small kernel (at
+// most 1.15 times; the estimate as it is 256, 1.38 times), of the 6700 forward and backward-data 47 (1.25; 107, 1.41).
+double product_us(const ConvGeom &g, const ChlastPlan &plan) { return plan.us - 2.5 + 4e-6 * g.K * g.C * g.R * g.S; }
+
 // Whether the channels-last product is the faster one with this workspace (against unfolding always), in few passes over the
 // batch (each is some launches) -- more where only the general kernels are left.
 bool chlast_faster(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t ws_bytes, ChlastPlan *plan)
@@ -390,25 +418,17 @@ bool chlast_faster(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t
     // less than half of the row-stationary kernel's partial sums: atomics (64 x 256 x 20x20 -> 128: 42 us, with them 15)
     if (dir == SN_CONV_BWD_FILTER && g.R == 3 && !image_runs(g, true) && rows_wgrad_supported(g) && rows_wgrad_partial_bytes(g) / 2 > ws_bytes) other += 30;
     if (other <= CHLAST_LEAST_US || !chlast_plan(g, dir, ws_bytes, plan)) return false;
-    // STAGED's forward and backward-data run the small layers' kernel, too, in place of its others and of the product where that is at
+    // STAGED's forward and backward-data run the small layers' kernel, too, in place of its tiles and of the product where that is at
     // its worst: reduction slices (a third launch) or channels that fill no whole runs (2 x 256 x 14x14, 256 channels: 17 us, the kernel 9; 2 x 24 x
     // 14x14 -> 40: 12 and 3.5).  On the rest (4 x 64 x 14x14 -> 128: 13 and 5) the name keeps the product, so that measurements have both to
     // choose from: AUTO without any takes the kernel, as DIRECT.
-    if (algo == SN_ALGO_STAGED && dir != SN_CONV_BWD_FILTER && small_us(g, dir) < plan->us) {
+    if (algo == SN_ALGO_STAGED && dir != SN_CONV_BWD_FILTER && small_us(g, dir) < product_us(g, *plan) && small_bf16_runs(g, dir, true)) {
         int m, n, threads, slices;
         chlast_config(*plan, dir, &m, &n, &threads, &slices);
         if (slices > 1 || (dir == SN_CONV_FWD ? g.C : g.K) % 64 != 0) return false;
     }
     const bool alone = dir == SN_CONV_BWD_FILTER ? !tile_wgrad_supported(g) : dir == SN_CONV_FWD && !tile_conv_supported(g, false);
     return plan->passes <= (alone ? 8 : 2) && plan->us < other;
-}
-
-// The product's estimate as it counts against direct_us.  Backward-filter's is too high on the least work (its launches) and too low where
-// dw is large (its partial sums): of 4600 layers this leaves 28 more than 5 % slower than without the small layers' kernel (at most 1.15 times; the
-// estimate as it is 256, 1.38 times).
-double product_us(const ConvGeom &g, sn_conv_dir dir, const ChlastPlan &plan)
-{
-    return dir == SN_CONV_BWD_FILTER ? plan.us - 2.5 + 4e-6 * g.K * g.C * g.R * g.S : plan.us;
 }
 
 sn_status own_query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *min_b, size_t *pref_b);
@@ -572,7 +592,9 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
     }
     // The channels-last product where it is the fastest, under the name that runs it with this budget.
     ChlastPlan cl;
-    const bool product = chlast_faster(g, dir, SN_ALGO_STAGED, budget, &cl) && product_us(g, dir, cl) <= direct_us(g, dir);
+    const double small = small_us(g, dir);
+    bool product = chlast_faster(g, dir, SN_ALGO_STAGED, budget, &cl) && product_us(g, cl) <= small;
+    if (product && dir == SN_CONV_FWD) product = cl.us <= image_fwd_us(g);
     for (sn_conv_algo a : {SN_ALGO_STAGED, SN_ALGO_IM2COL_GEMM}) {
         size_t mn = 0, pf = 0;
         if (!product || query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
@@ -594,7 +616,7 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
     for (sn_conv_algo a : kRanking) {
         size_t mn = 0, pf = 0;
         if (own_query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
-        if (a == SN_ALGO_STAGED && (pf == 0 || direct_us(g, dir) < 1e9)) continue;   // nothing to stage: the same kernel runs as DIRECT
+        if (a == SN_ALGO_STAGED && (pf == 0 || direct_faster(g, dir))) continue;   // nothing to stage: the same kernel runs as DIRECT, or a faster one
         if (a == SN_ALGO_WINOGRAD && !winograd_guessed(g, dir, budget)) continue;
         // The phase planes in passes: strided forward gains little over the zero-workspace kernel, so only
         // with the whole batch (below that STAGED forward is the gathering kernel, which needs the re-laid-out
@@ -660,7 +682,7 @@ size_t out_elem(const ConvGeom &g) { return g.out_bf16 ? 2 : 4; }
 hipError_t direct_fwd(const void *x, const void *w, void *y, const ConvGeom &g, hipStream_t st)
 {
     if (smallc_supported(g)) return launch_smallc_fwd(x, w, y, g, st, nullptr);
-    if (small_bf16_runs(g, SN_CONV_FWD)) return launch_small_bf16(x, w, y, g, false, st);
+    if (small_bf16_runs(g, SN_CONV_FWD, false)) return launch_small_bf16(x, w, y, g, false, st);
     if (image_fwd_us(g) < 1e9) return launch_image_fwd(x, w, y, g, st);
     if (tile_conv_supported(g, false)) return launch_tile_conv(x, w, y, g, false, nullptr, st);
     if (g.R == 1 && g.S == 1 && gather_fwd(g)) return launch_gather_conv_fwd(x, w, y, g, nullptr, st);
@@ -671,7 +693,7 @@ hipError_t direct_fwd(const void *x, const void *w, void *y, const ConvGeom &g, 
 hipError_t direct_bwd_data(const void *dy, const void *w, void *dx, const ConvGeom &g, hipStream_t st)
 {
     if (scatter_bwd_data(g)) return launch_pointwise(dy, w, dx, g, true, st);
-    if (small_bf16_runs(g, SN_CONV_BWD_DATA)) return launch_small_bf16(dy, w, dx, g, true, st);
+    if (small_bf16_runs(g, SN_CONV_BWD_DATA, false)) return launch_small_bf16(dy, w, dx, g, true, st);
     if (tile_conv_supported(g, true)) return launch_tile_conv(dy, w, dx, g, true, nullptr, st);
     if (small3x3_supported(g, true)) return launch_small3x3(dy, w, dx, g, true, st);
     return launch_generic_bwd_data(dy, w, dx, g, st);
@@ -684,7 +706,7 @@ sn_status run_fwd(const void *x, const void *w, void *y, const ConvGeom &g, sn_c
     if (algo == SN_ALGO_WINOGRAD) return launch_status(launch_winograd(x, w, y, g, false, ws, ws_bytes, st));
     ChlastPlan cl;
     if (chlast_runs(g, SN_CONV_FWD, algo, ws_bytes, &cl)) return launch_status(launch_chlast(x, w, y, g, SN_CONV_FWD, ws, &cl, st));
-    if (algo == SN_ALGO_STAGED && small_bf16_runs(g, SN_CONV_FWD)) return launch_status(launch_small_bf16(x, w, y, g, false, st));
+    if (algo == SN_ALGO_STAGED && small_bf16_runs(g, SN_CONV_FWD, true)) return launch_status(launch_small_bf16(x, w, y, g, false, st));
     PhasePlan pp;
     if (algo == SN_ALGO_STAGED && gather_fwd(g)) {
         const bool planes = phase_fwd_when_it_fits(g) && phase_plan(g, SN_CONV_FWD, &pp);
@@ -731,7 +753,7 @@ sn_status run_bwd_data(const void *dy, const void *w, void *dx, const ConvGeom &
     if (algo == SN_ALGO_STAGED && scatter_bwd_data(g)) return launch_status(launch_pointwise(dy, w, dx, g, true, st));
     ChlastPlan cl;
     if (chlast_runs(g, SN_CONV_BWD_DATA, algo, ws_bytes, &cl)) return launch_status(launch_chlast(dy, w, dx, g, SN_CONV_BWD_DATA, ws, &cl, st));
-    if (algo == SN_ALGO_STAGED && small_bf16_runs(g, SN_CONV_BWD_DATA)) return launch_status(launch_small_bf16(dy, w, dx, g, true, st));
+    if (algo == SN_ALGO_STAGED && small_bf16_runs(g, SN_CONV_BWD_DATA, true)) return launch_status(launch_small_bf16(dy, w, dx, g, true, st));
     PhasePlan pp;
     const bool phases = algo == SN_ALGO_STAGED && phase_plan(g, SN_CONV_BWD_DATA, &pp);
     if (phases && ws_bytes < phase_bytes(pp, SN_CONV_BWD_DATA, pp.chunkable ? 1 : g.N)) {   // less than the phase planes need: many passes
@@ -1048,7 +1070,7 @@ sn_status sn_conv2d_fwd_bn_stats(const void *x, const void *w, void *y, const sn
     // The kernel is the one run_fwd takes: y is sn_conv2d_fwd's, bit for bit.  (The channels-last product leaves the
     // statistics to a pass over y.)
     ChlastPlan cl;
-    if (tile_conv_supported(g, false) && !small_bf16_runs(g, SN_CONV_FWD) && (algo == SN_ALGO_DIRECT || (staged && !chlast_runs(g, SN_CONV_FWD, algo, workspace_bytes, &cl)))) {
+    if (tile_conv_supported(g, false) && !small_bf16_runs(g, SN_CONV_FWD, staged) && (algo == SN_ALGO_DIRECT || (staged && !chlast_runs(g, SN_CONV_FWD, algo, workspace_bytes, &cl)))) {
         // the tile kernels take the statistics from their accumulators: y is not read again
         const int tiles = tile_conv_stats_tiles(g, staged, true);
         if (tiles <= 0) return SN_ERR_UNSUPPORTED;

@@ -95,6 +95,7 @@ bool band_conv_runs(const ConvGeom &g, bool bwd_data, bool staged);   // launch_
 int band_conv_stats_tiles(const ConvGeom &g);
 hipError_t launch_band_conv(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, hipStream_t st, float *stats);
 double tile_conv_us(const ConvGeom &g, bool bwd_data);   // estimate; very large: everything is faster
+double tile_conv3x3_us(const ConvGeom &g, bool bwd_data, bool staged);   // the same for 3x3 with and without `packed`, closer on little work
 
 // Stride-1 bf16 backward-filter fast path.  partial == nullptr: the slices of the
 // (n,p,q) sum combine with atomics into a zero-filled dw; otherwise slice z writes
@@ -207,10 +208,9 @@ constexpr long long SMALL3X3_MACS = 1LL << 24;
 bool small3x3_supported(const ConvGeom &g, bool bwd_data);
 hipError_t launch_small3x3(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, hipStream_t st);
 
-// bf16 3x3 / stride-1 forward and backward-data of small layers in one launch (conv_small_bf16.hip), no workspace.  Of 400 layers of
-// 1 to 8 images all with an estimate below SMALL_BF16_US were faster on it than on the other kernels that take no workspace (up to
-// 12 times) but for one, 1.06 times slower; above it the tiles' larger operands win, one layer after the other.
-constexpr double SMALL_BF16_US = 16;
+// bf16 3x3 / stride-1 forward and backward-data of small layers in one launch (conv_small_bf16.hip), no workspace, up to SMALL_BF16_US of
+// estimate: from there on the tiles' larger operands win, one layer after the other.
+constexpr double SMALL_BF16_US = 26;
 double small_bf16_us(const ConvGeom &g, bool bwd_data);   // estimate; very large: not supported
 hipError_t launch_small_bf16(const void *in, const void *w, void *out, const ConvGeom &g, bool bwd_data, hipStream_t st);
 

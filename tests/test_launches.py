@@ -165,3 +165,23 @@ def test_small_layers_backward_filter_takes_the_faster_kernel(recorded):
     for i, (status, launches) in enumerate(recorded(calls)):
         one = [k[0] for k in launches if "small3x3_wgrad" in k[0]]
         assert status == 0 and (len(launches) == len(one) == 1 if i < len(small) else not one), ((small + product)[i], launches)
+
+
+def test_small_bf16_layers_take_the_faster_kernel(recorded):
+    """Forward and backward-data: the one launch on small layers; the tiles where there are few reduction channels and many outputs, the product
+    over copies where it has the workspace and is the faster one (each side timed on these shapes: 1.2 to 1.4 times)."""
+    sn.sn_planner_clear()
+    F, D, AUTO = sn.SN_CONV_FWD, sn.SN_CONV_BWD_DATA, sn.SN_ALGO_AUTO
+    STATS, NOALLOC = 3, 4
+    want = [(F, AUTO, 0, (9, 16, 55, 26, 320, 1), "conv_tile_kernel"), (F, AUTO, 0, (12, 16, 33, 33, 304, 1), "conv_tile_kernel"),
+            (D, AUTO, 0, (8, 360, 40, 40, 16, 1), "conv_tile_kernel"), (D, AUTO, 64 << 20, (2, 320, 53, 53, 48, 0), "cl_gemm_kernel"),
+            (D, AUTO, 64 << 20, (3, 480, 37, 37, 23, 1), "cl_gemm_kernel"), (F, AUTO, 64 << 20, (4, 128, 13, 54, 288, 1), "cl_gemm_kernel"),
+            (F, sn.SN_ALGO_STAGED, 8 << 20, (15, 32, 28, 28, 240, 1), "conv_tile2_kernel"), (NOALLOC, AUTO, 0, (15, 32, 28, 28, 240, 1), "conv_tile2_kernel"),
+            (STATS, AUTO, 0, (4, 32, 57, 57, 256, 1), "conv_tile_kernel")]
+    for d in (F, D, STATS):
+        for b in (0, 64 << 20):
+            want += [(d, AUTO, b, s, "small3x3_bf16_kernel") for s in ((2, 256, 14, 14, 256, 1), (8, 16, 16, 16, 16, 1), (1, 512, 7, 7, 512, 1))]
+    calls = [(d, a, b, sn.conv_shape(s[0], s[1], s[2], s[3], s[4], 3, 3, (1, 1), (s[5], s[5]), sn.SN_BF16, sn.SN_BF16)) for d, a, b, s, _ in want]
+    for w, (status, launches) in zip(want, recorded(calls)):
+        assert status == 0 and any(w[4] in k[0] for k in launches), (w, launches)
+        assert w[4] == "small3x3_bf16_kernel" or not any("small3x3" in k[0] for k in launches), (w, launches)
