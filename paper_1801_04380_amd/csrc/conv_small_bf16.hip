@@ -206,17 +206,21 @@ bool problem_of(const ConvGeom &g, bool bwd, int MT, SmallConv *p)
 int steps_of(const SmallConv &p, int MT) { return (p.Red * MT + 511) / 512; }
 long long workgroups(const ConvGeom &g, const SmallConv &p) { return (long long)p.tiles * g.N * p.mtiles; }
 
-double rounds_cost(long long wgs, int steps, int waves)
-{
-    const int fit = 256 * (MAXWAVES / waves);
-    return (double)((wgs + fit - 1) / fit) * ((steps + waves - 1) / waves + 1);
-}
-
 int waves_of(long long wgs, int steps)
 {
+    const auto cost = [&](int waves) {
+        const unsigned fit = 256 * (MAXWAVES / waves);
+        return (unsigned long long)(((unsigned)wgs + fit - 1) / fit) * ((unsigned)(steps + waves - 1) / waves + 1);
+    };
     int waves = 1;
-    for (int v = 2; v <= std::min(MAXWAVES, steps); ++v)
-        if (rounds_cost(wgs, steps, v) <= rounds_cost(wgs, steps, waves)) waves = v;
+    unsigned long long least = cost(1);
+    for (int v = 2; v <= std::min(MAXWAVES, steps); ++v) {
+        const unsigned long long c = cost(v);
+        if (c <= least) {
+            least = c;
+            waves = v;
+        }
+    }
     return waves;
 }
 

@@ -404,14 +404,14 @@ static double tiles_us(const ConvGeom &g, bool bwd_data, bool staged)
     const double rounds = std::max(1.0, std::ceil((double)pl.p.nptiles * pl.p.nktiles / 128) / 2);
     const double gather = staged ? 1 : p.Cin % 16 ? 1.9 : bwd_data ? 1 : 0.69;
     const double mb = 2e-6 * p.N * ((double)p.Cin * p.Hin * p.Win + (double)p.Kout * p.Pout * p.Qout);
-    double us = packed_tile_us(g, bwd_data);
+    double us = 0;
     const auto tiles = [&](const FewChannelsCost &t) {
         if (t.second == second && t.wide == pl.wide && t.kt64 == (pl.KT == 64) && t.NF == pl.NF)
             us = t.base + rounds * (t.chunk * gather * pl.p.nchunks + t.tile) + t.per_mb * mb;
     };
     if (staged) for (const FewChannelsCost &t : kFewChannels) tiles(t);
     else for (const FewChannelsCost &t : kFewChannelsDirect) tiles(t);
-    return us;
+    return us > 0 ? us : packed_tile_us(g, bwd_data);
 }
 
 // Few reduction channels: the streaming kernel where its estimate is below that of the tiles with or without workspace.  Of 590 layers that the

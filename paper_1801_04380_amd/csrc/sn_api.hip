@@ -342,30 +342,37 @@ double small_tiles_us(const ConvGeom &g, sn_conv_dir dir, bool staged)
     return staged ? (bwd ? 1.04 * us + 1.7 : 1.06 * us + 0.6) : (bwd ? 0.97 * us + 2.0 : 1.13 * us + 0.8);
 }
 
-// Whether DIRECT (STAGED) takes it in place of its tiles.  Of those 6700 layers DIRECT is more than 5 % slower than on the tiles on 18 (at most 1.25
-// times, as 5 * 16 * 33 x 33, 240 channels); without the comparison it was on 86 (1.46 times).  (No tile is estimated below 6.)
+// Whether an estimate of it is below that of DIRECT's (STAGED's) tiles.  Of those 6700 layers DIRECT is more than 5 % slower than on the tiles on 18 (at
+// most 1.25 times, as 5 x 16 x 33x33 -> 240); without the comparison it was on 86 (1.46 times).  The tiles need not be looked at below the least that they
+// are estimated at, by the coefficients of their chunks of 16 reduction channels.
+bool below_tiles(double us, const ConvGeom &g, sn_conv_dir dir, bool staged)
+{
+    const int red = dir == SN_CONV_BWD_DATA ? g.K : g.C;
+    return us < 6 + (red > 64 ? red / 20.0 : 0) || us < (staged ? 1.15 : 1.05) * small_tiles_us(g, dir, staged);
+}
+
 bool small_bf16_runs(const ConvGeom &g, sn_conv_dir dir, bool staged)
 {
     const double us = small_conv_us(g, dir);
-    return us < 1e9 && (us < 6 || us < (staged ? 1.15 : 1.05) * small_tiles_us(g, dir, staged));
+    return us < 1e9 && below_tiles(us, g, dir, staged);
 }
 
 // Its estimate; very large: DIRECT does not run it.
 double small_us(const ConvGeom &g, sn_conv_dir dir)
 {
     if (dir == SN_CONV_BWD_FILTER) return small_wgrad_runs(g) ? small_wgrad_us(g) : 1e9;
-    return small_bf16_runs(g, dir, false) ? small_conv_us(g, dir) : 1e9;
+    const double us = small_conv_us(g, dir);
+    return us < 1e9 && below_tiles(us, g, dir, false) ? us : 1e9;
 }
 
-// Whether there is nothing to stage: DIRECT's kernels are the faster ones, the small layers' or the tiles that such a layer takes without workspace
-// (12 x 48 x 42x42 -> 16, backward-data: the tiles 9.3 us, with a packed filter 13.6), or the image layer's forward.
-bool direct_faster(const ConvGeom &g, sn_conv_dir dir)
+// Whether there is nothing to stage: DIRECT's kernels are the faster ones, the small layers' (of estimate `small`) or the tiles that such a layer takes
+// without workspace (12 x 48 x 42x42 -> 16, backward-data: the tiles 9.3 us, with a packed filter 13.6), or the image layer's forward.
+bool direct_faster(const ConvGeom &g, sn_conv_dir dir, double small)
 {
-    if (dir == SN_CONV_BWD_FILTER) return small_wgrad_runs(g);
+    if (dir == SN_CONV_BWD_FILTER) return small < 1e9;
+    if (small < 1e9) return below_tiles(small, g, dir, true);
     if (dir == SN_CONV_FWD && image_fwd_us(g) < 1e9) return true;
-    const double us = small_conv_us(g, dir);
-    if (us >= 1e9) return false;
-    return (small_bf16_runs(g, dir, false) ? us : small_tiles_us(g, dir, false)) < 1.15 * small_tiles_us(g, dir, true);
+    return small_conv_us(g, dir) < 1e9 && small_tiles_us(g, dir, false) < 1.15 * small_tiles_us(g, dir, true);
 }
 
 // Estimated us of what runs instead (0: always keep that).  Kernels that read their operands where they are -- few input
@@ -409,6 +416,9 @@ double other_us(const ConvGeom &g, sn_conv_dir dir, size_t ws_bytes)
 // most 1.15 times; the estimate as it is 256, 1.38 times), of the 6700 forward and backward-data 47 (1.25; 107, 1.41).
 double product_us(const ConvGeom &g, const ChlastPlan &plan) { return plan.us - 2.5 + 4e-6 * g.K * g.C * g.R * g.S; }
 
+// What runs in less needs no plan to compare with (making one is 1 to 2 us of the host).
+constexpr double PRODUCT_LEAST_US = CHLAST_LEAST_US - 2.5;
+
 // Whether the channels-last product is the faster one with this workspace (against unfolding always), in few passes over the
 // batch (each is some launches) -- more where only the general kernels are left.
 bool chlast_faster(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t ws_bytes, ChlastPlan *plan)
@@ -422,10 +432,10 @@ bool chlast_faster(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t
     // its worst: reduction slices (a third launch) or channels that fill no whole runs (2 x 256 x 14x14, 256 channels: 17 us, the kernel 9; 2 x 24 x
     // 14x14 -> 40: 12 and 3.5).  On the rest (4 x 64 x 14x14 -> 128: 13 and 5) the name keeps the product, so that measurements have both to
     // choose from: AUTO without any takes the kernel, as DIRECT.
-    if (algo == SN_ALGO_STAGED && dir != SN_CONV_BWD_FILTER && small_us(g, dir) < product_us(g, *plan) && small_bf16_runs(g, dir, true)) {
+    if (algo == SN_ALGO_STAGED && dir != SN_CONV_BWD_FILTER) {
         int m, n, threads, slices;
         chlast_config(*plan, dir, &m, &n, &threads, &slices);
-        if (slices > 1 || (dir == SN_CONV_FWD ? g.C : g.K) % 64 != 0) return false;
+        if ((slices > 1 || (dir == SN_CONV_FWD ? g.C : g.K) % 64 != 0) && small_us(g, dir) < product_us(g, *plan) && small_bf16_runs(g, dir, true)) return false;
     }
     const bool alone = dir == SN_CONV_BWD_FILTER ? !tile_wgrad_supported(g) : dir == SN_CONV_FWD && !tile_conv_supported(g, false);
     return plan->passes <= (alone ? 8 : 2) && plan->us < other;
@@ -539,6 +549,14 @@ sn_status query(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *m
     return SN_OK;
 }
 
+// query's min_bytes alone: the product's own need counts in strided backward-data only.
+sn_status least_bytes(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t *min_b)
+{
+    size_t pf = 0;
+    if (algo == SN_ALGO_STAGED && dir == SN_CONV_BWD_DATA && (g.sh > 1 || g.sw > 1)) return query(g, dir, algo, min_b, &pf);
+    return own_query(g, dir, algo, min_b, &pf);
+}
+
 // ---- planner table ------------------------------------------------------------
 struct Record {
     sn_conv_shape shape;
@@ -593,7 +611,7 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
     // The channels-last product where it is the fastest, under the name that runs it with this budget.
     ChlastPlan cl;
     const double small = small_us(g, dir);
-    bool product = chlast_faster(g, dir, SN_ALGO_STAGED, budget, &cl) && product_us(g, cl) <= small;
+    bool product = small > PRODUCT_LEAST_US && chlast_faster(g, dir, SN_ALGO_STAGED, budget, &cl) && product_us(g, cl) <= small;
     if (product && dir == SN_CONV_FWD) product = cl.us <= image_fwd_us(g);
     for (sn_conv_algo a : {SN_ALGO_STAGED, SN_ALGO_IM2COL_GEMM}) {
         size_t mn = 0, pf = 0;
@@ -615,8 +633,9 @@ sn_status plan(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir, s
     }
     for (sn_conv_algo a : kRanking) {
         size_t mn = 0, pf = 0;
+        if (a == SN_ALGO_STAGED && (budget > 0 || small < 1e9) && direct_faster(g, dir, small)) continue;
         if (own_query(g, dir, a, &mn, &pf) != SN_OK || mn > budget) continue;
-        if (a == SN_ALGO_STAGED && (pf == 0 || direct_faster(g, dir))) continue;   // nothing to stage: the same kernel runs as DIRECT, or a faster one
+        if (a == SN_ALGO_STAGED && pf == 0) continue;   // nothing to stage: the same kernel runs as DIRECT
         if (a == SN_ALGO_WINOGRAD && !winograd_guessed(g, dir, budget)) continue;
         // The phase planes in passes: strided forward gains little over the zero-workspace kernel, so only
         // with the whole batch (below that STAGED forward is the gathering kernel, which needs the re-laid-out
@@ -660,8 +679,8 @@ sn_status resolve(const sn_conv_shape *shape, const ConvGeom &g, sn_conv_dir dir
         const size_t budget = *ws_bytes;
         return plan(shape, g, dir, budget, algo, ws_bytes, nullptr);
     }
-    size_t mn = 0, pf = 0;
-    sn_status s = query(g, dir, *algo, &mn, &pf);
+    size_t mn = 0;
+    sn_status s = least_bytes(g, dir, *algo, &mn);
     if (s != SN_OK) return s;
     if (mn > *ws_bytes) return SN_ERR_WORKSPACE_TOO_SMALL;
     return SN_OK;
@@ -1010,8 +1029,8 @@ sn_status sn_conv2d_fwd_noalloc(const void *x, const void *w, void *y, const sn_
     sn_status s = make_geom(shape, &g);
     if (s != SN_OK) return s;
     if (!x || !w || !y || !aligned(x, 16) || !aligned(w, 16) || !aligned(y, 16)) return SN_ERR_BAD_ARG;
-    size_t mn = 0, pf = 0;
-    s = query(g, SN_CONV_FWD, SN_ALGO_STAGED, &mn, &pf);
+    size_t mn = 0;
+    s = least_bytes(g, SN_CONV_FWD, SN_ALGO_STAGED, &mn);
     if (s != SN_OK) return s;
     if (mn > (size_t)SN_NOALLOC_SCRATCH_BYTES) return SN_ERR_WORKSPACE_TOO_SMALL;
     void *ws = nullptr;

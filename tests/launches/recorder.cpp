@@ -4,7 +4,9 @@
 // stdin, a line per call: dir (3: forward with statistics, 4: the forward that allocates nothing) algo workspace_bytes, then the 13 fields
 // of sn_conv_shape.  stdout per call: a line per launch
 //   launch <kernel> <grid x y z> <threads> <dynamic LDS> <LDS limit set for the kernel, or -1> <workspace bytes it reaches, or -1>
-// and `call <status>`.  What a launch reaches is known for the sum over slices (reduce_partials_kernel): the end of its slices.
+// and `call <status> <plans of the channels-last product that were made>`.  What a launch reaches is known for the sum over slices (reduce_partials_kernel): the end of its slices.
+#include <dlfcn.h>
+
 #include <cstdint>
 #include <cstdio>
 #include <map>
@@ -19,8 +21,21 @@ std::map<const void *, int> limits;
 Dim grid, block;
 size_t lds;
 void *stream;
+int plans;
 const char *const ws = reinterpret_cast<const char *>(uintptr_t(1) << 44);   // nothing is there; nothing is read or written
 }  // namespace
+
+namespace sn {   // counted, and passed on
+struct ConvGeom;
+struct ChlastPlan;
+bool chlast_plan(const ConvGeom &g, int dir, size_t budget, ChlastPlan *plan)
+{
+    static const auto next = reinterpret_cast<bool (*)(const ConvGeom &, int, size_t, ChlastPlan *)>(
+        dlsym(RTLD_NEXT, "_ZN2sn11chlast_planERKNS_8ConvGeomEimPNS_10ChlastPlanE"));
+    ++plans;
+    return next(g, dir, budget, plan);
+}
+}  // namespace sn
 
 extern "C" {
 void **__hipRegisterFatBinary(const void *) { static void *h; return &h; }
@@ -70,12 +85,13 @@ int main()
         void *const w = ws_bytes ? const_cast<char *>(ws) : nullptr;
         const auto tensor = [](uintptr_t i) { return reinterpret_cast<void *>(i << 40); };
         const auto call = dir == SN_CONV_FWD ? sn_conv2d_fwd : dir == SN_CONV_BWD_DATA ? sn_conv2d_bwd_data : sn_conv2d_bwd_filter;
+        plans = 0;
         float *const stats = static_cast<float *>(tensor(4));
         const int status = dir == 3 ? sn_conv2d_fwd_bn_stats(tensor(1), tensor(2), tensor(3), &s, (sn_conv_algo)algo, w, ws_bytes, stats, stats, 1e-5f,
                                                              tensor(5), sn_conv_bn_stats_scratch_bytes(&s), nullptr)
                            : dir == 4 ? sn_conv2d_fwd_noalloc(tensor(1), tensor(2), tensor(3), &s, nullptr)
                                       : call(tensor(1), tensor(2), tensor(3), &s, (sn_conv_algo)algo, w, ws_bytes, nullptr);
-        std::printf("call %d\n", status);
+        std::printf("call %d %d\n", status, plans);
     }
     return 0;
 }

@@ -23,9 +23,9 @@ def recorded():
     exe = os.path.join(HERE, "_build", "recorder")
     _lib.load()
     subprocess.run(["g++", "-O1", "-std=c++17", "-rdynamic", "-I", os.path.join(ROOT, "include"), "-o", exe, os.path.join(HERE, "recorder.cpp"),
-                    _lib.LIB_PATH, "-Wl,-rpath," + os.path.dirname(_lib.LIB_PATH), "-Wl,--allow-shlib-undefined"], check=True)
+                    _lib.LIB_PATH, "-ldl", "-Wl,-rpath," + os.path.dirname(_lib.LIB_PATH), "-Wl,--allow-shlib-undefined"], check=True)
 
-    def run(calls):
+    def run(calls, plans=None):
         lines = "\n".join(" ".join(map(str, (d, a, b) + tuple(getattr(s, f) for f in FIELDS))) for d, a, b, s in calls)
         env = dict(os.environ, LD_LIBRARY_PATH="/opt/rocm/lib:" + os.environ.get("LD_LIBRARY_PATH", ""))
         out = subprocess.run([exe], input=lines, stdout=subprocess.PIPE, text=True, check=True, env=env).stdout
@@ -34,6 +34,8 @@ def recorded():
             w = line.split()
             if w[0] == "call":
                 res.append((int(w[1]), launches))
+                if plans is not None:
+                    plans.append(int(w[2]))
                 launches = []
             else:
                 v = list(map(int, w[2:]))
@@ -185,3 +187,16 @@ def test_small_bf16_layers_take_the_faster_kernel(recorded):
     for w, (status, launches) in zip(want, recorded(calls)):
         assert status == 0 and any(w[4] in k[0] for k in launches), (w, launches)
         assert w[4] == "small3x3_bf16_kernel" or not any("small3x3" in k[0] for k in launches), (w, launches)
+
+
+def test_small_calls_make_few_plans(recorded):
+    """A plan of the channels-last product is 1 to 2 us of the host, as much as the rest of a call: none where the small layers' kernel is
+    estimated below the least that the product is, one where both are weighed, and a named algorithm's least workspace asks for none."""
+    sn.sn_planner_clear()
+    F, D, B, AUTO, NOALLOC = sn.SN_CONV_FWD, sn.SN_CONV_BWD_DATA, sn.SN_CONV_BWD_FILTER, sn.SN_ALGO_AUTO, 4
+    tiny, small, large = (8, 16, 16, 16, 16), (1, 512, 7, 7, 512), (32, 256, 56, 56, 256)
+    most = [(F, AUTO, 64 << 20, tiny, 0), (D, AUTO, 64 << 20, tiny, 0), (B, AUTO, 64 << 20, (2, 64, 14, 14, 64), 0), (F, AUTO, 64 << 20, small, 1),
+            (NOALLOC, 0, 0, small, 1), (NOALLOC, 0, 0, large, 1), (F, sn.SN_ALGO_STAGED, 64 << 20, large, 1), (D, sn.SN_ALGO_STAGED, 64 << 20, large, 1)]
+    plans = []
+    recorded([(d, a, b, sn.conv_shape(*s, 3, 3, (1, 1), (1, 1), sn.SN_BF16, sn.SN_BF16)) for d, a, b, s, _ in most], plans)
+    assert all(n <= m[4] for n, m in zip(plans, most)), list(zip(plans, most))
