@@ -202,7 +202,9 @@ sn_status sn_conv2d_fwd(const void *x, const void *w, void *y, const sn_conv_sha
  * themselves: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * It is sn_conv2d_fwd with algo = SN_ALGO_STAGED and a workspace of SN_NOALLOC_SCRATCH_BYTES (the same
  * kernels and bits as that call; with more or less workspace STAGED may run other kernels, whose sums
- * are in another order): the re-laid-out filter, or the copies of small inputs, in a fixed array that the library's code
+ * are in another order), but for small 3x3 layers on which STAGED by its name keeps the channels-last
+ * product so that measurements can choose: where their one-launch kernel is estimated to be the faster
+ * one, this call runs that.  The re-laid-out filter, or the copies of small inputs, are in a fixed array that the library's code
  * object holds on every GPU it is loaded on until the process ends.  No hipMalloc / hipFree or
  * other allocating call is made.  The first call on a device looks up the array's address there
  * (make that call outside a graph capture).

@@ -431,7 +431,7 @@ bool chlast_faster(const ConvGeom &g, sn_conv_dir dir, sn_conv_algo algo, size_t
     // STAGED's forward and backward-data run the small layers' kernel, too, in place of its tiles and of the product where that is at
     // its worst: reduction slices (a third launch) or channels that fill no whole runs (2 x 256 x 14x14, 256 channels: 17 us, the kernel 9; 2 x 24 x
     // 14x14 -> 40: 12 and 3.5).  On the rest (4 x 64 x 14x14 -> 128: 13 and 5) the name keeps the product, so that measurements have both to
-    // choose from: AUTO without any takes the kernel, as DIRECT.
+    // choose from: AUTO without any takes the kernel, as DIRECT, and so does the call that allocates nothing.
     if (algo == SN_ALGO_STAGED && dir != SN_CONV_BWD_FILTER) {
         int m, n, threads, slices;
         chlast_config(*plan, dir, &m, &n, &threads, &slices);
@@ -1036,9 +1036,18 @@ sn_status sn_conv2d_fwd_noalloc(const void *x, const void *w, void *y, const sn_
     void *ws = nullptr;
     s = scratch_of_current_device(&ws);
     if (s != SN_OK) return s;
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    // A small layer's kernel also where STAGED by its name keeps the product (chlast_faster): no measurement chooses for this call.
+    const double us = small_conv_us(g, SN_CONV_FWD);
+    if (us < 1e9 && below_tiles(us, g, SN_CONV_FWD, true)) {
+        ChlastPlan cl;
+        if (us <= PRODUCT_LEAST_US || !chlast_runs(g, SN_CONV_FWD, SN_ALGO_STAGED, SN_NOALLOC_SCRATCH_BYTES, &cl) || us < product_us(g, cl))
+            return launch_status(launch_small_bf16(x, w, y, g, false, st));
+        return launch_status(launch_chlast(x, w, y, g, SN_CONV_FWD, ws, &cl, st));
+    }
     // the packing and copying kernels write every item of what is read, padding included: nothing of an
     // earlier call's contents is
-    return run_fwd(x, w, y, g, SN_ALGO_STAGED, ws, SN_NOALLOC_SCRATCH_BYTES, static_cast<hipStream_t>(stream));
+    return run_fwd(x, w, y, g, SN_ALGO_STAGED, ws, SN_NOALLOC_SCRATCH_BYTES, st);
 }
 
 // Scratch of sn_conv2d_fwd_bn_stats: the per-tile triples of whichever tile kernel runs, or the

@@ -200,3 +200,17 @@ def test_small_calls_make_few_plans(recorded):
     plans = []
     recorded([(d, a, b, sn.conv_shape(*s, 3, 3, (1, 1), (1, 1), sn.SN_BF16, sn.SN_BF16)) for d, a, b, s, _ in most], plans)
     assert all(n <= m[4] for n, m in zip(plans, most)), list(zip(plans, most))
+
+
+def test_the_call_that_allocates_nothing_takes_the_faster_kernel(recorded):
+    """No measurement chooses for it: small layers run as one launch also on whole blocks of 64 channels, where STAGED by its name keeps the
+    channels-last product with the same workspace."""
+    sn.sn_planner_clear()
+    shapes = [(4, 64, 14, 14, 128), (1, 64, 28, 28, 64), (16, 64, 9, 9, 40)]
+    calls = [(d, sn.SN_ALGO_STAGED, sn.SN_NOALLOC_SCRATCH_BYTES, sn.conv_shape(*s, 3, 3, (1, 1), (1, 1), sn.SN_BF16, sn.SN_BF16))
+             for s in shapes for d in (sn.SN_CONV_FWD, 4)]
+    res = recorded(calls)
+    for i, s in enumerate(shapes):
+        (status, named), (status4, noalloc) = res[2 * i:2 * i + 2]
+        assert status == status4 == 0 and "cl_gemm_kernel" in named[1][0], (s, named)
+        assert len(noalloc) == 1 and "small3x3_bf16_kernel" in noalloc[0][0], (s, noalloc)

@@ -1,6 +1,6 @@
 """sn_conv2d_fwd_noalloc, the forward CONV for callers that cannot allocate: its workspace is a
 fixed array inside the library.  It runs the kernels of sn_conv2d_fwd with SN_ALGO_STAGED and a
-workspace of the array's size, so the outputs must be bit-identical; two calls in a row, the second on a smaller problem, share the array.
+workspace of the array's size (but for small layers, see the last test), so the outputs must be bit-identical; two calls in a row, the second on a smaller problem, share the array.
 Also checked against the fp64 oracle (relative L2 <= 5e-3, bf16 inputs)."""
 import ctypes
 
@@ -80,3 +80,20 @@ def test_sizes_beyond_the_array_are_refused():
     assert _raw_call(x, w, y, shape2) == 2
     torch.cuda.synchronize()
     assert bool((y == 7.0).all())
+
+
+@pytest.mark.parametrize("case", [(4, 64, 14, 14, 128), (2, 128, 14, 14, 128)], ids=lambda c: "x".join(map(str, c)))
+def test_small_layers_run_the_kernel_of_direct(case):
+    """Whole blocks of 64 channels: STAGED by its name is the channels-last product there, this call the small layers' kernel."""
+    N, C, H, W, K = case
+    layer = wl.Layer("t", C, H, W, K, 3, 3, (1, 1), (1, 1), True, None, 1, False, None)
+    x, w, _ = wl.conv_inputs(layer, N, "bf16", 7)
+    shape = sn.conv_shape(N, C, H, W, K, 3, 3, (1, 1), (1, 1), sn.SN_BF16, sn.SN_BF16)
+    xd, wd = x.cuda(), w.cuda()
+    want = torch.full((N, K, H, W), float("nan"), dtype=torch.bfloat16, device="cuda")
+    got = torch.full_like(want, float("nan"))
+    sn.sn_conv2d_fwd(xd, wd, want, shape, sn.SN_ALGO_DIRECT)
+    assert _raw_call(xd, wd, got, shape) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    assert rel_l2(f64(got), oracle.conv2d_fwd(f64(x), f64(w), (1, 1), (1, 1))) <= 5e-3
