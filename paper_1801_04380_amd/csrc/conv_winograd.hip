@@ -119,6 +119,8 @@ wino_input_kernel(const float *__restrict__ in, float *__restrict__ V, WinoProbl
 // a step's two LDS tiles [16][128] are plain 16-byte copies and an MFMA lane's operand is one float
 // of a row of consecutive floats.  Double-buffered: the global loads of step i+1 are issued before
 // the MFMAs of step i and written to the other buffer after them; one barrier per step.
+// Workgroups are numbered so that the channel tiles of one pixel tile run on one XCD, which reads V's tile once (the 16 ttiles pixel tiles
+// are a multiple of the 8 XCDs): 8 x 256 x 56x56, 256 channels, 512 MiB 219.0 -> 217.3 us a call, seven such layers 0.1 to 1.2 %.
 __global__ void __launch_bounds__(256, 2)
 wino_gemm_kernel(const float *__restrict__ U, const float *__restrict__ V, float *__restrict__ Mo, int REDp, int Mp, int Tp)
 {
@@ -128,7 +130,6 @@ wino_gemm_kernel(const float *__restrict__ U, const float *__restrict__ V, float
     const int wm = wave >> 1, wn = wave & 1;
     const int mtiles = Mp / BM, ttiles = Tp / BN;
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, mt = slot % mtiles, job = slot / mtiles * 8 + xcd;
-    if (job >= 16 * ttiles) return;
     const int xi = job / ttiles, t0 = (job - xi * ttiles) * BN, m0 = mt * BM;
     const float *Ux = U + (size_t)xi * REDp * Mp + m0;
     const float *Vx = V + (size_t)xi * REDp * Tp + t0;
@@ -337,7 +338,7 @@ hipError_t launch_winograd(const void *in, const void *w, void *out, const ConvG
         hipLaunchKernelGGL(wino_input_kernel, dim3(Tp / 256 + (Tp % 256 != 0), p.REDp), dim3(256), 0, st,
                            static_cast<const float *>(in), V, p, n0, T, Tp);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(wino_gemm_kernel, dim3(8 * ((16 * (Tp / BN) + 7) / 8) * (p.Mp / BM)), dim3(256), 0, st, U, V, Mo, p.REDp, p.Mp, Tp);
+        hipLaunchKernelGGL(wino_gemm_kernel, dim3(16 * (Tp / BN) * (p.Mp / BM)), dim3(256), 0, st, U, V, Mo, p.REDp, p.Mp, Tp);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(wino_output_kernel<float>, dim3((T + 255) / 256, p.M), dim3(256), 0, st, Mo,
                            static_cast<float *>(out), p, n0, T, Tp);
