@@ -14,7 +14,12 @@ pytestmark = pytest.mark.gpu
 # tiles and over; padding on every side, more than the filter reaches; several blocks a workgroup
 SHAPES = [(1, 3, 11, 11, 8, 11, 11, 4, 4, 0, 0), (1, 1, 7, 9, 33, 7, 7, 2, 2, 0, 0), (2, 3, 59, 67, 96, 11, 11, 4, 4, 0, 0),
           (2, 3, 40, 150, 64, 7, 7, 2, 2, 3, 3), (3, 4, 33, 131, 65, 5, 5, 2, 2, 2, 2), (1, 2, 50, 260, 31, 9, 16, 3, 4, 1, 7),
-          (2, 3, 21, 23, 40, 4, 8, 1, 2, 6, 5), (5, 3, 35, 64, 95, 11, 11, 4, 4, 2, 2), (70, 3, 63, 127, 48, 7, 7, 2, 2, 3, 3)]
+          (2, 3, 21, 23, 40, 4, 8, 1, 2, 6, 5), (5, 3, 35, 64, 95, 11, 11, 4, 4, 2, 2), (70, 3, 63, 127, 48, 7, 7, 2, 2, 3, 3),
+          (2, 1, 7, 16, 50, 7, 12, 4, 8, 0, 0), (1, 3, 16, 9, 8, 4, 4, 2, 2, 0, 0)]
+# blocks 32 columns wide, one to three channel tiles and either alignment of an operand: where they take fewer rounds, and where the
+# input rows of a wider one are too many
+SHAPES += [(40, 1, 62, 18, 32, 9, 9, 1, 2, 0, 0), (1, 4, 62, 291, 8, 11, 11, 3, 4, 0, 0), (40, 4, 48, 13, 50, 6, 8, 1, 2, 3, 2),
+           (1, 4, 40, 253, 33, 11, 11, 3, 4, 2, 0), (40, 2, 109, 13, 65, 3, 12, 2, 2, 1, 0), (1, 4, 86, 267, 65, 11, 8, 3, 4, 3, 2)]
 
 
 def _case(shape, out="bf16"):

@@ -15,6 +15,8 @@ pytestmark = pytest.mark.gpu
 # 16 and of 32 and output channels inside a tile; no padding and padding 2; more steps than waves; both tiles' own sizes
 SHAPES = [(1, 8, 1, 1, 8, 1), (1, 32, 4, 8, 32, 1), (2, 24, 5, 9, 33, 1), (3, 40, 9, 13, 70, 0), (1, 56, 6, 5, 8, 2), (1, 8, 3, 40, 17, 1),
           (1, 512, 7, 7, 512, 1), (2, 256, 14, 14, 256, 1), (2, 64, 56, 56, 64, 1), (4, 72, 17, 31, 104, 1), (1, 1024, 4, 4, 64, 1)]
+# the filter loaded together (nine steps and more, forward): a last step of fewer channels, output channels that fill no tile, of 16 and of 32
+SHAPES += [(1, 264, 7, 7, 40, 1), (1, 392, 7, 7, 300, 1), (1, 264, 12, 20, 300, 1)]
 
 
 @pytest.mark.parametrize("out", ["bf16", "f32"])
@@ -72,3 +74,41 @@ def test_infinities_stay_with_their_outputs(shape):
     assert bool(torch.isfinite(got[~hit]).all()) and bool(torch.isinf(got[hit]).all())
     sign = torch.stack([torch.stack([w[:, C - 1, 4 - h + 1, 5 - v + 1] for v in range(4, 7)], 1) for h in range(3, 6)], 1)
     assert np.array_equal((got[1, :, 3:6, 4:7] > 0).numpy(), (sign > 0).numpy())
+
+
+@pytest.mark.parametrize("shape", [(2, 24, 9, 9, 40, 1), (2, 256, 14, 14, 256, 1)], ids=["16", "32"])
+def test_infinite_gradients_stay_with_their_inputs(shape):
+    N, C, H, W, K, p = shape
+    dy = wl.activation((N, K, H, W), "bf16", 3)
+    w = wl.activation((K, C, 3, 3), "bf16", 4, scale=(2.0 / (9 * C)) ** 0.5)
+    w[w == 0] = 1e-3
+    dy[1, K - 1, 4, 5] = float("inf")
+    sh = sn.conv_shape(N, C, H, W, K, 3, 3, (1, 1), (p, p), sn.SN_BF16, sn.SN_BF16)
+    dx = torch.empty((N, C, H, W), dtype=torch.bfloat16, device="cuda")
+    sn.sn_conv2d_bwd_data(dy.cuda(), w.cuda(), dx, sh, sn.SN_ALGO_DIRECT)
+    torch.cuda.synchronize()
+    hit = torch.zeros((N, C, H, W), dtype=torch.bool)
+    hit[1, :, 3:6, 4:7] = True
+    got = dx.cpu()
+    assert bool(torch.isfinite(got[~hit]).all()) and bool(torch.isinf(got[hit]).all())
+    sign = torch.stack([torch.stack([w[K - 1, :, h - 4 + 1, v - 5 + 1] for v in range(4, 7)], 1) for h in range(3, 6)], 1)
+    assert np.array_equal((got[1, :, 3:6, 4:7] > 0).numpy(), (sign > 0).numpy())
+
+
+@pytest.mark.parametrize("shape", [(1, 264, 7, 7, 40, 1), (1, 264, 12, 20, 300, 1)], ids=["16", "32"])
+def test_an_infinite_filter_stays_with_its_output_channel(shape):
+    """The last step's pieces of the filter past an output channel's last input channel are the next one's first taps."""
+    N, C, H, W, K, p = shape
+    x = wl.activation((N, C, H, W), "bf16", 3).abs() + 0.5
+    w = wl.activation((K, C, 3, 3), "bf16", 4, scale=(2.0 / (9 * C)) ** 0.5)
+    for k in (1, 17, K - 1):
+        w[k, 0, 1, 1] = float("inf")
+    sh = sn.conv_shape(N, C, H, W, K, 3, 3, (1, 1), (p, p), sn.SN_BF16, sn.SN_BF16)
+    y = torch.empty((N, K, H, W), dtype=torch.bfloat16, device="cuda")
+    sn.sn_conv2d_fwd(x.to(torch.bfloat16).cuda(), w.cuda(), y, sh, sn.SN_ALGO_DIRECT)
+    torch.cuda.synchronize()
+    hit = torch.zeros((N, K, H, W), dtype=torch.bool)
+    for k in (1, 17, K - 1):
+        hit[:, k] = True
+    got = y.cpu()
+    assert bool(torch.isfinite(got[~hit]).all()) and bool(torch.isposinf(got[hit]).all())

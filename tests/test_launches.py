@@ -9,6 +9,10 @@ import pytest
 
 import paper_1801_04380_amd as sn
 import test_gpu_image
+import test_gpu_image_fwd
+import test_gpu_small3x3_mfma
+import test_gpu_small_bf16
+import test_gpu_small_wgrad
 from paper_1801_04380_amd import _lib
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -214,3 +218,33 @@ def test_the_call_that_allocates_nothing_takes_the_faster_kernel(recorded):
         (status, named), (status4, noalloc) = res[2 * i:2 * i + 2]
         assert status == status4 == 0 and "cl_gemm_kernel" in named[1][0], (s, named)
         assert len(noalloc) == 1 and "small3x3_bf16_kernel" in noalloc[0][0], (s, noalloc)
+
+
+def _kernels(res):
+    assert all(status == 0 for status, _ in res)
+    return [re.sub(r"^\d+", "", launches[0][0]).split("EvP")[0] for _, launches in res]
+
+
+def test_the_image_forward_tests_run_every_kernel(recorded):
+    """One to three channel tiles, blocks 64 and 32 columns wide, operands on 4 and 8 bytes."""
+    sn.sn_planner_clear()
+    shapes = [sn.conv_shape(N, C, H, W, K, R, S, (sh, sw), (ph, pw), sn.SN_BF16, sn.SN_BF16)
+              for N, C, H, W, K, R, S, sh, sw, ph, pw in test_gpu_image_fwd.SHAPES]
+    names = _kernels(recorded([(sn.SN_CONV_FWD, sn.SN_ALGO_DIRECT, 0, s) for s in shapes]))
+    assert all(n.startswith("image_fwd_kernel") for n in names) and len(set(names)) == 12, sorted(set(names))
+
+
+def test_the_small_layers_tests_run_the_kernels_that_they_name(recorded):
+    """As DIRECT, bf16 forward and backward-data on either tile, forward with the filter loaded by lane and together; the fp32 kernels on either
+    side of 16 reduction channels; backward-filter in both types."""
+    sn.sn_planner_clear()
+    F, D, B, direct = sn.SN_CONV_FWD, sn.SN_CONV_BWD_DATA, sn.SN_CONV_BWD_FILTER, sn.SN_ALGO_DIRECT
+    call = lambda d, s, t: (d, direct, 0, sn.conv_shape(*s[:5], 3, 3, (1, 1), (s[5], s[-1]), t, t))
+    names = _kernels(recorded([call(d, s, sn.SN_BF16) for s in test_gpu_small_bf16.SHAPES for d in (F, D)]))
+    assert all(n.startswith("small3x3_bf16_kernel") for n in names) and len(set(names)) == 6, sorted(set(names))
+    shapes = test_gpu_small3x3_mfma.SHAPES
+    names = _kernels(recorded([call(d, s, sn.SN_F32) for s in shapes for d in (F, D)]))
+    for n, red in zip(names, [c for s in shapes for c in (s[1], s[4])]):
+        assert n.startswith("small3x3_mfma_kernel" if red >= 16 else "small3x3_kernel"), (n, red)
+    names = _kernels(recorded([call(B, s, t) for s in test_gpu_small_wgrad.SHAPES for t in (sn.SN_BF16, sn.SN_F32)]))
+    assert all(n.startswith("small3x3_wgrad_kernel") for n in names) and len(set(names)) == 2, sorted(set(names))
