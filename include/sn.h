@@ -74,7 +74,15 @@ typedef enum { SN_CONV_FWD = 0, SN_CONV_BWD_DATA = 1, SN_CONV_BWD_FILTER = 2 } s
  *               backward-filter of up to four input channels under 33 to 384
  *               products (C * R * S; a network's first layer with a large filter) has
  *               a kernel of its own under DIRECT and STAGED where that is
- *               estimated to be the faster one.  Every other strided
+ *               estimated to be the faster one.  Forward of such a layer (bf16, up to 96
+ *               output channels, an even column stride, up to 16 filter columns) has
+ *               one under DIRECT, as long as the filter and a block of input rows
+ *               fit LDS (11x11 / 4 over three channels: any width up to 64 output
+ *               channels, 238 columns up to 96).  Small 3x3 / stride-1 layers are one
+ *               launch: fp32 forward and backward-data up to 2^24 multiplications,
+ *               bf16 forward (C a multiple of 8) and backward-data, and backward-filter in
+ *               either type, where that is estimated to be faster than what DIRECT
+ *               runs otherwise.  Every other strided
  *               backward-data works by residue classes of the input pixels
  *               (h mod stride_h, w mod stride_w): a class shares its taps, so only
  *               the taps that meet an output pixel are multiplied.
@@ -114,7 +122,11 @@ typedef enum { SN_CONV_FWD = 0, SN_CONV_BWD_DATA = 1, SN_CONV_BWD_FILTER = 2 } s
  *               order of the sums only); sn_conv_plan's bytes_used then says how
  *               much of the budget it takes, and sn_conv_autotune times both
  *               (backward-filter's own kernels under preferred_bytes + 256, with exactly
- *               which they run whatever the estimates say).
+ *               which they run whatever the estimates say).  Small bf16 3x3 layers run
+ *               forward and backward-data as the one launch that DIRECT has for them
+ *               where it is estimated to be faster than the tiles with a packed filter;
+ *               in place of the product only where that sums in slices or the reduction
+ *               channels are no multiple of 64, so that measurements have both to choose from.
  *  WINOGRAD     F(2x2, 3x3) for the fp32 path (3x3 filters, stride 1, forward and
  *               backward-data): the transformed filter, the transformed input
  *               tiles and the 16 products per tile live in the workspace, for as
@@ -152,9 +164,11 @@ int sn_out_dim(int in, int pad, int window, int stride);
 /* Workspace needs of one algorithm for one CONV step (Sec. 3.5: an algorithm is
  * memory-feasible iff its workspace fits the free bytes).
  *  min_bytes        least workspace with which the algorithm runs at all
- *  preferred_bytes  workspace beyond which it gets no faster, with one exception: STAGED's strided
+ *  preferred_bytes  workspace beyond which it gets no faster, with two exceptions: STAGED's strided
  *                   forward and its backward-filter report what their own kernels can use, and
- *                   may change to the channels-last product (about the tensors' own size) with more
+ *                   may change to the channels-last product (about the tensors' own size) with more;
+ *                   and on small layers of whole 64-channel blocks STAGED with the product's bytes
+ *                   is slower than with min_bytes, which run the one-launch kernel (see STAGED)
  * Returns SN_ERR_UNSUPPORTED if the algorithm cannot run this shape. */
 sn_status sn_conv_workspace_query(const sn_conv_shape *shape, sn_conv_dir dir, sn_conv_algo algo,
                                   size_t *min_bytes, size_t *preferred_bytes);
@@ -166,10 +180,13 @@ sn_status sn_conv_workspace_query(const sn_conv_shape *shape, sn_conv_dir dir, s
  * it was measured with, and a call with algo = AUTO runs the choice with just that
  * workspace.  With no feasible record the choice falls back to estimates and a
  * built-in ranking: first the channels-last product where the budget holds it and it is
- * estimated to be faster than what would run instead, as STAGED or, where STAGED has no
+ * estimated to be faster than what would run instead (DIRECT's one launch of small layers and the image layer's forward
+ * included), as STAGED or, where STAGED has no
  * kernel for the shape or does not fit, as IM2COL_GEMM (bytes_used is then at least that algorithm's
  * min_bytes); then WINOGRAD where it applies, C * K >= 8192 and at least 2048 tiles (or the whole batch) fit a pass, but for
- * small layers, which are one launch as DIRECT; STAGED, DIRECT; DIRECT before these for forward on few-channel inputs.  Among records within 3 % of the fastest the one with the
+ * small layers, which are one launch as DIRECT; STAGED, DIRECT; DIRECT before these for forward on few-channel inputs, and before
+ * STAGED where its kernels for small layers or for the image layer's forward run or, on small layers, its tiles are estimated to be
+ * the faster ones without a packed filter.  Among records within 3 % of the fastest the one with the
  * smallest workspace wins (then the faster).  DIRECT needs 0 bytes, so a plan always exists.  bytes_used = the workspace the choice will use
  * (<= budget_bytes).  predicted_ms may be NULL; it receives the recorded time
  * or a negative value if the choice came from the built-in ranking. */
@@ -223,7 +240,7 @@ sn_status sn_conv2d_fwd_noalloc(const void *x, const void *w, void *y, const sn_
  * as sn_conv2d_fwd writes it for the same algo and workspace, and
  *   save_mean[k] = mean over (n,p,q) of y[n,k,p,q], save_invstd[k] = 1/sqrt(biased var + eps),
  * of the values as stored (after rounding to out_dtype), i.e. what sn_bn_fwd(y) would save, up to
- * the order of the sums.  Where a tile kernel runs the CONV (stride 1, bf16 inputs) the
+ * the order of the sums.  Where a tile kernel runs the CONV (stride 1, bf16 inputs; not the small layers' one launch) the
  * statistics come out of its accumulators -- per tile and channel a count, a mean and a sum of
  * squared deviations, combined pairwise in fp64 in a fixed order -- and y is not read again;
  * elsewhere a pass over y follows the CONV.  sn_bn_apply / sn_bn_relu_pool2_apply then finish the

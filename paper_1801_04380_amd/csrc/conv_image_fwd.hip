@@ -9,6 +9,10 @@
 // one is multiplied; results leave through LDS in long runs.
 // A zero column meets a real element of x; where that is an Inf or a NaN, and the result so is not finite, the wave does its block again
 // with those elements cleared.
+// Where it runs: filters of up to 16 columns and at least two rows, strides and filter up to 64, whose operands and the input rows of a block (64 or 32
+// columns wide, 8 or 16 rows) fit 160 KB of LDS and 4096 pieces of 16 bytes.  7x7 / 2 and 5x5 / 2 over three channels fit at any width; 11x11 / 4 over three
+// at any width up to 64 output channels and, with 65 to 96, on images of up to 238 columns (without padding; 161 792 of 163 840 bytes at 227), over
+// four channels of up to 206 and 86.  Wider ones, and more than 96 output channels, are the general kernel's.
 // Bound by LDS reads (three operands of the filter and two of pixels for six MFMAs) and, half as long, the results' way out.  us, the
 // kernels before it (without workspace; with 512 MiB) -> this: 128 x 3 x 227x227, 96 channels 11x11 / 4 241 (110) -> 79, 32 x 3 x 224x224, 64
 // channels 7x7 / 2 80 (78) -> 37.  160 layers of 1 to 4 channels, 8 to 96 output channels, 5x5 to 11x11, batch 1 to 128: 0.57 of their time without
