@@ -343,8 +343,9 @@ double small_tiles_us(const ConvGeom &g, sn_conv_dir dir, bool staged)
 }
 
 // Whether an estimate of it is below that of DIRECT's (STAGED's) tiles.  Of those 6700 layers DIRECT is more than 5 % slower than on the tiles on 18 (at
-// most 1.25 times, as 5 x 16 x 33x33 -> 240); without the comparison it was on 86 (1.46 times).  The tiles need not be looked at below the least that they
-// are estimated at, by the coefficients of their chunks of 16 reduction channels.
+// most 1.25 times); without the comparison it was on 86 (1.46 times).  The packed tiles' estimate is the less sure one, and leaving the kernel wrongly
+// costs more than keeping it (13 x 16 x 45x45 -> 256: 18.0 us, packed 27.6 where 18 are estimated): 1.15.  The tiles need not be looked at below the
+// least that they are estimated at, by the coefficients of their chunks of 16 reduction channels.
 bool below_tiles(double us, const ConvGeom &g, sn_conv_dir dir, bool staged)
 {
     const int red = dir == SN_CONV_BWD_DATA ? g.K : g.C;
